@@ -104,7 +104,7 @@ nanospec_status vocab_call(nanospec_state* st, const int32_t* d_new, const int32
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (is_init) {
     st->policy = st->policy_next;
-    if (launch_vocab_clear(st, s) != hipSuccess) return NANOSPEC_EHIP;
+    return launch_vocab_init(st, d_new, noff, d_topk, toff, s) == hipSuccess ? NANOSPEC_OK : NANOSPEC_EHIP;
   }
   if (launch_vocab_apply(st, d_new, noff, d_topk, toff, replace_T, s) != hipSuccess) return NANOSPEC_EHIP;
   return NANOSPEC_OK;

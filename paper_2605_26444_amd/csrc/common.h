@@ -83,6 +83,8 @@ namespace nanospec {
 
 // vocab.hip
 hipError_t launch_vocab_clear(const nanospec_state* st, hipStream_t s);
+hipError_t launch_vocab_init(const nanospec_state* st, const int32_t* d_ctx, const Offsets& coff, const int32_t* d_topk,
+                             const Offsets& toff, hipStream_t s);
 hipError_t launch_vocab_apply(const nanospec_state* st, const int32_t* d_new, const Offsets& noff,
                               const int32_t* d_topk, const Offsets& toff, int replace_T, hipStream_t s);
 hipError_t vocab_configure(nanospec_state* st);

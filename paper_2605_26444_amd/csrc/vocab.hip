@@ -219,6 +219,11 @@ __device__ __forceinline__ void vocab_apply_body(const VocabPtrs& p, int b, cons
   if (bad) atomicOr(p.err, (int)NANOSPEC_DEV_BAD_ID);
 }
 
+__device__ __forceinline__ void load_window_bitmap(const VocabPtrs& p, int b, uint32_t* wb) {
+  const uint32_t* gw = p.wbit + (size_t)b * p.nwords;
+  for (int i = threadIdx.x * 4; i < p.nwords; i += kVocabThreads * 4) *reinterpret_cast<uint4*>(wb + i) = *reinterpret_cast<const uint4*>(gw + i);
+}
+
 __device__ __forceinline__ void load_bitmaps(const VocabPtrs& p, int b, uint32_t* wb, uint32_t* tb, int replace_T) {
   const uint32_t* gw = p.wbit + (size_t)b * p.nwords;
   const uint32_t* gt = p.tbit + (size_t)b * p.nwords;
@@ -474,6 +479,211 @@ __global__ __launch_bounds__(kVocabThreads) void vocab_apply_kernel(VocabPtrs p,
   vocab_apply_body(p, b, new_ids + noff.v[b], a, topk + toff.v[b], toff.v[b + 1] - toff.v[b], replace_T, wb, tb, sc, 0);
 }
 
+// src[0..n) with eight loads in flight per thread: f(index, value) for every element
+template <typename F>
+__device__ __forceinline__ void each8(const int32_t* src, int n, int tid, F f) {
+  for (int i0 = tid; i0 < n; i0 += 8 * kVocabThreads) {
+    int v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int i = i0 + u * kVocabThreads;
+      v[u] = src[i < n ? i : n - 1];
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (i0 + u * kVocabThreads < n) f(i0 + u * kVocabThreads, v[u]);
+  }
+}
+
+// Stream initialisation of short windows: one launch, one workgroup per sequence.  A counter is non-zero only if its id
+// is in the ring, so what an earlier stream left behind is undone through the ring (at most `window` scattered stores)
+// instead of clearing V counters in a launch of its own.  Latency-bound: every array is read with eight loads in flight
+// per thread.  Beyond the lengths below the additions to the counters -- a frequent token's all go to one address in L2,
+// about 2 us per 1024 tokens -- cost more than the second launch of the kernels that follow (V = 128256, |T| = 2000;
+// this / those, us: one sequence 5.9 / 7.0 at 256 tokens, 8.5 / 7.4 at 1024, 23.0 / 8.0 at 8192; 64 sequences 8.0 / 15.0 at
+// 256, 12.3 / 16.0 at 1024, 17.4 / 16.2 at 2048, 49 / 17.7 at 8192).
+constexpr int kInitFewSeqs = 16;
+constexpr int kInitSerialFew = 640, kInitSerialMany = 1536;
+
+__global__ __launch_bounds__(kVocabThreads) void vocab_init_kernel(VocabPtrs p, const int32_t* __restrict__ ctx, Offsets coff,
+                                                                   const int32_t* __restrict__ topk, Offsets toff) {
+  extern __shared__ uint32_t lds[];
+  const int b = blockIdx.x, tid = threadIdx.x;
+  const int nwords = p.nwords, V = p.V, W = p.window;
+  uint32_t* wb = lds;
+  uint32_t* tb = lds + nwords;
+  int* sc = reinterpret_cast<int*>(tb + nwords);
+  uint32_t* cnt = p.cnt + (size_t)b * V;
+  int32_t* ring = p.ring + (size_t)b * W;
+  const int32_t* src = ctx + coff.v[b];
+  const int a = coff.v[b + 1] - coff.v[b];
+  const int skip = a > W ? a - W : 0, ae = a - skip;
+  int bad = 0;
+  each8(ring, p.fill[b], tid, [&](int, int e) {
+    if (e >= 0) cnt[e] = 0u;
+  });
+  for (int i = tid * 4; i < 2 * nwords; i += kVocabThreads * 4) *reinterpret_cast<uint4*>(lds + i) = make_uint4(0, 0, 0, 0);
+  each8(src, skip, tid, [&](int, int v) { bad |= (unsigned)v >= (unsigned)V; });
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // the zeros have reached L2, where the additions below happen
+  __syncthreads();
+  each8(src + skip, ae, tid, [&](int i, int v) {
+    const bool ok = (unsigned)v < (unsigned)V;
+    if (ok) {
+      atomicAdd(&cnt[v], 1u);
+      atomicOr(&wb[v >> 5], 1u << (v & 31));
+    } else {
+      bad = 1;
+    }
+    ring[i] = ok ? v : -1;
+  });
+  each8(topk + toff.v[b], toff.v[b + 1] - toff.v[b], tid, [&](int, int t) {
+    if ((unsigned)t < (unsigned)V) atomicOr(&tb[t >> 5], 1u << (t & 31));
+    else bad = 1;
+  });
+  __syncthreads();
+  const int total = compact_bitmap(
+      [&](int i) {
+        const uint4 x = *reinterpret_cast<const uint4*>(wb + i), c = *reinterpret_cast<const uint4*>(tb + i);
+        return make_uint4(x.x | c.x, x.y | c.y, x.z | c.z, x.w | c.w);
+      }, nwords, p.ids + (size_t)b * p.cap, p.cap, sc, tid);
+  for (int i = tid * 4; i < nwords; i += kVocabThreads * 4) {
+    *reinterpret_cast<uint4*>(p.wbit + (size_t)b * nwords + i) = *reinterpret_cast<const uint4*>(wb + i);
+    *reinterpret_cast<uint4*>(p.tbit + (size_t)b * nwords + i) = *reinterpret_cast<const uint4*>(tb + i);
+  }
+  if (tid == 0) {
+    p.n[b] = total < p.cap ? total : p.cap;
+    p.pos[b] = ae < W ? ae : 0;
+    p.fill[b] = ae;
+  }
+  if (bad) atomicOr(p.err, (int)NANOSPEC_DEV_BAD_ID);
+}
+
+// Longer windows: the initialisation is spread over the chip.  A workgroup counts the ids of one range (RANGE of them)
+// among the tokens of sequence b in LDS, where a frequent token -- a tenth of a Zipf stream is one id -- costs a bank conflict
+// and not thousands of additions to one address in L2; the tokens are read once per range, out of L2.
+//   OWN: the workgroup (r, 0, b) sees all tokens, so it knows its range's counters and bitmap words and stores them as they
+//        are; nothing has to be cleared first.
+//   else: (r, s, b) sees segment s only and adds to what vocab_clear_kernel has zeroed: from kInitOwnMax tokens on, where
+//        one workgroup's walk over them takes longer than the third launch (12.0 / 11.8 us at 32768, 43.6 / 16.3 at 235000;
+//        a single workgroup with additions in L2 and 1024 tokens in flight took 437 us there).
+// Many sequences fill the chip with fewer, larger ranges: 64 sequences of 4096 tokens 16.3 us with 16384 ids per range,
+// 27.4 with 4096; 16 sequences 11.2 with either; one sequence 9.3 and 7.7.
+constexpr int kRangeFew = 4096, kRangeMany = 16384;   // ids per range for few / many sequences: 16 / 64 KB of LDS
+constexpr int kSegTokens = 16 * kVocabThreads;        // tokens per segment
+constexpr int kInitOwnMax = 2 * kSegTokens;
+
+template <bool OWN, int RANGE>
+__global__ __launch_bounds__(kVocabThreads) void vocab_init_count_kernel(VocabPtrs p, const int32_t* __restrict__ ctx, Offsets coff,
+                                                                         const int32_t* __restrict__ topk, Offsets toff) {
+  extern __shared__ uint32_t lds[];
+  uint32_t* c = lds;                                         // [RANGE] counters
+  uint32_t* tw = lds + RANGE;                                // [RANGE / 32] T's bitmap words
+  const int r = blockIdx.x, s = blockIdx.y, b = blockIdx.z, tid = threadIdx.x, lane = tid & 63;
+  const int V = p.V, W = p.window, nwords = p.nwords;
+  const int32_t* src = ctx + coff.v[b];
+  const int a = coff.v[b + 1] - coff.v[b];
+  const int skip = a > W ? a - W : 0, ae = a - skip;
+  const int base = r * RANGE, w0 = base / 32;
+  const int first = OWN ? 0 : s * kSegTokens;
+  const int len = OWN ? ae : (ae - first < kSegTokens ? ae - first : kSegTokens);
+  uint32_t* gw = p.wbit + (size_t)b * nwords;
+  uint32_t* gt = p.tbit + (size_t)b * nwords;
+  int bad = 0;
+  for (int i = tid; i < RANGE; i += kVocabThreads) c[i] = 0u;
+  if (tid < RANGE / 32) tw[tid] = 0u;
+  __syncthreads();
+  if (OWN || s == 0) {
+    each8(topk + toff.v[b], toff.v[b + 1] - toff.v[b], tid, [&](int, int t) {
+      if ((unsigned)(t - base) < (unsigned)RANGE && t < V) atomicOr(&tw[(t - base) >> 5], 1u << (t & 31));
+      bad |= (unsigned)t >= (unsigned)V;
+    });
+    if (r == 0) each8(src, skip, tid, [&](int, int v) { bad |= (unsigned)v >= (unsigned)V; });   // tokens the window has left behind
+    if (r == 0 && tid == 0) {
+      p.pos[b] = ae < W ? ae : 0;
+      p.fill[b] = ae;
+    }
+  }
+  int32_t* ring = p.ring + (size_t)b * W + first;
+  each8(src + skip + first, len, tid, [&](int i, int v) {
+    if ((unsigned)(v - base) < (unsigned)RANGE && v < V) atomicAdd(&c[v - base], 1u);
+    if (r == 0) {
+      const bool ok = (unsigned)v < (unsigned)V;
+      ring[i] = ok ? v : -1;
+      bad |= ok ? 0 : 1;
+    }
+  });
+  __syncthreads();
+  for (int i = tid; i < RANGE; i += kVocabThreads) {     // 64 consecutive ids per wavefront: two bitmap words
+    const uint32_t x = c[i];
+    if (base + i < V && (OWN || x)) {
+      if (OWN) p.cnt[(size_t)b * V + base + i] = x;
+      else atomicAdd(&p.cnt[(size_t)b * V + base + i], x);
+    }
+    const unsigned long long on = __ballot(x != 0u);
+    const uint32_t word = (lane & 32) ? (uint32_t)(on >> 32) : (uint32_t)on;
+    const int w = w0 + i / 32;
+    if ((lane & 31) == 0 && w < nwords) {
+      if (OWN) gw[w] = word;
+      else if (word) atomicOr(&gw[w], word);
+    }
+  }
+  if ((OWN || s == 0) && tid < RANGE / 32 && w0 + tid < nwords) gt[w0 + tid] = tw[tid];
+  if (bad) atomicOr(p.err, (int)NANOSPEC_DEV_BAD_ID);
+}
+
+// Ascending list of (window | T) from the bitmaps in HBM.  Workgroup (r, b) emits the ids of range r; where they start in
+// the list it finds by counting the bits of all lower ranges itself (a few thousand words out of L2), so no workgroup
+// waits for another.
+constexpr int kEmitThreads = 256;
+
+template <int RANGE>
+__global__ __launch_bounds__(kEmitThreads) void vocab_emit_kernel(VocabPtrs p) {
+  __shared__ int sc[2 * (kEmitThreads / 64)];
+  const int r = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int nwords = p.nwords;
+  const uint32_t* gw = p.wbit + (size_t)b * nwords;
+  const uint32_t* gt = p.tbit + (size_t)b * nwords;
+  constexpr int IPT = RANGE / kEmitThreads;                  // ids per thread: 16 (half a bitmap word) or 64 (two words)
+  static_assert(IPT == 16 || IPT == 64, "half a bitmap word or two");
+  const int w0 = r * (RANGE / 32);                           // a multiple of 4, as nwords is
+  unsigned long long bits = 0;
+  if constexpr (IPT == 16) {
+    const int w = w0 + (tid >> 1);
+    const uint32_t x = w < nwords ? gw[w] | gt[w] : 0u;
+    bits = (tid & 1) ? x >> 16 : x & 0xffffu;
+  } else {
+    const int w = w0 + 2 * tid;                              // nwords is even
+    if (w < nwords) {
+      const uint2 x = *reinterpret_cast<const uint2*>(gw + w), y = *reinterpret_cast<const uint2*>(gt + w);
+      bits = ((unsigned long long)(x.y | y.y) << 32) | (x.x | y.x);
+    }
+  }
+  int below = 0;
+#pragma unroll 8
+  for (int i = tid * 4; i < w0; i += kEmitThreads * 4) {
+    const uint4 x = *reinterpret_cast<const uint4*>(gw + i), y = *reinterpret_cast<const uint4*>(gt + i);
+    below += __popc(x.x | y.x) + __popc(x.y | y.y) + __popc(x.z | y.z) + __popc(x.w | y.w);
+  }
+  const int mine = __popcll(bits);
+  const int incl = wave_incl_scan(mine, lane), binc = wave_incl_scan(below, lane);
+  if (lane == 63) {
+    sc[wave] = incl;
+    sc[kEmitThreads / 64 + wave] = binc;
+  }
+  __syncthreads();
+  int off = incl - mine, total = 0;
+#pragma unroll
+  for (int q = 0; q < kEmitThreads / 64; ++q) {
+    off += (q < wave ? sc[q] : 0) + sc[kEmitThreads / 64 + q];
+    total += sc[q] + sc[kEmitThreads / 64 + q];
+  }
+  int32_t* out = p.ids + (size_t)b * p.cap;
+  const int id0 = r * RANGE + tid * IPT;
+  for (; bits; bits &= bits - 1ull, ++off)
+    if (off < p.cap) out[off] = id0 + __ffsll((long long)bits) - 1;
+  if (r == (int)gridDim.x - 1 && tid == 0) p.n[b] = total < p.cap ? total : p.cap;
+}
+
 // Eq. 3 with the candidate set built on the device: the ids of cand[b][0..per_seq) (for instance the
 // top-k ids of all draft-tree nodes, straight from nanospec_topk_remap's output) are de-duplicated
 // through a scratch bitmap in LDS and appended to the stream of sequence b in ascending id order;
@@ -516,7 +726,14 @@ __global__ __launch_bounds__(kVocabThreads) void vocab_append_unique_kernel(Voca
 // the oldest members have made room.  src is walked in chunks of one workgroup: a thread's id is new if
 // neither bitmap (members, seen-in-this-call) has it and no earlier thread of the chunk holds the same
 // id; a ballot + prefix over the wavefronts gives every new id its place in the order.
-// wb/tb: LDS bitmaps (stores issued by this workgroup), ub: zeroed LDS bitmap, cl: kVocabThreads ints.
+// Equal ids of a chunk meet in a hash table in LDS (open addressing; a slot holds the lowest thread that has the id, and
+// the chunk's ids say which id that is; a scan of the earlier threads' ids took 68 us per chunk of 1024 tokens, the table 1.7).
+// wb: LDS bitmap (stores issued by this workgroup), ub: zeroed LDS bitmap, tb: room for T's bitmap, fetched here once the
+// chunks are through -- until then its first kFifoHash ints are the table --, cl: kVocabThreads ints.
+// DISTINCT: the ids of src are all different, no table is needed.
+constexpr int kFifoHash = 2 * kVocabThreads;
+
+template <bool DISTINCT>
 __device__ __forceinline__ void fifo_apply_body(const VocabPtrs& p, int b, const int32_t* src, int a, const int32_t* ts,
                                                 int nt, int replace_T, uint32_t* wb, uint32_t* tb, uint32_t* ub, int* sc,
                                                 int32_t* cl, int bad) {
@@ -529,26 +746,42 @@ __device__ __forceinline__ void fifo_apply_body(const VocabPtrs& p, int b, const
   int32_t* stage = reinterpret_cast<int32_t*>(p.cnt + (size_t)b * V);   // W slots, entry k of the call at k % W
   const int pos = p.pos[b], fill = p.fill[b];
 
-  __syncthreads();                                           // LDS bitmaps complete
-  int nF = 0;
+  int nF = 0, next = tid < a ? src[tid] : -1;
+  int* hash = reinterpret_cast<int*>(tb);
+  if (!DISTINCT)
+    for (int i = tid; i < kFifoHash; i += kVocabThreads) hash[i] = INT_MAX;
+  __syncthreads();                                           // LDS bitmaps and table complete
   for (int c0 = 0; c0 < a; c0 += kVocabThreads) {
     const int i = c0 + tid;
-    const int v = i < a ? src[i] : -1;
-    cl[tid] = v;
-    __syncthreads();
+    const int v = next;
+    next = i + kVocabThreads < a ? src[i + kVocabThreads] : -1;   // on its way while this chunk is worked on
     const bool ok = (unsigned)v < (unsigned)V;
     if (i < a && !ok) bad = 1;
     bool isnew = ok && !((wb[v >> 5] >> (v & 31)) & 1u) && !((ub[v >> 5] >> (v & 31)) & 1u);
-    if (isnew)
-      for (int j = 0; j < tid; ++j)
-        if (cl[j] == v) {
-          isnew = false;
-          break;
+    int slot = -1;
+    if (!DISTINCT) {
+      cl[tid] = v;
+      __syncthreads();
+      if (isnew) {
+        slot = (int)((uint32_t)v * 2654435761u >> 7) & (kFifoHash - 1);
+        for (;;) {                                           // at most kVocabThreads of the slots are ever taken: ends
+          const int old = atomicCAS(&hash[slot], INT_MAX, tid);
+          if (old == INT_MAX) break;
+          if (cl[old] == v) {                                // whichever thread is in the slot, it holds this id
+            atomicMin(&hash[slot], tid);
+            break;
+          }
+          slot = (slot + 1) & (kFifoHash - 1);
         }
+      }
+      __syncthreads();
+      isnew = isnew && hash[slot] == tid;
+    }
     const unsigned long long bal = __ballot(isnew);
     const int before = __popcll(bal & ((1ull << lane) - 1ull));
     if (lane == 0) sc[wave] = __popcll(bal);
     __syncthreads();
+    if (slot >= 0) hash[slot] = INT_MAX;                     // empty again for the next chunk
     int off = nF, tot = 0;
     for (int w = 0; w < kVocabThreads / 64; ++w) {
       const int t = sc[w];
@@ -561,8 +794,10 @@ __device__ __forceinline__ void fifo_apply_body(const VocabPtrs& p, int b, const
       const int k = off + before;
       if (k >= nF - W) stage[k % W] = v;                     // older entries of the call can never stay
     }
-    __syncthreads();                                         // cl, sc and ub are reused by the next chunk
+    __syncthreads();                                         // cl, sc, hash and ub are reused by the next chunk
   }
+  for (int i = tid * 4; i < nwords; i += kVocabThreads * 4)
+    *reinterpret_cast<uint4*>(tb + i) = replace_T ? make_uint4(0, 0, 0, 0) : *reinterpret_cast<const uint4*>(gt + i);
   const int keep = nF < W ? nF : W;
   int n_evict = fill + keep - W;
   if (n_evict < 0) n_evict = 0;
@@ -574,7 +809,9 @@ __device__ __forceinline__ void fifo_apply_body(const VocabPtrs& p, int b, const
   }
   __syncthreads();                                           // slots about to be overwritten have been read
   for (int i = tid; i < keep; i += kVocabThreads) {
-    const int v = stage[(nF - keep + i) % W];
+    int32_t* sp = stage + (nF - keep + i) % W;
+    const int v = *sp;
+    *sp = 0;                                                 // counters outside the ring are zero, whatever the policy (vocab_init_kernel)
     ring[(pos + i) % W] = v;
     atomicOr(&wb[v >> 5], 1u << (v & 31));
   }
@@ -694,16 +931,16 @@ __global__ __launch_bounds__(kVocabThreads) void vocab_fifo_kernel(VocabPtrs p, 
   const int b = blockIdx.x, tid = threadIdx.x, nwords = p.nwords;
   uint32_t* wb = lds;
   uint32_t* tb = lds + nwords;
-  int* sc = reinterpret_cast<int*>(tb + nwords);
+  int* sc = reinterpret_cast<int*>(tb + (nwords > kFifoHash ? nwords : kFifoHash));
   uint32_t* ub = reinterpret_cast<uint32_t*>(sc + 32);
   int32_t* cl = reinterpret_cast<int32_t*>(ub + nwords);
   const int a = noff.v[b + 1] - noff.v[b];
   if (!replace_T && a <= kIncMax && a <= p.window && a <= p.V &&
       fifo_apply_incremental(p, b, new_ids + noff.v[b], a, reinterpret_cast<int*>(lds)))
     return;
-  load_bitmaps(p, b, wb, tb, replace_T);
+  load_window_bitmap(p, b, wb);
   for (int i = tid * 4; i < nwords; i += kVocabThreads * 4) *reinterpret_cast<uint4*>(ub + i) = make_uint4(0, 0, 0, 0);
-  fifo_apply_body(p, b, new_ids + noff.v[b], a, topk + toff.v[b], toff.v[b + 1] - toff.v[b], replace_T, wb, tb, ub, sc, cl, 0);
+  fifo_apply_body<false>(p, b, new_ids + noff.v[b], a, topk + toff.v[b], toff.v[b + 1] - toff.v[b], replace_T, wb, tb, ub, sc, cl, 0);
 }
 
 // candidate set built on the device, queue reading: distinct valid candidates in ascending order, then one batch
@@ -717,7 +954,7 @@ __global__ __launch_bounds__(kVocabThreads) void vocab_fifo_append_unique_kernel
   uint32_t* ub = reinterpret_cast<uint32_t*>(sc + 32);
   int32_t* cl = reinterpret_cast<int32_t*>(ub + nwords);
   int32_t* ulist = cl + kVocabThreads;
-  load_bitmaps(p, b, wb, tb, 0);
+  load_window_bitmap(p, b, wb);
   for (int i = tid * 4; i < nwords; i += kVocabThreads * 4) *reinterpret_cast<uint4*>(ub + i) = make_uint4(0, 0, 0, 0);
   __syncthreads();
   int bad = 0;
@@ -731,7 +968,7 @@ __global__ __launch_bounds__(kVocabThreads) void vocab_fifo_append_unique_kernel
   a = a < ucap ? a : ucap;
   __syncthreads();
   for (int i = tid * 4; i < nwords; i += kVocabThreads * 4) *reinterpret_cast<uint4*>(ub + i) = make_uint4(0, 0, 0, 0);
-  fifo_apply_body(p, b, ulist, a, nullptr, 0, 0, wb, tb, ub, sc, cl, bad);
+  fifo_apply_body<true>(p, b, ulist, a, nullptr, 0, 0, wb, tb, ub, sc, cl, bad);
 }
 
 hipError_t vocab_configure(nanospec_state* st) {
@@ -741,7 +978,7 @@ hipError_t vocab_configure(nanospec_state* st) {
   st->unique_cap = (160 * 1024 - 512) / 4 - (3 * st->vp.nwords + 32 + kVocabThreads);
   if (st->unique_cap < st->m_cap * st->k_cap) return hipErrorInvalidValue;
   st->unique_lds_bytes = (3 * st->vp.nwords + 32 + kVocabThreads + st->unique_cap) * 4;
-  st->fifo_lds_bytes = (3 * st->vp.nwords + 32 + kVocabThreads) * 4;
+  st->fifo_lds_bytes = (2 * st->vp.nwords + (st->vp.nwords > kFifoHash ? st->vp.nwords : kFifoHash) + 32 + kVocabThreads) * 4;
   return hipSuccess;
 }
 
@@ -749,7 +986,9 @@ hipError_t vocab_configure(nanospec_state* st) {
 // (a per-state limit would be lowered by the next, smaller state under a live larger one).
 hipError_t vocab_configure_device() {
   const void* fns[] = {reinterpret_cast<const void*>(vocab_apply_kernel), reinterpret_cast<const void*>(vocab_append_unique_kernel),
-                       reinterpret_cast<const void*>(vocab_fifo_append_unique_kernel), reinterpret_cast<const void*>(vocab_fifo_kernel)};
+                       reinterpret_cast<const void*>(vocab_fifo_append_unique_kernel), reinterpret_cast<const void*>(vocab_fifo_kernel),
+                       reinterpret_cast<const void*>(vocab_init_kernel), reinterpret_cast<const void*>(vocab_init_count_kernel<true, kRangeMany>),
+                       reinterpret_cast<const void*>(vocab_init_count_kernel<false, kRangeMany>)};
   for (const void* f : fns) {
     hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (e != hipSuccess) return e;
@@ -763,6 +1002,46 @@ hipError_t launch_vocab_clear(const nanospec_state* st, hipStream_t s) {
   if (blocks > 4096) blocks = 4096;
   vocab_clear_kernel<<<blocks, 256, 0, s>>>(st->vp, st->batch);
   return hipGetLastError();
+}
+
+template <int RANGE>
+static hipError_t run_vocab_init(const nanospec_state* st, const int32_t* d_ctx, const Offsets& coff, const int32_t* d_topk, const Offsets& toff,
+                                 int longest, hipStream_t s) {
+  constexpr int LDS = (RANGE + RANGE / 32) * 4;
+  const int ranges = (st->V + RANGE - 1) / RANGE;
+  hipError_t e;
+  if (longest <= kInitOwnMax) {
+    vocab_init_count_kernel<true, RANGE><<<dim3(ranges, 1, st->batch), kVocabThreads, LDS, s>>>(st->vp, d_ctx, coff, d_topk, toff);
+  } else {
+    e = launch_vocab_clear(st, s);
+    if (e != hipSuccess) return e;
+    const int segs = (longest + kSegTokens - 1) / kSegTokens;
+    vocab_init_count_kernel<false, RANGE><<<dim3(ranges, segs, st->batch), kVocabThreads, LDS, s>>>(st->vp, d_ctx, coff, d_topk, toff);
+  }
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  vocab_emit_kernel<RANGE><<<dim3(ranges, st->batch), kEmitThreads, 0, s>>>(st->vp);
+  return hipGetLastError();
+}
+
+hipError_t launch_vocab_init(const nanospec_state* st, const int32_t* d_ctx, const Offsets& coff, const int32_t* d_topk,
+                             const Offsets& toff, hipStream_t s) {
+  if (st->policy == NANOSPEC_POLICY_FIFO) {
+    hipError_t e = launch_vocab_clear(st, s);
+    return e == hipSuccess ? launch_vocab_apply(st, d_ctx, coff, d_topk, toff, 1, s) : e;
+  }
+  int longest = 0;
+  for (int b = 0; b < st->batch; ++b) {
+    const int a = coff.v[b + 1] - coff.v[b];
+    const int ae = a < st->window ? a : st->window;
+    longest = ae > longest ? ae : longest;
+  }
+  if (longest <= (st->batch <= kInitFewSeqs ? kInitSerialFew : kInitSerialMany)) {
+    vocab_init_kernel<<<st->batch, kVocabThreads, st->vocab_lds_bytes, s>>>(st->vp, d_ctx, coff, d_topk, toff);
+    return hipGetLastError();
+  }
+  return st->batch <= kInitFewSeqs ? run_vocab_init<kRangeFew>(st, d_ctx, coff, d_topk, toff, longest, s)
+                                   : run_vocab_init<kRangeMany>(st, d_ctx, coff, d_topk, toff, longest, s);
 }
 
 hipError_t launch_vocab_apply(const nanospec_state* st, const int32_t* d_new, const Offsets& noff,
