@@ -813,10 +813,10 @@ hipError_t launch_head(const void* W, const void* H, const int32_t* ids, const i
                        float* logits, float* partial, int64_t partial_bytes, const int32_t* opos, hipStream_t s) {
   const uint16_t* Wp = static_cast<const uint16_t*>(W);
   const uint16_t* Hp = static_cast<const uint16_t*>(H);
-  // more than 16 hidden rows of one sequence: the register-blocked product wherever it is the faster one (many rows: the
+  // more than 16 hidden rows: the register-blocked product wherever it is the faster one (many rows: the
   // dense comparison point of wide trees and batches; a few thousand rows: wide trees, instead of split-K + reduce)
-  if (wide_supported(M, d, batch, cap_rows))
-    return launch_head_wide(W, H, ids, n_dev, n_fixed, cap_rows, V, M, d, ld_logits, logits, opos, s);
+  if (wide_supported(V, M, d, batch, cap_rows))
+    return launch_head_wide(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld_logits, ids_stride, logits, opos, s);
   if (M <= 64)
     return launch_head_64(Wp, Hp, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld_logits, ids_stride, logits, partial,
                           partial_bytes, opos, s);

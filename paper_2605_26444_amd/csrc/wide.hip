@@ -25,11 +25,17 @@ constexpr int kWidePad = 32;     // bytes between LDS rows: rows r and r+4 share
 // Workgroup order: the chip hands consecutive workgroups to its eight dies in turn and each die has its own L2, so
 // the hidden-row blocks of one row block run back to back on one die (blockIdx -> (row block, hidden block) below)
 // and find the row block's weights in that L2.
-template <int WR, int WH, int FR, int FH, int BK, int D>
+// Several sequences (batch > 1): list, row count, hidden rows, logits and columns of sequence b lie at b times their
+// strides, and the sequences take turns (sequence fastest), so that one die works for few sequences and keeps their
+// hidden rows in its L2.
+// TAIL: any d % 8 == 0 -- the last step's pieces past column d are fetched from column 0 and parked as zeros, and the
+// number of steps may be odd.  Without it d % (D * BK) == 0.
+template <int WR, int WH, int FR, int FH, int BK, int D, bool TAIL>
 __global__ __launch_bounds__(64 * WR * WH) void head_wide_kernel(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H,
                                                         const int32_t* __restrict__ ids, const int32_t* __restrict__ n_dev, int n_fixed,
-                                                        int V, int M, int d, int64_t ld, float* __restrict__ logits, int row_blocks,
-                                                        int hid_blocks, const int32_t* __restrict__ opos, int opos_len) {
+                                                        int V, int batch, int M, int d, int64_t ld, int64_t ids_stride,
+                                                        float* __restrict__ logits, int row_blocks, int hid_blocks,
+                                                        const int32_t* __restrict__ opos, int opos_len) {
   constexpr int NT = 64 * WR * WH;
   constexpr int BM = WR * FR * 16, BN = WH * FH * 16;
   constexpr int CPR = BK / 8;                      // 16-byte pieces per row and step
@@ -42,18 +48,33 @@ __global__ __launch_bounds__(64 * WR * WH) void head_wide_kernel(const uint16_t*
   extern __shared__ __attribute__((aligned(16))) char smem[];
 
   // blockIdx -> die x = blockIdx % 8, slot r = blockIdx / 8; hidden block = r % hid_blocks, row block = (r / hid_blocks) * 8 + x
-  const int xq = blockIdx.x & 7, xr = blockIdx.x >> 3;
-  const int hb = xr % hid_blocks, rb = (xr / hid_blocks) * 8 + xq;
+  // several sequences: sequence = blockIdx % batch, hidden block and row block follow
+  int b = 0, hb, rb;
+  if (batch == 1) {
+    const int xq = blockIdx.x & 7, xr = blockIdx.x >> 3;
+    hb = xr % hid_blocks;
+    rb = (xr / hid_blocks) * 8 + xq;
+  } else {
+    const int xr = blockIdx.x / batch;
+    b = blockIdx.x % batch;
+    hb = xr % hid_blocks;
+    rb = xr / hid_blocks;
+  }
   if (rb >= row_blocks) return;
-  const int n = n_dev ? n_dev[0] : n_fixed;
+  const int n = n_dev ? n_dev[b] : n_fixed;
   const int j0 = rb * BM, m0 = hb * BN;
   if (j0 >= n) return;
+
+  if (ids) ids += b * ids_stride;
+  if (opos) opos += b * ids_stride;
+  H += (int64_t)b * M * d;
+  logits += (int64_t)b * M * ld;
 
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int wr = w / WH, wh = w % WH;
   const int pc = tid % CPR, pr = tid / CPR;        // this thread's 16-byte piece and first row of a pass
 
-  // byte offsets of this thread's pieces from W and H (below 4 GB each: checked by the launcher)
+  // byte offsets of this thread's rows from W and H (below 4 GB each: checked by the launcher)
   uint32_t aoff[NA], boff[NB];
   int rowv[NA];
 #pragma unroll
@@ -69,13 +90,13 @@ __global__ __launch_bounds__(64 * WR * WH) void head_wide_kernel(const uint16_t*
   for (int i = 0; i < NA; ++i) {
     int64_t row = rowv[i];
     row = row < 0 ? 0 : (row >= V ? V - 1 : row);
-    aoff[i] = (uint32_t)(row * d * 2 + pc * 16);
+    aoff[i] = (uint32_t)(row * d * 2);
   }
 #pragma unroll
   for (int i = 0; i < NB; ++i) {
     int m = m0 + pr + i * RPP;
     m = m < M ? m : M - 1;
-    boff[i] = (uint32_t)((int64_t)m * d * 2 + pc * 16);
+    boff[i] = (uint32_t)((int64_t)m * d * 2);
   }
   const char* Wb = reinterpret_cast<const char*>(W);
   const char* Hbase = reinterpret_cast<const char*>(H);
@@ -85,15 +106,24 @@ __global__ __launch_bounds__(64 * WR * WH) void head_wide_kernel(const uint16_t*
   // x BK x 2 bytes -- are in flight per workgroup all the time
   u32x4 ga[D][NA], gb[D][NB];
   auto fetch = [&](int ks, int set) {
-    const uint32_t off = (uint32_t)ks * BK * 2;
+    uint32_t off = (uint32_t)ks * BK * 2 + pc * 16;
+    if (TAIL && off >= (uint32_t)d * 2) off = 0;    // past the end of the row: its start instead, parked as zeros
 #pragma unroll
     for (int i = 0; i < NA; ++i) ga[set][i] = *reinterpret_cast<const u32x4*>(Wb + (aoff[i] + off));
 #pragma unroll
     for (int i = 0; i < NB; ++i) gb[set][i] = *reinterpret_cast<const u32x4*>(Hbase + (boff[i] + off));
   };
-  auto park = [&](int stage, int set) {
+  auto park = [&](int stage, int set, int ks) {
     char* As = smem + stage * STAGE;
     char* Bs = As + BM * STR;
+    if (TAIL && ks * BK + BK > d) {                 // uniform: only the last step
+      const bool in = ks * BK + pc * 8 < d;
+      const u32x4 zero = u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+      for (int i = 0; i < NA; ++i) ga[set][i] = in ? ga[set][i] : zero;
+#pragma unroll
+      for (int i = 0; i < NB; ++i) gb[set][i] = in ? gb[set][i] : zero;
+    }
 #pragma unroll
     for (int i = 0; i < NA; ++i) *reinterpret_cast<u32x4*>(As + (pr + i * RPP) * STR + pc * 16) = ga[set][i];
 #pragma unroll
@@ -171,13 +201,13 @@ __global__ __launch_bounds__(64 * WR * WH) void head_wide_kernel(const uint16_t*
   // Every fetch is unconditional -- past the end the last step is fetched again and never used -- because a load
   // under a branch makes the number of loads in flight unknowable at compile time, and every wait for one register
   // set then becomes a wait for all of them.  Set s % D receives step s + D right after it was parked for step s.
-  // D == 2: nk is even (the launcher checks d % (2 * BK) == 0) and the loop body has no branch at all; D = 4, 6, ..: any nk,
-  // the steps past the end skip their matrix work (a uniform branch around LDS reads and matrix instructions only).
-  const int nk = d / BK;
+  // Without TAIL and with D == 2, nk is even and the loop body has no branch at all; else any nk, and the steps past the
+  // end skip their matrix work (a uniform branch around LDS reads and matrix instructions only).
+  const int nk = (d + BK - 1) / BK;
 #pragma unroll
   for (int j = 0; j < D; ++j) fetch(j < nk ? j : nk - 1, j);
   __builtin_amdgcn_sched_barrier(0);
-  park(0, 0);
+  park(0, 0, 0);
   __syncthreads();
   for (int ks = 0; ks < nk; ks += D) {
 #pragma unroll
@@ -185,8 +215,8 @@ __global__ __launch_bounds__(64 * WR * WH) void head_wide_kernel(const uint16_t*
       const int st = ks + j;                        // LDS stage j & 1 holds this step, set (j + 1) % D holds (or awaits) the next
       fetch(st + D < nk ? st + D : nk - 1, j);
       __builtin_amdgcn_sched_barrier(0);            // the loads go out before the matrix work, not after it
-      if (D == 2 || st < nk) multiply(j & 1);
-      park((j + 1) & 1, (j + 1) % D);               // that stage's last readers passed the previous barrier
+      if ((D == 2 && !TAIL) || st < nk) multiply(j & 1);
+      park((j + 1) & 1, (j + 1) % D, st + 1 < nk ? st + 1 : nk - 1);               // that stage's last readers passed the previous barrier
       __syncthreads();
     }
   }
@@ -220,19 +250,26 @@ __global__ __launch_bounds__(64 * WR * WH) void head_wide_kernel(const uint16_t*
 
 template <int WR, int WH, int FR, int FH, int BK, int D>
 static hipError_t run_wide(const uint16_t* W, const uint16_t* H, const int32_t* ids, const int32_t* n_dev, int32_t n_fixed, int32_t cap_rows,
-                           int32_t V, int32_t M, int32_t d, int64_t ld, float* logits, const int32_t* opos, hipStream_t s) {
+                           int32_t V, int32_t batch, int32_t M, int32_t d, int64_t ld, int64_t ids_stride, float* logits, const int32_t* opos,
+                           hipStream_t s) {
   constexpr int BM = WR * FR * 16, BN = WH * FH * 16;
   constexpr int LDS = 2 * (BM + BN) * (BK * 2 + kWidePad);
   const int row_blocks = (cap_rows + BM - 1) / BM, hid_blocks = (M + BN - 1) / BN;
-  const int64_t grid = (int64_t)((row_blocks + 7) / 8) * hid_blocks * 8;
+  const int64_t grid = batch == 1 ? (int64_t)((row_blocks + 7) / 8) * hid_blocks * 8 : (int64_t)row_blocks * hid_blocks * batch;
   if (grid > 0x7fffffff || (int64_t)V * d * 2 > 0xffffffffll || (int64_t)M * d * 2 > 0xffffffffll) return hipErrorInvalidValue;
-  head_wide_kernel<WR, WH, FR, FH, BK, D><<<dim3((unsigned)grid), 64 * WR * WH, LDS, s>>>(W, H, ids, n_dev, n_fixed, V, M, d, ld, logits, row_blocks, hid_blocks, opos, cap_rows / 4 * 4);
+  if (d % (D * BK) == 0)
+    head_wide_kernel<WR, WH, FR, FH, BK, D, false><<<dim3((unsigned)grid), 64 * WR * WH, LDS, s>>>(
+        W, H, ids, n_dev, n_fixed, V, batch, M, d, ld, ids_stride, logits, row_blocks, hid_blocks, opos, cap_rows / 4 * 4);
+  else
+    head_wide_kernel<WR, WH, FR, FH, BK, D, true><<<dim3((unsigned)grid), 64 * WR * WH, LDS, s>>>(
+        W, H, ids, n_dev, n_fixed, V, batch, M, d, ld, ids_stride, logits, row_blocks, hid_blocks, opos, cap_rows / 4 * 4);
   return hipGetLastError();
 }
 
-hipError_t wide_configure_device() {
-  const void* fns[] = {reinterpret_cast<const void*>(head_wide_kernel<4, 1, 2, 4, 64, 2>), reinterpret_cast<const void*>(head_wide_kernel<4, 2, 4, 4, 64, 2>),
-                       reinterpret_cast<const void*>(head_wide_kernel<2, 4, 8, 4, 64, 2>), reinterpret_cast<const void*>(head_wide_kernel<2, 2, 1, 1, 256, 2>)};
+template <int WR, int WH, int FR, int FH, int BK, int D>
+static hipError_t configure_wide() {
+  const void* fns[] = {reinterpret_cast<const void*>(head_wide_kernel<WR, WH, FR, FH, BK, D, false>),
+                       reinterpret_cast<const void*>(head_wide_kernel<WR, WH, FR, FH, BK, D, true>)};
   for (const void* f : fns) {
     hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (e != hipSuccess) return e;
@@ -240,28 +277,47 @@ hipError_t wide_configure_device() {
   return hipSuccess;
 }
 
-// Which row capacities the register-blocked product takes (one sequence or the dense head, 16 < M, no column map):
-//   at least 16384 rows and d % 128 == 0: the three block shapes of launch_head_wide below;
-//   a few thousand rows, M <= 64 and d % 512 == 0: the 32 x 32 shape (no split of K, one launch) from the capacity on
-//   at which it beats split-K + reduce (measured at d = 3584, M = 64 / 32, live rows = capacity: 8.9 against 10.7 us
-//   at 1000 rows, 11.6 / 11.7 at 2000, 14.9 / 12.3 at 3000, 25.4 / 21.2 at 8000; M = 32: 12.7 / 12.4 at 3000, 17.6 / 13.3
-//   at 5000).
-bool wide_supported(int32_t M, int32_t d, int32_t batch, int32_t cap_rows) {
-  if (batch != 1 || M <= 16) return false;
-  if (cap_rows >= 16384) return d % 128 == 0;                    // an even number of 64-column steps
-  return M <= 64 && d % 512 == 0 && cap_rows >= (M <= 32 ? 4096 : 2560);
+hipError_t wide_configure_device() {
+  hipError_t e = configure_wide<2, 2, 1, 1, 128, 4>();
+  if (e == hipSuccess) e = configure_wide<2, 4, 1, 1, 128, 2>();
+  if (e == hipSuccess) e = configure_wide<2, 4, 2, 1, 128, 2>();
+  if (e == hipSuccess) e = configure_wide<4, 1, 1, 2, 128, 2>();
+  if (e == hipSuccess) e = configure_wide<4, 1, 2, 2, 64, 2>();
+  if (e == hipSuccess) e = configure_wide<4, 1, 2, 4, 64, 2>();
+  if (e == hipSuccess) e = configure_wide<4, 2, 4, 4, 64, 2>();
+  if (e == hipSuccess) e = configure_wide<2, 4, 8, 4, 64, 2>();
+  return e;
 }
 
-// One sequence (or the dense head), more than 16 hidden rows.
-//   a few thousand rows (wide draft trees): latency-bound.  32 x 32 logits per workgroup of four wavefronts, 256-column
-//     steps (512 bytes of a row per load pass, 64 KB in flight per workgroup) -- the rows alone cannot fill the chip,
-//     so the hidden rows are split in two as well.  3000 rows x 64 hidden rows, d = 3584: 12.2 us in one launch against
-//     10 + 4 us for split-K and its reduce.  The time is the 458 KB every workgroup pulls through its compute unit's
-//     L1 (11.7 us without any matrix work); three or four register sets in flight instead of two: 13.6 / 14.1 us;
-//     128-column steps 13.6; 64 x 16 logits 14.9.
-//   many rows, up to 64 hidden rows: memory-bound.  128 x 64 logits per workgroup of four wavefronts, 60 KB of LDS, two
-//     workgroups per compute unit (dense 152k x 3584 head at 64 hidden rows: 205-219 us, the vendor GEMM 205-208,
-//     5.2 TB/s; 256-byte steps with one workgroup per compute unit: 209 us).
+// Which products the register-blocked kernel takes: more than 16 hidden rows, rows that 32-bit byte offsets reach, and
+//   * any number of rows while d <= 2048: one launch whose time is its d / 128 steps (6.0 us at d = 1152, 7.2 at 2048) against
+//     two launches of split-K + reduce (9.6, 8.9);
+//   * longer rows from the capacity on at which it beats split-K + reduce, whose workgroups each walk 512 columns only
+//     (d = 4096: M = 64, 1000 live rows 11.1 against 9.5 us, 2000: 10.7 / 11.4, 3000: 11.7 / 12.4; M = 24, 2000 live rows
+//     11.6 / 10.7, 3000: 12.4 / 13.1).
+bool wide_supported(int32_t V, int32_t M, int32_t d, int32_t batch, int32_t cap_rows) {
+  if (M <= 16 || (int64_t)V * d * 2 > 0xffffffffll || (int64_t)M * d * 2 > 0xffffffffll) return false;
+  const int64_t rows = (int64_t)cap_rows * batch;
+  if (rows * ((M + 31) / 32) > 0x40000000ll) return false;         // workgroups of one launch
+  if (M > 64 && batch == 1 && rows < 16384) return false;          // many hidden rows on a short list: 64 at a time
+  return d <= 2048 || rows >= (M <= 32 ? 4096 : 2560);
+}
+
+// The block shapes.  Up to 64 hidden rows a launch is bound by the bytes a compute unit has in flight over the memory
+// latency (few rows) or by HBM (many), so the block grows with the rows: the smallest one while larger blocks would leave
+// compute units without work, larger ones to fetch the hidden rows (and, beyond 32 x 32, W_head) less often.  A launch
+// only knows the capacity of the lists; thresholds are for live rows around 0.6 of it, dense heads (live == capacity) count double.
+//   32 x 32, four register sets of 128 columns: d = 3584, M = 64, 3000 live rows 11.7 us; two sets of 256 columns 12.2;
+//     two of 128 13.3; four of 64 13.1; 32 x 64 15.4; 64 x 64 19.8.  With d = 3712 12.3 (split-K + reduce with bounds tests 16.4).
+//   32 x 64, eight wavefronts: 4 sequences of 2000 rows, M = 60, d = 4096: 18.1 us; 32 x 32 23.7, 64 x 64 22.6 (slice-loop
+//     kernel of head.hip 28.4); at 2 sequences 16.9 against 14.3 for 32 x 32.
+//   64 x 64, eight wavefronts: 8 sequences of 2000 rows 25.1 us; 32 x 64 31.5, 32 x 32 38.1, 128 x 64 37.1 (slice-loop kernel
+//     36.4); one list of 12000 rows 26.8 against 34.2 / 39.0.
+//   128 x 64, four wavefronts, 60 KB of LDS, two workgroups per compute unit: 64 sequences of 2300 rows, d = 2048: 92 us; 64 x 64
+//     98 (slice-loop kernel 119); the dense 128k x 4096 head 187 us = 5.6 TB/s, 64 x 64 203.
+//   up to 32 hidden rows: 32 x 32 (16 sequences of 1500 rows 32 us, slice-loop kernel 49), on long lists 64 x 32 (64 sequences of
+//     2000 rows, M = 17: 104 us; 32 x 32 115, 128 x 64 121, slice-loop kernel 181) and, dense, 128 x 32 (128k x 4096, M = 24: 159 us
+//     = 6.6 TB/s; 128 x 64 170, 64 x 32 169).
 //   up to 128: 256 x 128 logits, eight wavefronts of 64 x 64.
 //   more: compute-bound.  256 x 256 logits per workgroup, eight wavefronts of 128 x 64 (one fragment read feeds four or
 //     eight matrix instructions), all 160 KB of LDS for the two stages.  512 hidden rows on the 128k x 4096 matrix:
@@ -269,13 +325,23 @@ bool wide_supported(int32_t M, int32_t d, int32_t batch, int32_t cap_rows) {
 //     logits 844 us (one wavefront per SIMD: nothing overlaps an LDS round trip), eight of 64 x 64 644 us, with the
 //     scheduling groups 614 us, 256 x 256 logits in 32-column steps 553 us.
 hipError_t launch_head_wide(const void* W, const void* H, const int32_t* ids, const int32_t* n_dev, int32_t n_fixed, int32_t cap_rows,
-                            int32_t V, int32_t M, int32_t d, int64_t ld, float* logits, const int32_t* opos, hipStream_t s) {
+                            int32_t V, int32_t batch, int32_t M, int32_t d, int64_t ld, int64_t ids_stride, float* logits,
+                            const int32_t* opos, hipStream_t s) {
   const uint16_t* Wp = static_cast<const uint16_t*>(W);
   const uint16_t* Hp = static_cast<const uint16_t*>(H);
-  if (cap_rows < 16384) return run_wide<2, 2, 1, 1, 256, 2>(Wp, Hp, ids, n_dev, n_fixed, cap_rows, V, M, d, ld, logits, opos, s);
-  if (M <= 64) return run_wide<4, 1, 2, 4, 64, 2>(Wp, Hp, ids, n_dev, n_fixed, cap_rows, V, M, d, ld, logits, opos, s);
-  if (M <= 128) return run_wide<4, 2, 4, 4, 64, 2>(Wp, Hp, ids, n_dev, n_fixed, cap_rows, V, M, d, ld, logits, opos, s);
-  return run_wide<2, 4, 8, 4, 64, 2>(Wp, Hp, ids, n_dev, n_fixed, cap_rows, V, M, d, ld, logits, opos, s);
+  const int64_t rows = (int64_t)cap_rows * batch * (n_dev ? 1 : 2);
+  auto run = [&](auto shape) { return shape(Wp, Hp, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s); };
+  if (M <= 32) {
+    if (rows < 65536 && n_dev) return run(run_wide<2, 2, 1, 1, 128, 4>);
+    if (n_dev) return run(run_wide<4, 1, 1, 2, 128, 2>);
+    return run(run_wide<4, 1, 2, 2, 64, 2>);
+  }
+  if (rows < 10240) return run(run_wide<2, 2, 1, 1, 128, 4>);
+  if (rows < 18432) return run(run_wide<2, 4, 1, 1, 128, 2>);
+  if (rows < (n_dev ? 98304 : 49152)) return run(run_wide<2, 4, 2, 1, 128, 2>);
+  if (M <= 64 || batch > 1) return run(run_wide<4, 1, 2, 4, 64, 2>);
+  if (M <= 128) return run(run_wide<4, 2, 4, 4, 64, 2>);
+  return run(run_wide<2, 4, 8, 4, 64, 2>);
 }
 
 }  // namespace nanospec

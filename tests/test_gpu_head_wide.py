@@ -1,0 +1,63 @@
+"""The register-blocked head (more than 16 hidden rows) on every block shape it is launched in: ragged batches with an
+empty and a one-row list, lists that end inside a block, hidden sizes that are no whole number of column steps (down to
+one 16-byte piece) or an odd number of them, hidden rows that end inside a block.  Against fp64; the bound is that of an
+fp32 sum of d exact products in any order, d * 2^-24 * sum |w h|."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2605_26444_amd import binding as B
+
+from harness import csr, dev_ids
+
+pytestmark = pytest.mark.gpu
+
+
+def _normal(seed, *shape):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    return torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+
+
+def _check(got, W, H, what):
+    w, h = W.double(), H.double()
+    bound = W.shape[1] * 2.0 ** -24 * (h.abs() @ w.abs().T)
+    assert torch.all((got.double() - h @ w.T).abs() <= bound), what
+
+
+@pytest.mark.parametrize("batch,M,d,window", [
+    (1, 17, 8, 100), (1, 64, 520, 3000), (2, 33, 640, 700), (4, 32, 1096, 3000),       # 32 x 32
+    (2, 70, 264, 300),                                                                 # ... more hidden rows than 64 per sequence
+    (1, 64, 4104, 2500), (1, 20, 2056, 700),                                           # both sides of the split-K line
+    (3, 64, 136, 4100), (3, 40, 384, 4100),                                            # 32 x 64
+    (7, 64, 200, 4100), (5, 50, 768, 5000),                                            # 64 x 64
+    (40, 20, 72, 2000), (40, 32, 264, 2000),                                           # 64 x 32
+    (30, 64, 72, 4000), (30, 35, 192, 4000),                                           # 128 x 64
+])
+def test_ragged_batches(batch, M, d, window):
+    V = 20000
+    rng = np.random.default_rng(batch * 1000 + M)
+    n = rng.integers(window // 2, window + 1, batch)
+    n[0] = window
+    if batch > 2:
+        n[1], n[2] = 0, 1
+    ids = [np.sort(rng.permutation(V)[:x]).astype(np.int32) for x in n]
+    W, H = _normal(1, V, d), _normal(2, batch, M, d)
+    st = B.State(V, d, batch, window, 1, M, 1)
+    flat, off = csr(ids)
+    B.nanospec_vocab_init(st.h, dev_ids(flat), off, None, np.zeros(batch + 1, np.int32))
+    logits = torch.full((batch, M, st.capacity), 7.0, dtype=torch.float32, device="cuda")
+    B.nanospec_sparse_head(st.h, W, H, M, logits)
+    for b in range(batch):
+        _check(logits[b, :, :n[b]], W[torch.from_numpy(ids[b]).long().cuda()], H[b], b)
+    st.close()
+
+
+@pytest.mark.parametrize("V,M,d", [(30001, 24, 200), (17000, 33, 72), (40002, 64, 1032), (50000, 100, 192), (33333, 200, 72), (20000, 300, 520)])
+def test_dense(V, M, d):
+    W, H = _normal(3, V, d), _normal(4, M, d)
+    logits = torch.full((M + 1, V), 7.0, dtype=torch.float32, device="cuda")
+    B.nanospec_dense_head(W, H, V, d, M, logits[:M])
+    _check(logits[:M], W, H, "dense")
+    assert torch.all(logits[M] == 7.0)
