@@ -118,12 +118,10 @@ __device__ __forceinline__ void wave_select(float (&v)[EPT], int k, int lane, Em
 constexpr int kLaneCand = 4;   // candidates per lane the owner path keeps in registers
 
 template <int EPT, int NW, bool FINAL, bool LSE>
-__global__ __launch_bounds__(64 * NW) void topk_select_kernel(const float* __restrict__ logits, int64_t ld,
-                                                             const int32_t* __restrict__ ids, int64_t ids_stride,
-                                                             const int32_t* __restrict__ n_dev, int n_fixed, int M, int k,
-                                                             int32_t* __restrict__ out_ids, float* __restrict__ out_vals,
-                                                             float* __restrict__ cand_val, int32_t* __restrict__ cand_pos,
-                                                             float2* __restrict__ cand_ms) {
+__device__ __forceinline__ void topk_select(const float* __restrict__ logits, int64_t ld, const int32_t* __restrict__ ids, int64_t ids_stride,
+                                            const int32_t* __restrict__ n_dev, int n_fixed, int M, int k, int32_t* __restrict__ out_ids,
+                                            float* __restrict__ out_vals, float* __restrict__ cand_val, int32_t* __restrict__ cand_pos,
+                                            float2* __restrict__ cand_ms) {
   constexpr int E2 = (NW * kMaxK + 63) / 64;
   __shared__ float s_val[NW * kMaxK];
   __shared__ int s_pos[NW * kMaxK];
@@ -147,8 +145,29 @@ __global__ __launch_bounds__(64 * NW) void topk_select_kernel(const float* __res
       v[e + 3] = x.w;
     }
   } else {
+    // rows at any 4-byte address: one 16-byte load more from the aligned address below the run, shifted into place (16 single
+    // loads per lane, 64 bytes apart, took twice the time: 60 rows of 30001 18 against 10 us); the pieces that reach over the row's ends are read element by element
+    const int sh = (int)(((uint32_t)reinterpret_cast<uintptr_t>(src) & 15u) >> 2);   // uniform: elements from that address to the run
+    float w[EPT + 4];
 #pragma unroll
-    for (int e = 0; e < EPT; ++e) v[e] = (p0 + e < ld) ? src[p0 + e] : -INFINITY;
+    for (int e = 0; e < EPT + 4; e += 4) {
+      const int q = p0 - sh + e;
+      float4 x = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+      if (q >= 0 && q + 3 < ld) {
+        x = *reinterpret_cast<const float4*>(src + q);
+      } else if (q + 3 >= 0 && q < ld) {
+        if (q >= 0) x.x = src[q];
+        if (q + 1 >= 0 && q + 1 < ld) x.y = src[q + 1];
+        if (q + 2 >= 0 && q + 2 < ld) x.z = src[q + 2];
+        if (q + 3 < ld) x.w = src[q + 3];
+      }
+      w[e] = x.x;
+      w[e + 1] = x.y;
+      w[e + 2] = x.z;
+      w[e + 3] = x.w;
+    }
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) v[e] = sel(sh & 2, sel(sh & 1, w[e + 3], w[e + 2]), sel(sh & 1, w[e + 1], w[e]));
   }
   const int n = n_dev ? n_dev[b] : n_fixed;
 #pragma unroll
@@ -398,6 +417,336 @@ __global__ __launch_bounds__(64 * NW) void topk_select_kernel(const float* __res
   }
 }
 
+template <int EPT, int NW, bool FINAL, bool LSE>
+__global__ __launch_bounds__(64 * NW) void topk_select_kernel(const float* __restrict__ logits, int64_t ld,
+                                                             const int32_t* __restrict__ ids, int64_t ids_stride,
+                                                             const int32_t* __restrict__ n_dev, int n_fixed, int M, int k,
+                                                             int32_t* __restrict__ out_ids, float* __restrict__ out_vals,
+                                                             float* __restrict__ cand_val, int32_t* __restrict__ cand_pos,
+                                                             float2* __restrict__ cand_ms) {
+  topk_select<EPT, NW, FINAL, LSE>(logits, ld, ids, ids_stride, n_dev, n_fixed, M, k, out_ids, out_vals, cand_val, cand_pos, cand_ms);
+}
+
+// Long rows (more positions than one workgroup's registers hold): one workgroup per row walks it in pieces of 16 logits
+// per thread, two pieces' loads in flight behind the one that is worked on.  The first piece gives a threshold exactly as
+// above; what reaches it goes to a list in LDS, the list's k-th best becomes the threshold, and of the later pieces only
+// what is strictly greater is appended (an equal value at a higher position loses the tie against k earlier ones).
+// A full list is cut back to its k best.  A piece that alone overflows it (a ramp, thousands of equal values) raises the
+// threshold to the exact k-th largest lane maximum: fewer than k lanes then hold anything greater (16 values each at most, they
+// fit), and of the values equal to it the k first by position.
+// The final order is by (value, position) explicitly, so slots are handed out by an atomic counter.
+// Bound by the row's bytes; a thread's loads are consecutive 16-byte pieces across the workgroup from the row's first
+// aligned element on -- the up to three elements before it and after the last whole piece are single loads -- so rows of
+// any stride stream at the same rate.
+constexpr int kStreamList = 2048;
+
+template <int NW, bool LSE>
+__device__ __forceinline__ void topk_stream(const float* __restrict__ logits, int64_t ld, const int32_t* __restrict__ ids, int64_t ids_stride,
+                                            const int32_t* __restrict__ n_dev, int n_fixed, int M, int k, int32_t* __restrict__ out_ids,
+                                            float* __restrict__ out_vals) {
+  constexpr int NT = 64 * NW, QP = 4 * NT;                 // threads; 16-byte pieces per step
+  __shared__ __attribute__((aligned(16))) float s_v[kStreamList + 4];
+  __shared__ __attribute__((aligned(16))) int s_p[kStreamList + 4];
+  __shared__ int s_r[kStreamList];
+  __shared__ int s_n;
+  __shared__ float s_thr[NW], s_max[NW], s_sum[NW];
+  __shared__ float s_kth;
+  __shared__ int s_eq[NW];
+  const int m = blockIdx.y, b = blockIdx.z;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int64_t row = (int64_t)b * M + m;
+  const float* src = logits + row * ld;
+  const int head = (int)((16u - ((uint32_t)reinterpret_cast<uintptr_t>(src) & 15u)) & 15u) >> 2;   // elements before the first aligned one
+  const float4* base = reinterpret_cast<const float4*>(src + head);
+  const int qcap = (int)((ld - head) >> 2);                // whole pieces inside the row's stride (the launcher sends long rows only)
+  float4 x[3][4];
+  auto load = [&](int p, float4(&v)[4]) {                  // unconditional: past the end the last piece again, masked later
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int q = p * QP + j * NT + tid;
+      v[j] = base[q < qcap ? q : qcap - 1];
+    }
+  };
+  load(0, x[0]);
+  load(1, x[1]);
+  const int n = n_dev ? n_dev[b] : n_fixed;
+  const int nq = n > head ? (n - head) >> 2 : 0;
+  const int steps = nq > QP ? (nq + QP - 1) / QP : 1;
+  // the elements outside the whole pieces: threads 0-3 before, 4-7 behind
+  const int xpos = tid < 4 ? (tid < head ? tid : n) : head + 4 * nq + tid - 4;
+  const bool has_x = tid < 8 && xpos < n && xpos < ld;
+  const float xv = has_x ? src[xpos] : -INFINITY;
+  if (tid == 0) s_n = 0;
+
+  float T = -INFINITY;                                     // at least k elements so far are >= T (or T is -inf)
+  int held = 0;                                            // list entries before the piece; both uniform over the workgroup
+  float lm = has_x ? xv : -INFINITY, ls = has_x ? 1.f : 0.f;   // this thread's running maximum and sum of exp(z - maximum)
+
+  // k-th largest over the lanes' maxima, as in topk_select_kernel; one barrier
+  auto vote = [&](float ml, int valid) -> float {
+    int nwe = (valid + 32) / 64;
+    nwe = nwe < 1 ? 1 : (nwe > NW ? NW : nwe);
+    const int rounds = (k + nwe - 1) / nwe;
+    float y = ml, thr = -INFINITY;
+    for (int r = 0; r < rounds; ++r) {
+      thr = wave_max(y);
+      const unsigned long long ball = __ballot(y == thr);
+      const int L = ball ? __ffsll(ball) - 1 : 0;
+      if (lane == L) y = -INFINITY;
+    }
+    if (lane == 0) s_thr[wave] = thr;
+    __syncthreads();
+    float t = s_thr[0];
+#pragma unroll
+    for (int ww = 1; ww < NW; ++ww) t = fminf(t, ww < nwe ? s_thr[ww] : INFINITY);
+    return t;
+  };
+  // every list entry's rank (value descending, position ascending) into s_r; the list is complete at the call
+  auto rank_list = [&](int C) {
+    if (tid < 4) {
+      s_v[C + tid] = __builtin_nanf("");
+      s_p[C + tid] = INT_MAX;
+    }
+    for (int t = tid; t < C; t += NT) s_r[t] = 0;
+    __syncthreads();
+    const int lg = C <= 1 ? 0 : 32 - __clz(C - 1);
+    const int items = ((C + 3) >> 2) << lg;
+    for (int i = tid; i < items; i += NT) {
+      const int t = i & ((1 << lg) - 1), q = (i >> lg) * 4;
+      if (t < C) {
+        const float val = s_v[t];
+        const int pos = s_p[t];
+        const float4 o = *reinterpret_cast<const float4*>(&s_v[q]);
+        const int4 op = *reinterpret_cast<const int4*>(&s_p[q]);
+        int r = (o.x > val || (o.x == val && op.x < pos)) ? 1 : 0;
+        r += (o.y > val || (o.y == val && op.y < pos)) ? 1 : 0;
+        r += (o.z > val || (o.z == val && op.z < pos)) ? 1 : 0;
+        r += (o.w > val || (o.w == val && op.w < pos)) ? 1 : 0;
+        if (r) atomicAdd(&s_r[t], r);
+      }
+    }
+    __syncthreads();
+  };
+  // the list's k best stay, in order; the k-th is the threshold from here on
+  auto cut_back = [&](int C) {
+    rank_list(C);
+    float kv[kStreamList / NT];
+    int kp[kStreamList / NT], kr[kStreamList / NT];
+#pragma unroll
+    for (int i = 0; i < kStreamList / NT; ++i) {
+      const int t = tid + i * NT;
+      kr[i] = t < C ? s_r[t] : k;
+      kv[i] = t < C ? s_v[t] : 0.f;
+      kp[i] = t < C ? s_p[t] : 0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kStreamList / NT; ++i)
+      if (kr[i] < k) {
+        s_v[kr[i]] = kv[i];
+        s_p[kr[i]] = kp[i];
+      }
+    if (tid == 0) s_n = k;
+    __syncthreads();
+    T = s_v[k - 1];
+  };
+  auto append = [&](const float4(&v)[4], int p, float t, bool equal_too) {
+    uint32_t f = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const bool in = p * QP + j * NT + tid < nq;
+      f |= (uint32_t)(in && (v[j].x > t || (equal_too && v[j].x == t))) << (4 * j);
+      f |= (uint32_t)(in && (v[j].y > t || (equal_too && v[j].y == t))) << (4 * j + 1);
+      f |= (uint32_t)(in && (v[j].z > t || (equal_too && v[j].z == t))) << (4 * j + 2);
+      f |= (uint32_t)(in && (v[j].w > t || (equal_too && v[j].w == t))) << (4 * j + 3);
+    }
+    if (f) {
+      int at = atomicAdd(&s_n, __popc(f));
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float e4[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if ((f >> (4 * j + e)) & 1u) {
+            if (at < kStreamList) {
+              s_v[at] = e4[e];
+              s_p[at] = head + 4 * (p * QP + j * NT + tid) + e;
+            }
+            ++at;
+          }
+      }
+    }
+  };
+  // The piece's values do not fit the list (uniform; the list holds `held` entries of earlier pieces, kStreamList / 4 at most)
+  auto overflow = [&](const float4(&v)[4], int p, float ml) {
+    static_assert(kStreamList - kStreamList / 4 >= NT && kStreamList - kStreamList / 4 >= 16 * kMaxK + kMaxK + 8, "room behind the held entries");
+    __syncthreads();                                       // everybody knows that it overflowed
+    float* lane_max = s_v + (kStreamList - NT);
+    lane_max[tid] = ml;
+    if (tid == 0) s_n = held;
+    __syncthreads();
+    int r = 0;
+    for (int q = 0; q < NT; q += 4) {
+      const float4 o = *reinterpret_cast<const float4*>(&lane_max[q]);
+      r += (o.x > ml || (o.x == ml && q < tid)) + (o.y > ml || (o.y == ml && q + 1 < tid)) + (o.z > ml || (o.z == ml && q + 2 < tid)) +
+           (o.w > ml || (o.w == ml && q + 3 < tid));
+    }
+    if (r == k - 1) s_kth = ml;                            // ranks are distinct and k <= 64 <= NT: one thread
+    __syncthreads();
+    const float t = s_kth;
+    const bool raised = t > T || p == 0;                   // else: nothing equal to T is wanted, and fewer than k lanes hold more
+    if (raised) T = t;
+    append(v, p, T, false);
+    if (raised) {
+      int taken = 0;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {                        // position order: j, then thread, then element
+        const float e4[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
+        const bool in = p * QP + j * NT + tid < nq;
+        int mine = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) mine += (in && e4[e] == T) ? 1 : 0;
+        int incl = mine;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+          const int u = __shfl_up(incl, o);
+          incl += lane >= o ? u : 0;
+        }
+        if (lane == 63) s_eq[wave] = incl;
+        __syncthreads();
+        int off = incl - mine, tot = 0;
+        for (int ww = 0; ww < NW; ++ww) {
+          off += ww < wave ? s_eq[ww] : 0;
+          tot += s_eq[ww];
+        }
+        off += taken;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (in && e4[e] == T) {
+            if (off < k) {
+              const int at = atomicAdd(&s_n, 1);
+              s_v[at] = e4[e];
+              s_p[at] = head + 4 * (p * QP + j * NT + tid) + e;
+            }
+            ++off;
+          }
+        taken += tot;
+        __syncthreads();
+      }
+    }
+  };
+  auto process = [&](float4(&v)[4], int p) {
+    float ml = -INFINITY;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const bool in = p * QP + j * NT + tid < nq;
+      v[j].x = in ? v[j].x : -INFINITY;
+      v[j].y = in ? v[j].y : -INFINITY;
+      v[j].z = in ? v[j].z : -INFINITY;
+      v[j].w = in ? v[j].w : -INFINITY;
+      ml = fmaxf(ml, fmaxf(fmaxf(v[j].x, v[j].y), fmaxf(v[j].z, v[j].w)));
+    }
+    if (LSE) {
+      const float nm = fmaxf(lm, ml);
+      const float ref = nm == -INFINITY ? 0.f : nm;
+      float se = 0.f;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) se += (__expf(v[j].x - ref) + __expf(v[j].y - ref)) + (__expf(v[j].z - ref) + __expf(v[j].w - ref));
+      ls = ls * __expf(lm - ref) + se;                     // lm == -inf: the factor is 0
+      lm = nm;
+    }
+    const int valid = nq - p * QP < NT ? nq - p * QP : NT;
+    if (p == 0) T = vote(ml, valid);                       // its barrier also publishes s_n = 0
+    append(v, p, T, p == 0);
+    __syncthreads();
+    int C = s_n;
+    if (C > kStreamList - 8) {                             // uniform; eight entries are kept for the elements outside the pieces
+      overflow(v, p, ml);
+      __syncthreads();
+      C = s_n;
+    }
+    if (p + 1 < steps && (p == 0 || C > kStreamList / 4)) {   // a full piece: C >= k
+      cut_back(C);
+      held = k;
+    } else {
+      __syncthreads();                                     // s_n has been read by all before the next piece adds to it
+      held = C;
+    }
+  };
+  for (int p = 0; p < steps; p += 3) {
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      load(p + j + 2, x[(j + 2) % 3]);
+      if (p + j < steps) process(x[j], p + j);
+    }
+  }
+
+  float lse = 0.f;
+  if (LSE) {                                               // lanes, then wavefronts, in a fixed order
+    const float wm = wave_max(lm);
+    const float ws = wave_add(ls * __expf(lm - (wm == -INFINITY ? 0.f : wm)));
+    if (lane == 0) {
+      s_max[wave] = wm;
+      s_sum[wave] = ws;
+    }
+    __syncthreads();
+    const float pm = lane < NW ? s_max[lane] : -INFINITY;
+    float zmax = wave_max(pm);
+    zmax = zmax == -INFINITY ? 0.f : zmax;
+    lse = zmax + logf(wave_add(lane < NW ? s_sum[lane] * expf(pm - zmax) : 0.f));
+  }
+  auto write = [&](int r, int pos, float val, int gid) {
+    out_ids[row * k + r] = gid;
+    if (out_vals) out_vals[row * k + r] = (LSE && val != -INFINITY) ? val - lse : val;
+  };
+  if (has_x) {                                             // a superset of the winners is listed: the rank decides
+    const int at = atomicAdd(&s_n, 1);
+    s_v[at] = xv;
+    s_p[at] = xpos;
+  }
+  __syncthreads();
+  const int C = s_n;
+  {
+    int gid[kStreamList / NT];                             // requested before the ranking, used behind it
+#pragma unroll
+    for (int i = 0; i < kStreamList / NT; ++i) {
+      const int t = tid + i * NT;
+      gid[i] = t < C ? s_p[t] : 0;
+      if (ids && t < C) gid[i] = ids[b * ids_stride + gid[i]];
+    }
+    __syncthreads();
+    rank_list(C);
+#pragma unroll
+    for (int i = 0; i < kStreamList / NT; ++i) {
+      const int t = tid + i * NT;
+      if (t < C && s_r[t] < k) write(s_r[t], s_p[t], s_v[t], gid[i]);
+    }
+  }
+  if (tid >= C && tid < k) {                            // padding slots when fewer than k exist
+    out_ids[row * k + tid] = -1;
+    if (out_vals) out_vals[row * k + tid] = -INFINITY;
+  }
+}
+
+template <int NW, bool LSE>
+__global__ __launch_bounds__(64 * NW) void topk_stream_kernel(const float* __restrict__ logits, int64_t ld, const int32_t* __restrict__ ids,
+                                                              int64_t ids_stride, const int32_t* __restrict__ n_dev, int n_fixed, int M,
+                                                              int k, int32_t* __restrict__ out_ids, float* __restrict__ out_vals) {
+  topk_stream<NW, LSE>(logits, ld, ids, ids_stride, n_dev, n_fixed, M, k, out_ids, out_vals);
+}
+
+// Lists whose capacity is beyond one workgroup's registers but whose live row count mostly is not: one launch that selects
+// either way, by the count on the device.
+template <bool LSE>
+__global__ __launch_bounds__(1024) void topk_list_kernel(const float* __restrict__ logits, int64_t ld, const int32_t* __restrict__ ids,
+                                                         int64_t ids_stride, const int32_t* __restrict__ n_dev, int n_fixed, int M, int k,
+                                                         int32_t* __restrict__ out_ids, float* __restrict__ out_vals) {
+  if ((n_dev ? n_dev[blockIdx.z] : n_fixed) <= kTopkChunk)
+    topk_select<16, 16, true, LSE>(logits, ld, ids, ids_stride, n_dev, n_fixed, M, k, out_ids, out_vals, nullptr, nullptr, nullptr);
+  else
+    topk_stream<16, LSE>(logits, ld, ids, ids_stride, n_dev, n_fixed, M, k, out_ids, out_vals);
+}
+
 // Merge the per-chunk winners of one row (nchunks*k <= 1024 candidates, in position order).
 template <bool LSE>
 __global__ __launch_bounds__(64) void topk_merge_kernel(const float* __restrict__ cand_val, const int32_t* __restrict__ cand_pos,
@@ -481,6 +830,25 @@ static hipError_t launch_topk_t(const float* logits, int64_t ld, const int32_t* 
   const int nch = chunks_for(cap);
   const int64_t need = topk_workspace_bytes(cap, batch * M, k);
   if (nch * k > 1024 || ws == nullptr || ws_bytes < need) return hipErrorInvalidValue;
+  // Beyond that, one workgroup per row for many rows and for lists (whose live rows are a fraction of their capacity, and
+  // where a second launch costs more than the steps), else -- few dense rows -- chunks and a merge.  Measured, chunks + merge
+  // against one workgroup per row: 1024 rows of 128256, k = 3: 202 / 97 us (5.4 TB/s; of 128255 381 / 97), 256 rows 48 / 27, 128
+  // rows 28 / 21, 64 rows, k = 10: 19 / 23, 8 rows 12 / 23; lists for 16 hidden rows: 8400 ids in a capacity of 33k 6.6 / 5.0, 32800
+  // ids 12.5 / 11.0.  Eight wavefronts instead of sixteen from 512 rows on (2048 rows of 32000, k = 5: 52 against 77 us; 500 rows
+  // of 50001, k = 40: 45 against 42).
+  const int64_t nrows = (int64_t)batch * M;
+  if (nrows >= 512) {
+    topk_stream_kernel<8, LSE><<<rows, 512, 0, s>>>(logits, ld, ids, ids_stride, n_dev, n_fixed, M, k, out_ids, out_vals);
+    return hipGetLastError();
+  }
+  if (n_dev) {
+    topk_list_kernel<LSE><<<rows, 1024, 0, s>>>(logits, ld, ids, ids_stride, n_dev, n_fixed, M, k, out_ids, out_vals);
+    return hipGetLastError();
+  }
+  if (nrows >= 96) {
+    topk_stream_kernel<16, LSE><<<rows, 1024, 0, s>>>(logits, ld, ids, ids_stride, n_dev, n_fixed, M, k, out_ids, out_vals);
+    return hipGetLastError();
+  }
   const int64_t slots = (int64_t)batch * M * nch * k;
   float* cv = reinterpret_cast<float*>(ws);
   int32_t* cp = reinterpret_cast<int32_t*>(ws + slots * 4);

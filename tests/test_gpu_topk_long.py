@@ -1,0 +1,86 @@
+"""Selection on rows longer than one workgroup's registers: one workgroup per row in steps, for lists and for many dense
+rows, and the chunks of few dense rows.  Row strides of every alignment, counts around the step and piece boundaries, and
+the inputs that overflow the candidate list: ramps, plateaus, all values equal.  Ids and values must be exactly those of a
+stable descending sort (ties by lower id); log-probabilities within 1e-5 of the fp64 value (an fp32 sum of at most 1e5 positive
+terms per row, added in trees of 4 and 6 levels behind runs of 16: below 2e-6 relative)."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2605_26444_amd import binding as B
+
+from harness import csr, dev_ids
+
+pytestmark = pytest.mark.gpu
+
+
+def _rows(kind, rows, n):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n + rows)
+    x = torch.empty((rows, n), device="cuda").normal_(generator=g)
+    i = torch.arange(n, device="cuda", dtype=torch.float32)
+    if kind == "up":
+        return (i * 1e-3).expand(rows, n).contiguous()
+    if kind == "down":
+        return (-i * 1e-3).expand(rows, n).contiguous()
+    if kind == "equal":
+        return torch.zeros((rows, n), device="cuda")
+    if kind == "plateaus":
+        return torch.floor(i / 5000).expand(rows, n).contiguous()
+    if kind == "coarse":
+        return torch.round(x * 2) / 2
+    return x
+
+
+def _expect(x, k):
+    v, i = torch.sort(x, dim=1, descending=True, stable=True)
+    k2 = min(k, x.shape[1])
+    return i[:, :k2], v[:, :k2]
+
+
+@pytest.mark.parametrize("kind", ["normal", "up", "down", "equal", "plateaus", "coarse"])
+@pytest.mark.parametrize("rows,V,k", [(1, 16385, 64), (3, 40003, 10), (95, 16386, 1), (96, 32771, 40), (130, 50001, 64), (512, 16387, 3), (515, 24589, 64)])
+def test_dense_rows(kind, rows, V, k):
+    x = _rows(kind, rows, V)
+    nbytes = B.nanospec_dense_topk_workspace(V, rows, k)
+    ws = torch.empty(max(nbytes, 16), dtype=torch.uint8, device="cuda")
+    ids = torch.full((rows, k), -7, dtype=torch.int32, device="cuda")
+    vals = torch.full((rows, k), 9.0, device="cuda")
+    B.nanospec_dense_topk(x, V, rows, k, ids, vals, ws, nbytes)
+    ei, ev = _expect(x, k)
+    assert torch.equal(ids.long(), ei) and torch.equal(vals, ev)
+
+
+@pytest.mark.parametrize("kind", ["normal", "up", "equal", "coarse"])
+@pytest.mark.parametrize("n", [0, 1, 37, 16384, 16385, 16388, 32768, 32770, 39999])
+@pytest.mark.parametrize("batch,M,k", [(2, 3, 10), (1, 2, 64), (16, 32, 5)])
+def test_lists(kind, n, batch, M, k):
+    V, window = 60000, 40000
+    st = B.State(V, 8, batch, window, 1, M, k)
+    assert st.capacity > 16384
+    rng = np.random.default_rng(n + 1)
+    live = [n if b % 2 == 0 else n // 3 for b in range(batch)]
+    lists = [np.sort(rng.permutation(V)[:x]).astype(np.int32) for x in live]
+    flat, off = csr(lists)
+    B.nanospec_vocab_init(st.h, dev_ids(flat) if len(flat) else None, off, None, np.zeros(batch + 1, np.int32))
+    logits = torch.full((batch, M, st.capacity), 1e30, device="cuda")       # what lies behind a list must not matter
+    ids = torch.full((batch, M, k), -7, dtype=torch.int32, device="cuda")
+    vals, logp = torch.full((batch, M, k), 9.0, device="cuda"), torch.full((batch, M, k), 9.0, device="cuda")
+    for b in range(batch):
+        if live[b]:
+            logits[b, :, :live[b]] = _rows(kind, M, live[b])
+    B.nanospec_topk_remap(st.h, logits, M, k, ids, vals)
+    ids2 = torch.full_like(ids, -7)
+    B.nanospec_topk_logprob_remap(st.h, logits, M, k, ids2, logp)
+    assert torch.equal(ids, ids2)
+    for b in range(batch):
+        have = min(k, live[b])
+        assert torch.all(ids[b, :, have:] == -1) and torch.all(vals[b, :, have:] == -torch.inf) and torch.all(logp[b, :, have:] == -torch.inf)
+        if have:
+            x = logits[b, :, :live[b]]
+            ei, ev = _expect(x, k)
+            assert torch.equal(ids[b, :, :have].long(), torch.from_numpy(lists[b]).long().cuda()[ei]) and torch.equal(vals[b, :, :have], ev)
+            z = ev.double() - torch.logsumexp(x.double(), dim=1, keepdim=True)
+            assert torch.all((logp[b, :, :have].double() - z).abs() <= 1e-5 * (1 + z.abs())), b
+    st.close()
