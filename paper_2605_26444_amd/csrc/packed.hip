@@ -99,15 +99,152 @@ __global__ __launch_bounds__(kSyncThreads) void packed_sync_kernel(VocabPtrs p, 
   }
 }
 
-// Copy the listed rows W[id] -> buf[slot]: the weight-gather kernel.  Workgroup x takes list entries x, x + grid, ...
-__global__ __launch_bounds__(256) void packed_copy_kernel(const uint4* __restrict__ W, PackedPtrs k, int row_vec /* 16-byte pieces per row */) {
+// The same for capacities of up to Q x 4096 slots in two memory round trips and one scan (the walk above takes two round
+// trips, two ranks and their stores' latency per 1024 slots and again per 1024 ids: 8.4 us at 3750 slots).  Thread t holds slots and list
+// positions q * 4096 + 4t .. + 3: slot ids and listed ids are asked for together, then the bitmap words of the former
+// and the slots of the latter -- a listed id's slot is not freed by this call, so the two do not wait for each other.
+// Free slots and ids without a slot are ranked in one scan; the free list lives in LDS.  All stores come last: the
+// f-th free slot is taken by the f-th new id, so the thread that frees a slot clears its tables only if it stays free.
+template <int Q>
+__global__ __launch_bounds__(kSyncThreads) void packed_sync_short_kernel(VocabPtrs p, PackedPtrs k) {
+  constexpr int NW = kSyncThreads / 64;
+  __shared__ int s_free[Q * 4096];
+  __shared__ int2 s_tot[Q][NW];
+  __shared__ int s_top;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int cap = k.cap;                                   // a multiple of 64, as are the lists' lengths
+  int sid[Q][4], id[Q][4], sl[Q][4];
+  uint32_t fr[Q], nw[Q];                                   // bit e: slot free (bit 4 + e: by this call) / id without a slot
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int s = q * 4096 + tid * 4;
+    const int4 a = *reinterpret_cast<const int4*>(k.slot_id + (s < cap ? s : 0));
+    const int4 b = *reinterpret_cast<const int4*>(p.ids + (s < cap ? s : 0));
+    sid[q][0] = a.x; sid[q][1] = a.y; sid[q][2] = a.z; sid[q][3] = a.w;
+    id[q][0] = b.x; id[q][1] = b.y; id[q][2] = b.z; id[q][3] = b.w;
+  }
+  const int n = p.n[0];
+  if (tid == 0) s_top = -1;
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int s = q * 4096 + tid * 4;
+    uint32_t word[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int w = sid[q][e] >= 0 ? sid[q][e] >> 5 : 0;
+      word[e] = p.wbit[w] | p.tbit[w];
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) sl[q][e] = k.slot_of[s + e < n ? id[q][e] : 0];   // entries past n may be anything
+    fr[q] = nw[q] = 0u;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const bool gone = sid[q][e] >= 0 && !((word[e] >> (sid[q][e] & 31)) & 1u);
+      if (s < cap && (sid[q][e] < 0 || gone)) fr[q] |= (gone ? 17u : 1u) << e;
+      if (s + e < n && sl[q][e] < 0) nw[q] |= 1u << e;
+    }
+  }
+  // ranks in (q, thread, e) order = ascending slots / ids
+  int2 incl[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    incl[q] = make_int2(__popc(fr[q] & 15u), __popc(nw[q]));
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int x = __shfl_up(incl[q].x, o), y = __shfl_up(incl[q].y, o);
+      incl[q].x += lane >= o ? x : 0;
+      incl[q].y += lane >= o ? y : 0;
+    }
+    if (lane == 63) s_tot[q][wave] = incl[q];
+  }
+  __syncthreads();
+  int fbase[Q], nbase[Q], ftot = 0, ncopy = 0;
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    int fo = ftot, no = ncopy;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const int2 t = s_tot[q][w];
+      fo += w < wave ? t.x : 0;
+      no += w < wave ? t.y : 0;
+      ftot += t.x;
+      ncopy += t.y;
+    }
+    fbase[q] = fo + incl[q].x - __popc(fr[q] & 15u);
+    nbase[q] = no + incl[q].y - __popc(nw[q]);
+  }
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    int f = fbase[q];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if ((fr[q] >> e) & 1u) s_free[f++] = q * 4096 + tid * 4 + e;
+  }
+  __syncthreads();
+  int top = -1;
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    int r = nbase[q];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if ((nw[q] >> e) & 1u) sl[q][e] = s_free[r++];       // n <= cap and every active id holds one slot: there is one
+      if (q * 4096 + tid * 4 + e < n) top = max(top, sl[q][e]);
+    }
+  }
+  for (int o = 32; o > 0; o >>= 1) top = max(top, __shfl_xor(top, o));
+  if (lane == 0) atomicMax(&s_top, top);
+  __syncthreads();
+  if (tid == 0) {
+    k.scal[0] = s_top + 1;                                 // hi
+    k.scal[1] = ncopy;
+  }
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    int f = fbase[q], r = nbase[q];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int s = q * 4096 + tid * 4 + e;                // slot and list position
+      if ((fr[q] >> (4 + e)) & 1u) {
+        k.slot_of[sid[q][e]] = -1;
+        if (f >= ncopy) {
+          k.slot_id[s] = -1;
+          k.out_pos[s] = -1;
+        }
+      }
+      f += (fr[q] >> e) & 1u;
+      if (s < n) k.out_pos[sl[q][e]] = s;
+      if ((nw[q] >> e) & 1u) {
+        k.slot_of[id[q][e]] = sl[q][e];
+        k.slot_id[sl[q][e]] = id[q][e];
+        k.copy_list[2 * r] = id[q][e];
+        k.copy_list[2 * r + 1] = sl[q][e];
+        ++r;
+      }
+    }
+  }
+}
+
+// Copy the listed rows W[id] -> buf[slot]: the weight-gather kernel.  One workgroup per compute unit (a decoding step copies a
+// row or two, and then the launch is all there is), four 16-byte pieces per thread in flight for the first gather.
+__global__ __launch_bounds__(1024) void packed_copy_kernel(const uint4* __restrict__ W, PackedPtrs k, int row_vec /* 16-byte pieces per row */) {
   const int ncopy = k.scal[1];
   uint4* buf = reinterpret_cast<uint4*>(k.buf);
-  for (int e = blockIdx.x; e < ncopy; e += gridDim.x) {
-    const int64_t id = k.copy_list[2 * e], sl = k.copy_list[2 * e + 1];
-    const uint4* src = W + id * row_vec;
-    uint4* dst = buf + sl * row_vec;
-    for (int i = threadIdx.x; i < row_vec; i += 256) dst[i] = src[i];
+  const int64_t total = (int64_t)ncopy * row_vec, stride = (int64_t)gridDim.x * 1024;
+  for (int64_t t0 = (int64_t)blockIdx.x * 1024 + threadIdx.x; t0 < total; t0 += 4 * stride) {
+    uint4 v[4];
+    int64_t to[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t t = t0 + u * stride;
+      const uint32_t tc = (uint32_t)(t < total ? t : t0);   // below 2^32: capacity * d / 8
+      const uint32_t e = tc / (uint32_t)row_vec, i = tc % (uint32_t)row_vec;
+      const int2 cs = *reinterpret_cast<const int2*>(k.copy_list + 2 * (int64_t)e);
+      v[u] = W[(int64_t)cs.x * row_vec + i];
+      to[u] = (int64_t)cs.y * row_vec + i;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (t0 + u * stride < total) buf[to[u]] = v[u];
   }
 }
 
@@ -130,11 +267,13 @@ hipError_t launch_packed_reset(const nanospec_state* st, hipStream_t s) {
 }
 
 hipError_t launch_packed_gather(const nanospec_state* st, const void* W, hipStream_t s) {
-  packed_sync_kernel<<<1, kSyncThreads, 0, s>>>(st->vp, st->pk);
+  const int cap = st->pk.cap;
+  if (cap <= 4096) packed_sync_short_kernel<1><<<1, kSyncThreads, 0, s>>>(st->vp, st->pk);
+  else if (cap <= 8192) packed_sync_short_kernel<2><<<1, kSyncThreads, 0, s>>>(st->vp, st->pk);
+  else packed_sync_kernel<<<1, kSyncThreads, 0, s>>>(st->vp, st->pk);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const int grid = st->pk.cap < 1024 ? st->pk.cap : 1024;
-  packed_copy_kernel<<<grid, 256, 0, s>>>(static_cast<const uint4*>(W), st->pk, st->d / 8);
+  packed_copy_kernel<<<256, 1024, 0, s>>>(static_cast<const uint4*>(W), st->pk, st->d / 8);
   return hipGetLastError();
 }
 
