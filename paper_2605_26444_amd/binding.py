@@ -62,8 +62,8 @@ def lib() -> C.CDLL:
         L.nanospec_create.argtypes = [C.POINTER(vp)] + [i32] * 7
         L.nanospec_destroy.argtypes = [vp]
         L.nanospec_set_stream_policy.argtypes = [vp, i32]
-        L.nanospec_vocab_init.argtypes = [vp, vp, i32p, vp, i32p, vp]
-        L.nanospec_vocab_update.argtypes = [vp, vp, i32p, vp, i32p, vp]
+        L.nanospec_vocab_init.argtypes = [vp] * 6           # host offsets as plain addresses, see _off
+        L.nanospec_vocab_update.argtypes = [vp] * 6
         L.nanospec_vocab_append_unique.argtypes = [vp, vp, i32, i64, vp]
         L.nanospec_vocab_view.argtypes = [vp, C.POINTER(vp), C.POINTER(vp), i32p]
         L.nanospec_sparse_head.argtypes = [vp, vp, vp, i32, vp, vp]
@@ -119,18 +119,32 @@ def _ptr(t):
     return t.data_ptr()
 
 
+_current_stream = None
+
+
 def _stream(stream):
+    """stream handle; None: torch's current stream of the current device, asked for as a plain handle -- building torch's
+    stream object costs as much as the rest of a call's marshalling"""
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        global _current_stream
+        if _current_stream is None:
+            import torch
+            raw = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (lambda dev: torch.cuda.current_stream(dev).cuda_stream)
+            device = torch.cuda.current_device
+            _current_stream = lambda: raw(device())
+        return _current_stream()
     return stream if isinstance(stream, int) else stream.cuda_stream
 
 
 def _off(a):
+    """(array to keep alive, address) of host offsets as contiguous int32.  The address comes from the buffer protocol: numpy's own
+    ways to it build two ctypes objects (2.6 us a call against 0.5)."""
     if a is None:
         return None, None
     arr = np.ascontiguousarray(a, dtype=np.int32)
-    return arr, arr.ctypes.data_as(C.POINTER(C.c_int32))
+    if arr.flags.writeable and arr.size:
+        return arr, C.addressof(C.c_char.from_buffer(arr))
+    return arr, arr.ctypes.data
 
 
 def nanospec_state_layout(V, d, batch, window, topk_cap, m_cap, k_cap) -> Layout:
