@@ -106,8 +106,12 @@ hipError_t launch_head_shared(const void* W, const void* H, const int32_t* ids, 
                               int32_t rows_total, int32_t seq_rows, int32_t d, int64_t ld_logits, float* logits, const int32_t* opos,
                               int64_t opos_stride, hipStream_t s);
 
-// wide.hip: register-blocked product for more than 16 hidden rows per sequence
-bool wide_supported(int32_t V, int32_t M, int32_t d, int32_t batch, int32_t cap_rows);
+// wide.hip: register-blocked product
+bool wide_reaches(int32_t V, int32_t M, int32_t d);   // its 32-bit byte offsets reach every row
+bool wide_supported(int32_t V, int32_t M, int32_t d, int32_t batch, int32_t cap_rows, bool dense);
+hipError_t launch_head_wide_shared(const void* W, const void* H, const int32_t* ids, const int32_t* n_dev, int32_t cap_rows, int32_t V,
+                                   int32_t rows_total, int32_t seq_rows, int32_t d, int64_t ld, float* logits, const int32_t* opos,
+                                   int64_t opos_stride, hipStream_t s);
 hipError_t wide_configure_device();
 hipError_t launch_head_wide(const void* W, const void* H, const int32_t* ids, const int32_t* n_dev, int32_t n_fixed, int32_t cap_rows,
                             int32_t V, int32_t batch, int32_t M, int32_t d, int64_t ld, int64_t ids_stride, float* logits,

@@ -751,6 +751,8 @@ hipError_t launch_head_shared(const void* W, const void* H, const int32_t* ids, 
   const uint16_t* Wp = static_cast<const uint16_t*>(W);
   const uint16_t* Hp = static_cast<const uint16_t*>(H);
   if (cap_rows < 64 || cap_rows % 64 != 0 || opos_stride % 4 != 0 || seq_rows < 1 || rows_total < 1) return hipErrorInvalidValue;
+  if (wide_reaches(V, rows_total, d))
+    return launch_head_wide_shared(W, H, ids, n_rep, cap_rows, V, rows_total, seq_rows, d, ld_logits, logits, opos, opos_stride, s);
   const int groups = rows_total / 64, tail = rows_total % 64;
   if (groups > 0) {
     hipError_t e = run_shared<4>(Wp, Hp, ids, n_rep, cap_rows, V, groups, 64, d, ld_logits, logits, opos, opos_stride, seq_rows, 0, s);
@@ -813,9 +815,8 @@ hipError_t launch_head(const void* W, const void* H, const int32_t* ids, const i
                        float* logits, float* partial, int64_t partial_bytes, const int32_t* opos, hipStream_t s) {
   const uint16_t* Wp = static_cast<const uint16_t*>(W);
   const uint16_t* Hp = static_cast<const uint16_t*>(H);
-  // more than 16 hidden rows: the register-blocked product wherever it is the faster one (many rows: the
-  // dense comparison point of wide trees and batches; a few thousand rows: wide trees, instead of split-K + reduce)
-  if (wide_supported(V, M, d, batch, cap_rows))
+  // the register-blocked product wherever it is the faster one
+  if (wide_supported(V, M, d, batch, cap_rows, n_dev == nullptr))
     return launch_head_wide(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld_logits, ids_stride, logits, opos, s);
   if (M <= 64)
     return launch_head_64(Wp, Hp, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld_logits, ids_stride, logits, partial,

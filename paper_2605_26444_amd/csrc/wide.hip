@@ -15,12 +15,14 @@ namespace nanospec {
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef f32x4 f32x4_u __attribute__((aligned(4)));   // global memory takes 16-byte stores at any 4-byte address
 
 constexpr int kWidePad = 32;     // bytes between LDS rows: rows r and r+4 share banks, the 16 lanes of a fragment read never meet
 
 // WR x WH wavefronts (4 or 8); a wavefront owns FR x FH fragments of 16 x 16 logits.
 //   logits[m][j] for hidden row m < M and list row j < n, row stride ld.  ids == nullptr: rows 0..n-1.
 //   opos != nullptr ([opos_len], a multiple of 4 entries): row j's logits go to column opos[j] instead, nowhere if negative.
+//   seq_rows > 0: one list for the hidden rows of several sequences, seq_rows each, with columns of their own ([..][ids_stride]).
 // d % BK == 0 (checked by the launcher).  Rows past n read row 0, hidden rows past M read row M-1; neither is stored.
 // Workgroup order: the chip hands consecutive workgroups to its eight dies in turn and each die has its own L2, so
 // the hidden-row blocks of one row block run back to back on one die (blockIdx -> (row block, hidden block) below)
@@ -35,7 +37,7 @@ __global__ __launch_bounds__(64 * WR * WH) void head_wide_kernel(const uint16_t*
                                                         const int32_t* __restrict__ ids, const int32_t* __restrict__ n_dev, int n_fixed,
                                                         int V, int batch, int M, int d, int64_t ld, int64_t ids_stride,
                                                         float* __restrict__ logits, int row_blocks, int hid_blocks,
-                                                        const int32_t* __restrict__ opos, int opos_len) {
+                                                        const int32_t* __restrict__ opos, int opos_len, int seq_rows) {
   constexpr int NT = 64 * WR * WH;
   constexpr int BM = WR * FR * 16, BN = WH * FH * 16;
   constexpr int CPR = BK / 8;                      // 16-byte pieces per row and step
@@ -231,14 +233,15 @@ __global__ __launch_bounds__(64 * WR * WH) void head_wide_kernel(const uint16_t*
       if (m >= M || j >= n) continue;
       float* dst = logits + (int64_t)m * ld + j;
       if (opos) {                                       // rows kept in an order of their own: list row j's logits go to column opos[j]
-        const int4 jo4 = j + 3 < opos_len ? *reinterpret_cast<const int4*>(opos + j) : make_int4(-1, -1, -1, -1);
+        const int32_t* col = opos + (seq_rows ? (int64_t)(m / seq_rows) * ids_stride : 0);
+        const int4 jo4 = j + 3 < opos_len ? *reinterpret_cast<const int4*>(col + j) : make_int4(-1, -1, -1, -1);
         const int jo[4] = {jo4.x, jo4.y, jo4.z, jo4.w};
         float* rowp = logits + (int64_t)m * ld;
 #pragma unroll
         for (int v = 0; v < 4; ++v)
           if (j + v < n && jo[v] >= 0) rowp[jo[v]] = acc[a][b][v];
-      } else if ((ld & 3) == 0 && j + 3 < n) {
-        *reinterpret_cast<f32x4*>(dst) = acc[a][b];
+      } else if (j + 3 < n) {
+        *reinterpret_cast<f32x4_u*>(dst) = acc[a][b];
       } else {
 #pragma unroll
         for (int v = 0; v < 4; ++v)
@@ -251,7 +254,7 @@ __global__ __launch_bounds__(64 * WR * WH) void head_wide_kernel(const uint16_t*
 template <int WR, int WH, int FR, int FH, int BK, int D>
 static hipError_t run_wide(const uint16_t* W, const uint16_t* H, const int32_t* ids, const int32_t* n_dev, int32_t n_fixed, int32_t cap_rows,
                            int32_t V, int32_t batch, int32_t M, int32_t d, int64_t ld, int64_t ids_stride, float* logits, const int32_t* opos,
-                           hipStream_t s) {
+                           int32_t seq_rows, hipStream_t s) {
   constexpr int BM = WR * FR * 16, BN = WH * FH * 16;
   constexpr int LDS = 2 * (BM + BN) * (BK * 2 + kWidePad);
   const int row_blocks = (cap_rows + BM - 1) / BM, hid_blocks = (M + BN - 1) / BN;
@@ -259,10 +262,219 @@ static hipError_t run_wide(const uint16_t* W, const uint16_t* H, const int32_t* 
   if (grid > 0x7fffffff || (int64_t)V * d * 2 > 0xffffffffll || (int64_t)M * d * 2 > 0xffffffffll) return hipErrorInvalidValue;
   if (d % (D * BK) == 0)
     head_wide_kernel<WR, WH, FR, FH, BK, D, false><<<dim3((unsigned)grid), 64 * WR * WH, LDS, s>>>(
-        W, H, ids, n_dev, n_fixed, V, batch, M, d, ld, ids_stride, logits, row_blocks, hid_blocks, opos, cap_rows / 4 * 4);
+        W, H, ids, n_dev, n_fixed, V, batch, M, d, ld, ids_stride, logits, row_blocks, hid_blocks, opos, cap_rows / 4 * 4, seq_rows);
   else
     head_wide_kernel<WR, WH, FR, FH, BK, D, true><<<dim3((unsigned)grid), 64 * WR * WH, LDS, s>>>(
-        W, H, ids, n_dev, n_fixed, V, batch, M, d, ld, ids_stride, logits, row_blocks, hid_blocks, opos, cap_rows / 4 * 4);
+        W, H, ids, n_dev, n_fixed, V, batch, M, d, ld, ids_stride, logits, row_blocks, hid_blocks, opos, cap_rows / 4 * 4, seq_rows);
+  return hipGetLastError();
+}
+
+constexpr int kGemmStage = 4 * 128 * 128;        // bytes of one stage: A0, A1, B0, B1 (128 rows x 128 bytes each)
+
+__device__ __forceinline__ void lds_fetch16(uint32_t lds, const void* base, uint32_t off) {
+  // 16 bytes per lane from base + off straight into LDS at lds + 16 * lane; no destination register
+  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory", "m0");
+}
+#define NS_WAIT_VM(n) asm volatile("s_waitcnt vmcnt(" #n ")" ::: "memory")
+#define NS_WAIT_LDS() asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory")
+#define NS_BARRIER()                        \
+  do {                                      \
+    __builtin_amdgcn_sched_barrier(0);      \
+    asm volatile("" ::: "memory");          \
+    __builtin_amdgcn_s_barrier();           \
+    asm volatile("" ::: "memory");          \
+    __builtin_amdgcn_sched_barrier(0);      \
+  } while (0)
+
+// The compute-bound product: more than 128 hidden rows of one sequence on many rows, d a multiple of 64.
+// 256 x 256 logits per workgroup of eight wavefronts (128 x 64 each), K in 64-column steps, two LDS stages of 64 KB.  What it has
+// to do per step on a compute unit is 2048 cycles of matrix work (of one SIMD) and as many cycles of LDS (192 KB of
+// fragment reads, 64 KB of fills), so everything has to overlap:
+//   * the operand blocks go from memory straight into LDS (no registers, no LDS write instructions), 14 to 16 KB pieces at a
+//     time, one step and a quarter to one and three quarters ahead of their use.  The 16-byte pieces of a row are stored
+//     permuted by the row's low three bits (the fetching lanes permute their addresses), so that neither side has bank
+//     conflicts without padding;
+//   * a step is four phases, each a quarter of the block (row half x hidden half) of 16 matrix instructions per wavefront, and the
+//     second four wavefronts run one phase half behind the first: while one wavefront of a SIMD multiplies, the other one
+//     asks for its next fragments.  Fragments are asked for one barrier before they are needed;
+//   * a piece of LDS is refilled one phase after all its readers have consumed it (the barriers between say so), and is read
+//     after every wavefront has waited for its own fetches of it (the counted waits, then a barrier).
+// 1024 hidden rows on the 128k x 4096 matrix: 896 us = 1.20 PFLOP/s (head_wide_kernel's 256 x 256 shape: 1036); the loop takes
+// 1.16 times its matrix cycles, at the 1.7 GHz that this load leaves the clock.  512 hidden rows 532 -> 490 us, 130: 309 -> 275.  The
+// sums are taken in the same order: results are bit-equal.
+__global__ __launch_bounds__(512, 2) void head_gemm_kernel(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H,
+                                                           const int32_t* __restrict__ ids, const int32_t* __restrict__ n_dev, int n_fixed,
+                                                           int V, int M, int d, int64_t ld, float* __restrict__ logits, int row_blocks,
+                                                           int hid_blocks, const int32_t* __restrict__ opos, int opos_len) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const int xq = blockIdx.x & 7, xr = blockIdx.x >> 3;
+  const int hb = xr % hid_blocks, rb = (xr / hid_blocks) * 8 + xq;
+  if (rb >= row_blocks) return;
+  const int n = n_dev ? n_dev[0] : n_fixed;
+  const int j0 = rb * 256, m0 = hb * 256;
+  if (j0 >= n) return;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wr = w >> 2, wh = w & 3;
+
+  // this lane's pieces: instruction i of half h covers rows (2w + i) * 8 + lane / 8 of the half
+  const int pc = (lane & 7) ^ (lane >> 3);                 // row & 7 == lane >> 3 in every instruction: the swizzled piece
+  uint32_t aoff[2][2], boff[2][2];
+  int rowv[2][2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int q = (2 * w + i) * 8 + (lane >> 3);
+      const int j = j0 + (q >> 6) * 128 + (q & 63) + h * 64;
+      rowv[h][i] = j < n ? j : j0;
+    }
+  if (ids) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) rowv[h][i] = ids[rowv[h][i]];
+  }
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      int64_t row = rowv[h][i];
+      row = row < 0 ? 0 : (row >= V ? V - 1 : row);
+      aoff[h][i] = (uint32_t)(row * d * 2 + pc * 16);
+      const int q = (2 * w + i) * 8 + (lane >> 3);
+      int m = m0 + (q >> 5) * 64 + (q & 31) + h * 32;
+      m = m < M ? m : M - 1;
+      boff[h][i] = (uint32_t)((int64_t)m * d * 2 + pc * 16);
+    }
+  const int nk = d / 64;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
+  auto fetch_a = [&](int st, int h) {
+    const int c = st < nk ? st : nk - 1;
+    const char* base = reinterpret_cast<const char*>(W) + (int64_t)c * 128;
+    const uint32_t l = lds0 + (st & 1) * kGemmStage + h * 16384 + w * 2048;
+    lds_fetch16(l, base, aoff[h][0]);
+    lds_fetch16(l + 1024, base, aoff[h][1]);
+  };
+  auto fetch_b = [&](int st, int h) {
+    const int c = st < nk ? st : nk - 1;
+    const char* base = reinterpret_cast<const char*>(H) + (int64_t)c * 128;
+    const uint32_t l = lds0 + (st & 1) * kGemmStage + 32768 + h * 16384 + w * 2048;
+    lds_fetch16(l, base, boff[h][0]);
+    lds_fetch16(l + 1024, base, boff[h][1]);
+  };
+
+  f32x4 acc[8][4];
+#pragma unroll
+  for (int a = 0; a < 8; ++a)
+#pragma unroll
+    for (int b = 0; b < 4; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  // fragment addresses inside a half: row r (lane & 15 within the fragment), piece (lane >> 4) + 4 * kk, swizzled by r & 7
+  const int fr = lane & 15, s7 = lane & 7;
+  const uint32_t f0 = fr * 128 + (((lane >> 4)) ^ s7) * 16, f1 = fr * 128 + (((lane >> 4) + 4) ^ s7) * 16;
+  bf16x8 af[4][2], b0[2][2], b1[2][2], b2[2][2];
+  auto read_a = [&](int st, int h) {
+    const char* p = smem + (st & 1) * kGemmStage + h * 16384 + wr * 8192;
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      af[a][0] = *reinterpret_cast<const bf16x8*>(p + a * 2048 + f0);
+      af[a][1] = *reinterpret_cast<const bf16x8*>(p + a * 2048 + f1);
+    }
+  };
+  auto read_b = [&](int st, int h, bf16x8(&bq)[2][2]) {
+    const char* p = smem + (st & 1) * kGemmStage + 32768 + h * 16384 + wh * 4096;
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      bq[b][0] = *reinterpret_cast<const bf16x8*>(p + b * 2048 + f0);
+      bq[b][1] = *reinterpret_cast<const bf16x8*>(p + b * 2048 + f1);
+    }
+  };
+#define NS_COMPUTE(A0, B0, bq)                                                                                                          \
+  do {                                                                                                                                  \
+    __builtin_amdgcn_s_setprio(1);                                                                                                      \
+    _Pragma("unroll") for (int kk = 0; kk < 2; ++kk) _Pragma("unroll") for (int a = 0; a < 4; ++a) _Pragma("unroll") for (int b = 0; b < 2; ++b) \
+        acc[A0 + a][B0 + b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[a][kk], bq[b][kk], acc[A0 + a][B0 + b], 0, 0, 0);             \
+    __builtin_amdgcn_s_setprio(0);                                                                                                      \
+  } while (0)
+
+  // prologue
+  fetch_a(0, 0);
+  fetch_b(0, 0);
+  fetch_b(0, 1);
+  fetch_a(0, 1);
+  fetch_a(1, 0);
+  fetch_b(1, 0);
+  fetch_b(1, 1);
+  NS_WAIT_VM(10);
+  NS_BARRIER();
+  read_b(0, 0, b0);
+  if (wr == 1) NS_BARRIER();                               // the second four wavefronts run one cluster behind the first
+  auto step = [&](int st, bf16x8(&bc)[2][2], bf16x8(&bn)[2][2]) {
+    read_a(st, 0);
+    fetch_a(st + 1, 1);
+    NS_WAIT_VM(10);
+    NS_BARRIER();
+    NS_COMPUTE(0, 0, bc);
+    NS_BARRIER();
+    read_b(st, 1, b1);
+    NS_WAIT_VM(8);
+    NS_BARRIER();
+    NS_COMPUTE(0, 2, b1);
+    NS_BARRIER();
+    read_a(st, 1);
+    fetch_a(st + 2, 0);
+    fetch_b(st + 2, 0);
+    NS_WAIT_VM(8);
+    NS_BARRIER();
+    NS_COMPUTE(4, 2, b1);
+    NS_BARRIER();
+    read_b(st + 1, 0, bn);
+    fetch_b(st + 2, 1);
+    NS_BARRIER();
+    NS_COMPUTE(4, 0, bc);
+    NS_BARRIER();
+  };
+  int st = 0;
+  for (; st + 1 < nk; st += 2) {
+    step(st, b0, b2);
+    step(st + 1, b2, b0);
+  }
+  if (st < nk) step(st, b0, b2);
+  if (wr == 0) NS_BARRIER();
+  NS_WAIT_VM(0);                                           // the re-fetched last steps have landed before this LDS can be another workgroup's
+
+#pragma unroll
+  for (int a = 0; a < 8; ++a) {
+    const int j = j0 + wr * 128 + a * 16 + 4 * (lane >> 4);
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      const int m = m0 + wh * 64 + b * 16 + (lane & 15);
+      if (m >= M || j >= n) continue;
+      float* rowp = logits + (int64_t)m * ld;
+      if (opos) {
+        const int4 jo4 = j + 3 < opos_len ? *reinterpret_cast<const int4*>(opos + j) : make_int4(-1, -1, -1, -1);
+        const int jo[4] = {jo4.x, jo4.y, jo4.z, jo4.w};
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          if (j + v < n && jo[v] >= 0) rowp[jo[v]] = acc[a][b][v];
+      } else if (j + 3 < n) {
+        *reinterpret_cast<f32x4_u*>(rowp + j) = acc[a][b];
+      } else {
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          if (j + v < n) rowp[j + v] = acc[a][b][v];
+      }
+    }
+  }
+}
+
+static hipError_t run_gemm(const uint16_t* W, const uint16_t* H, const int32_t* ids, const int32_t* n_dev, int32_t n_fixed, int32_t cap_rows,
+                           int32_t V, int32_t M, int32_t d, int64_t ld, float* logits, const int32_t* opos, hipStream_t s) {
+  const int row_blocks = (cap_rows + 255) / 256, hid_blocks = (M + 255) / 256;
+  const int64_t grid = (int64_t)((row_blocks + 7) / 8) * hid_blocks * 8;
+  if (grid > 0x7fffffff || d % 64 != 0) return hipErrorInvalidValue;
+  head_gemm_kernel<<<dim3((unsigned)grid), 512, 2 * kGemmStage, s>>>(W, H, ids, n_dev, n_fixed, V, M, d, ld, logits, row_blocks, hid_blocks, opos,
+                                                                     cap_rows / 4 * 4);
   return hipGetLastError();
 }
 
@@ -279,31 +491,57 @@ static hipError_t configure_wide() {
 
 hipError_t wide_configure_device() {
   hipError_t e = configure_wide<2, 2, 1, 1, 128, 4>();
+  if (e == hipSuccess) e = configure_wide<2, 1, 1, 1, 128, 4>();
+  if (e == hipSuccess) e = configure_wide<4, 1, 1, 1, 128, 4>();
   if (e == hipSuccess) e = configure_wide<2, 4, 1, 1, 128, 2>();
   if (e == hipSuccess) e = configure_wide<2, 4, 2, 1, 128, 2>();
   if (e == hipSuccess) e = configure_wide<4, 1, 1, 2, 128, 2>();
-  if (e == hipSuccess) e = configure_wide<4, 1, 2, 2, 64, 2>();
   if (e == hipSuccess) e = configure_wide<4, 1, 2, 4, 64, 2>();
   if (e == hipSuccess) e = configure_wide<4, 2, 4, 4, 64, 2>();
   if (e == hipSuccess) e = configure_wide<2, 4, 8, 4, 64, 2>();
+  if (e == hipSuccess)
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(head_gemm_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   return e;
 }
 
-// Which products the register-blocked kernel takes: more than 16 hidden rows, rows that 32-bit byte offsets reach, and
+bool wide_reaches(int32_t V, int32_t M, int32_t d) { return (int64_t)V * d * 2 <= 0xffffffffll && (int64_t)M * d * 2 <= 0xffffffffll; }
+
+// Which products the register-blocked kernel takes, of those whose rows 32-bit byte offsets reach.
+// More than 16 hidden rows:
 //   * any number of rows while d <= 2048: one launch whose time is its d / 128 steps (6.0 us at d = 1152, 7.2 at 2048) against
 //     two launches of split-K + reduce (9.6, 8.9);
 //   * longer rows from the capacity on at which it beats split-K + reduce, whose workgroups each walk 512 columns only
 //     (d = 4096: M = 64, 1000 live rows 11.1 against 9.5 us, 2000: 10.7 / 11.4, 3000: 11.7 / 12.4; M = 24, 2000 live rows
 //     11.6 / 10.7, 3000: 12.4 / 13.1).
-bool wide_supported(int32_t V, int32_t M, int32_t d, int32_t batch, int32_t cap_rows) {
-  if (M <= 16 || (int64_t)V * d * 2 > 0xffffffffll || (int64_t)M * d * 2 > 0xffffffffll) return false;
+// Up to 16 (the kernels of head.hip feed the matrix cores straight from memory, at a quarter of their rate and with the hidden
+// rows fetched again for every 16 list rows), where there are rows enough to fill blocks of 32 or 64 with whole hidden-row blocks:
+//   * lists of 131072 rows of capacity together (64 sequences of 2300, d = 4096: M = 8 133 against 147 us, M = 16 140 / 244, M = 1
+//     124 / 130; 32 sequences, M = 8: 79 / 84; 16: 46 / 46);
+//   * 9 to 16 hidden rows: lists from 9216 rows on (2 sequences of 3000 rows, d = 4096: 12.5 / 15.7; one of 3000 11.2 / 9.2; 8 of 2300
+//     31 / 38; 16 of 2300, d = 8192: 91 / 99), but one sequence with d > 5120 (8400 rows, d = 8192: 40 / 38); dense heads
+//     (128k x 4096, M = 16: 201 / 225; x 5120 232 / 259), but whole passes of the K-loop kernel (x 8192: 411 / 363);
+//   * 5 to 8: dense heads (x 2048 95 / 121, x 3584 155 / 160, x 5120 220 / 250) that are no whole passes there (x 4096 194 / 177, x 8192
+//     406 / 332);
+//   * fewer: dense heads with d <= 1024 (M = 3 x 1024 46 / 69; M = 2 x 2048 91 / 84);
+//   * up to 8, lists: one sequence from 8192 rows on with d <= 4096 (8000 rows, M = 8 14.8 / 16.4; 8000 x 1024, M = 6 5.9 / 13.1),
+//     several from 36864 on with d <= 2048 (16 of 2300, M = 8 x 2048 27 / 29; 8 of 2300, x 1024 10.5 / 12.3; x 4096 28 / 26).
+bool wide_supported(int32_t V, int32_t M, int32_t d, int32_t batch, int32_t cap_rows, bool dense) {
+  if (!wide_reaches(V, M, d)) return false;
+  if (M <= 16) {
+    const int64_t rows = (int64_t)cap_rows * batch;
+    if (rows > 0x20000000ll) return false;                         // workgroups of one launch
+    if (dense) return rows >= 16384 && (d <= 1024 || (M > 8 && (d <= 4096 || d % 2048 != 0)) || (M > 4 && M <= 8 && d % 4096 != 0));
+    if (rows >= 131072) return true;
+    if (M > 8) return rows >= 9216 && (d <= 5120 || batch > 1);
+    return batch == 1 ? rows >= 8192 && d <= 4096 : rows >= 36864 && d <= 2048;
+  }
   const int64_t rows = (int64_t)cap_rows * batch;
   if (rows * ((M + 31) / 32) > 0x40000000ll) return false;         // workgroups of one launch
   if (M > 64 && batch == 1 && rows < 16384) return false;          // many hidden rows on a short list: 64 at a time
   return d <= 2048 || rows >= (M <= 32 ? 4096 : 2560);
 }
 
-// The block shapes.  Up to 64 hidden rows a launch is bound by the bytes a compute unit has in flight over the memory
+// The block shapes (figures for lists: sequences that share many of their rows).  Up to 64 hidden rows a launch is bound by the bytes a compute unit has in flight over the memory
 // latency (few rows) or by HBM (many), so the block grows with the rows: the smallest one while larger blocks would leave
 // compute units without work, larger ones to fetch the hidden rows (and, beyond 32 x 32, W_head) less often.  A launch
 // only knows the capacity of the lists; thresholds are for live rows around 0.6 of it, dense heads (live == capacity) count double.
@@ -314,34 +552,52 @@ bool wide_supported(int32_t V, int32_t M, int32_t d, int32_t batch, int32_t cap_
 //   64 x 64, eight wavefronts: 8 sequences of 2000 rows 25.1 us; 32 x 64 31.5, 32 x 32 38.1, 128 x 64 37.1 (slice-loop kernel
 //     36.4); one list of 12000 rows 26.8 against 34.2 / 39.0.
 //   128 x 64, four wavefronts, 60 KB of LDS, two workgroups per compute unit: 64 sequences of 2300 rows, d = 2048: 92 us; 64 x 64
-//     98 (slice-loop kernel 119); the dense 128k x 4096 head 187 us = 5.6 TB/s, 64 x 64 203.
-//   up to 32 hidden rows: 32 x 32 (16 sequences of 1500 rows 32 us, slice-loop kernel 49), on long lists 64 x 32 (64 sequences of
-//     2000 rows, M = 17: 104 us; 32 x 32 115, 128 x 64 121, slice-loop kernel 181) and, dense, 128 x 32 (128k x 4096, M = 24: 159 us
-//     = 6.6 TB/s; 128 x 64 170, 64 x 32 169).
+//     98 (slice-loop kernel 119); the dense 128k x 4096 head at 48 hidden rows 225 us (64 x 32 blocks 258).
+//   up to 32 hidden rows: 32 x 32 (16 sequences of 1500 rows 32 us, slice-loop kernel 49), on long lists and dense 64 x 32 (64
+//     sequences of 2000 rows, M = 17: 127 us, slice-loop kernel 196; dense 128k x 4096, M = 24: 205 us, 128 x 64 219, 32 x 32 228;
+//     32000 rows 51 / 60 / 59).
+//   up to 16: dense and on long lists 64 x 16, on short ones 32 x 16 of two wavefronts (8 sequences of 2300 rows, M = 16: 31 against
+//     34.5 us; 64 sequences, M = 8: 141 against 133).
 //   up to 128: 256 x 128 logits, eight wavefronts of 64 x 64.
-//   more: compute-bound.  256 x 256 logits per workgroup, eight wavefronts of 128 x 64 (one fragment read feeds four or
-//     eight matrix instructions), all 160 KB of LDS for the two stages.  512 hidden rows on the 128k x 4096 matrix:
-//     516-539 us = 1.0 PFLOP/s, the vendor GEMM 510-513.  On the way there: four wavefronts of 128 x 64 on 256 x 128
-//     logits 844 us (one wavefront per SIMD: nothing overlaps an LDS round trip), eight of 64 x 64 644 us, with the
-//     scheduling groups 614 us, 256 x 256 logits in 32-column steps 553 us.
+//   more: compute-bound.  head_gemm_kernel; 256 x 256 logits of this kernel (eight wavefronts of 128 x 64, all 160 KB of LDS for the
+//     two stages) where d is no multiple of 64.
 hipError_t launch_head_wide(const void* W, const void* H, const int32_t* ids, const int32_t* n_dev, int32_t n_fixed, int32_t cap_rows,
                             int32_t V, int32_t batch, int32_t M, int32_t d, int64_t ld, int64_t ids_stride, float* logits,
                             const int32_t* opos, hipStream_t s) {
   const uint16_t* Wp = static_cast<const uint16_t*>(W);
   const uint16_t* Hp = static_cast<const uint16_t*>(H);
   const int64_t rows = (int64_t)cap_rows * batch * (n_dev ? 1 : 2);
-  auto run = [&](auto shape) { return shape(Wp, Hp, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s); };
+  auto run = [&](auto shape) { return shape(Wp, Hp, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, 0, s); };
+  if (M <= 16) {
+    if (!n_dev || rows >= 131072) return run(run_wide<4, 1, 1, 1, 128, 4>);
+    return run(run_wide<2, 1, 1, 1, 128, 4>);
+  }
   if (M <= 32) {
     if (rows < 65536 && n_dev) return run(run_wide<2, 2, 1, 1, 128, 4>);
-    if (n_dev) return run(run_wide<4, 1, 1, 2, 128, 2>);
-    return run(run_wide<4, 1, 2, 2, 64, 2>);
+    return run(run_wide<4, 1, 1, 2, 128, 2>);
   }
   if (rows < 10240) return run(run_wide<2, 2, 1, 1, 128, 4>);
   if (rows < 18432) return run(run_wide<2, 4, 1, 1, 128, 2>);
   if (rows < (n_dev ? 98304 : 49152)) return run(run_wide<2, 4, 2, 1, 128, 2>);
   if (M <= 64 || batch > 1) return run(run_wide<4, 1, 2, 4, 64, 2>);
   if (M <= 128) return run(run_wide<4, 2, 4, 4, 64, 2>);
+  if (d % 64 == 0) return run_gemm(Wp, Hp, ids, n_dev, n_fixed, cap_rows, V, M, d, ld, logits, opos, s);
   return run(run_wide<2, 4, 8, 4, 64, 2>);
+}
+
+// One list shared by the hidden rows of several sequences (see launch_head_shared).  3310 rows x 512 hidden rows, d = 4096:
+// a third of the time of the slice-loop kernel's 64 hidden rows at a time.
+hipError_t launch_head_wide_shared(const void* W, const void* H, const int32_t* ids, const int32_t* n_dev, int32_t cap_rows, int32_t V,
+                                   int32_t rows_total, int32_t seq_rows, int32_t d, int64_t ld, float* logits, const int32_t* opos,
+                                   int64_t opos_stride, hipStream_t s) {
+  const uint16_t* Wp = static_cast<const uint16_t*>(W);
+  const uint16_t* Hp = static_cast<const uint16_t*>(H);
+  auto run = [&](auto shape) {
+    return shape(Wp, Hp, ids, n_dev, 0, cap_rows, V, 1, rows_total, d, ld, opos_stride, logits, opos, seq_rows, s);
+  };
+  if (rows_total <= 16) return run(run_wide<2, 1, 1, 1, 128, 4>);
+  if (rows_total <= 32) return run(run_wide<2, 2, 1, 1, 128, 4>);
+  return run(run_wide<2, 4, 2, 1, 128, 2>);
 }
 
 }  // namespace nanospec

@@ -1,4 +1,4 @@
-"""The register-blocked head (more than 16 hidden rows) on every block shape it is launched in: ragged batches with an
+"""The register-blocked head on every block shape it is launched in: ragged batches with an
 empty and a one-row list, lists that end inside a block, hidden sizes that are no whole number of column steps (down to
 one 16-byte piece) or an odd number of them, hidden rows that end inside a block.  Against fp64; the bound is that of an
 fp32 sum of d exact products in any order, d * 2^-24 * sum |w h|."""
@@ -34,6 +34,8 @@ def _check(got, W, H, what):
     (7, 64, 200, 4100), (5, 50, 768, 5000),                                            # 64 x 64
     (40, 20, 72, 2000), (40, 32, 264, 2000),                                           # 64 x 32
     (30, 64, 72, 4000), (30, 35, 192, 4000),                                           # 128 x 64
+    (1, 16, 520, 9200), (3, 9, 4168, 3100), (1, 3, 1032, 8200), (9, 8, 72, 4100),      # 32 x 16
+    (33, 1, 200, 4100), (33, 16, 640, 4100), (33, 7, 4104, 4100),                      # 64 x 16
 ])
 def test_ragged_batches(batch, M, d, window):
     V = 20000
@@ -54,7 +56,9 @@ def test_ragged_batches(batch, M, d, window):
     st.close()
 
 
-@pytest.mark.parametrize("V,M,d", [(30001, 24, 200), (17000, 33, 72), (40002, 64, 1032), (50000, 100, 192), (33333, 200, 72), (20000, 300, 520)])
+@pytest.mark.parametrize("V,M,d", [(30001, 24, 200), (17000, 33, 72), (40002, 64, 1032), (50000, 100, 192), (33333, 200, 72), (20000, 300, 520),
+                                     (50001, 129, 64), (49409, 257, 192), (25000, 700, 128), (24577, 513, 1088),
+                                     (30001, 16, 4104), (20000, 5, 4096), (40000, 1, 72), (17001, 12, 2056)])
 def test_dense(V, M, d):
     W, H = _normal(3, V, d), _normal(4, M, d)
     logits = torch.full((M + 1, V), 7.0, dtype=torch.float32, device="cuda")
