@@ -453,7 +453,8 @@ static hipError_t run_quad_auto(const uint16_t* W, const uint16_t* H, const int3
                                 int32_t cap_rows, int32_t V, int32_t batch, int32_t M, int32_t d, int64_t ld,
                                 int64_t ids_stride, float* logits, const int32_t* opos, hipStream_t s) {
   const int64_t rows = (int64_t)cap_rows * batch;
-  if (d > 512 * KS) {
+  constexpr bool LONG = KS == 8 || MT > 2 && KS == 4;       // the other instantiations are chosen for d <= 512 * KS only
+  if constexpr (LONG) if (d > 512 * KS) {
     // (tiles past the end leave at once in this kernel, so what counts is the live rows: 4 rows per workgroup while they
     // fit 256 workgroups -- about 0.8 of the capacity in the workloads here; 7.0 us at 1000 live rows, 10.1 us at 1091)
     if (rows <= 5 * 256) return run_quad_private<1, MT, KS, 4>(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s);
@@ -702,15 +703,28 @@ static hipError_t launch_head_64(const uint16_t* W, const uint16_t* H, const int
                                  int32_t n_fixed, int32_t cap_rows, int32_t V, int32_t batch, int32_t M, int32_t d,
                                  int64_t ld, int64_t ids_stride, float* logits, float* partial, int64_t partial_bytes,
                                  const int32_t* opos, hipStream_t s) {
-  if (M <= 4) return run_quad_auto<1, 8>(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s);
-  if (M <= 8) return run_quad_auto<2, 8>(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s);
+  // No more loads per row and wavefront than d has columns for (a load past d reads column 0 and is multiplied with zeros; eight
+  // against two or four: 3000 rows x 8, d = 1024 4.34 -> 3.32 us, d = 2048 5.01 -> 4.47; 349 rows, d = 512 3.34 -> 2.32; 8 sequences
+  // of 1500 rows x 8, d = 1024 9.8 -> 7.5).
+  if (M <= 4) {
+    if (d <= 1024) return run_quad_auto<1, 2>(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s);
+    if (d <= 2048) return run_quad_auto<1, 4>(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s);
+    return run_quad_auto<1, 8>(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s);
+  }
+  if (M <= 8) {
+    if (d <= 1024) return run_quad_auto<2, 2>(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s);
+    if (d <= 2048) return run_quad_auto<2, 4>(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s);
+    return run_quad_auto<2, 8>(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s);
+  }
   // 9..16 hidden rows: 8 loads per row and wavefront when that makes d a single K-iteration (up to 128 KB of
   // LDS for the hidden-row operands), else 4
   if (M <= 12) {
+    if (d <= 1024) return run_quad_auto<3, 2>(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s);
     if (d > 2048 && d <= 4096) return run_quad_auto<3, 8>(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s);
     return run_quad_auto<3, 4>(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s);
   }
   if (M <= 16) {
+    if (d <= 1024) return run_quad_auto<4, 2>(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s);
     if (d > 2048 && d <= 4096) return run_quad_auto<4, 8>(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s);
     return run_quad_auto<4, 4>(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s);
   }
@@ -800,6 +814,12 @@ static hipError_t configure_tile64() {
 
 hipError_t head_configure_device() {
   hipError_t e = configure_quad<1, 8>();
+  if (e == hipSuccess) e = configure_quad<1, 2>();
+  if (e == hipSuccess) e = configure_quad<1, 4>();
+  if (e == hipSuccess) e = configure_quad<2, 2>();
+  if (e == hipSuccess) e = configure_quad<2, 4>();
+  if (e == hipSuccess) e = configure_quad<3, 2>();
+  if (e == hipSuccess) e = configure_quad<4, 2>();
   if (e == hipSuccess) e = configure_quad<2, 8>();
   if (e == hipSuccess) e = configure_quad<3, 8>();
   if (e == hipSuccess) e = configure_quad<3, 4>();
