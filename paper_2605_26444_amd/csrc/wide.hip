@@ -37,7 +37,7 @@ __global__ __launch_bounds__(64 * WR * WH) void head_wide_kernel(const uint16_t*
                                                         const int32_t* __restrict__ ids, const int32_t* __restrict__ n_dev, int n_fixed,
                                                         int V, int batch, int M, int d, int64_t ld, int64_t ids_stride,
                                                         float* __restrict__ logits, int row_blocks, int hid_blocks,
-                                                        const int32_t* __restrict__ opos, int opos_len, int seq_rows) {
+                                                        const int32_t* __restrict__ opos, int opos_len, int seq_rows, int by_die) {
   constexpr int NT = 64 * WR * WH;
   constexpr int BM = WR * FR * 16, BN = WH * FH * 16;
   constexpr int CPR = BK / 8;                      // 16-byte pieces per row and step
@@ -50,20 +50,27 @@ __global__ __launch_bounds__(64 * WR * WH) void head_wide_kernel(const uint16_t*
   extern __shared__ __attribute__((aligned(16))) char smem[];
 
   // blockIdx -> die x = blockIdx % 8, slot r = blockIdx / 8; hidden block = r % hid_blocks, row block = (r / hid_blocks) * 8 + x
-  // several sequences: sequence = blockIdx % batch, hidden block and row block follow
-  int b = 0, hb, rb;
+  // several sequences: sequence = blockIdx % batch, hidden block and row block follow; by_die: die x takes the x-th eighth of every
+  // sequence's row blocks (the cuts move by up to a block from sequence to sequence, so that the eighths even out)
+  int b = 0, hb, rb, n;
   if (batch == 1) {
     const int xq = blockIdx.x & 7, xr = blockIdx.x >> 3;
     hb = xr % hid_blocks;
     rb = (xr / hid_blocks) * 8 + xq;
+    n = n_dev ? n_dev[0] : n_fixed;
   } else {
-    const int xr = blockIdx.x / batch;
-    b = blockIdx.x % batch;
-    hb = xr % hid_blocks;
-    rb = xr / hid_blocks;
+    const int x = blockIdx.x & 7, xr = by_die ? blockIdx.x >> 3 : blockIdx.x;
+    hb = by_die ? xr % hid_blocks : xr / batch % hid_blocks;
+    b = (by_die ? xr / hid_blocks : xr) % batch;
+    rb = xr / batch / hid_blocks;
+    n = n_dev ? n_dev[b] : n_fixed;
+    if (by_die) {
+      const int blocks = (n + BM - 1) / BM, end = ((x + 1) * blocks + (b & 7)) >> 3;
+      rb += (x * blocks + (b & 7)) >> 3;
+      if (rb >= end) return;
+    }
   }
   if (rb >= row_blocks) return;
-  const int n = n_dev ? n_dev[b] : n_fixed;
   const int j0 = rb * BM, m0 = hb * BN;
   if (j0 >= n) return;
 
@@ -254,18 +261,20 @@ __global__ __launch_bounds__(64 * WR * WH) void head_wide_kernel(const uint16_t*
 template <int WR, int WH, int FR, int FH, int BK, int D>
 static hipError_t run_wide(const uint16_t* W, const uint16_t* H, const int32_t* ids, const int32_t* n_dev, int32_t n_fixed, int32_t cap_rows,
                            int32_t V, int32_t batch, int32_t M, int32_t d, int64_t ld, int64_t ids_stride, float* logits, const int32_t* opos,
-                           int32_t seq_rows, hipStream_t s) {
+                           int32_t seq_rows, int by_die, hipStream_t s) {
   constexpr int BM = WR * FR * 16, BN = WH * FH * 16;
   constexpr int LDS = 2 * (BM + BN) * (BK * 2 + kWidePad);
   const int row_blocks = (cap_rows + BM - 1) / BM, hid_blocks = (M + BN - 1) / BN;
-  const int64_t grid = batch == 1 ? (int64_t)((row_blocks + 7) / 8) * hid_blocks * 8 : (int64_t)row_blocks * hid_blocks * batch;
+  const int64_t grid = batch == 1 ? (int64_t)((row_blocks + 7) / 8) * hid_blocks * 8
+                       : by_die     ? (int64_t)((row_blocks + 7) / 8) * hid_blocks * batch * 8
+                                    : (int64_t)row_blocks * hid_blocks * batch;
   if (grid > 0x7fffffff || (int64_t)V * d * 2 > 0xffffffffll || (int64_t)M * d * 2 > 0xffffffffll) return hipErrorInvalidValue;
   if (d % (D * BK) == 0)
     head_wide_kernel<WR, WH, FR, FH, BK, D, false><<<dim3((unsigned)grid), 64 * WR * WH, LDS, s>>>(
-        W, H, ids, n_dev, n_fixed, V, batch, M, d, ld, ids_stride, logits, row_blocks, hid_blocks, opos, cap_rows / 4 * 4, seq_rows);
+        W, H, ids, n_dev, n_fixed, V, batch, M, d, ld, ids_stride, logits, row_blocks, hid_blocks, opos, cap_rows / 4 * 4, seq_rows, by_die);
   else
     head_wide_kernel<WR, WH, FR, FH, BK, D, true><<<dim3((unsigned)grid), 64 * WR * WH, LDS, s>>>(
-        W, H, ids, n_dev, n_fixed, V, batch, M, d, ld, ids_stride, logits, row_blocks, hid_blocks, opos, cap_rows / 4 * 4, seq_rows);
+        W, H, ids, n_dev, n_fixed, V, batch, M, d, ld, ids_stride, logits, row_blocks, hid_blocks, opos, cap_rows / 4 * 4, seq_rows, by_die);
   return hipGetLastError();
 }
 
@@ -524,7 +533,8 @@ bool wide_reaches(int32_t V, int32_t M, int32_t d) { return (int64_t)V * d * 2 <
 //     406 / 332);
 //   * fewer: dense heads with d <= 1024 (M = 3 x 1024 46 / 69; M = 2 x 2048 91 / 84);
 //   * up to 8, lists: one sequence from 8192 rows on with d <= 4096 (8000 rows, M = 8 14.8 / 16.4; 8000 x 1024, M = 6 5.9 / 13.1),
-//     several from 36864 on with d <= 2048 (16 of 2300, M = 8 x 2048 27 / 29; 8 of 2300, x 1024 10.5 / 12.3; x 4096 28 / 26).
+//     several from 36864 on with d <= 2048 (16 of 2300, M = 8 x 2048 27 / 29; 8 of 2300, x 1024 10.5 / 12.3; x 4096 28 / 26), eight
+//     or more from 73728 on with d <= 4096 (16 of 2300, x 4096, each die its eighth of the lists: 43 / 46).
 bool wide_supported(int32_t V, int32_t M, int32_t d, int32_t batch, int32_t cap_rows, bool dense) {
   if (!wide_reaches(V, M, d)) return false;
   if (M <= 16) {
@@ -533,7 +543,7 @@ bool wide_supported(int32_t V, int32_t M, int32_t d, int32_t batch, int32_t cap_
     if (dense) return rows >= 16384 && (d <= 1024 || (M > 8 && (d <= 4096 || d % 2048 != 0)) || (M > 4 && M <= 8 && d % 4096 != 0));
     if (rows >= 131072) return true;
     if (M > 8) return rows >= 9216 && (d <= 5120 || batch > 1);
-    return batch == 1 ? rows >= 8192 && d <= 4096 : rows >= 36864 && d <= 2048;
+    return batch == 1 ? rows >= 8192 && d <= 4096 : (rows >= 36864 && d <= 2048) || (rows >= 73728 && d <= 4096 && batch >= 8);
   }
   const int64_t rows = (int64_t)cap_rows * batch;
   if (rows * ((M + 31) / 32) > 0x40000000ll) return false;         // workgroups of one launch
@@ -567,7 +577,12 @@ hipError_t launch_head_wide(const void* W, const void* H, const int32_t* ids, co
   const uint16_t* Wp = static_cast<const uint16_t*>(W);
   const uint16_t* Hp = static_cast<const uint16_t*>(H);
   const int64_t rows = (int64_t)cap_rows * batch * (n_dev ? 1 : 2);
-  auto run = [&](auto shape) { return shape(Wp, Hp, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, 0, s); };
+  // Sequences hold many of the same rows, and a die's L2 sees a row again only if the sequences that hold it run there at the
+  // same time: for few hidden rows each die takes one eighth of every list (64 sequences of 2300 rows, M = 8: 135 -> 130.5 us, 32: 79
+  // -> 73.5, 16: 47 -> 43; 8, M = 16: 31.1 -> 29.4), but not where the hidden rows of all sequences, which every die then needs, are as
+  // many bytes as the rows (64 sequences, M = 16: 140 -> 145; M = 60 on 8 sequences 25 -> 26).
+  const int by_die = batch >= 8 && M <= 16 && (M <= 8 || rows < 131072);
+  auto run = [&](auto shape) { return shape(Wp, Hp, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, 0, by_die, s); };
   if (M <= 16) {
     if (!n_dev || rows >= 131072) return run(run_wide<4, 1, 1, 1, 128, 4>);
     return run(run_wide<2, 1, 1, 1, 128, 4>);
@@ -593,7 +608,7 @@ hipError_t launch_head_wide_shared(const void* W, const void* H, const int32_t* 
   const uint16_t* Wp = static_cast<const uint16_t*>(W);
   const uint16_t* Hp = static_cast<const uint16_t*>(H);
   auto run = [&](auto shape) {
-    return shape(Wp, Hp, ids, n_dev, 0, cap_rows, V, 1, rows_total, d, ld, opos_stride, logits, opos, seq_rows, s);
+    return shape(Wp, Hp, ids, n_dev, 0, cap_rows, V, 1, rows_total, d, ld, opos_stride, logits, opos, seq_rows, 0, s);
   };
   if (rows_total <= 16) return run(run_wide<2, 1, 1, 1, 128, 4>);
   if (rows_total <= 32) return run(run_wide<2, 2, 1, 1, 128, 4>);

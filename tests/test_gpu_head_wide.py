@@ -35,6 +35,7 @@ def _check(got, W, H, what):
     (40, 20, 72, 2000), (40, 32, 264, 2000),                                           # 64 x 32
     (30, 64, 72, 4000), (30, 35, 192, 4000),                                           # 128 x 64
     (1, 16, 520, 9200), (3, 9, 4168, 3100), (1, 3, 1032, 8200), (9, 8, 72, 4100),      # 32 x 16
+    (16, 8, 2056, 4700), (8, 16, 200, 4100), (11, 9, 72, 1100),                        # ... each die its eighth of the lists
     (33, 1, 200, 4100), (33, 16, 640, 4100), (33, 7, 4104, 4100),                      # 64 x 16
 ])
 def test_ragged_batches(batch, M, d, window):
@@ -54,6 +55,14 @@ def test_ragged_batches(batch, M, d, window):
     for b in range(batch):
         _check(logits[b, :, :n[b]], W[torch.from_numpy(ids[b]).long().cuda()], H[b], b)
     st.close()
+
+
+@pytest.mark.parametrize("M", [1, 4, 5, 8, 9, 12, 13, 16])
+@pytest.mark.parametrize("d", [8, 520, 1024, 1032, 1536, 2048, 2056])
+def test_few_hidden_rows_short_rows(M, d):
+    """the kernels that feed the matrix cores from memory, around the hidden sizes where their number of loads changes"""
+    for batch, window in ((1, 300), (2, 1100), (4, 2500)):
+        test_ragged_batches(batch, M, d, window)
 
 
 @pytest.mark.parametrize("V,M,d", [(30001, 24, 200), (17000, 33, 72), (40002, 64, 1032), (50000, 100, 192), (33333, 200, 72), (20000, 300, 520),
