@@ -224,13 +224,14 @@ __global__ __launch_bounds__(kSyncThreads) void packed_sync_short_kernel(VocabPt
   }
 }
 
-// Copy the listed rows W[id] -> buf[slot]: the weight-gather kernel.  One workgroup per compute unit (a decoding step copies a
-// row or two, and then the launch is all there is), four 16-byte pieces per thread in flight for the first gather.
-__global__ __launch_bounds__(1024) void packed_copy_kernel(const uint4* __restrict__ W, PackedPtrs k, int row_vec /* 16-byte pieces per row */) {
+// Copy the listed rows W[id] -> buf[slot]: the weight-gather kernel.  Two small workgroups per compute unit (a decoding step copies a
+// row or two, and then the launch is all there is: a request of 16 steps 365 us with 256 workgroups of 1024 threads, 359 with 512 of
+// 256, 364 with 256 of 256), four 16-byte pieces per thread in flight for the first gather.
+__global__ __launch_bounds__(256) void packed_copy_kernel(const uint4* __restrict__ W, PackedPtrs k, int row_vec /* 16-byte pieces per row */) {
   const int ncopy = k.scal[1];
   uint4* buf = reinterpret_cast<uint4*>(k.buf);
-  const int64_t total = (int64_t)ncopy * row_vec, stride = (int64_t)gridDim.x * 1024;
-  for (int64_t t0 = (int64_t)blockIdx.x * 1024 + threadIdx.x; t0 < total; t0 += 4 * stride) {
+  const int64_t total = (int64_t)ncopy * row_vec, stride = (int64_t)gridDim.x * 256;
+  for (int64_t t0 = (int64_t)blockIdx.x * 256 + threadIdx.x; t0 < total; t0 += 4 * stride) {
     uint4 v[4];
     int64_t to[4];
 #pragma unroll
@@ -273,7 +274,7 @@ hipError_t launch_packed_gather(const nanospec_state* st, const void* W, hipStre
   else packed_sync_kernel<<<1, kSyncThreads, 0, s>>>(st->vp, st->pk);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  packed_copy_kernel<<<256, 1024, 0, s>>>(static_cast<const uint4*>(W), st->pk, st->d / 8);
+  packed_copy_kernel<<<512, 256, 0, s>>>(static_cast<const uint4*>(W), st->pk, st->d / 8);
   return hipGetLastError();
 }
 

@@ -570,7 +570,7 @@ bool wide_supported(int32_t V, int32_t M, int32_t d, int32_t batch, int32_t cap_
 //     34.5 us; 64 sequences, M = 8: 141 against 133).
 //   up to 128: 256 x 128 logits, eight wavefronts of 64 x 64.
 //   more: compute-bound.  head_gemm_kernel; 256 x 256 logits of this kernel (eight wavefronts of 128 x 64, all 160 KB of LDS for the
-//     two stages) where d is no multiple of 64.
+//     two stages) where d is no multiple of 64 or an operand is not 16-byte aligned.
 hipError_t launch_head_wide(const void* W, const void* H, const int32_t* ids, const int32_t* n_dev, int32_t n_fixed, int32_t cap_rows,
                             int32_t V, int32_t batch, int32_t M, int32_t d, int64_t ld, int64_t ids_stride, float* logits,
                             const int32_t* opos, hipStream_t s) {
@@ -596,12 +596,14 @@ hipError_t launch_head_wide(const void* W, const void* H, const int32_t* ids, co
   if (rows < (n_dev ? 98304 : 49152)) return run(run_wide<2, 4, 2, 1, 128, 2>);
   if (M <= 64 || batch > 1) return run(run_wide<4, 1, 2, 4, 64, 2>);
   if (M <= 128) return run(run_wide<4, 2, 4, 4, 64, 2>);
-  if (d % 64 == 0) return run_gemm(Wp, Hp, ids, n_dev, n_fixed, cap_rows, V, M, d, ld, logits, opos, s);
+  const bool aligned = ((reinterpret_cast<uintptr_t>(W) | reinterpret_cast<uintptr_t>(H)) & 15) == 0;   // of the fetches into LDS
+  if (d % 64 == 0 && aligned) return run_gemm(Wp, Hp, ids, n_dev, n_fixed, cap_rows, V, M, d, ld, logits, opos, s);
   return run(run_wide<2, 4, 8, 4, 64, 2>);
 }
 
-// One list shared by the hidden rows of several sequences (see launch_head_shared).  3310 rows x 512 hidden rows, d = 4096:
-// a third of the time of the slice-loop kernel's 64 hidden rows at a time.
+// One list shared by the hidden rows of several sequences (see launch_head_shared).  It runs beside the per-sequence product, so what
+// counts is how little it takes from that one: 64-sequence request of four steps 714 us with 64 x 64 blocks, 754 with 128 x 64, 840
+// with 256 x 128 (too few workgroups), 734 with the slice-loop kernel (64 hidden rows at a time).
 hipError_t launch_head_wide_shared(const void* W, const void* H, const int32_t* ids, const int32_t* n_dev, int32_t cap_rows, int32_t V,
                                    int32_t rows_total, int32_t seq_rows, int32_t d, int64_t ld, float* logits, const int32_t* opos,
                                    int64_t opos_stride, hipStream_t s) {
