@@ -7,8 +7,8 @@
 // lane maxima, a ballot of the lanes that hold that maximum (the lowest such lane owns the
 // lowest-position occurrence), one readlane for the register index, and the winner is blanked.
 // The wavefronts' winners meet in LDS in position order and one wavefront repeats the rounds over
-// them.  Rows longer than one workgroup's reach are cut into chunks whose winners a second kernel
-// merges the same way.  Values of -inf mark "nothing left" (logits are finite by contract).
+// them.  Few dense rows longer than one workgroup reaches are cut into chunks whose winners a second kernel
+// ranks.  Values of -inf mark "nothing left" (logits are finite by contract).
 //
 // Fast path in front of the rounds: lane l of wavefront w always holds positions (64w + l)*EPT ..., whatever
 // the row's length n, so the logits are requested before n has arrived and masked afterwards.  The nwe
@@ -30,7 +30,7 @@
 // LSE variants (Sec. 4.2: the draft distribution is the softmax renormalised over the active set):
 // the same selection, with the values written as log-probabilities z - log(sum_i exp z_i), i over the
 // row's n entries.  The row maximum falls out of the first threshold round, the sum of exp(z - max)
-// is taken wavefront by wavefront and added in wavefront order (chunk order in the merge kernel), so
+// is taken wavefront by wavefront and added in wavefront order, so
 // the result does not depend on timing.
 #include <limits.h>
 
@@ -117,11 +117,10 @@ __device__ __forceinline__ void wave_select(float (&v)[EPT], int k, int lane, Em
 // final result itself, the other chunks leave at once and the merge kernel has nothing to do.
 constexpr int kLaneCand = 4;   // candidates per lane the owner path keeps in registers
 
-template <int EPT, int NW, bool FINAL, bool LSE>
+template <int EPT, int NW, bool FINAL, bool LSE>   // LSE: whole rows only
 __device__ __forceinline__ void topk_select(const float* __restrict__ logits, int64_t ld, const int32_t* __restrict__ ids, int64_t ids_stride,
                                             const int32_t* __restrict__ n_dev, int n_fixed, int M, int k, int32_t* __restrict__ out_ids,
-                                            float* __restrict__ out_vals, float* __restrict__ cand_val, int32_t* __restrict__ cand_pos,
-                                            float2* __restrict__ cand_ms) {
+                                            float* __restrict__ out_vals, float* __restrict__ cand_val, int32_t* __restrict__ cand_pos) {
   constexpr int E2 = (NW * kMaxK + 63) / 64;
   __shared__ float s_val[NW * kMaxK];
   __shared__ int s_pos[NW * kMaxK];
@@ -241,8 +240,7 @@ __device__ __forceinline__ void topk_select(const float* __restrict__ logits, in
       float zmax = wave_max(wm);
       zmax = zmax == -INFINITY ? 0.f : zmax;                // empty chunk: every factor below is exp(-inf) = 0
       const float se = wave_add(lane < NW ? s_sum[lane] * expf(wm - zmax) : 0.f);
-      if (fin) lse = zmax + logf(se);
-      else if (tid == 0) cand_ms[row * gridDim.x + c] = make_float2(zmax, se);
+      lse = zmax + logf(se);
     }
     uint32_t flags = 0;
 #pragma unroll
@@ -422,9 +420,8 @@ __global__ __launch_bounds__(64 * NW) void topk_select_kernel(const float* __res
                                                              const int32_t* __restrict__ ids, int64_t ids_stride,
                                                              const int32_t* __restrict__ n_dev, int n_fixed, int M, int k,
                                                              int32_t* __restrict__ out_ids, float* __restrict__ out_vals,
-                                                             float* __restrict__ cand_val, int32_t* __restrict__ cand_pos,
-                                                             float2* __restrict__ cand_ms) {
-  topk_select<EPT, NW, FINAL, LSE>(logits, ld, ids, ids_stride, n_dev, n_fixed, M, k, out_ids, out_vals, cand_val, cand_pos, cand_ms);
+                                                             float* __restrict__ cand_val, int32_t* __restrict__ cand_pos) {
+  topk_select<EPT, NW, FINAL, LSE>(logits, ld, ids, ids_stride, n_dev, n_fixed, M, k, out_ids, out_vals, cand_val, cand_pos);
 }
 
 // Long rows (more positions than one workgroup's registers hold): one workgroup per row walks it in pieces of 16 logits
@@ -742,61 +739,53 @@ __global__ __launch_bounds__(1024) void topk_list_kernel(const float* __restrict
                                                          int64_t ids_stride, const int32_t* __restrict__ n_dev, int n_fixed, int M, int k,
                                                          int32_t* __restrict__ out_ids, float* __restrict__ out_vals) {
   if ((n_dev ? n_dev[blockIdx.z] : n_fixed) <= kTopkChunk)
-    topk_select<16, 16, true, LSE>(logits, ld, ids, ids_stride, n_dev, n_fixed, M, k, out_ids, out_vals, nullptr, nullptr, nullptr);
+    topk_select<16, 16, true, LSE>(logits, ld, ids, ids_stride, n_dev, n_fixed, M, k, out_ids, out_vals, nullptr, nullptr);
   else
     topk_stream<16, LSE>(logits, ld, ids, ids_stride, n_dev, n_fixed, M, k, out_ids, out_vals);
 }
 
-// Merge the per-chunk winners of one row (nchunks*k <= 1024 candidates, in position order).
-template <bool LSE>
-__global__ __launch_bounds__(64) void topk_merge_kernel(const float* __restrict__ cand_val, const int32_t* __restrict__ cand_pos,
-                                                        const float2* __restrict__ cand_ms, int nchunks,
-                                                        const int32_t* __restrict__ ids, int64_t ids_stride, int M, int k,
-                                                        int32_t* __restrict__ out_ids, float* __restrict__ out_vals,
-                                                        const int32_t* __restrict__ n_dev, int n_fixed) {
-  constexpr int EPT = 16;
-  const int m = blockIdx.y, b = blockIdx.z, lane = threadIdx.x;
-  if ((n_dev ? n_dev[b] : n_fixed) <= kTopkChunk) return;   // the first chunk's workgroup has written the result
-  const int64_t row = (int64_t)b * M + m;
+// Merge the per-chunk winners of one row (nchunks*k <= 1024 candidates, in position order): one candidate per thread, its rank
+// among all of them as (candidate, group of four) work items over the workgroup.  (17 rows of 128256, k = 40,
+// selection and merge: 24.9 -> 19.7 us against rounds of one wavefront; k = 10 11.9 -> 9.6; 8 rows of 32000, k = 40 22.9 -> 9.1; 256
+// threads instead of 1024: k = 40 39 us.)  Dense rows only: positions are ids.
+__global__ __launch_bounds__(1024) void topk_merge_kernel(const float* __restrict__ cand_val, const int32_t* __restrict__ cand_pos,
+                                                          int nchunks, int k,
+                                                          int32_t* __restrict__ out_ids, float* __restrict__ out_vals) {
+  __shared__ __attribute__((aligned(16))) float s_v[1024 + 4];
+  __shared__ int s_r[1024];
+  const int tid = threadIdx.x;
+  const int64_t row = blockIdx.y;
   const int total = nchunks * k;
-  const float* cv = cand_val + row * total;
-  const int32_t* cp = cand_pos + row * total;
-  float v[EPT];
-#pragma unroll
-  for (int e = 0; e < EPT; ++e) {
-    const int q = lane * EPT + e;
-    v[e] = (q < total) ? cv[q] : -INFINITY;
+  float val = -INFINITY;
+  int pos = -1;
+  if (tid < total) {
+    val = cand_val[row * total + tid];
+    pos = cand_pos[row * total + tid];
+    s_v[tid] = val;
+    s_r[tid] = 0;
   }
-  float lse = 0.f;
-  if (LSE) {                                              // chunk (max, sum) pairs -> one log sum exp, in chunk order
-    const float2* ms = cand_ms + row * nchunks;
-    float zmax = -INFINITY;
-    for (int q = lane; q < nchunks; q += 64) zmax = fmaxf(zmax, ms[q].y > 0.f ? ms[q].x : -INFINITY);
-    zmax = wave_max(zmax);
-    zmax = zmax == -INFINITY ? 0.f : zmax;
-    float se = 0.f;
-    for (int q0 = 0; q0 < nchunks; q0 += 64) {
-      const int q = q0 + lane;
-      float t = 0.f;
-      if (q < nchunks && ms[q].y > 0.f) t = ms[q].y * expf(ms[q].x - zmax);
-      se += wave_add(t);
+  if (tid < 4) s_v[total + tid] = __builtin_nanf("");       // pads the last group of four; compares false with everything
+  __syncthreads();
+  const int lg = total <= 1 ? 0 : 32 - __clz(total - 1);
+  const int items = ((total + 3) >> 2) << lg;
+  for (int w = tid; w < items; w += 1024) {
+    const int t = w & ((1 << lg) - 1), q = (w >> lg) * 4;
+    if (t < total) {
+      const float x = s_v[t];
+      const float4 o = *reinterpret_cast<const float4*>(&s_v[q]);
+      int r = (o.x > x || (o.x == x && q < t)) ? 1 : 0;             // list order is position order
+      r += (o.y > x || (o.y == x && q + 1 < t)) ? 1 : 0;
+      r += (o.z > x || (o.z == x && q + 2 < t)) ? 1 : 0;
+      r += (o.w > x || (o.w == x && q + 3 < t)) ? 1 : 0;
+      if (r) atomicAdd(&s_r[t], r);
     }
-    lse = zmax + logf(se);
   }
-  float wval = -INFINITY;
-  int wq = 0;
-  wave_select<EPT>(v, k, lane, [&](int r, float val, int q) {
-    if (lane == r) {
-      wval = val;
-      wq = q;
-    }
-  });
-  if (lane < k) {
-    const bool none = (wval == -INFINITY);
-    const int pos = none ? -1 : cp[wq];
-    const int64_t o = row * k + lane;
-    out_ids[o] = none ? -1 : (ids ? ids[b * ids_stride + pos] : pos);
-    if (out_vals) out_vals[o] = (LSE && !none) ? wval - lse : wval;
+  __syncthreads();
+  if (tid < total && s_r[tid] < k) {
+    const bool none = val == -INFINITY;                     // fewer than k exist
+    const int64_t o = row * k + s_r[tid];
+    out_ids[o] = none ? -1 : pos;
+    if (out_vals) out_vals[o] = val;
   }
 }
 
@@ -804,7 +793,7 @@ static int chunks_for(int32_t cap) { return (cap + kTopkChunk - 1) / kTopkChunk;
 
 int64_t topk_workspace_bytes(int32_t cap, int32_t rows, int32_t k) {
   if (cap <= kTopkChunk) return 0;
-  return (int64_t)rows * chunks_for(cap) * (k * 8 + 8);   // (value, position) per winner + (max, sum) per chunk
+  return (int64_t)rows * chunks_for(cap) * (k * 8 + 8);   // (value, position) per winner; the eight bytes per chunk more are unused, the size is part of the interface
 }
 
 template <bool LSE>
@@ -814,17 +803,17 @@ static hipError_t launch_topk_t(const float* logits, int64_t ld, const int32_t* 
   const dim3 rows(1, M, batch);
   if (cap <= 4096) {
     topk_select_kernel<16, 4, true, LSE><<<rows, 256, 0, s>>>(logits, ld, ids, ids_stride, n_dev, n_fixed, M, k, out_ids,
-                                                            out_vals, nullptr, nullptr, nullptr);
+                                                            out_vals, nullptr, nullptr);
     return hipGetLastError();
   }
   if (cap <= 8192) {   // eight wavefronts beat sixteen (c3: 6.2 -> 5.0 us, c4: 8.2 -> 5.8 us) and four with 32 logits per lane (5.5, 6.1)
     topk_select_kernel<16, 8, true, LSE><<<rows, 512, 0, s>>>(logits, ld, ids, ids_stride, n_dev, n_fixed, M, k, out_ids,
-                                                            out_vals, nullptr, nullptr, nullptr);
+                                                            out_vals, nullptr, nullptr);
     return hipGetLastError();
   }
   if (cap <= kTopkChunk) {
     topk_select_kernel<16, 16, true, LSE><<<rows, 1024, 0, s>>>(logits, ld, ids, ids_stride, n_dev, n_fixed, M, k, out_ids,
-                                                              out_vals, nullptr, nullptr, nullptr);
+                                                              out_vals, nullptr, nullptr);
     return hipGetLastError();
   }
   const int nch = chunks_for(cap);
@@ -852,12 +841,11 @@ static hipError_t launch_topk_t(const float* logits, int64_t ld, const int32_t* 
   const int64_t slots = (int64_t)batch * M * nch * k;
   float* cv = reinterpret_cast<float*>(ws);
   int32_t* cp = reinterpret_cast<int32_t*>(ws + slots * 4);
-  float2* ms = reinterpret_cast<float2*>(ws + slots * 8);
-  topk_select_kernel<16, 16, false, LSE><<<dim3(nch, M, batch), 1024, 0, s>>>(logits, ld, ids, ids_stride, n_dev, n_fixed, M,
-                                                                            k, out_ids, out_vals, cv, cp, ms);
+  topk_select_kernel<16, 16, false, false><<<dim3(nch, M, batch), 1024, 0, s>>>(logits, ld, ids, ids_stride, n_dev, n_fixed, M, k, out_ids,
+                                                                              out_vals, cv, cp);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  topk_merge_kernel<LSE><<<rows, 64, 0, s>>>(cv, cp, ms, nch, ids, ids_stride, M, k, out_ids, out_vals, n_dev, n_fixed);
+  topk_merge_kernel<<<dim3(1, (unsigned)nrows), 1024, 0, s>>>(cv, cp, nch, k, out_ids, out_vals);
   return hipGetLastError();
 }
 
