@@ -524,8 +524,10 @@ __device__ __forceinline__ void topk_stream(const float* __restrict__ logits, in
     }
     __syncthreads();
   };
-  // the list's k best stay, in order; the k-th is the threshold from here on
+  // The list's k best stay, in order; the k-th is the threshold from here on.  Fewer than k entries (a first piece of
+  // NaNs, which never enter the list) all stay and there is no threshold yet.
   auto cut_back = [&](int C) {
+    const int kept = C < k ? C : k;
     rank_list(C);
     float kv[kStreamList / NT];
     int kp[kStreamList / NT], kr[kStreamList / NT];
@@ -543,9 +545,10 @@ __device__ __forceinline__ void topk_stream(const float* __restrict__ logits, in
         s_v[kr[i]] = kv[i];
         s_p[kr[i]] = kp[i];
       }
-    if (tid == 0) s_n = k;
+    if (tid == 0) s_n = kept;
     __syncthreads();
-    T = s_v[k - 1];
+    T = C < k ? -INFINITY : s_v[k - 1];
+    held = kept;
   };
   auto append = [&](const float4(&v)[4], int p, float t, bool equal_too) {
     uint32_t f = 0;
@@ -662,9 +665,8 @@ __device__ __forceinline__ void topk_stream(const float* __restrict__ logits, in
       __syncthreads();
       C = s_n;
     }
-    if (p + 1 < steps && (p == 0 || C > kStreamList / 4)) {   // a full piece: C >= k
+    if (p + 1 < steps && (p == 0 || C > kStreamList / 4)) {
       cut_back(C);
-      held = k;
     } else {
       __syncthreads();                                     // s_n has been read by all before the next piece adds to it
       held = C;
@@ -696,7 +698,7 @@ __device__ __forceinline__ void topk_stream(const float* __restrict__ logits, in
     out_ids[row * k + r] = gid;
     if (out_vals) out_vals[row * k + r] = (LSE && val != -INFINITY) ? val - lse : val;
   };
-  if (has_x) {                                             // a superset of the winners is listed: the rank decides
+  if (has_x && xv == xv) {                                 // not a NaN, which has no rank; a superset of the winners is listed: the rank decides
     const int at = atomicAdd(&s_n, 1);
     s_v[at] = xv;
     s_p[at] = xpos;

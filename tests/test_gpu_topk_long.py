@@ -84,3 +84,71 @@ def test_lists(kind, n, batch, M, k):
             z = ev.double() - torch.logsumexp(x.double(), dim=1, keepdim=True)
             assert torch.all((logp[b, :, :have].double() - z).abs() <= 1e-5 * (1 + z.abs())), b
     st.close()
+
+
+def _with_nans(x, how):
+    """the first piece or nearly everything NaN, or single ones at the row's ends and across the pieces"""
+    n = x.shape[1]
+    x = x.clone()
+    if how == "all":
+        x[:] = torch.nan
+    elif how == "front":
+        x[:, :min(n, 16400)] = torch.nan
+    elif how == "front_but_few":
+        keep = x[:, 100:120].clone()
+        x[:, :min(n, 16400)] = torch.nan
+        x[:, 100:120] = keep
+    elif how == "all_but_few":
+        keep = x[:, n // 2:n // 2 + 7].clone()
+        x[:] = torch.nan
+        x[:, n // 2:n // 2 + 7] = keep
+    else:
+        x[:, ::3] = torch.nan
+        x[:, :3] = torch.nan
+        x[:, -3:] = torch.nan
+    return x
+
+
+def _check_missing(x, ids, vals, k, names=None):
+    """x: logits with -inf where an element cannot be selected; slots without one hold -1 and -inf"""
+    ei, ev = _expect(x, k)
+    none = ev == -torch.inf
+    ei = ei if names is None else names[ei]
+    assert torch.equal(ids.long(), torch.where(none, -1, ei)) and torch.equal(vals, ev)
+
+
+NANS = ["all", "front", "front_but_few", "all_but_few", "scattered"]
+
+
+@pytest.mark.parametrize("how", NANS)
+@pytest.mark.parametrize("rows,V,k", [(3, 40003, 10), (96, 32771, 40), (515, 24589, 64)])
+def test_dense_rows_with_nans(how, rows, V, k):
+    """NaN logits are no candidates: a row has fewer winners, the slots left over are padding"""
+    x = _with_nans(_rows("normal", rows, V), how)
+    nbytes = B.nanospec_dense_topk_workspace(V, rows, k)
+    ws = torch.empty(max(nbytes, 16), dtype=torch.uint8, device="cuda")
+    ids = torch.full((rows, k), -7, dtype=torch.int32, device="cuda")
+    vals = torch.full((rows, k), 9.0, device="cuda")
+    B.nanospec_dense_topk(x, V, rows, k, ids, vals, ws, nbytes)
+    _check_missing(torch.nan_to_num(x, nan=-torch.inf), ids, vals, k)
+
+
+@pytest.mark.parametrize("how", NANS)
+@pytest.mark.parametrize("n", [16388, 32770, 39999])
+@pytest.mark.parametrize("batch,M,k", [(2, 3, 10), (1, 2, 64), (16, 32, 5)])
+def test_lists_with_nans(how, n, batch, M, k):
+    V, window = 60000, 40000
+    st = B.State(V, 8, batch, window, 1, M, k)
+    ids_of = np.sort(np.random.default_rng(n).permutation(V)[:n]).astype(np.int32)
+    flat, off = csr([ids_of] * batch)
+    B.nanospec_vocab_init(st.h, dev_ids(flat), off, None, np.zeros(batch + 1, np.int32))
+    logits = torch.full((batch, M, st.capacity), 1e30, device="cuda")
+    x = _with_nans(_rows("normal", batch * M, n), how)
+    logits[:, :, :n] = x.view(batch, M, n)
+    ids, vals = torch.full((batch * M, k), -7, dtype=torch.int32, device="cuda"), torch.full((batch * M, k), 9.0, device="cuda")
+    B.nanospec_topk_remap(st.h, logits, M, k, ids, vals)
+    ids2, logp = torch.full_like(ids, -7), torch.empty_like(vals)
+    B.nanospec_topk_logprob_remap(st.h, logits, M, k, ids2, logp)
+    _check_missing(torch.nan_to_num(x, nan=-torch.inf), ids, vals, k, torch.from_numpy(ids_of).long().cuda())
+    assert torch.equal(ids, ids2)
+    st.close()
