@@ -525,7 +525,7 @@ __device__ __forceinline__ void topk_stream(const float* __restrict__ logits, in
     __syncthreads();
   };
   // The list's k best stay, in order; the k-th is the threshold from here on.  Fewer than k entries (a first piece of
-  // NaNs, which never enter the list) all stay and there is no threshold yet.
+  // -inf and NaN, which never enter the list) all stay and there is no threshold yet.
   auto cut_back = [&](int C) {
     const int kept = C < k ? C : k;
     rank_list(C);
@@ -657,7 +657,7 @@ __device__ __forceinline__ void topk_stream(const float* __restrict__ logits, in
     }
     const int valid = nq - p * QP < NT ? nq - p * QP : NT;
     if (p == 0) T = vote(ml, valid);                       // its barrier also publishes s_n = 0
-    append(v, p, T, p == 0);
+    append(v, p, T, p == 0 && T != -INFINITY);             // -inf is no candidate: it is what an empty slot holds
     __syncthreads();
     int C = s_n;
     if (C > kStreamList - 8) {                             // uniform; eight entries are kept for the elements outside the pieces
@@ -698,7 +698,7 @@ __device__ __forceinline__ void topk_stream(const float* __restrict__ logits, in
     out_ids[row * k + r] = gid;
     if (out_vals) out_vals[row * k + r] = (LSE && val != -INFINITY) ? val - lse : val;
   };
-  if (has_x && xv == xv) {                                 // not a NaN, which has no rank; a superset of the winners is listed: the rank decides
+  if (has_x && xv > -INFINITY) {                           // neither a NaN, which has no rank, nor -inf; a superset of the winners is listed: the rank decides
     const int at = atomicAdd(&s_n, 1);
     s_v[at] = xv;
     s_p[at] = xpos;

@@ -86,26 +86,26 @@ def test_lists(kind, n, batch, M, k):
     st.close()
 
 
-def _with_nans(x, how):
-    """the first piece or nearly everything NaN, or single ones at the row's ends and across the pieces"""
+def _without(x, how, what=torch.nan):
+    """`what` in the first piece or nearly everywhere, or at single places at the row's ends and across the pieces"""
     n = x.shape[1]
     x = x.clone()
     if how == "all":
-        x[:] = torch.nan
+        x[:] = what
     elif how == "front":
-        x[:, :min(n, 16400)] = torch.nan
+        x[:, :min(n, 16400)] = what
     elif how == "front_but_few":
         keep = x[:, 100:120].clone()
-        x[:, :min(n, 16400)] = torch.nan
+        x[:, :min(n, 16400)] = what
         x[:, 100:120] = keep
     elif how == "all_but_few":
         keep = x[:, n // 2:n // 2 + 7].clone()
-        x[:] = torch.nan
+        x[:] = what
         x[:, n // 2:n // 2 + 7] = keep
     else:
-        x[:, ::3] = torch.nan
-        x[:, :3] = torch.nan
-        x[:, -3:] = torch.nan
+        x[:, ::3] = what
+        x[:, :3] = what
+        x[:, -3:] = what
     return x
 
 
@@ -117,14 +117,14 @@ def _check_missing(x, ids, vals, k, names=None):
     assert torch.equal(ids.long(), torch.where(none, -1, ei)) and torch.equal(vals, ev)
 
 
-NANS = ["all", "front", "front_but_few", "all_but_few", "scattered"]
+HOW = ["all", "front", "front_but_few", "all_but_few", "scattered"]
 
 
-@pytest.mark.parametrize("how", NANS)
+@pytest.mark.parametrize("how", HOW)
 @pytest.mark.parametrize("rows,V,k", [(3, 40003, 10), (96, 32771, 40), (515, 24589, 64)])
 def test_dense_rows_with_nans(how, rows, V, k):
     """NaN logits are no candidates: a row has fewer winners, the slots left over are padding"""
-    x = _with_nans(_rows("normal", rows, V), how)
+    x = _without(_rows("normal", rows, V), how)
     nbytes = B.nanospec_dense_topk_workspace(V, rows, k)
     ws = torch.empty(max(nbytes, 16), dtype=torch.uint8, device="cuda")
     ids = torch.full((rows, k), -7, dtype=torch.int32, device="cuda")
@@ -133,7 +133,7 @@ def test_dense_rows_with_nans(how, rows, V, k):
     _check_missing(torch.nan_to_num(x, nan=-torch.inf), ids, vals, k)
 
 
-@pytest.mark.parametrize("how", NANS)
+@pytest.mark.parametrize("how", HOW)
 @pytest.mark.parametrize("n", [16388, 32770, 39999])
 @pytest.mark.parametrize("batch,M,k", [(2, 3, 10), (1, 2, 64), (16, 32, 5)])
 def test_lists_with_nans(how, n, batch, M, k):
@@ -143,7 +143,7 @@ def test_lists_with_nans(how, n, batch, M, k):
     flat, off = csr([ids_of] * batch)
     B.nanospec_vocab_init(st.h, dev_ids(flat), off, None, np.zeros(batch + 1, np.int32))
     logits = torch.full((batch, M, st.capacity), 1e30, device="cuda")
-    x = _with_nans(_rows("normal", batch * M, n), how)
+    x = _without(_rows("normal", batch * M, n), how)
     logits[:, :, :n] = x.view(batch, M, n)
     ids, vals = torch.full((batch * M, k), -7, dtype=torch.int32, device="cuda"), torch.full((batch * M, k), 9.0, device="cuda")
     B.nanospec_topk_remap(st.h, logits, M, k, ids, vals)
@@ -151,4 +151,31 @@ def test_lists_with_nans(how, n, batch, M, k):
     B.nanospec_topk_logprob_remap(st.h, logits, M, k, ids2, logp)
     _check_missing(torch.nan_to_num(x, nan=-torch.inf), ids, vals, k, torch.from_numpy(ids_of).long().cuda())
     assert torch.equal(ids, ids2)
+    st.close()
+
+
+@pytest.mark.parametrize("how", HOW)
+@pytest.mark.parametrize("rows,V,k", [(3, 40003, 10), (96, 32771, 40), (515, 24589, 64)])
+def test_rows_with_minus_infinity(how, rows, V, k):
+    """in a long row a logit of -inf (a masked token) is an empty slot, as a dense row and as a list of the same length"""
+    x = _without(_rows("normal", rows, V), how, -torch.inf)
+    nbytes = B.nanospec_dense_topk_workspace(V, rows, k)
+    ws = torch.empty(max(nbytes, 16), dtype=torch.uint8, device="cuda")
+    ids = torch.full((rows, k), -7, dtype=torch.int32, device="cuda")
+    vals = torch.full((rows, k), 9.0, device="cuda")
+    B.nanospec_dense_topk(x, V, rows, k, ids, vals, ws, nbytes)
+    _check_missing(x, ids, vals, k)
+    st = B.State(V, 8, 1, V, 1, rows, k)
+    names = torch.arange(V, dtype=torch.int32, device="cuda")
+    B.nanospec_vocab_init(st.h, names, np.array([0, V], np.int32), None, np.zeros(2, np.int32))
+    logits = torch.full((rows, st.capacity), 1e30, device="cuda")
+    logits[:, :V] = x
+    ids2, vals2 = torch.full_like(ids, -7), torch.full_like(vals, 9.0)
+    B.nanospec_topk_remap(st.h, logits, rows, k, ids2, vals2)
+    assert torch.equal(ids, ids2) and torch.equal(vals, vals2)
+    B.nanospec_topk_logprob_remap(st.h, logits, rows, k, ids2, vals2)
+    assert torch.equal(ids, ids2)
+    z = torch.where(vals == -torch.inf, vals.double(), vals.double() - torch.logsumexp(x.double(), dim=1, keepdim=True))
+    assert torch.equal(vals2 == -torch.inf, z == -torch.inf)
+    assert torch.all(torch.where(z == -torch.inf, 0.0, (vals2.double() - z).abs()) <= 1e-5 * (1 + torch.where(z == -torch.inf, 0.0, z.abs())))
     st.close()
