@@ -121,9 +121,9 @@ HOW = ["all", "front", "front_but_few", "all_but_few", "scattered"]
 
 
 @pytest.mark.parametrize("how", HOW)
-@pytest.mark.parametrize("rows,V,k", [(3, 40003, 10), (96, 32771, 40), (515, 24589, 64)])
+@pytest.mark.parametrize("rows,V,k", [(96, 32771, 40), (515, 24589, 64)])
 def test_dense_rows_with_nans(how, rows, V, k):
-    """NaN logits are no candidates: a row has fewer winners, the slots left over are padding"""
+    """rows walked by one workgroup: NaN logits are no candidates, a row has fewer winners and the slots left over are padding"""
     x = _without(_rows("normal", rows, V), how)
     nbytes = B.nanospec_dense_topk_workspace(V, rows, k)
     ws = torch.empty(max(nbytes, 16), dtype=torch.uint8, device="cuda")
