@@ -1,0 +1,164 @@
+// Which kernel and which block shape a head call takes: plain host arithmetic on sizes, without HIP, so that the launchers
+// and the CPU model of the kernels' addresses (tests/test_head_address_model.py) read the same lines.  The kernels themselves and
+// what bounds them: head.hip, wide.hip.
+#pragma once
+#include <stdint.h>
+
+namespace nanospec {
+
+// ---- the register-blocked product (wide.hip) ----------------------------------------------------------------------
+
+// its 32-bit byte offsets reach every row
+inline bool wide_reaches(int32_t V, int32_t M, int32_t d) { return (int64_t)V * d * 2 <= 0xffffffffll && (int64_t)M * d * 2 <= 0xffffffffll; }
+
+// Which products the register-blocked kernel takes, of those whose rows 32-bit byte offsets reach.
+// More than 16 hidden rows:
+//   * any number of rows while d <= 2048: one launch whose time is its d / 128 steps (6.0 us at d = 1152, 7.2 at 2048) against
+//     two launches of split-K + reduce (9.6, 8.9);
+//   * longer rows from the capacity on at which it beats split-K + reduce, whose workgroups each walk 512 columns only
+//     (d = 4096: M = 64, 1000 live rows 11.1 against 9.5 us, 2000: 10.7 / 11.4, 3000: 11.7 / 12.4; M = 24, 2000 live rows
+//     11.6 / 10.7, 3000: 12.4 / 13.1).
+// Up to 16 (the kernels of head.hip feed the matrix cores straight from memory, at a quarter of their rate and with the hidden
+// rows fetched again for every 16 list rows), where there are rows enough to fill blocks of 32 or 64 with whole hidden-row blocks:
+//   * lists of 131072 rows of capacity together (64 sequences of 2300, d = 4096: M = 8 133 against 147 us, M = 16 140 / 244, M = 1
+//     124 / 130; 32 sequences, M = 8: 79 / 84; 16: 46 / 46);
+//   * 9 to 16 hidden rows: lists from 9216 rows on (2 sequences of 3000 rows, d = 4096: 12.5 / 15.7; one of 3000 11.2 / 9.2; 8 of 2300
+//     31 / 38; 16 of 2300, d = 8192: 91 / 99), but one sequence with d > 5120 (8400 rows, d = 8192: 40 / 38); dense heads
+//     (128k x 4096, M = 16: 201 / 225; x 5120 232 / 259), but whole passes of the K-loop kernel (x 8192: 411 / 363);
+//   * 5 to 8: dense heads (x 2048 95 / 121, x 3584 155 / 160, x 5120 220 / 250) that are no whole passes there (x 4096 194 / 177, x 8192
+//     406 / 332);
+//   * fewer: dense heads with d <= 1024 (M = 3 x 1024 46 / 69; M = 2 x 2048 91 / 84);
+//   * up to 8, lists: one sequence from 8192 rows on with d <= 4096 (8000 rows, M = 8 14.8 / 16.4; 8000 x 1024, M = 6 5.9 / 13.1),
+//     several from 36864 on with d <= 2048 (16 of 2300, M = 8 x 2048 27 / 29; 8 of 2300, x 1024 10.5 / 12.3; x 4096 28 / 26), eight
+//     or more from 73728 on with d <= 4096 (16 of 2300, x 4096, each die its eighth of the lists: 43 / 46).
+inline bool wide_supported(int32_t V, int32_t M, int32_t d, int32_t batch, int32_t cap_rows, bool dense) {
+  if (!wide_reaches(V, M, d)) return false;
+  if (M <= 16) {
+    const int64_t rows = (int64_t)cap_rows * batch;
+    if (rows > 0x20000000ll) return false;                         // workgroups of one launch
+    if (dense) return rows >= 16384 && (d <= 1024 || (M > 8 && (d <= 4096 || d % 2048 != 0)) || (M > 4 && M <= 8 && d % 4096 != 0));
+    if (rows >= 131072) return true;
+    if (M > 8) return rows >= 9216 && (d <= 5120 || batch > 1);
+    return batch == 1 ? rows >= 8192 && d <= 4096 : (rows >= 36864 && d <= 2048) || (rows >= 73728 && d <= 4096 && batch >= 8);
+  }
+  const int64_t rows = (int64_t)cap_rows * batch;
+  if (rows * ((M + 31) / 32) > 0x40000000ll) return false;         // workgroups of one launch
+  if (M > 64 && batch == 1 && rows < 16384) return false;          // many hidden rows on a short list: 64 at a time
+  return d <= 2048 || rows >= (M <= 32 ? 4096 : 2560);
+}
+
+// Block shapes as (logit rows x hidden rows); kWideGemm is head_gemm_kernel.
+enum WideShape : int32_t { kWide32x16, kWide64x16, kWide32x32, kWide64x32, kWide32x64, kWide64x64, kWide128x64, kWide256x128, kWide256x256, kWideGemm, kWideShapes };
+
+// What the shapes are made of: WR x WH wavefronts of FR x FH fragments of 16 x 16 logits, K in steps of BK columns, D register sets.
+struct WideBlock {
+  int32_t WR, WH, FR, FH, BK, D;
+};
+constexpr WideBlock kWideBlocks[kWideShapes] = {{2, 1, 1, 1, 128, 4}, {4, 1, 1, 1, 128, 4}, {2, 2, 1, 1, 128, 4}, {4, 1, 1, 2, 128, 2}, {2, 4, 1, 1, 128, 2},
+                                                {2, 4, 2, 1, 128, 2}, {4, 1, 2, 4, 64, 2},  {4, 2, 4, 4, 64, 2},  {2, 4, 8, 4, 64, 2},  {2, 4, 8, 4, 64, 2}};
+
+// The block shapes (figures for lists: sequences that share many of their rows).  Up to 64 hidden rows a launch is bound by the bytes a compute unit has in flight over the memory
+// latency (few rows) or by HBM (many), so the block grows with the rows: the smallest one while larger blocks would leave
+// compute units without work, larger ones to fetch the hidden rows (and, beyond 32 x 32, W_head) less often.  A launch
+// only knows the capacity of the lists; thresholds are for live rows around 0.6 of it, dense heads (live == capacity) count double.
+//   32 x 32, four register sets of 128 columns: d = 3584, M = 64, 3000 live rows 11.7 us; two sets of 256 columns 12.2;
+//     two of 128 13.3; four of 64 13.1; 32 x 64 15.4; 64 x 64 19.8.  With d = 3712 12.3 (split-K + reduce with bounds tests 16.4).
+//   32 x 64, eight wavefronts: 4 sequences of 2000 rows, M = 60, d = 4096: 18.1 us; 32 x 32 23.7, 64 x 64 22.6 (slice-loop
+//     kernel of head.hip 28.4); at 2 sequences 16.9 against 14.3 for 32 x 32.
+//   64 x 64, eight wavefronts: 8 sequences of 2000 rows 25.1 us; 32 x 64 31.5, 32 x 32 38.1, 128 x 64 37.1 (slice-loop kernel
+//     36.4); one list of 12000 rows 26.8 against 34.2 / 39.0.
+//   128 x 64, four wavefronts, 60 KB of LDS, two workgroups per compute unit: 64 sequences of 2300 rows, d = 2048: 92 us; 64 x 64
+//     98 (slice-loop kernel 119); the dense 128k x 4096 head at 48 hidden rows 225 us (64 x 32 blocks 258).
+//   up to 32 hidden rows: 32 x 32 (16 sequences of 1500 rows 32 us, slice-loop kernel 49), on long lists and dense 64 x 32 (64
+//     sequences of 2000 rows, M = 17: 127 us, slice-loop kernel 196; dense 128k x 4096, M = 24: 205 us, 128 x 64 219, 32 x 32 228;
+//     32000 rows 51 / 60 / 59).
+//   up to 16: dense and on long lists 64 x 16, on short ones 32 x 16 of two wavefronts (8 sequences of 2300 rows, M = 16: 31 against
+//     34.5 us; 64 sequences, M = 8: 141 against 133).
+//   up to 128: 256 x 128 logits, eight wavefronts of 64 x 64.
+//   more: compute-bound.  head_gemm_kernel; 256 x 256 logits of this kernel (eight wavefronts of 128 x 64, all 160 KB of LDS for the
+//     two stages) where d is no multiple of 64 or an operand is not 16-byte aligned.
+inline WideShape wide_shape(int32_t M, int32_t d, int32_t batch, int32_t cap_rows, bool dense, bool aligned) {
+  const int64_t rows = (int64_t)cap_rows * batch * (dense ? 2 : 1);
+  if (M <= 16) return dense || rows >= 131072 ? kWide64x16 : kWide32x16;
+  if (M <= 32) return rows < 65536 && !dense ? kWide32x32 : kWide64x32;
+  if (rows < 10240) return kWide32x32;
+  if (rows < 18432) return kWide32x64;
+  if (rows < (dense ? 49152 : 98304)) return kWide64x64;
+  if (M <= 64 || batch > 1) return kWide128x64;
+  if (M <= 128) return kWide256x128;
+  return d % 64 == 0 && aligned ? kWideGemm : kWide256x256;
+}
+
+// Sequences hold many of the same rows, and a die's L2 sees a row again only if the sequences that hold it run there at the
+// same time: for few hidden rows each die takes one eighth of every list (64 sequences of 2300 rows, M = 8: 135 -> 130.5 us, 32: 79
+// -> 73.5, 16: 47 -> 43; 8, M = 16: 31.1 -> 29.4), but not where the hidden rows of all sequences, which every die then needs, are as
+// many bytes as the rows (64 sequences, M = 16: 140 -> 145; M = 60 on 8 sequences 25 -> 26).
+inline bool wide_by_die(int32_t M, int32_t batch, int32_t cap_rows, bool dense) {
+  const int64_t rows = (int64_t)cap_rows * batch * (dense ? 2 : 1);
+  return batch >= 8 && M <= 16 && (M <= 8 || rows < 131072);
+}
+
+// One list shared by the hidden rows of several sequences (see launch_head_shared).  It runs beside the per-sequence product, so what
+// counts is how little it takes from that one: 64-sequence request of four steps 714 us with 64 x 64 blocks, 754 with 128 x 64, 840
+// with 256 x 128 (too few workgroups), 734 with the slice-loop kernel (64 hidden rows at a time).
+inline WideShape wide_shared_shape(int32_t rows_total) { return rows_total <= 16 ? kWide32x16 : rows_total <= 32 ? kWide32x32 : kWide64x64; }
+
+// ---- the kernels of head.hip, up to 64 hidden rows per sequence and launch ----------------------------------------------
+
+// Up to 16 hidden rows: MT row tiles of four hidden rows, KS loads per row and wavefront; head_quad_kernel with NRG row groups of 4 * RT rows
+// or, with a K loop, head_quad_private_kernel with 4 * RT rows per workgroup.
+struct QuadPlan {
+  int32_t MT, KS, NRG, RT;
+  bool loop;
+};
+
+// Which kernel (all measured on MI355X):
+//  * d fits one K-iteration (d <= 512*KS): the shared-hidden-row kernel.  Rows per workgroup follow the
+//    row capacity so that small vocabularies still spread over the chip (16 / 8 / 4 rows); with tens
+//    of thousands of rows it still wins (dense 128k head, M = 8: 174 us against 188 us barrier-free and
+//    184 us for the vendor GEMM library), and for several sequences 2 row groups of 8 rows do best
+//    (64 sequences of 2.3k rows: 189 us against 223 us barrier-free).
+//  * d needs a K loop: the barrier-free kernel (with a loop the shared form pays two barriers per
+//    iteration: 264 us against 118 us at 32k rows of d = 8192, 11.0 against 9.6 us at 1.3k rows).
+inline QuadPlan quad_plan(int32_t M, int32_t d, int32_t batch, int32_t cap_rows) {
+  const int64_t rows = (int64_t)cap_rows * batch;
+  QuadPlan q = {(M + 3) / 4, 8, 1, 1, false};
+  // No more loads per row and wavefront than d has columns for (a load past d reads column 0 and is multiplied with zeros; eight
+  // against two or four: 3000 rows x 8, d = 1024 4.34 -> 3.32 us, d = 2048 5.01 -> 4.47; 349 rows, d = 512 3.34 -> 2.32; 8 sequences
+  // of 1500 rows x 8, d = 1024 9.8 -> 7.5).  9..16 hidden rows: 8 loads when that makes d a single K-iteration (up to 128 KB of
+  // LDS for the hidden-row operands), else 4.
+  if (d <= 1024) q.KS = 2;
+  else if (d <= 2048 || (M > 8 && d > 4096)) q.KS = 4;
+  if (d > 512 * q.KS) {
+    // (tiles past the end leave at once in this kernel, so what counts is the live rows: 4 rows per workgroup while they
+    // fit 256 workgroups -- about 0.8 of the capacity in the workloads here; 7.0 us at 1000 live rows, 10.1 us at 1091)
+    q.loop = true;
+    q.RT = rows <= 5 * 256 ? 1 : (q.MT <= 2 || rows < 8192) ? 2 : 4;
+    return q;
+  }
+  if (batch > 1 && rows >= 8192) {
+    q.NRG = q.RT = 2;
+    return q;
+  }
+  // 16 / 8 / 4 rows per workgroup: the coarsest shape that still gives every workgroup of the launch (sized by the
+  // capacity) a compute unit of its own.  A workgroup without rows costs as much as one with rows here (its loads
+  // are unconditional), so one workgroup more than the chip has compute units puts two on one unit and the launch
+  // waits for that unit: measured at d = 4096, M = 8, live rows = 0.8 capacity, 8 rows per workgroup: 4.85 us at
+  // capacity 2048 (256 workgroups), 6.30 us at 2304 (288); with the earlier thresholds (1440 / 2880 rows) capacity
+  // 1280 took 4.88 us (now 4.00) and 2752 took 7.50 us (now 6.52).
+  q.NRG = rows > 8 * 256 ? 4 : rows > 4 * 256 ? 2 : 1;
+  return q;
+}
+
+// Wide trees: split K across workgroups while the rows alone cannot fill the chip.
+constexpr int32_t kSplitRowsMax = 16384;       // split-K partial logits are only used while the row count is small; bounds their footprint
+inline bool head_split(int32_t M, int32_t d, int32_t batch, int32_t cap_rows, bool dense, int64_t partial_bytes, int64_t ld) {
+  const int64_t S = (d + 511) / 512;
+  return !dense && S >= 2 && S * batch * M * cap_rows * 4 <= partial_bytes && (int64_t)cap_rows * batch <= kSplitRowsMax && cap_rows % 64 == 0 &&
+         ld % 4 == 0;
+}
+
+// head_tile64_kernel's FAST: 0 = every load tested, 1 = whole slices, hidden rows clamped, 2 = and every wavefront's sixteen hidden rows exist
+inline int32_t tile64_fast(int32_t M, int32_t d) { return d % 512 != 0 ? 0 : (M == 64 ? 2 : 1); }
+
+}  // namespace nanospec

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "choose.h"
 #include "nanospec.h"
 
 namespace nanospec {
@@ -107,8 +108,6 @@ hipError_t launch_head_shared(const void* W, const void* H, const int32_t* ids, 
                               int64_t opos_stride, hipStream_t s);
 
 // wide.hip: register-blocked product
-bool wide_reaches(int32_t V, int32_t M, int32_t d);   // its 32-bit byte offsets reach every row
-bool wide_supported(int32_t V, int32_t M, int32_t d, int32_t batch, int32_t cap_rows, bool dense);
 hipError_t launch_head_wide_shared(const void* W, const void* H, const int32_t* ids, const int32_t* n_dev, int32_t cap_rows, int32_t V,
                                    int32_t rows_total, int32_t seq_rows, int32_t d, int64_t ld, float* logits, const int32_t* opos,
                                    int64_t opos_stride, hipStream_t s);

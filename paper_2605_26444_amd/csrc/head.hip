@@ -440,36 +440,21 @@ static hipError_t run_quad(const uint16_t* W, const uint16_t* H, const int32_t* 
   return hipGetLastError();
 }
 
-// Which kernel (all measured on MI355X):
-//  * d fits one K-iteration (d <= 512*KS): the shared-hidden-row kernel.  Rows per workgroup follow the
-//    row capacity so that small vocabularies still spread over the chip (16 / 8 / 4 rows); with tens
-//    of thousands of rows it still wins (dense 128k head, M = 8: 174 us against 188 us barrier-free and
-//    184 us for the vendor GEMM library), and for several sequences 2 row groups of 8 rows do best
-//    (64 sequences of 2.3k rows: 189 us against 223 us barrier-free).
-//  * d needs a K loop: the barrier-free kernel (with a loop the shared form pays two barriers per
-//    iteration: 264 us against 118 us at 32k rows of d = 8192, 11.0 against 9.6 us at 1.3k rows).
 template <int MT, int KS>
-static hipError_t run_quad_auto(const uint16_t* W, const uint16_t* H, const int32_t* ids, const int32_t* n_dev, int32_t n_fixed,
+static hipError_t run_quad_plan(const QuadPlan& q, const uint16_t* W, const uint16_t* H, const int32_t* ids, const int32_t* n_dev, int32_t n_fixed,
                                 int32_t cap_rows, int32_t V, int32_t batch, int32_t M, int32_t d, int64_t ld,
                                 int64_t ids_stride, float* logits, const int32_t* opos, hipStream_t s) {
-  const int64_t rows = (int64_t)cap_rows * batch;
-  constexpr bool LONG = KS == 8 || MT > 2 && KS == 4;       // the other instantiations are chosen for d <= 512 * KS only
-  if constexpr (LONG) if (d > 512 * KS) {
-    // (tiles past the end leave at once in this kernel, so what counts is the live rows: 4 rows per workgroup while they
-    // fit 256 workgroups -- about 0.8 of the capacity in the workloads here; 7.0 us at 1000 live rows, 10.1 us at 1091)
-    if (rows <= 5 * 256) return run_quad_private<1, MT, KS, 4>(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s);
-    if (MT <= 2 || rows < 8192) return run_quad_private<2, MT, KS, 4>(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s);
-    return run_quad_private<4, MT, KS, 4>(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s);
+  if (q.loop) {
+    if constexpr (KS == (MT <= 2 ? 8 : 4)) {                 // the other numbers of loads are chosen for rows of one K-iteration only
+      if (q.RT == 1) return run_quad_private<1, MT, KS, 4>(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s);
+      if (q.RT == 2) return run_quad_private<2, MT, KS, 4>(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s);
+      return run_quad_private<4, MT, KS, 4>(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s);
+    }
+    return hipErrorInvalidValue;
   }
-  if (batch > 1 && rows >= 8192) return run_quad<2, 2, MT, KS>(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s);
-  // 16 / 8 / 4 rows per workgroup: the coarsest shape that still gives every workgroup of the launch (sized by the
-  // capacity) a compute unit of its own.  A workgroup without rows costs as much as one with rows here (its loads
-  // are unconditional), so one workgroup more than the chip has compute units puts two on one unit and the launch
-  // waits for that unit: measured at d = 4096, M = 8, live rows = 0.8 capacity, 8 rows per workgroup: 4.85 us at
-  // capacity 2048 (256 workgroups), 6.30 us at 2304 (288); with the earlier thresholds (1440 / 2880 rows) capacity
-  // 1280 took 4.88 us (now 4.00) and 2752 took 7.50 us (now 6.52).
-  if (rows > 8 * 256) return run_quad<4, 1, MT, KS>(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s);
-  if (rows > 4 * 256) return run_quad<2, 1, MT, KS>(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s);
+  if (q.RT == 2) return run_quad<2, 2, MT, KS>(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s);
+  if (q.NRG == 4) return run_quad<4, 1, MT, KS>(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s);
+  if (q.NRG == 2) return run_quad<2, 1, MT, KS>(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s);
   return run_quad<1, 1, MT, KS>(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s);
 }
 
@@ -672,7 +657,7 @@ static hipError_t run_splitk(const uint16_t* W, const uint16_t* H, const int32_t
                              int32_t V, int32_t batch, int32_t M, int32_t d, int64_t ld, int64_t ids_stride, float* logits,
                              float* partial, int S, const int32_t* opos, hipStream_t s) {
   constexpr int LDS = 4 * 16 * (1024 + kTilePad);
-  const int fast = d % 512 != 0 ? 0 : (M == 64 ? 2 : 1);   // 2: every wavefront's sixteen hidden rows exist
+  const int fast = tile64_fast(M, d);
   hipError_t e;
   const dim3 grid((cap_rows + 63) / 64, S, batch);
   if (fast == 2) head_tile64_kernel<MT, false, 2><<<grid, 256, LDS, s>>>(W, H, ids, n_dev, 0, V, M, d, cap_rows, ids_stride, partial, nullptr, 0, 0, 0);
@@ -690,7 +675,7 @@ static hipError_t run_tile64(const uint16_t* W, const uint16_t* H, const int32_t
                              int32_t cap_rows, int32_t V, int32_t batch, int32_t M, int32_t d, int64_t ld, int64_t ids_stride,
                              float* logits, const int32_t* opos, hipStream_t s) {
   constexpr int LDS = 4 * 16 * (1024 + kTilePad);
-  const int fast = d % 512 != 0 ? 0 : (M == 64 ? 2 : 1);   // 2: every wavefront's sixteen hidden rows exist
+  const int fast = tile64_fast(M, d);
   const dim3 grid((cap_rows + 63) / 64, 1, batch);
   if (fast == 2) head_tile64_kernel<MT, true, 2><<<grid, 256, LDS, s>>>(W, H, ids, n_dev, n_fixed, V, M, d, ld, ids_stride, logits, opos, ids_stride, 0, 0);
   else if (fast == 1) head_tile64_kernel<MT, true, 1><<<grid, 256, LDS, s>>>(W, H, ids, n_dev, n_fixed, V, M, d, ld, ids_stride, logits, opos, ids_stride, 0, 0);
@@ -703,37 +688,16 @@ static hipError_t launch_head_64(const uint16_t* W, const uint16_t* H, const int
                                  int32_t n_fixed, int32_t cap_rows, int32_t V, int32_t batch, int32_t M, int32_t d,
                                  int64_t ld, int64_t ids_stride, float* logits, float* partial, int64_t partial_bytes,
                                  const int32_t* opos, hipStream_t s) {
-  // No more loads per row and wavefront than d has columns for (a load past d reads column 0 and is multiplied with zeros; eight
-  // against two or four: 3000 rows x 8, d = 1024 4.34 -> 3.32 us, d = 2048 5.01 -> 4.47; 349 rows, d = 512 3.34 -> 2.32; 8 sequences
-  // of 1500 rows x 8, d = 1024 9.8 -> 7.5).
-  if (M <= 4) {
-    if (d <= 1024) return run_quad_auto<1, 2>(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s);
-    if (d <= 2048) return run_quad_auto<1, 4>(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s);
-    return run_quad_auto<1, 8>(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s);
-  }
-  if (M <= 8) {
-    if (d <= 1024) return run_quad_auto<2, 2>(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s);
-    if (d <= 2048) return run_quad_auto<2, 4>(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s);
-    return run_quad_auto<2, 8>(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s);
-  }
-  // 9..16 hidden rows: 8 loads per row and wavefront when that makes d a single K-iteration (up to 128 KB of
-  // LDS for the hidden-row operands), else 4
-  if (M <= 12) {
-    if (d <= 1024) return run_quad_auto<3, 2>(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s);
-    if (d > 2048 && d <= 4096) return run_quad_auto<3, 8>(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s);
-    return run_quad_auto<3, 4>(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s);
-  }
   if (M <= 16) {
-    if (d <= 1024) return run_quad_auto<4, 2>(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s);
-    if (d > 2048 && d <= 4096) return run_quad_auto<4, 8>(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s);
-    return run_quad_auto<4, 4>(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s);
+    const QuadPlan q = quad_plan(M, d, batch, cap_rows);
+    auto run = [&](auto plan) { return plan(q, W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s); };
+    if (q.MT == 1) return q.KS == 2 ? run(run_quad_plan<1, 2>) : q.KS == 4 ? run(run_quad_plan<1, 4>) : run(run_quad_plan<1, 8>);
+    if (q.MT == 2) return q.KS == 2 ? run(run_quad_plan<2, 2>) : q.KS == 4 ? run(run_quad_plan<2, 4>) : run(run_quad_plan<2, 8>);
+    if (q.MT == 3) return q.KS == 2 ? run(run_quad_plan<3, 2>) : q.KS == 4 ? run(run_quad_plan<3, 4>) : run(run_quad_plan<3, 8>);
+    return q.KS == 2 ? run(run_quad_plan<4, 2>) : q.KS == 4 ? run(run_quad_plan<4, 4>) : run(run_quad_plan<4, 8>);
   }
-  // wide trees: split K across workgroups while the rows alone cannot fill the chip
-  const int S = (d + 511) / 512;
-  const int64_t need = (int64_t)S * batch * M * cap_rows * 4;
-  const bool split = n_dev != nullptr && partial != nullptr && S >= 2 && need <= partial_bytes &&
-                     (int64_t)cap_rows * batch <= 16384 && cap_rows % 64 == 0 && ld % 4 == 0;
-  if (split) {
+  if (head_split(M, d, batch, cap_rows, n_dev == nullptr, partial ? partial_bytes : -1, ld)) {
+    const int S = (d + 511) / 512;
     if (M <= 32) return run_splitk<2>(W, H, ids, n_dev, cap_rows, V, batch, M, d, ld, ids_stride, logits, partial, S, opos, s);
     return run_splitk<4>(W, H, ids, n_dev, cap_rows, V, batch, M, d, ld, ids_stride, logits, partial, S, opos, s);
   }
@@ -751,7 +715,7 @@ static hipError_t run_shared(const uint16_t* W, const uint16_t* H, const int32_t
                              int32_t groups, int32_t M, int32_t d, int64_t ld, float* logits, const int32_t* opos, int64_t opos_stride,
                              int32_t seq_rows, int32_t row0, hipStream_t s) {
   constexpr int LDS = 4 * 16 * (1024 + kTilePad);
-  const int fast = d % 512 != 0 ? 0 : (M == 64 ? 2 : 1);
+  const int fast = tile64_fast(M, d);
   const dim3 grid(cap_rows / 64, 1, groups);
   if (fast == 2) head_tile64_kernel<MT, true, 2><<<grid, 256, LDS, s>>>(W, H, ids, n_rep, 0, V, M, d, ld, 0, logits, opos, opos_stride, seq_rows, row0);
   else if (fast == 1) head_tile64_kernel<MT, true, 1><<<grid, 256, LDS, s>>>(W, H, ids, n_rep, 0, V, M, d, ld, 0, logits, opos, opos_stride, seq_rows, row0);

@@ -492,10 +492,11 @@ static hipError_t run_gemm(const uint16_t* W, const uint16_t* H, const int32_t* 
   return hipGetLastError();
 }
 
-template <int WR, int WH, int FR, int FH, int BK, int D>
+template <WideShape SHAPE>
 static hipError_t configure_wide() {
-  const void* fns[] = {reinterpret_cast<const void*>(head_wide_kernel<WR, WH, FR, FH, BK, D, false>),
-                       reinterpret_cast<const void*>(head_wide_kernel<WR, WH, FR, FH, BK, D, true>)};
+  constexpr WideBlock b = kWideBlocks[SHAPE];
+  const void* fns[] = {reinterpret_cast<const void*>(head_wide_kernel<b.WR, b.WH, b.FR, b.FH, b.BK, b.D, false>),
+                       reinterpret_cast<const void*>(head_wide_kernel<b.WR, b.WH, b.FR, b.FH, b.BK, b.D, true>)};
   for (const void* f : fns) {
     hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (e != hipSuccess) return e;
@@ -504,122 +505,60 @@ static hipError_t configure_wide() {
 }
 
 hipError_t wide_configure_device() {
-  hipError_t e = configure_wide<2, 2, 1, 1, 128, 4>();
-  if (e == hipSuccess) e = configure_wide<2, 1, 1, 1, 128, 4>();
-  if (e == hipSuccess) e = configure_wide<4, 1, 1, 1, 128, 4>();
-  if (e == hipSuccess) e = configure_wide<2, 4, 1, 1, 128, 2>();
-  if (e == hipSuccess) e = configure_wide<2, 4, 2, 1, 128, 2>();
-  if (e == hipSuccess) e = configure_wide<4, 1, 1, 2, 128, 2>();
-  if (e == hipSuccess) e = configure_wide<4, 1, 2, 4, 64, 2>();
-  if (e == hipSuccess) e = configure_wide<4, 2, 4, 4, 64, 2>();
-  if (e == hipSuccess) e = configure_wide<2, 4, 8, 4, 64, 2>();
+  hipError_t e = configure_wide<kWide32x16>();
+  if (e == hipSuccess) e = configure_wide<kWide64x16>();
+  if (e == hipSuccess) e = configure_wide<kWide32x32>();
+  if (e == hipSuccess) e = configure_wide<kWide64x32>();
+  if (e == hipSuccess) e = configure_wide<kWide32x64>();
+  if (e == hipSuccess) e = configure_wide<kWide64x64>();
+  if (e == hipSuccess) e = configure_wide<kWide128x64>();
+  if (e == hipSuccess) e = configure_wide<kWide256x128>();
+  if (e == hipSuccess) e = configure_wide<kWide256x256>();
   if (e == hipSuccess)
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(head_gemm_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   return e;
 }
 
-bool wide_reaches(int32_t V, int32_t M, int32_t d) { return (int64_t)V * d * 2 <= 0xffffffffll && (int64_t)M * d * 2 <= 0xffffffffll; }
-
-// Which products the register-blocked kernel takes, of those whose rows 32-bit byte offsets reach.
-// More than 16 hidden rows:
-//   * any number of rows while d <= 2048: one launch whose time is its d / 128 steps (6.0 us at d = 1152, 7.2 at 2048) against
-//     two launches of split-K + reduce (9.6, 8.9);
-//   * longer rows from the capacity on at which it beats split-K + reduce, whose workgroups each walk 512 columns only
-//     (d = 4096: M = 64, 1000 live rows 11.1 against 9.5 us, 2000: 10.7 / 11.4, 3000: 11.7 / 12.4; M = 24, 2000 live rows
-//     11.6 / 10.7, 3000: 12.4 / 13.1).
-// Up to 16 (the kernels of head.hip feed the matrix cores straight from memory, at a quarter of their rate and with the hidden
-// rows fetched again for every 16 list rows), where there are rows enough to fill blocks of 32 or 64 with whole hidden-row blocks:
-//   * lists of 131072 rows of capacity together (64 sequences of 2300, d = 4096: M = 8 133 against 147 us, M = 16 140 / 244, M = 1
-//     124 / 130; 32 sequences, M = 8: 79 / 84; 16: 46 / 46);
-//   * 9 to 16 hidden rows: lists from 9216 rows on (2 sequences of 3000 rows, d = 4096: 12.5 / 15.7; one of 3000 11.2 / 9.2; 8 of 2300
-//     31 / 38; 16 of 2300, d = 8192: 91 / 99), but one sequence with d > 5120 (8400 rows, d = 8192: 40 / 38); dense heads
-//     (128k x 4096, M = 16: 201 / 225; x 5120 232 / 259), but whole passes of the K-loop kernel (x 8192: 411 / 363);
-//   * 5 to 8: dense heads (x 2048 95 / 121, x 3584 155 / 160, x 5120 220 / 250) that are no whole passes there (x 4096 194 / 177, x 8192
-//     406 / 332);
-//   * fewer: dense heads with d <= 1024 (M = 3 x 1024 46 / 69; M = 2 x 2048 91 / 84);
-//   * up to 8, lists: one sequence from 8192 rows on with d <= 4096 (8000 rows, M = 8 14.8 / 16.4; 8000 x 1024, M = 6 5.9 / 13.1),
-//     several from 36864 on with d <= 2048 (16 of 2300, M = 8 x 2048 27 / 29; 8 of 2300, x 1024 10.5 / 12.3; x 4096 28 / 26), eight
-//     or more from 73728 on with d <= 4096 (16 of 2300, x 4096, each die its eighth of the lists: 43 / 46).
-bool wide_supported(int32_t V, int32_t M, int32_t d, int32_t batch, int32_t cap_rows, bool dense) {
-  if (!wide_reaches(V, M, d)) return false;
-  if (M <= 16) {
-    const int64_t rows = (int64_t)cap_rows * batch;
-    if (rows > 0x20000000ll) return false;                         // workgroups of one launch
-    if (dense) return rows >= 16384 && (d <= 1024 || (M > 8 && (d <= 4096 || d % 2048 != 0)) || (M > 4 && M <= 8 && d % 4096 != 0));
-    if (rows >= 131072) return true;
-    if (M > 8) return rows >= 9216 && (d <= 5120 || batch > 1);
-    return batch == 1 ? rows >= 8192 && d <= 4096 : (rows >= 36864 && d <= 2048) || (rows >= 73728 && d <= 4096 && batch >= 8);
-  }
-  const int64_t rows = (int64_t)cap_rows * batch;
-  if (rows * ((M + 31) / 32) > 0x40000000ll) return false;         // workgroups of one launch
-  if (M > 64 && batch == 1 && rows < 16384) return false;          // many hidden rows on a short list: 64 at a time
-  return d <= 2048 || rows >= (M <= 32 ? 4096 : 2560);
+template <WideShape SHAPE, typename... A>
+static hipError_t run_shape(A... a) {
+  constexpr WideBlock b = kWideBlocks[SHAPE];
+  return run_wide<b.WR, b.WH, b.FR, b.FH, b.BK, b.D>(a...);
 }
 
-// The block shapes (figures for lists: sequences that share many of their rows).  Up to 64 hidden rows a launch is bound by the bytes a compute unit has in flight over the memory
-// latency (few rows) or by HBM (many), so the block grows with the rows: the smallest one while larger blocks would leave
-// compute units without work, larger ones to fetch the hidden rows (and, beyond 32 x 32, W_head) less often.  A launch
-// only knows the capacity of the lists; thresholds are for live rows around 0.6 of it, dense heads (live == capacity) count double.
-//   32 x 32, four register sets of 128 columns: d = 3584, M = 64, 3000 live rows 11.7 us; two sets of 256 columns 12.2;
-//     two of 128 13.3; four of 64 13.1; 32 x 64 15.4; 64 x 64 19.8.  With d = 3712 12.3 (split-K + reduce with bounds tests 16.4).
-//   32 x 64, eight wavefronts: 4 sequences of 2000 rows, M = 60, d = 4096: 18.1 us; 32 x 32 23.7, 64 x 64 22.6 (slice-loop
-//     kernel of head.hip 28.4); at 2 sequences 16.9 against 14.3 for 32 x 32.
-//   64 x 64, eight wavefronts: 8 sequences of 2000 rows 25.1 us; 32 x 64 31.5, 32 x 32 38.1, 128 x 64 37.1 (slice-loop kernel
-//     36.4); one list of 12000 rows 26.8 against 34.2 / 39.0.
-//   128 x 64, four wavefronts, 60 KB of LDS, two workgroups per compute unit: 64 sequences of 2300 rows, d = 2048: 92 us; 64 x 64
-//     98 (slice-loop kernel 119); the dense 128k x 4096 head at 48 hidden rows 225 us (64 x 32 blocks 258).
-//   up to 32 hidden rows: 32 x 32 (16 sequences of 1500 rows 32 us, slice-loop kernel 49), on long lists and dense 64 x 32 (64
-//     sequences of 2000 rows, M = 17: 127 us, slice-loop kernel 196; dense 128k x 4096, M = 24: 205 us, 128 x 64 219, 32 x 32 228;
-//     32000 rows 51 / 60 / 59).
-//   up to 16: dense and on long lists 64 x 16, on short ones 32 x 16 of two wavefronts (8 sequences of 2300 rows, M = 16: 31 against
-//     34.5 us; 64 sequences, M = 8: 141 against 133).
-//   up to 128: 256 x 128 logits, eight wavefronts of 64 x 64.
-//   more: compute-bound.  head_gemm_kernel; 256 x 256 logits of this kernel (eight wavefronts of 128 x 64, all 160 KB of LDS for the
-//     two stages) where d is no multiple of 64 or an operand is not 16-byte aligned.
+template <typename... A>
+static hipError_t run_wide_shape(WideShape shape, A... a) {
+  switch (shape) {
+    case kWide32x16: return run_shape<kWide32x16>(a...);
+    case kWide64x16: return run_shape<kWide64x16>(a...);
+    case kWide32x32: return run_shape<kWide32x32>(a...);
+    case kWide64x32: return run_shape<kWide64x32>(a...);
+    case kWide32x64: return run_shape<kWide32x64>(a...);
+    case kWide64x64: return run_shape<kWide64x64>(a...);
+    case kWide128x64: return run_shape<kWide128x64>(a...);
+    case kWide256x128: return run_shape<kWide256x128>(a...);
+    case kWide256x256: return run_shape<kWide256x256>(a...);
+    default: return hipErrorInvalidValue;
+  }
+}
+
 hipError_t launch_head_wide(const void* W, const void* H, const int32_t* ids, const int32_t* n_dev, int32_t n_fixed, int32_t cap_rows,
                             int32_t V, int32_t batch, int32_t M, int32_t d, int64_t ld, int64_t ids_stride, float* logits,
                             const int32_t* opos, hipStream_t s) {
   const uint16_t* Wp = static_cast<const uint16_t*>(W);
   const uint16_t* Hp = static_cast<const uint16_t*>(H);
-  const int64_t rows = (int64_t)cap_rows * batch * (n_dev ? 1 : 2);
-  // Sequences hold many of the same rows, and a die's L2 sees a row again only if the sequences that hold it run there at the
-  // same time: for few hidden rows each die takes one eighth of every list (64 sequences of 2300 rows, M = 8: 135 -> 130.5 us, 32: 79
-  // -> 73.5, 16: 47 -> 43; 8, M = 16: 31.1 -> 29.4), but not where the hidden rows of all sequences, which every die then needs, are as
-  // many bytes as the rows (64 sequences, M = 16: 140 -> 145; M = 60 on 8 sequences 25 -> 26).
-  const int by_die = batch >= 8 && M <= 16 && (M <= 8 || rows < 131072);
-  auto run = [&](auto shape) { return shape(Wp, Hp, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, 0, by_die, s); };
-  if (M <= 16) {
-    if (!n_dev || rows >= 131072) return run(run_wide<4, 1, 1, 1, 128, 4>);
-    return run(run_wide<2, 1, 1, 1, 128, 4>);
-  }
-  if (M <= 32) {
-    if (rows < 65536 && n_dev) return run(run_wide<2, 2, 1, 1, 128, 4>);
-    return run(run_wide<4, 1, 1, 2, 128, 2>);
-  }
-  if (rows < 10240) return run(run_wide<2, 2, 1, 1, 128, 4>);
-  if (rows < 18432) return run(run_wide<2, 4, 1, 1, 128, 2>);
-  if (rows < (n_dev ? 98304 : 49152)) return run(run_wide<2, 4, 2, 1, 128, 2>);
-  if (M <= 64 || batch > 1) return run(run_wide<4, 1, 2, 4, 64, 2>);
-  if (M <= 128) return run(run_wide<4, 2, 4, 4, 64, 2>);
+  const bool dense = n_dev == nullptr;
   const bool aligned = ((reinterpret_cast<uintptr_t>(W) | reinterpret_cast<uintptr_t>(H)) & 15) == 0;   // of the fetches into LDS
-  if (d % 64 == 0 && aligned) return run_gemm(Wp, Hp, ids, n_dev, n_fixed, cap_rows, V, M, d, ld, logits, opos, s);
-  return run(run_wide<2, 4, 8, 4, 64, 2>);
+  const WideShape shape = wide_shape(M, d, batch, cap_rows, dense, aligned);
+  if (shape == kWideGemm) return run_gemm(Wp, Hp, ids, n_dev, n_fixed, cap_rows, V, M, d, ld, logits, opos, s);
+  return run_wide_shape(shape, Wp, Hp, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, 0,
+                        (int)wide_by_die(M, batch, cap_rows, dense), s);
 }
 
-// One list shared by the hidden rows of several sequences (see launch_head_shared).  It runs beside the per-sequence product, so what
-// counts is how little it takes from that one: 64-sequence request of four steps 714 us with 64 x 64 blocks, 754 with 128 x 64, 840
-// with 256 x 128 (too few workgroups), 734 with the slice-loop kernel (64 hidden rows at a time).
 hipError_t launch_head_wide_shared(const void* W, const void* H, const int32_t* ids, const int32_t* n_dev, int32_t cap_rows, int32_t V,
                                    int32_t rows_total, int32_t seq_rows, int32_t d, int64_t ld, float* logits, const int32_t* opos,
                                    int64_t opos_stride, hipStream_t s) {
-  const uint16_t* Wp = static_cast<const uint16_t*>(W);
-  const uint16_t* Hp = static_cast<const uint16_t*>(H);
-  auto run = [&](auto shape) {
-    return shape(Wp, Hp, ids, n_dev, 0, cap_rows, V, 1, rows_total, d, ld, opos_stride, logits, opos, seq_rows, 0, s);
-  };
-  if (rows_total <= 16) return run(run_wide<2, 1, 1, 1, 128, 4>);
-  if (rows_total <= 32) return run(run_wide<2, 2, 1, 1, 128, 4>);
-  return run(run_wide<2, 4, 2, 1, 128, 2>);
+  return run_wide_shape(wide_shared_shape(rows_total), static_cast<const uint16_t*>(W), static_cast<const uint16_t*>(H), ids, n_dev, 0, cap_rows, V, 1,
+                        rows_total, d, ld, opos_stride, logits, opos, seq_rows, 0, s);
 }
 
 }  // namespace nanospec

@@ -1,0 +1,95 @@
+"""The launchers' own choice of kernel and block shape (csrc/choose.h, plain host arithmetic), compiled with g++ for the CPU
+tests.  Not collected by pytest."""
+from __future__ import annotations
+
+import ctypes as C
+import os
+import subprocess
+import tempfile
+from collections import namedtuple
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+_ABI = r"""
+#include "choose.h"
+using namespace nanospec;
+extern "C" {
+int c_wide_supported(int V, int M, int d, int batch, int cap, int dense) { return wide_supported(V, M, d, batch, cap, dense != 0); }
+int c_wide_reaches(int V, int M, int d) { return wide_reaches(V, M, d); }
+int c_wide_shape(int M, int d, int batch, int cap, int dense, int aligned) { return wide_shape(M, d, batch, cap, dense != 0, aligned != 0); }
+int c_wide_by_die(int M, int batch, int cap, int dense) { return wide_by_die(M, batch, cap, dense != 0); }
+int c_wide_shared_shape(int rows) { return wide_shared_shape(rows); }
+void c_wide_block(int shape, int* o) { const WideBlock b = kWideBlocks[shape]; o[0] = b.WR; o[1] = b.WH; o[2] = b.FR; o[3] = b.FH; o[4] = b.BK; o[5] = b.D; }
+int c_gemm_shape() { return kWideGemm; }
+void c_quad_plan(int M, int d, int batch, int cap, int dense, int* o) {
+  const QuadPlan q = quad_plan(M, d, batch, cap);
+  o[0] = q.MT; o[1] = q.KS; o[2] = q.NRG; o[3] = q.RT; o[4] = q.loop;
+}
+int c_head_split(int M, int d, int batch, int cap, int dense, long long partial_bytes, long long ld) { return head_split(M, d, batch, cap, dense != 0, partial_bytes, ld); }
+int c_tile64_fast(int M, int d) { return tile64_fast(M, d); }
+}
+"""
+
+Quad = namedtuple("Quad", "MT KS NRG RT loop")
+Block = namedtuple("Block", "WR WH FR FH BK D")
+
+
+def _load():
+    with tempfile.TemporaryDirectory() as tmp:
+        src, so = os.path.join(tmp, "choose.cpp"), os.path.join(tmp, "choose.so")
+        with open(src, "w") as f:
+            f.write(_ABI)
+        subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", os.path.join(ROOT, "paper_2605_26444_amd", "csrc"), "-o", so, src],
+                       check=True)
+        return C.CDLL(so)
+
+
+_lib = _load()
+_lib.c_head_split.argtypes = [C.c_int] * 5 + [C.c_longlong] * 2
+GEMM = _lib.c_gemm_shape()
+
+
+def wide_supported(V, M, d, batch, cap, dense=False):
+    return bool(_lib.c_wide_supported(V, M, d, batch, cap, int(dense)))
+
+
+def wide_reaches(V, M, d):
+    return bool(_lib.c_wide_reaches(V, M, d))
+
+
+def wide_shape(M, d, batch, cap, dense=False, aligned=True):
+    return _lib.c_wide_shape(M, d, batch, cap, int(dense), int(aligned))
+
+
+def wide_by_die(M, batch, cap, dense=False):
+    return bool(_lib.c_wide_by_die(M, batch, cap, int(dense)))
+
+
+def wide_shared_shape(rows_total):
+    return _lib.c_wide_shared_shape(rows_total)
+
+
+def block(shape):
+    o = (C.c_int * 6)()
+    _lib.c_wide_block(shape, o)
+    return Block(*o)
+
+
+def rows_by_hidden(shape):
+    """'64x32': logit rows x hidden rows of a block"""
+    b = block(shape)
+    return "gemm" if shape == GEMM else f"{b.WR * b.FR * 16}x{b.WH * b.FH * 16}"
+
+
+def quad_plan(M, d, batch, cap, dense=False):
+    o = (C.c_int * 5)()
+    _lib.c_quad_plan(M, d, batch, cap, int(dense), o)
+    return Quad(*o[:4], bool(o[4]))
+
+
+def head_split(M, d, batch, cap, dense, partial_bytes, ld):
+    return bool(_lib.c_head_split(M, d, batch, cap, int(dense), partial_bytes, ld))
+
+
+def tile64_fast(M, d):
+    return _lib.c_tile64_fast(M, d)
