@@ -19,27 +19,34 @@ inline bool wide_reaches(int32_t V, int32_t M, int32_t d) { return (int64_t)V * 
 //     (d = 4096: M = 64, 1000 live rows 11.1 against 9.5 us, 2000: 10.7 / 11.4, 3000: 11.7 / 12.4; M = 24, 2000 live rows
 //     11.6 / 10.7, 3000: 12.4 / 13.1).
 // Up to 16 (the kernels of head.hip feed the matrix cores straight from memory, at a quarter of their rate and with the hidden
-// rows fetched again for every 16 list rows), where there are rows enough to fill blocks of 32 or 64 with whole hidden-row blocks:
-//   * lists of 131072 rows of capacity together (64 sequences of 2300, d = 4096: M = 8 133 against 147 us, M = 16 140 / 244, M = 1
-//     124 / 130; 32 sequences, M = 8: 79 / 84; 16: 46 / 46);
-//   * 9 to 16 hidden rows: lists from 9216 rows on (2 sequences of 3000 rows, d = 4096: 12.5 / 15.7; one of 3000 11.2 / 9.2; 8 of 2300
-//     31 / 38; 16 of 2300, d = 8192: 91 / 99), but one sequence with d > 5120 (8400 rows, d = 8192: 40 / 38); dense heads
-//     (128k x 4096, M = 16: 201 / 225; x 5120 232 / 259), but whole passes of the K-loop kernel (x 8192: 411 / 363);
+// rows fetched again for every 16 list rows), where there are rows enough to fill blocks of 32 or 64 with whole hidden-row blocks.  Lists
+// are chosen by their capacity; measured with a quarter, half and most of it live (this kernel against head.hip's, whose launches are sized by the capacity
+// and so gain most by fewer live rows, except with the K loop of d > 4096, where tiles past the end cost nothing):
+//   * one sequence: from the capacity on at which no more is lost with most rows live than is gained with a quarter.  d = 4096, M = 8:
+//     capacity 8192 11.3 / 9.2 us with 2000 live rows, 17.0 / 16.5 with 8000; 16384 11.8 / 14.0 and 26.7 / 25.6 (13000); M = 1: 16384 11.3 / 10.0 and
+//     26.7 / 23.3, 40960 11.2 / 18.3 and 26.5 / 31.0; M = 16: 9216 11.9 / 13.7 (3000), 24.3 / 22.9 (9000).  d = 2048, M = 8: 8192 7.7 / 5.7 (2000), 16384
+//     7.7 / 8.1 and 16.0 / 14.0 (13000).  d = 5120, M = 16: 9216 14.3 / 12.4 (3000), 24576 0.88 to 0.93 of the time from a quarter on;
+//   * 8 or more sequences (each die takes one eighth of every list): M = 8 from 65536 rows together (64 sequences of 2300, d = 4096 133 / 147 us, 32 79 / 84, 16
+//     of 2300 43 / 46; below, 1.07 to 0.9 of the time); M > 8 from 20480 (8 of 2300, d = 4096 31 / 38; 64 140 / 244);
+//   * 2 to 7 sequences: M > 8 only, longer rows than 2048 (d = 4096, 2 of 2000 out of 8192 12.5 / 11.9, of 4000 17.8 / 21.4; M = 12, d = 2048, 4 of
+//     4600 out of 9216 1.08 of the time; M = 8, d = 1024, 4 of 2000 7.1 / 6.5, d = 2048 9.8 / 9.2);
+//   * 131072 rows together: all but d > 5120 for a few sequences (one list of 147456, d = 4096, M = 1: 30000 live 53 / 87, 100000 160 / 150; d = 8192:
+//     3000 live 24.4 / 15.9, 100000 308 / 264);
+//   * dense heads, M 9 to 16 (128k x 4096, M = 16: 201 / 225; x 5120 232 / 259), but whole passes of the K-loop kernel (x 8192: 411 / 363);
 //   * 5 to 8: dense heads (x 2048 95 / 121, x 3584 155 / 160, x 5120 220 / 250) that are no whole passes there (x 4096 194 / 177, x 8192
 //     406 / 332);
-//   * fewer: dense heads with d <= 1024 (M = 3 x 1024 46 / 69; M = 2 x 2048 91 / 84);
-//   * up to 8, lists: one sequence from 8192 rows on with d <= 4096 (8000 rows, M = 8 14.8 / 16.4; 8000 x 1024, M = 6 5.9 / 13.1),
-//     several from 36864 on with d <= 2048 (16 of 2300, M = 8 x 2048 27 / 29; 8 of 2300, x 1024 10.5 / 12.3; x 4096 28 / 26), eight
-//     or more from 73728 on with d <= 4096 (16 of 2300, x 4096, each die its eighth of the lists: 43 / 46).
+//   * fewer: dense heads with d <= 1024 (M = 3 x 1024 46 / 69; M = 2 x 2048 91 / 84).
 inline bool wide_supported(int32_t V, int32_t M, int32_t d, int32_t batch, int32_t cap_rows, bool dense) {
   if (!wide_reaches(V, M, d)) return false;
   if (M <= 16) {
     const int64_t rows = (int64_t)cap_rows * batch;
     if (rows > 0x20000000ll) return false;                         // workgroups of one launch
     if (dense) return rows >= 16384 && (d <= 1024 || (M > 8 && (d <= 4096 || d % 2048 != 0)) || (M > 4 && M <= 8 && d % 4096 != 0));
-    if (rows >= 131072) return true;
-    if (M > 8) return rows >= 9216 && (d <= 5120 || batch > 1);
-    return batch == 1 ? rows >= 8192 && d <= 4096 : (rows >= 36864 && d <= 2048) || (rows >= 73728 && d <= 4096 && batch >= 8);
+    if (rows >= 131072) return d <= 5120 || batch >= 8;
+    if (batch >= 8) return M > 8 ? rows >= 20480 : rows >= 65536 && d <= 4096;
+    if (batch > 1) return M > 8 && d > 2048 && rows >= 16384;
+    if (M > 8) return d <= 5120 && rows >= (d <= 2048 ? 16384 : d <= 4096 ? 9216 : 24576);
+    return d <= 4096 && rows >= (M <= 4 ? 24576 : d <= 2048 ? 16384 : 12288);
   }
   const int64_t rows = (int64_t)cap_rows * batch;
   if (rows * ((M + 31) / 32) > 0x40000000ll) return false;         // workgroups of one launch

@@ -37,9 +37,13 @@ def _check(got, W, H, what):
     (1, 16, 520, 9200), (3, 9, 4168, 3100), (1, 3, 1032, 8200), (9, 8, 72, 4100),      # 32 x 16
     (16, 8, 2056, 4700), (8, 16, 200, 4100), (11, 9, 72, 1100),                        # ... each die its eighth of the lists
     (33, 1, 200, 4100), (33, 16, 640, 4100), (33, 7, 4104, 4100),                      # 64 x 16
+    (1, 16, 520, 16400), (1, 9, 4096, 9200), (1, 3, 1032, 24600), (1, 7, 2056, 12300), (3, 9, 4168, 5500),   # 32 x 16, on either side of its lines
+    (1, 16, 520, 16300), (1, 9, 4096, 9100), (1, 3, 1032, 24500), (1, 7, 2056, 12200), (3, 9, 4168, 5400),
+    (9, 8, 72, 7400), (9, 1, 4096, 7400), (11, 9, 72, 1900), (9, 8, 72, 7200), (11, 9, 72, 1800),            # ... each die its eighth
+    (4, 3, 264, 33000), (4, 8, 5128, 33000),                                                                 # 64 x 16, and not beyond d = 5120
 ])
 def test_ragged_batches(batch, M, d, window):
-    V = 20000
+    V = 20000 if window < 20000 else 34000
     rng = np.random.default_rng(batch * 1000 + M)
     n = rng.integers(window // 2, window + 1, batch)
     n[0] = window
