@@ -32,16 +32,25 @@ inline bool wide_reaches(int32_t V, int32_t M, int32_t d) { return (int64_t)V * 
 //     4600 out of 9216 1.08 of the time; M = 8, d = 1024, 4 of 2000 7.1 / 6.5, d = 2048 9.8 / 9.2);
 //   * 131072 rows together: all but d > 5120 for a few sequences (one list of 147456, d = 4096, M = 1: 30000 live 53 / 87, 100000 160 / 150; d = 8192:
 //     3000 live 24.4 / 15.9, 100000 308 / 264);
-//   * dense heads, M 9 to 16 (128k x 4096, M = 16: 201 / 225; x 5120 232 / 259), but whole passes of the K-loop kernel (x 8192: 411 / 363);
-//   * 5 to 8: dense heads (x 2048 95 / 121, x 3584 155 / 160, x 5120 220 / 250) that are no whole passes there (x 4096 194 / 177, x 8192
-//     406 / 332);
-//   * fewer: dense heads with d <= 1024 (M = 3 x 1024 46 / 69; M = 2 x 2048 91 / 84).
+//   * dense heads where the other kernel's K walk does not fit d -- it works in passes of 1024, 2048 or 4096 columns, zeros included --, and enough rows:
+//     M 9 to 16, d no multiple of 2048 (128k rows, M = 16: x 2560 0.74 of the time, x 3584 0.80, x 5120 0.92; M = 9: 0.80, 0.90, 0.99; x 4096 1.08 and so
+//     left, but from 13 hidden rows on 0.95; x 2048 0.98 to 1.10, x 6144 1.01 to 1.08; 16400 rows, M = 16 x 3072 0.92, x 1536 1.07, x 5120 0.98);
+//     M 5 to 8, d just beyond one pass or two (x 2560 0.94, x 5120 0.91, x 7168 0.95; x 3072, x 3584, x 6144 0.98 to 1.02; below 28000 rows 1.06 to 1.17);
+//     d <= 512 (four loads a wavefront would do: 128k rows, M = 1 0.48 against 0.61 of the eight-load form's time, M = 16 0.58 / 0.74; x 768 0.73 / 0.65; x 1024 M = 1
+//     0.71 / 0.71, M = 16 0.79 / 0.85).
 inline bool wide_supported(int32_t V, int32_t M, int32_t d, int32_t batch, int32_t cap_rows, bool dense) {
   if (!wide_reaches(V, M, d)) return false;
   if (M <= 16) {
     const int64_t rows = (int64_t)cap_rows * batch;
     if (rows > 0x20000000ll) return false;                         // workgroups of one launch
-    if (dense) return rows >= 16384 && (d <= 1024 || (M > 8 && (d <= 4096 || d % 2048 != 0)) || (M > 4 && M <= 8 && d % 4096 != 0));
+    if (dense) {
+      if (d <= 512) return rows >= (M > 8 ? 20480 : 28672);
+      if (M <= 4) return false;
+      if (d <= 1024) return M > 8 && d > 896 && rows >= 28672;
+      if (M <= 8) return rows >= 28672 && ((d > 2048 && d <= 2560) || (d > 4096 && d % 2048 != 0));
+      if (d % 2048 != 0) return rows >= (d > 2048 && d < (M > 12 ? 4096 : 3080) ? 16384 : 24576);
+      return M > 12 && d == 4096 && rows >= 24576;
+    }
     if (rows >= 131072) return d <= 5120 || batch >= 8;
     if (batch >= 8) return M > 8 ? rows >= 20480 : rows >= 65536 && d <= 4096;
     if (batch > 1) return M > 8 && d > 2048 && rows >= 16384;
@@ -127,15 +136,16 @@ struct QuadPlan {
 //    (64 sequences of 2.3k rows: 189 us against 223 us barrier-free).
 //  * d needs a K loop: the barrier-free kernel (with a loop the shared form pays two barriers per
 //    iteration: 264 us against 118 us at 32k rows of d = 8192, 11.0 against 9.6 us at 1.3k rows).
-inline QuadPlan quad_plan(int32_t M, int32_t d, int32_t batch, int32_t cap_rows) {
+inline QuadPlan quad_plan(int32_t M, int32_t d, int32_t batch, int32_t cap_rows, bool dense) {
   const int64_t rows = (int64_t)cap_rows * batch;
   QuadPlan q = {(M + 3) / 4, 8, 1, 1, false};
   // No more loads per row and wavefront than d has columns for (a load past d reads column 0 and is multiplied with zeros; eight
   // against two or four: 3000 rows x 8, d = 1024 4.34 -> 3.32 us, d = 2048 5.01 -> 4.47; 349 rows, d = 512 3.34 -> 2.32; 8 sequences
   // of 1500 rows x 8, d = 1024 9.8 -> 7.5).  9..16 hidden rows: 8 loads when that makes d a single K-iteration (up to 128 KB of
-  // LDS for the hidden-row operands), else 4.
+  // LDS for the hidden-row operands), else 4.  Up to four on the rows of a dense head, bound by the bytes in flight: eight in half of the wavefronts
+  // instead of four in all (100k rows x 2048 and more 0.96 to 0.97 of the time; 65k 0.98, 50k 1.0; x 1536 1.09).
   if (d <= 1024) q.KS = 2;
-  else if (d <= 2048 || (M > 8 && d > 4096)) q.KS = 4;
+  else if ((d <= 2048 && !(dense && M <= 4 && d > 1792 && rows >= 65536)) || (M > 8 && d > 4096)) q.KS = 4;
   if (d > 512 * q.KS) {
     // (tiles past the end leave at once in this kernel, so what counts is the live rows: 4 rows per workgroup while they
     // fit 256 workgroups -- about 0.8 of the capacity in the workloads here; 7.0 us at 1000 live rows, 10.1 us at 1091)

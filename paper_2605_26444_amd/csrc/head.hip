@@ -689,7 +689,7 @@ static hipError_t launch_head_64(const uint16_t* W, const uint16_t* H, const int
                                  int64_t ld, int64_t ids_stride, float* logits, float* partial, int64_t partial_bytes,
                                  const int32_t* opos, hipStream_t s) {
   if (M <= 16) {
-    const QuadPlan q = quad_plan(M, d, batch, cap_rows);
+    const QuadPlan q = quad_plan(M, d, batch, cap_rows, n_dev == nullptr);
     auto run = [&](auto plan) { return plan(q, W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld, ids_stride, logits, opos, s); };
     if (q.MT == 1) return q.KS == 2 ? run(run_quad_plan<1, 2>) : q.KS == 4 ? run(run_quad_plan<1, 4>) : run(run_quad_plan<1, 8>);
     if (q.MT == 2) return q.KS == 2 ? run(run_quad_plan<2, 2>) : q.KS == 4 ? run(run_quad_plan<2, 4>) : run(run_quad_plan<2, 8>);

@@ -22,7 +22,7 @@ int c_wide_shared_shape(int rows) { return wide_shared_shape(rows); }
 void c_wide_block(int shape, int* o) { const WideBlock b = kWideBlocks[shape]; o[0] = b.WR; o[1] = b.WH; o[2] = b.FR; o[3] = b.FH; o[4] = b.BK; o[5] = b.D; }
 int c_gemm_shape() { return kWideGemm; }
 void c_quad_plan(int M, int d, int batch, int cap, int dense, int* o) {
-  const QuadPlan q = quad_plan(M, d, batch, cap);
+  const QuadPlan q = quad_plan(M, d, batch, cap, dense != 0);
   o[0] = q.MT; o[1] = q.KS; o[2] = q.NRG; o[3] = q.RT; o[4] = q.loop;
 }
 int c_head_split(int M, int d, int batch, int cap, int dense, long long partial_bytes, long long ld) { return head_split(M, d, batch, cap, dense != 0, partial_bytes, ld); }

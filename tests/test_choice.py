@@ -26,3 +26,21 @@ def list_kernel(M, d, batch, cap, dense=False, rows=V):
 ])
 def test_few_hidden_rows_on_lists(M, d, batch, cap, want):
     assert list_kernel(M, d, batch, cap, rows=200000) == want
+
+
+@pytest.mark.parametrize("M,d,rows,want", [
+    (1, 512, 128256, "64x16"), (4, 512, 16400, "head.hip"), (1, 1024, 128256, "head.hip"), (16, 768, 128256, "head.hip"),
+    (9, 2048, 50001, "head.hip"), (16, 2048, 16400, "head.hip"), (9, 4096, 128256, "head.hip"), (16, 4096, 128256, "64x16"), (16, 4096, 16400, "head.hip"),
+    (9, 2560, 16400, "64x16"), (16, 3584, 128256, "64x16"), (16, 5120, 128256, "64x16"), (16, 6144, 128256, "head.hip"), (16, 8192, 128256, "head.hip"),
+    (8, 2048, 128256, "head.hip"), (8, 2560, 128256, "64x16"), (5, 3072, 50001, "head.hip"), (8, 3584, 128256, "head.hip"), (8, 4096, 128256, "head.hip"),
+    (8, 5120, 128256, "64x16"), (8, 5120, 16400, "head.hip"), (4, 2048, 128256, "head.hip"),
+    (16, 1024, 128256, "64x16"), (8, 1024, 128256, "head.hip"), (16, 512, 24000, "64x16"), (16, 3584, 24000, "64x16"), (9, 3584, 20480, "head.hip"),
+])
+def test_few_hidden_rows_dense(M, d, rows, want):
+    assert list_kernel(M, d, 1, rows, dense=True, rows=rows) == want
+
+
+def test_loads_per_wavefront():
+    assert choose.quad_plan(4, 2048, 1, 128256, dense=True).KS == 8 and choose.quad_plan(4, 2048, 1, 50001, dense=True).KS == 4
+    assert choose.quad_plan(4, 1536, 1, 128256, dense=True).KS == 4 and choose.quad_plan(8, 2048, 1, 128256, dense=True).KS == 4
+    assert choose.quad_plan(4, 2048, 1, 8192).KS == 4 and choose.quad_plan(4, 1024, 1, 8192).KS == 2 and choose.quad_plan(4, 2056, 1, 8192).KS == 8

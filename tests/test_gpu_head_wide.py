@@ -71,7 +71,9 @@ def test_few_hidden_rows_short_rows(M, d):
 
 @pytest.mark.parametrize("V,M,d", [(30001, 24, 200), (17000, 33, 72), (40002, 64, 1032), (50000, 100, 192), (33333, 200, 72), (20000, 300, 520),
                                      (50001, 129, 64), (49409, 257, 192), (25000, 700, 128), (24577, 513, 1088),
-                                     (30001, 16, 4104), (20000, 5, 4096), (40000, 1, 72), (17001, 12, 2056)])
+                                     (30001, 16, 4104), (20000, 5, 4096), (40000, 1, 72), (17001, 12, 2056),
+                                     (30001, 9, 2048), (30001, 13, 4096), (30001, 8, 2504), (28673, 7, 5000), (66001, 3, 2040), (30001, 2, 520),
+                                     (24577, 11, 1544), (28001, 4, 512)])
 def test_dense(V, M, d):
     W, H = _normal(3, V, d), _normal(4, M, d)
     logits = torch.full((M + 1, V), 7.0, dtype=torch.float32, device="cuda")
