@@ -10,7 +10,6 @@ namespace {
 
 inline int64_t round_up(int64_t x, int64_t a) { return (x + a - 1) / a * a; }
 
-constexpr int kSplitMax = 16;
 
 bool fill_layout(int32_t V, int32_t d, int32_t batch, int32_t window, int32_t topk_cap, int32_t m_cap, int32_t k_cap,
                  nanospec_layout* L) {

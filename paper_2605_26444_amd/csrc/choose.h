@@ -6,6 +6,10 @@
 
 namespace nanospec {
 
+// split-K partial logits of head.hip: at most this many slices of 512 columns, and only while the row count is small, to bound their footprint
+constexpr int32_t kSplitMax = 16;
+constexpr int32_t kSplitRowsMax = 16384;
+
 // ---- the register-blocked product (wide.hip) ----------------------------------------------------------------------
 
 // its 32-bit byte offsets reach every row
@@ -13,11 +17,15 @@ inline bool wide_reaches(int32_t V, int32_t M, int32_t d) { return (int64_t)V * 
 
 // Which products the register-blocked kernel takes, of those whose rows 32-bit byte offsets reach.
 // More than 16 hidden rows:
-//   * any number of rows while d <= 2048: one launch whose time is its d / 128 steps (6.0 us at d = 1152, 7.2 at 2048) against
-//     two launches of split-K + reduce (9.6, 8.9);
+//   * any number of rows of one launch's d / 128 steps against two launches of split-K + reduce while that is the shorter walk (d = 1152 6.0 us against 9.6,
+//     2048 7.2 against 8.9): d <= 2048, up to 32 hidden rows d <= 1792 (2048: 8.9 against 8.5; from 4096 rows on 0.98);
 //   * longer rows from the capacity on at which it beats split-K + reduce, whose workgroups each walk 512 columns only
 //     (d = 4096: M = 64, 1000 live rows 11.1 against 9.5 us, 2000: 10.7 / 11.4, 3000: 11.7 / 12.4; M = 24, 2000 live rows
-//     11.6 / 10.7, 3000: 12.4 / 13.1).
+//     11.6 / 10.7, 3000: 12.4 / 13.1);
+//   * several sequences, whose split is over their rows together and so finer, from the rows on where the two are even over a quarter, 0.6 and most of the capacity
+//     live (this kernel's time over split-K's: d = 4096, 2 of 2560 M = 17 1.19 / 1.05 / 0.82, M = 33 1.13 / 1.02 / 1.16, M = 64 1.04 / 0.94 / 1.10; 8 of 1088 M = 33 1.04 /
+//     0.95 / 0.96; d = 8192, 2 of 2560 M = 17 1.45 / 1.15 / 0.86, 8 of 1088 1.27 / 0.85 / 0.94; 8 of 320 M = 33 1.8 / 1.5 / 1.1, 2 of 5120 1.22 / 0.93 / 1.01, M = 64
+//     1.11 / 0.90 / 1.14, 8 of 1088 0.92 / 0.95 / 1.02), but for more than 64 hidden rows, which split-K does not take.
 // Up to 16 (the kernels of head.hip feed the matrix cores straight from memory, at a quarter of their rate and with the hidden
 // rows fetched again for every 16 list rows), where there are rows enough to fill blocks of 32 or 64 with whole hidden-row blocks.  Lists
 // are chosen by their capacity; measured with a quarter, half and most of it live (this kernel against head.hip's, whose launches are sized by the capacity
@@ -60,7 +68,9 @@ inline bool wide_supported(int32_t V, int32_t M, int32_t d, int32_t batch, int32
   const int64_t rows = (int64_t)cap_rows * batch;
   if (rows * ((M + 31) / 32) > 0x40000000ll) return false;         // workgroups of one launch
   if (M > 64 && batch == 1 && rows < 16384) return false;          // many hidden rows on a short list: 64 at a time
-  return d <= 2048 || rows >= (M <= 32 ? 4096 : 2560);
+  if (d <= (M <= 32 ? 1792 : 2048)) return true;
+  if (d <= 2048 || batch == 1 || M > 64 || d > 512 * kSplitMax) return rows >= (M <= 32 ? 4096 : 2560);
+  return M <= 32 ? rows >= (d <= 4096 ? 4096 : 8192) : rows * M >= (d <= 4096 ? 262144 : 393216);
 }
 
 // Block shapes as (logit rows x hidden rows); kWideGemm is head_gemm_kernel.
@@ -168,7 +178,6 @@ inline QuadPlan quad_plan(int32_t M, int32_t d, int32_t batch, int32_t cap_rows,
 }
 
 // Wide trees: split K across workgroups while the rows alone cannot fill the chip.
-constexpr int32_t kSplitRowsMax = 16384;       // split-K partial logits are only used while the row count is small; bounds their footprint
 inline bool head_split(int32_t M, int32_t d, int32_t batch, int32_t cap_rows, bool dense, int64_t partial_bytes, int64_t ld) {
   const int64_t S = (d + 511) / 512;
   return !dense && S >= 2 && S * batch * M * cap_rows * 4 <= partial_bytes && (int64_t)cap_rows * batch <= kSplitRowsMax && cap_rows % 64 == 0 &&

@@ -44,3 +44,14 @@ def test_loads_per_wavefront():
     assert choose.quad_plan(4, 2048, 1, 128256, dense=True).KS == 8 and choose.quad_plan(4, 2048, 1, 50001, dense=True).KS == 4
     assert choose.quad_plan(4, 1536, 1, 128256, dense=True).KS == 4 and choose.quad_plan(8, 2048, 1, 128256, dense=True).KS == 4
     assert choose.quad_plan(4, 2048, 1, 8192).KS == 4 and choose.quad_plan(4, 1024, 1, 8192).KS == 2 and choose.quad_plan(4, 2056, 1, 8192).KS == 8
+
+
+@pytest.mark.parametrize("M,d,batch,cap,want", [
+    (17, 2048, 1, 1088, "head.hip"), (17, 1792, 1, 1088, "32x32"), (33, 2048, 1, 1088, "32x32"), (32, 2048, 2, 2560, "32x32"), (32, 4096, 1, 4352, "32x32"),
+    (64, 4096, 1, 2560, "32x32"), (64, 4096, 1, 2496, "head.hip"), (17, 4096, 2, 2560, "32x32"), (17, 8192, 2, 2560, "head.hip"), (17, 8192, 2, 5120, "32x32"),
+    (33, 4096, 2, 2560, "head.hip"), (33, 4096, 8, 1088, "32x32"), (64, 4096, 2, 2560, "32x32"), (33, 4096, 8, 320, "head.hip"), (33, 8192, 8, 1088, "head.hip"),
+    (64, 8192, 8, 1088, "32x32"), (64, 8192, 2, 2560, "head.hip"), (17, 8192, 2, 9216, "32x32"), (64, 4096, 2, 5120, "32x64"), (60, 4096, 8, 4096, "64x64"),
+    (70, 4096, 2, 2560, "32x32"), (130, 8192, 2, 3072, "32x32"), (17, 12288, 2, 2560, "32x32"),
+])
+def test_17_to_64_hidden_rows_on_lists(M, d, batch, cap, want):
+    assert list_kernel(M, d, batch, cap) == want

@@ -40,6 +40,7 @@ def _check(got, W, H, what):
     (1, 16, 520, 16400), (1, 9, 4096, 9200), (1, 3, 1032, 24600), (1, 7, 2056, 12300), (3, 9, 4168, 5500),   # 32 x 16, on either side of its lines
     (1, 16, 520, 16300), (1, 9, 4096, 9100), (1, 3, 1032, 24500), (1, 7, 2056, 12200), (3, 9, 4168, 5400),
     (9, 8, 72, 7400), (9, 1, 4096, 7400), (11, 9, 72, 1900), (9, 8, 72, 7200), (11, 9, 72, 1800),            # ... each die its eighth
+    (2, 17, 4104, 2500), (2, 64, 3080, 2000), (2, 64, 3080, 2100), (8, 33, 4096, 300), (2, 17, 8192, 9200), (2, 20, 2048, 1000), (2, 20, 12288, 2500),   # split-K and beside it
     (4, 3, 264, 33000), (4, 8, 5128, 33000),                                                                 # 64 x 16, and not beyond d = 5120
 ])
 def test_ragged_batches(batch, M, d, window):
