@@ -86,7 +86,8 @@ constexpr WideBlock kWideBlocks[kWideShapes] = {{2, 1, 1, 1, 128, 4}, {4, 1, 1, 
 // The block shapes (figures for lists: sequences that share many of their rows).  Up to 64 hidden rows a launch is bound by the bytes a compute unit has in flight over the memory
 // latency (few rows) or by HBM (many), so the block grows with the rows: the smallest one while larger blocks would leave
 // compute units without work, larger ones to fetch the hidden rows (and, beyond 32 x 32, W_head) less often.  A launch
-// only knows the capacity of the lists; thresholds are for live rows around 0.6 of it, dense heads (live == capacity) count double.
+// only knows the capacity of the lists; thresholds are for live rows around 0.6 of it, dense heads (live == capacity) count double, or less where the
+// work is bound by the matrix cores.
 //   32 x 32, four register sets of 128 columns: d = 3584, M = 64, 3000 live rows 11.7 us; two sets of 256 columns 12.2;
 //     two of 128 13.3; four of 64 13.1; 32 x 64 15.4; 64 x 64 19.8.  With d = 3712 12.3 (split-K + reduce with bounds tests 16.4).
 //   32 x 64, eight wavefronts: 4 sequences of 2000 rows, M = 60, d = 4096: 18.1 us; 32 x 32 23.7, 64 x 64 22.6 (slice-loop
@@ -100,18 +101,28 @@ constexpr WideBlock kWideBlocks[kWideShapes] = {{2, 1, 1, 1, 128, 4}, {4, 1, 1, 
 //     32000 rows 51 / 60 / 59).
 //   up to 16: dense and on long lists 64 x 16, on short ones 32 x 16 of two wavefronts (8 sequences of 2300 rows, M = 16: 31 against
 //     34.5 us; 64 sequences, M = 8: 141 against 133).
-//   up to 128: 256 x 128 logits, eight wavefronts of 64 x 64.
-//   more: compute-bound.  head_gemm_kernel; 256 x 256 logits of this kernel (eight wavefronts of 128 x 64, all 160 KB of LDS for the
+//   dense heads of 33 to 64 hidden rows: 128 x 64 from the rows on that this kernel takes them from (20480 x 2048, M = 64: 64 x 64 takes 1.06 times as long, 17000 x 8192 1.11,
+//     16400 0.95).
+//   more than 64, one sequence: compute-bound.  64 x 64 blocks while they are few -- rows times blocks of 64 hidden rows --, where larger ones would leave compute
+//     units without work.  Against 256 x 128: up to 65536 by capacity, 49152 dense (d = 4096: M = 70, 32000 of 32768 rows 78 / 82 us, 65000 161 / 124; M = 128, 20000 of
+//     24576 67 / 79, 30000 of 49152 90 / 86; dense 24000 x 128 0.86 of the time, 36000 1.14); against head_gemm_kernel: 98304, 81920 (M = 130, 20000 of 24576 74 / 83, 30000 of 49152
+//     108 / 93; M = 256, 14000 of 24576, d = 2048 41 / 51, 32000 of 32768 146 / 105; M = 512, 10000 of 16448 123 / 88, 32000 of 32768 286 / 119; dense 20480 x 200 79 / 84,
+//     24000 x 256 1.1, 16400 x 512 1.6 of the time).
+//   then up to 128: 256 x 128 logits, eight wavefronts of 64 x 64;
+//   more: head_gemm_kernel; 256 x 256 logits of this kernel (eight wavefronts of 128 x 64, all 160 KB of LDS for the
 //     two stages) where d is no multiple of 64 or an operand is not 16-byte aligned.
 inline WideShape wide_shape(int32_t M, int32_t d, int32_t batch, int32_t cap_rows, bool dense, bool aligned) {
   const int64_t rows = (int64_t)cap_rows * batch * (dense ? 2 : 1);
   if (M <= 16) return dense || rows >= 131072 ? kWide64x16 : kWide32x16;
   if (M <= 32) return rows < 65536 && !dense ? kWide32x32 : kWide64x32;
-  if (rows < 10240) return kWide32x32;
-  if (rows < 18432) return kWide32x64;
-  if (rows < (dense ? 49152 : 98304)) return kWide64x64;
-  if (M <= 64 || batch > 1) return kWide128x64;
-  if (M <= 128) return kWide256x128;
+  if (M <= 64 || batch > 1) {
+    if (rows < 10240) return kWide32x32;
+    if (rows < 18432) return kWide32x64;
+    return rows < (dense ? 32768 : 98304) ? kWide64x64 : kWide128x64;
+  }
+  const int64_t work = (int64_t)cap_rows * ((M + 63) / 64);
+  if (M <= 128) return work <= (dense ? 49152 : 65536) ? kWide64x64 : kWide256x128;
+  if (work <= (dense ? 81920 : 98304)) return kWide64x64;
   return d % 64 == 0 && aligned ? kWideGemm : kWide256x256;
 }
 

@@ -55,3 +55,15 @@ def test_loads_per_wavefront():
 ])
 def test_17_to_64_hidden_rows_on_lists(M, d, batch, cap, want):
     assert list_kernel(M, d, batch, cap) == want
+
+
+@pytest.mark.parametrize("M,rows,dense,want", [
+    (70, 16448, False, "64x64"), (70, 32768, False, "64x64"), (128, 49152, False, "256x128"), (128, 98240, False, "256x128"), (130, 24576, False, "64x64"),
+    (130, 49152, False, "gemm"), (256, 24576, False, "64x64"), (256, 32768, False, "gemm"), (512, 16448, False, "gemm"), (512, 98240, False, "gemm"),
+    (65, 24000, True, "64x64"), (128, 36000, True, "256x128"), (200, 20480, True, "64x64"), (128, 50001, True, "256x128"), (129, 16400, True, "64x64"), (200, 24000, True, "gemm"), (512, 16400, True, "gemm"), (1024, 24000, True, "gemm"),
+    (64, 24000, True, "128x64"), (33, 16384, True, "128x64"), (64, 12000, True, "64x64"),
+])
+def test_shapes_for_many_hidden_rows(M, rows, dense, want):
+    assert list_kernel(M, 4096, 1, rows, dense=dense, rows=rows) == want
+    assert choose.rows_by_hidden(choose.wide_shape(M, 4096, 1, rows, dense, aligned=False)) == want.replace("gemm", "256x256")
+    assert choose.rows_by_hidden(choose.wide_shape(M, 4104, 1, rows, dense)) == want.replace("gemm", "256x256")

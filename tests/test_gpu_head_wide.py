@@ -81,3 +81,34 @@ def test_dense(V, M, d):
     B.nanospec_dense_head(W, H, V, d, M, logits[:M])
     _check(logits[:M], W, H, "dense")
     assert torch.all(logits[M] == 7.0)
+
+
+@pytest.mark.parametrize("n", [0, 1, 257, 1000, 33000])
+@pytest.mark.parametrize("M,d", [(100, 192), (100, 200), (129, 128), (300, 192), (300, 136), (300, 4096)])
+def test_many_hidden_rows_on_a_long_list(M, d, n):
+    """256 x 128 and 256 x 256 logits and head_gemm_kernel on gathered rows, and on the packed buffer, whose logits go to columns of their own"""
+    V, window = 50000, 33000                                  # a capacity at which the larger blocks are taken
+    W, H = _normal(5, V, d), _normal(6, 1, M, d)
+    ids = np.sort(np.random.default_rng(n + M).permutation(V)[:n]).astype(np.int32)
+    st = B.State(V, d, 1, window, 1, M, 1)
+    B.nanospec_packed_enable(st.h)
+    B.nanospec_vocab_init(st.h, dev_ids(ids), np.array([0, n], np.int32), None, np.zeros(2, np.int32))
+    out = [torch.full((M + 1, st.capacity), 7.0, dtype=torch.float32, device="cuda") for _ in range(2)]
+    B.nanospec_sparse_head(st.h, W, H, M, out[0][:M])
+    B.nanospec_packed_gather(st.h, W)
+    B.nanospec_packed_head(st.h, H, M, out[1][:M])
+    for logits in out:
+        _check(logits[:M, :n], W[torch.from_numpy(ids).long().cuda()], H[0], n)
+        assert torch.all(logits[M] == 7.0)
+    st.close()
+
+
+@pytest.mark.parametrize("V,M,d", [(24600, 300, 192), (16400, 513, 64), (50000, 100, 192), (17000, 64, 72)])
+def test_dense_on_operands_at_any_address(V, M, d):
+    """operands that start between two 16-byte addresses: what fetches straight into LDS cannot take goes to the kernel beside it"""
+    W, H = _normal(7, V * d + 8)[4:4 + V * d].view(V, d), _normal(8, M * d + 8)[4:4 + M * d].view(M, d)
+    assert W.data_ptr() % 16 and H.data_ptr() % 16
+    logits = torch.full((M + 1, V), 7.0, dtype=torch.float32, device="cuda")
+    B.nanospec_dense_head(W, H, V, d, M, logits[:M])
+    _check(logits[:M], W, H, "dense")
+    assert torch.all(logits[M] == 7.0)
