@@ -498,13 +498,7 @@ __device__ __forceinline__ void each8(const int32_t* src, int n, int tid, F f) {
 // Stream initialisation of short windows: one launch, one workgroup per sequence.  A counter is non-zero only if its id
 // is in the ring, so what an earlier stream left behind is undone through the ring (at most `window` scattered stores)
 // instead of clearing V counters in a launch of its own.  Latency-bound: every array is read with eight loads in flight
-// per thread.  Beyond the lengths below the additions to the counters -- a frequent token's all go to one address in L2,
-// about 2 us per 1024 tokens -- cost more than the second launch of the kernels that follow (V = 128256, |T| = 2000;
-// this / those, us: one sequence 5.9 / 7.0 at 256 tokens, 8.5 / 7.4 at 1024, 23.0 / 8.0 at 8192; 64 sequences 8.0 / 15.0 at
-// 256, 12.3 / 16.0 at 1024, 17.4 / 16.2 at 2048, 49 / 17.7 at 8192).
-constexpr int kInitFewSeqs = 16;
-constexpr int kInitSerialFew = 640, kInitSerialMany = 1536;
-
+// per thread.  For which prompts and windows: vocab_init_serial in choose.h.
 __global__ __launch_bounds__(kVocabThreads) void vocab_init_kernel(VocabPtrs p, const int32_t* __restrict__ ctx, Offsets coff,
                                                                    const int32_t* __restrict__ topk, Offsets toff) {
   extern __shared__ uint32_t lds[];
@@ -1036,7 +1030,7 @@ hipError_t launch_vocab_init(const nanospec_state* st, const int32_t* d_ctx, con
     const int ae = a < st->window ? a : st->window;
     longest = ae > longest ? ae : longest;
   }
-  if (longest <= (st->batch <= kInitFewSeqs ? kInitSerialFew : kInitSerialMany)) {
+  if (vocab_init_serial(st->batch, st->window, longest)) {
     vocab_init_kernel<<<st->batch, kVocabThreads, st->vocab_lds_bytes, s>>>(st->vp, d_ctx, coff, d_topk, toff);
     return hipGetLastError();
   }

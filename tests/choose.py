@@ -26,6 +26,7 @@ void c_quad_plan(int M, int d, int batch, int cap, int dense, int* o) {
   o[0] = q.MT; o[1] = q.KS; o[2] = q.NRG; o[3] = q.RT; o[4] = q.loop;
 }
 int c_head_split(int M, int d, int batch, int cap, int dense, long long partial_bytes, long long ld) { return head_split(M, d, batch, cap, dense != 0, partial_bytes, ld); }
+int c_vocab_init_serial(int batch, int window, int longest) { return vocab_init_serial(batch, window, longest); }
 int c_tile64_fast(int M, int d) { return tile64_fast(M, d); }
 }
 """
@@ -93,3 +94,7 @@ def head_split(M, d, batch, cap, dense, partial_bytes, ld):
 
 def tile64_fast(M, d):
     return _lib.c_tile64_fast(M, d)
+
+
+def vocab_init_serial(batch, window, longest):
+    return bool(_lib.c_vocab_init_serial(batch, window, longest))

@@ -67,3 +67,12 @@ def test_shapes_for_many_hidden_rows(M, rows, dense, want):
     assert list_kernel(M, 4096, 1, rows, dense=dense, rows=rows) == want
     assert choose.rows_by_hidden(choose.wide_shape(M, 4096, 1, rows, dense, aligned=False)) == want.replace("gemm", "256x256")
     assert choose.rows_by_hidden(choose.wide_shape(M, 4104, 1, rows, dense)) == want.replace("gemm", "256x256")
+
+
+@pytest.mark.parametrize("batch,window,longest,want", [
+    (1, 256, 256, True), (1, 1024, 64, True), (1, 1024, 256, False), (1, 1024, 600, False), (1, 8192, 64, False), (1, 235312, 500, False), (1, 16384, 0, False), (16, 1024, 512, True), (16, 16384, 64, False),
+    (64, 1024, 1024, True), (64, 8192, 600, True), (64, 8192, 1500, False), (64, 16384, 600, False), (64, 235312, 64, False), (17, 2048, 1500, False), (200, 8192, 1500, True),
+])
+def test_stream_initialisation(batch, window, longest, want):
+    """a short prompt for a wide window may follow a stream that filled it, and one workgroup would undo it token by token"""
+    assert choose.vocab_init_serial(batch, window, longest) == want
