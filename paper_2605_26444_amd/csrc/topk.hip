@@ -736,14 +736,14 @@ __global__ __launch_bounds__(64 * NW) void topk_stream_kernel(const float* __res
 
 // Lists whose capacity is beyond one workgroup's registers but whose live row count mostly is not: one launch that selects
 // either way, by the count on the device.
-template <bool LSE>
-__global__ __launch_bounds__(1024) void topk_list_kernel(const float* __restrict__ logits, int64_t ld, const int32_t* __restrict__ ids,
-                                                         int64_t ids_stride, const int32_t* __restrict__ n_dev, int n_fixed, int M, int k,
-                                                         int32_t* __restrict__ out_ids, float* __restrict__ out_vals) {
-  if ((n_dev ? n_dev[blockIdx.z] : n_fixed) <= kTopkChunk)
-    topk_select<16, 16, true, LSE>(logits, ld, ids, ids_stride, n_dev, n_fixed, M, k, out_ids, out_vals, nullptr, nullptr);
+template <int NW, bool LSE>
+__global__ __launch_bounds__(64 * NW) void topk_list_kernel(const float* __restrict__ logits, int64_t ld, const int32_t* __restrict__ ids,
+                                                            int64_t ids_stride, const int32_t* __restrict__ n_dev, int n_fixed, int M, int k,
+                                                            int32_t* __restrict__ out_ids, float* __restrict__ out_vals) {
+  if ((n_dev ? n_dev[blockIdx.z] : n_fixed) <= NW * 1024)
+    topk_select<16, NW, true, LSE>(logits, ld, ids, ids_stride, n_dev, n_fixed, M, k, out_ids, out_vals, nullptr, nullptr);
   else
-    topk_stream<16, LSE>(logits, ld, ids, ids_stride, n_dev, n_fixed, M, k, out_ids, out_vals);
+    topk_stream<NW, LSE>(logits, ld, ids, ids_stride, n_dev, n_fixed, M, k, out_ids, out_vals);
 }
 
 // Merge the per-chunk winners of one row (nchunks*k <= 1024 candidates, in position order): one candidate per thread, its rank
@@ -826,14 +826,16 @@ static hipError_t launch_topk_t(const float* logits, int64_t ld, const int32_t* 
   // against one workgroup per row: 1024 rows of 128256, k = 3: 202 / 97 us (5.4 TB/s; of 128255 381 / 97), 256 rows 48 / 27, 128
   // rows 28 / 21, 64 rows, k = 10: 19 / 23, 8 rows 12 / 23; lists for 16 hidden rows: 8400 ids in a capacity of 33k 6.6 / 5.0, 32800
   // ids 12.5 / 11.0.  Eight wavefronts instead of sixteen from 512 rows on (2048 rows of 32000, k = 5: 52 against 77 us; 500 rows
-  // of 50001, k = 40: 45 against 42).
+  // of 50001, k = 40: 45 against 42); lists that fit those registers -- 8192 ids -- are selected as short ones there too (512 rows, 3000 of 32768 ids: k = 10 5.6 against 14.3 us in
+  // steps and 15.6 in chunks, k = 40 8.6 / 18.2 / 18.2; 2048 rows, k = 40 24 / 46 / 48; 32000 ids 20.0 / 19.5 / 31.6).
   const int64_t nrows = (int64_t)batch * M;
-  if (nrows >= 512) {
-    topk_stream_kernel<8, LSE><<<rows, 512, 0, s>>>(logits, ld, ids, ids_stride, n_dev, n_fixed, M, k, out_ids, out_vals);
+  if (n_dev) {
+    if (nrows >= 512) topk_list_kernel<8, LSE><<<rows, 512, 0, s>>>(logits, ld, ids, ids_stride, n_dev, n_fixed, M, k, out_ids, out_vals);
+    else topk_list_kernel<16, LSE><<<rows, 1024, 0, s>>>(logits, ld, ids, ids_stride, n_dev, n_fixed, M, k, out_ids, out_vals);
     return hipGetLastError();
   }
-  if (n_dev) {
-    topk_list_kernel<LSE><<<rows, 1024, 0, s>>>(logits, ld, ids, ids_stride, n_dev, n_fixed, M, k, out_ids, out_vals);
+  if (nrows >= 512) {
+    topk_stream_kernel<8, LSE><<<rows, 512, 0, s>>>(logits, ld, ids, ids_stride, n_dev, n_fixed, M, k, out_ids, out_vals);
     return hipGetLastError();
   }
   if (nrows >= 96) {

@@ -53,7 +53,7 @@ def test_dense_rows(kind, rows, V, k):
 
 
 @pytest.mark.parametrize("kind", ["normal", "up", "equal", "coarse"])
-@pytest.mark.parametrize("n", [0, 1, 37, 16384, 16385, 16388, 32768, 32770, 39999])
+@pytest.mark.parametrize("n", [0, 1, 37, 8191, 8192, 8193, 16384, 16385, 16388, 32768, 32770, 39999])
 @pytest.mark.parametrize("batch,M,k", [(2, 3, 10), (1, 2, 64), (16, 32, 5)])
 def test_lists(kind, n, batch, M, k):
     V, window = 60000, 40000
