@@ -213,4 +213,22 @@ inline bool vocab_init_serial(int32_t batch, int32_t window, int32_t longest) {
   return longest + window / 16 <= most;
 }
 
+// ---- selection from rows that one workgroup's registers do not hold (topk.hip) --------------------------------------------------
+
+constexpr int32_t kTopkChunk = 16384;          // elements per workgroup in the two-pass top-k
+
+// How many ids a list is likely to hold, of which the launcher knows only the capacity: a candidate set is as large as the room made for it, a queue of distinct
+// ids fills its window, and a window of raw tokens holds about a sixth of its length (Zipf streams: 8400 of 33k, 32800 of 235k).
+inline int64_t topk_expected(int32_t topk_cap, int32_t window, bool distinct) { return (int64_t)topk_cap + (distinct ? window : window / 6); }
+
+// Chunks of every row all over the chip and a second launch that merges their winners, or one workgroup per row (which walks it, or, a list of up to 16384 live
+// ids, selects it at once; in chunks such a list waits for the second launch).  Measured, one workgroup / chunks, us: 8 rows, k = 10, 3000 ids 5.1 / 6.3, 17000 10.3 /
+// 8.4, 50000 14.7 / 9.9, 128000 22.2 / 9.1; k = 1, 32000 10.5 / 8.1; k = 16, 128000 23.3 / 9.4; 64 rows, k = 10, 32000 11.1 / 10.1, 128000 22.2 / 16.8; 88 rows 128000 23.3 /
+// 22.5, 64 dense rows 23 / 19, 128 21 / 28, 1024, k = 3 97 (5.4 TB/s; rows of 128255 the same) / 202 (381).  Larger k: 8 rows, k = 40, 32000 12.4 / 10.9, 17000 13.0 / 41 (a last
+// chunk of fewer than 16 k elements goes the slow way), 80000 21.7 / 14.5, 128000 34.8 / 21.2.
+inline bool topk_chunks(bool list, int64_t rows, int32_t k, int64_t expected) {
+  if (!list) return rows < 96;
+  return rows <= 64 && expected > (k <= 16 ? kTopkChunk : 65536);
+}
+
 }  // namespace nanospec

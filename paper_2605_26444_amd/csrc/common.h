@@ -10,7 +10,6 @@ namespace nanospec {
 
 constexpr int kVocabThreads = 1024;   // one workgroup per sequence in the vocabulary kernel
 constexpr int kTopkThreads = 1024;    // single-pass top-k workgroup
-constexpr int kTopkChunk = 16384;     // elements per workgroup in the two-pass top-k
 constexpr int kMaxK = 64;
 constexpr int kCandMax = 256;          // top-k fast path: most candidates ranked directly
 
@@ -124,8 +123,8 @@ hipError_t launch_union_build(const nanospec_state* st, hipStream_t s);
 // topk.hip
 int64_t topk_workspace_bytes(int32_t cap, int32_t rows, int32_t k);
 hipError_t launch_topk(const float* logits, int64_t ld, const int32_t* ids, int64_t ids_stride, const int32_t* n_dev,
-                       int32_t n_fixed, int32_t cap, int32_t batch, int32_t M, int32_t k, int32_t* out_ids,
-                       float* out_vals, bool logprob, char* ws, int64_t ws_bytes, hipStream_t s);
+                       int32_t n_fixed, int32_t cap, int64_t expected /* see topk_expected */, int32_t batch, int32_t M, int32_t k,
+                       int32_t* out_ids, float* out_vals, bool logprob, char* ws, int64_t ws_bytes, hipStream_t s);
 
 // packed.hip
 hipError_t launch_packed_reset(const nanospec_state* st, hipStream_t s);

@@ -49,7 +49,7 @@ nanospec_status nanospec_dense_topk_static(const float* d_logits, int32_t V, int
   if (!ws) return NANOSPEC_EHIP;
   // every candidate slot the merge kernel reads is written by the selection kernel of the same call, so
   // nothing in the array has to be cleared between calls
-  hipError_t e = launch_topk(d_logits, V, nullptr, 0, nullptr, V, V, 1, M_total, k, d_out_ids, d_out_vals, false,
+  hipError_t e = launch_topk(d_logits, V, nullptr, 0, nullptr, V, V, V, 1, M_total, k, d_out_ids, d_out_vals, false,
                              static_cast<char*>(ws), kScratchBytes, static_cast<hipStream_t>(hip_stream));
   return e == hipSuccess ? NANOSPEC_OK : NANOSPEC_EHIP;
 }

@@ -7,7 +7,7 @@
 // lane maxima, a ballot of the lanes that hold that maximum (the lowest such lane owns the
 // lowest-position occurrence), one readlane for the register index, and the winner is blanked.
 // The wavefronts' winners meet in LDS in position order and one wavefront repeats the rounds over
-// them.  Few dense rows longer than one workgroup reaches are cut into chunks whose winners a second kernel
+// them.  Few rows longer than one workgroup reaches are cut into chunks whose winners a second kernel
 // ranks.  Values of -inf mark "nothing left" (logits are finite by contract).
 //
 // Fast path in front of the rounds: lane l of wavefront w always holds positions (64w + l)*EPT ..., whatever
@@ -30,7 +30,7 @@
 // LSE variants (Sec. 4.2: the draft distribution is the softmax renormalised over the active set):
 // the same selection, with the values written as log-probabilities z - log(sum_i exp z_i), i over the
 // row's n entries.  The row maximum falls out of the first threshold round, the sum of exp(z - max)
-// is taken wavefront by wavefront and added in wavefront order, so
+// is taken wavefront by wavefront and added in wavefront order (chunk order in the merge kernel), so
 // the result does not depend on timing.
 #include <limits.h>
 
@@ -117,10 +117,11 @@ __device__ __forceinline__ void wave_select(float (&v)[EPT], int k, int lane, Em
 // final result itself, the other chunks leave at once and the merge kernel has nothing to do.
 constexpr int kLaneCand = 4;   // candidates per lane the owner path keeps in registers
 
-template <int EPT, int NW, bool FINAL, bool LSE>   // LSE: whole rows only
+template <int EPT, int NW, bool FINAL, bool LSE>
 __device__ __forceinline__ void topk_select(const float* __restrict__ logits, int64_t ld, const int32_t* __restrict__ ids, int64_t ids_stride,
                                             const int32_t* __restrict__ n_dev, int n_fixed, int M, int k, int32_t* __restrict__ out_ids,
-                                            float* __restrict__ out_vals, float* __restrict__ cand_val, int32_t* __restrict__ cand_pos) {
+                                            float* __restrict__ out_vals, float* __restrict__ cand_val, int32_t* __restrict__ cand_pos,
+                                            float2* __restrict__ cand_ms) {
   constexpr int E2 = (NW * kMaxK + 63) / 64;
   __shared__ float s_val[NW * kMaxK];
   __shared__ int s_pos[NW * kMaxK];
@@ -240,7 +241,8 @@ __device__ __forceinline__ void topk_select(const float* __restrict__ logits, in
       float zmax = wave_max(wm);
       zmax = zmax == -INFINITY ? 0.f : zmax;                // empty chunk: every factor below is exp(-inf) = 0
       const float se = wave_add(lane < NW ? s_sum[lane] * expf(wm - zmax) : 0.f);
-      lse = zmax + logf(se);
+      if (fin) lse = zmax + logf(se);
+      else if (tid == 0) cand_ms[row * gridDim.x + c] = make_float2(zmax, se);
     }
     uint32_t flags = 0;
 #pragma unroll
@@ -420,8 +422,9 @@ __global__ __launch_bounds__(64 * NW) void topk_select_kernel(const float* __res
                                                              const int32_t* __restrict__ ids, int64_t ids_stride,
                                                              const int32_t* __restrict__ n_dev, int n_fixed, int M, int k,
                                                              int32_t* __restrict__ out_ids, float* __restrict__ out_vals,
-                                                             float* __restrict__ cand_val, int32_t* __restrict__ cand_pos) {
-  topk_select<EPT, NW, FINAL, LSE>(logits, ld, ids, ids_stride, n_dev, n_fixed, M, k, out_ids, out_vals, cand_val, cand_pos);
+                                                             float* __restrict__ cand_val, int32_t* __restrict__ cand_pos,
+                                                             float2* __restrict__ cand_ms) {
+  topk_select<EPT, NW, FINAL, LSE>(logits, ld, ids, ids_stride, n_dev, n_fixed, M, k, out_ids, out_vals, cand_val, cand_pos, cand_ms);
 }
 
 // Long rows (more positions than one workgroup's registers hold): one workgroup per row walks it in pieces of 16 logits
@@ -727,11 +730,10 @@ __device__ __forceinline__ void topk_stream(const float* __restrict__ logits, in
   }
 }
 
-template <int NW, bool LSE>
-__global__ __launch_bounds__(64 * NW) void topk_stream_kernel(const float* __restrict__ logits, int64_t ld, const int32_t* __restrict__ ids,
-                                                              int64_t ids_stride, const int32_t* __restrict__ n_dev, int n_fixed, int M,
-                                                              int k, int32_t* __restrict__ out_ids, float* __restrict__ out_vals) {
-  topk_stream<NW, LSE>(logits, ld, ids, ids_stride, n_dev, n_fixed, M, k, out_ids, out_vals);
+template <int NW>
+__global__ __launch_bounds__(64 * NW) void topk_stream_kernel(const float* __restrict__ logits, int64_t ld, int n, int M, int k,
+                                                              int32_t* __restrict__ out_ids, float* __restrict__ out_vals) {
+  topk_stream<NW, false>(logits, ld, nullptr, 0, nullptr, n, M, k, out_ids, out_vals);
 }
 
 // Lists whose capacity is beyond one workgroup's registers but whose live row count mostly is not: one launch that selects
@@ -741,7 +743,7 @@ __global__ __launch_bounds__(64 * NW) void topk_list_kernel(const float* __restr
                                                             int64_t ids_stride, const int32_t* __restrict__ n_dev, int n_fixed, int M, int k,
                                                             int32_t* __restrict__ out_ids, float* __restrict__ out_vals) {
   if ((n_dev ? n_dev[blockIdx.z] : n_fixed) <= NW * 1024)
-    topk_select<16, NW, true, LSE>(logits, ld, ids, ids_stride, n_dev, n_fixed, M, k, out_ids, out_vals, nullptr, nullptr);
+    topk_select<16, NW, true, LSE>(logits, ld, ids, ids_stride, n_dev, n_fixed, M, k, out_ids, out_vals, nullptr, nullptr, nullptr);
   else
     topk_stream<NW, LSE>(logits, ld, ids, ids_stride, n_dev, n_fixed, M, k, out_ids, out_vals);
 }
@@ -749,14 +751,19 @@ __global__ __launch_bounds__(64 * NW) void topk_list_kernel(const float* __restr
 // Merge the per-chunk winners of one row (nchunks*k <= 1024 candidates, in position order): one candidate per thread, its rank
 // among all of them as (candidate, group of four) work items over the workgroup.  (17 rows of 128256, k = 40,
 // selection and merge: 24.9 -> 19.7 us against rounds of one wavefront; k = 10 11.9 -> 9.6; 8 rows of 32000, k = 40 22.9 -> 9.1; 256
-// threads instead of 1024: k = 40 39 us.)  Dense rows only: positions are ids.
+// threads instead of 1024: k = 40 39 us.)
+template <bool LSE>
 __global__ __launch_bounds__(1024) void topk_merge_kernel(const float* __restrict__ cand_val, const int32_t* __restrict__ cand_pos,
-                                                          int nchunks, int k,
-                                                          int32_t* __restrict__ out_ids, float* __restrict__ out_vals) {
+                                                          const float2* __restrict__ cand_ms, int nchunks,
+                                                          const int32_t* __restrict__ ids, int64_t ids_stride, int M, int k,
+                                                          int32_t* __restrict__ out_ids, float* __restrict__ out_vals,
+                                                          const int32_t* __restrict__ n_dev, int n_fixed) {
   __shared__ __attribute__((aligned(16))) float s_v[1024 + 4];
   __shared__ int s_r[1024];
-  const int tid = threadIdx.x;
-  const int64_t row = blockIdx.y;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int m = blockIdx.y, b = blockIdx.z;
+  if ((n_dev ? n_dev[b] : n_fixed) <= kTopkChunk) return;   // the first chunk's workgroup has written the result
+  const int64_t row = (int64_t)b * M + m;
   const int total = nchunks * k;
   float val = -INFINITY;
   int pos = -1;
@@ -767,6 +774,14 @@ __global__ __launch_bounds__(1024) void topk_merge_kernel(const float* __restric
     s_r[tid] = 0;
   }
   if (tid < 4) s_v[total + tid] = __builtin_nanf("");       // pads the last group of four; compares false with everything
+  const int gid = ids && val != -INFINITY ? ids[b * ids_stride + pos] : pos;   // requested before the ranking, used behind it
+  float lse = 0.f;
+  if (LSE) {                                              // chunk (max, sum) pairs -> one log sum exp; at most 16 chunks
+    const float2 ms = lane < nchunks ? cand_ms[row * nchunks + lane] : make_float2(0.f, 0.f);
+    float zmax = wave_max(ms.y > 0.f ? ms.x : -INFINITY);
+    zmax = zmax == -INFINITY ? 0.f : zmax;
+    lse = zmax + logf(wave_add(ms.y > 0.f ? ms.y * expf(ms.x - zmax) : 0.f));
+  }
   __syncthreads();
   const int lg = total <= 1 ? 0 : 32 - __clz(total - 1);
   const int items = ((total + 3) >> 2) << lg;
@@ -786,8 +801,8 @@ __global__ __launch_bounds__(1024) void topk_merge_kernel(const float* __restric
   if (tid < total && s_r[tid] < k) {
     const bool none = val == -INFINITY;                     // fewer than k exist
     const int64_t o = row * k + s_r[tid];
-    out_ids[o] = none ? -1 : pos;
-    if (out_vals) out_vals[o] = val;
+    out_ids[o] = none ? -1 : gid;
+    if (out_vals) out_vals[o] = (LSE && !none) ? val - lse : val;
   }
 }
 
@@ -795,70 +810,65 @@ static int chunks_for(int32_t cap) { return (cap + kTopkChunk - 1) / kTopkChunk;
 
 int64_t topk_workspace_bytes(int32_t cap, int32_t rows, int32_t k) {
   if (cap <= kTopkChunk) return 0;
-  return (int64_t)rows * chunks_for(cap) * (k * 8 + 8);   // (value, position) per winner; the eight bytes per chunk more are unused, the size is part of the interface
+  return (int64_t)rows * chunks_for(cap) * (k * 8 + 8);   // (value, position) per winner + (max, sum) per chunk
 }
 
 template <bool LSE>
 static hipError_t launch_topk_t(const float* logits, int64_t ld, const int32_t* ids, int64_t ids_stride, const int32_t* n_dev,
-                                int32_t n_fixed, int32_t cap, int32_t batch, int32_t M, int32_t k, int32_t* out_ids,
+                                int32_t n_fixed, int32_t cap, int64_t expected, int32_t batch, int32_t M, int32_t k, int32_t* out_ids,
                                 float* out_vals, char* ws, int64_t ws_bytes, hipStream_t s) {
   const dim3 rows(1, M, batch);
+  if (LSE && !n_dev) return hipErrorInvalidValue;           // log-probabilities are taken over lists only
   if (cap <= 4096) {
     topk_select_kernel<16, 4, true, LSE><<<rows, 256, 0, s>>>(logits, ld, ids, ids_stride, n_dev, n_fixed, M, k, out_ids,
-                                                            out_vals, nullptr, nullptr);
+                                                            out_vals, nullptr, nullptr, nullptr);
     return hipGetLastError();
   }
   if (cap <= 8192) {   // eight wavefronts beat sixteen (c3: 6.2 -> 5.0 us, c4: 8.2 -> 5.8 us) and four with 32 logits per lane (5.5, 6.1)
     topk_select_kernel<16, 8, true, LSE><<<rows, 512, 0, s>>>(logits, ld, ids, ids_stride, n_dev, n_fixed, M, k, out_ids,
-                                                            out_vals, nullptr, nullptr);
+                                                            out_vals, nullptr, nullptr, nullptr);
     return hipGetLastError();
   }
   if (cap <= kTopkChunk) {
     topk_select_kernel<16, 16, true, LSE><<<rows, 1024, 0, s>>>(logits, ld, ids, ids_stride, n_dev, n_fixed, M, k, out_ids,
-                                                              out_vals, nullptr, nullptr);
+                                                              out_vals, nullptr, nullptr, nullptr);
     return hipGetLastError();
   }
   const int nch = chunks_for(cap);
   const int64_t need = topk_workspace_bytes(cap, batch * M, k);
   if (nch * k > 1024 || ws == nullptr || ws_bytes < need) return hipErrorInvalidValue;
-  // Beyond that, one workgroup per row for many rows and for lists (whose live rows are a fraction of their capacity, and
-  // where a second launch costs more than the steps), else -- few dense rows -- chunks and a merge.  Measured, chunks + merge
-  // against one workgroup per row: 1024 rows of 128256, k = 3: 202 / 97 us (5.4 TB/s; of 128255 381 / 97), 256 rows 48 / 27, 128
-  // rows 28 / 21, 64 rows, k = 10: 19 / 23, 8 rows 12 / 23; lists for 16 hidden rows: 8400 ids in a capacity of 33k 6.6 / 5.0, 32800
-  // ids 12.5 / 11.0.  Eight wavefronts instead of sixteen from 512 rows on (2048 rows of 32000, k = 5: 52 against 77 us; 500 rows
-  // of 50001, k = 40: 45 against 42); lists that fit those registers -- 8192 ids -- are selected as short ones there too (512 rows, 3000 of 32768 ids: k = 10 5.6 against 14.3 us in
-  // steps and 15.6 in chunks, k = 40 8.6 / 18.2 / 18.2; 2048 rows, k = 40 24 / 46 / 48; 32000 ids 20.0 / 19.5 / 31.6).
   const int64_t nrows = (int64_t)batch * M;
-  if (n_dev) {
-    if (nrows >= 512) topk_list_kernel<8, LSE><<<rows, 512, 0, s>>>(logits, ld, ids, ids_stride, n_dev, n_fixed, M, k, out_ids, out_vals);
-    else topk_list_kernel<16, LSE><<<rows, 1024, 0, s>>>(logits, ld, ids, ids_stride, n_dev, n_fixed, M, k, out_ids, out_vals);
-    return hipGetLastError();
-  }
-  if (nrows >= 512) {
-    topk_stream_kernel<8, LSE><<<rows, 512, 0, s>>>(logits, ld, ids, ids_stride, n_dev, n_fixed, M, k, out_ids, out_vals);
-    return hipGetLastError();
-  }
-  if (nrows >= 96) {
-    topk_stream_kernel<16, LSE><<<rows, 1024, 0, s>>>(logits, ld, ids, ids_stride, n_dev, n_fixed, M, k, out_ids, out_vals);
+  if (!topk_chunks(n_dev != nullptr, nrows, k, expected)) {
+    // Eight wavefronts instead of sixteen from 512 rows on (2048 rows of 32000, k = 5: 52 against 77 us; 500 rows of 50001, k = 40: 45 against 42); lists that fit
+    // those registers -- 8192 ids -- are selected as short ones there too (512 rows, 3000 of 32768 ids: k = 10 5.6 against 14.3 us in
+    // steps and 15.6 in chunks, k = 40 8.6 / 18.2 / 18.2; 2048 rows, k = 40 24 / 46 / 48; 32000 ids 20.0 / 19.5 / 31.6).
+    if (n_dev) {
+      if (nrows >= 512) topk_list_kernel<8, LSE><<<rows, 512, 0, s>>>(logits, ld, ids, ids_stride, n_dev, n_fixed, M, k, out_ids, out_vals);
+      else topk_list_kernel<16, LSE><<<rows, 1024, 0, s>>>(logits, ld, ids, ids_stride, n_dev, n_fixed, M, k, out_ids, out_vals);
+    } else if constexpr (!LSE) {
+      if (nrows >= 512) topk_stream_kernel<8><<<rows, 512, 0, s>>>(logits, ld, n_fixed, M, k, out_ids, out_vals);
+      else topk_stream_kernel<16><<<rows, 1024, 0, s>>>(logits, ld, n_fixed, M, k, out_ids, out_vals);
+    }
     return hipGetLastError();
   }
   const int64_t slots = (int64_t)batch * M * nch * k;
   float* cv = reinterpret_cast<float*>(ws);
   int32_t* cp = reinterpret_cast<int32_t*>(ws + slots * 4);
-  topk_select_kernel<16, 16, false, false><<<dim3(nch, M, batch), 1024, 0, s>>>(logits, ld, ids, ids_stride, n_dev, n_fixed, M, k, out_ids,
-                                                                              out_vals, cv, cp);
+  float2* ms = reinterpret_cast<float2*>(ws + slots * 8);
+  topk_select_kernel<16, 16, false, LSE><<<dim3(nch, M, batch), 1024, 0, s>>>(logits, ld, ids, ids_stride, n_dev, n_fixed, M, k, out_ids,
+                                                                            out_vals, cv, cp, ms);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  topk_merge_kernel<<<dim3(1, (unsigned)nrows), 1024, 0, s>>>(cv, cp, nch, k, out_ids, out_vals);
+  topk_merge_kernel<LSE><<<rows, 1024, 0, s>>>(cv, cp, ms, nch, ids, ids_stride, M, k, out_ids, out_vals, n_dev, n_fixed);
   return hipGetLastError();
 }
 
 hipError_t launch_topk(const float* logits, int64_t ld, const int32_t* ids, int64_t ids_stride, const int32_t* n_dev,
-                       int32_t n_fixed, int32_t cap, int32_t batch, int32_t M, int32_t k, int32_t* out_ids,
+                       int32_t n_fixed, int32_t cap, int64_t expected, int32_t batch, int32_t M, int32_t k, int32_t* out_ids,
                        float* out_vals, bool logprob, char* ws, int64_t ws_bytes, hipStream_t s) {
-  return logprob ? launch_topk_t<true>(logits, ld, ids, ids_stride, n_dev, n_fixed, cap, batch, M, k, out_ids, out_vals, ws,
+  return logprob ? launch_topk_t<true>(logits, ld, ids, ids_stride, n_dev, n_fixed, cap, expected, batch, M, k, out_ids, out_vals, ws,
                                        ws_bytes, s)
-                 : launch_topk_t<false>(logits, ld, ids, ids_stride, n_dev, n_fixed, cap, batch, M, k, out_ids, out_vals, ws,
+                 : launch_topk_t<false>(logits, ld, ids, ids_stride, n_dev, n_fixed, cap, expected, batch, M, k, out_ids, out_vals, ws,
                                         ws_bytes, s);
 }
 

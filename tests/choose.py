@@ -27,6 +27,7 @@ void c_quad_plan(int M, int d, int batch, int cap, int dense, int* o) {
 }
 int c_head_split(int M, int d, int batch, int cap, int dense, long long partial_bytes, long long ld) { return head_split(M, d, batch, cap, dense != 0, partial_bytes, ld); }
 int c_vocab_init_serial(int batch, int window, int longest) { return vocab_init_serial(batch, window, longest); }
+int c_topk_chunks(int list, long long rows, int k, int topk_cap, int window, int distinct) { return topk_chunks(list != 0, rows, k, topk_expected(topk_cap, window, distinct != 0)); }
 int c_tile64_fast(int M, int d) { return tile64_fast(M, d); }
 }
 """
@@ -47,6 +48,7 @@ def _load():
 
 _lib = _load()
 _lib.c_head_split.argtypes = [C.c_int] * 5 + [C.c_longlong] * 2
+_lib.c_topk_chunks.argtypes = [C.c_int, C.c_longlong] + [C.c_int] * 4
 GEMM = _lib.c_gemm_shape()
 
 
@@ -98,3 +100,7 @@ def tile64_fast(M, d):
 
 def vocab_init_serial(batch, window, longest):
     return bool(_lib.c_vocab_init_serial(batch, window, longest))
+
+
+def topk_chunks(rows, k, topk_cap=0, window=0, distinct=False, dense=False):
+    return bool(_lib.c_topk_chunks(int(not dense), rows, k, topk_cap, window, int(distinct)))

@@ -76,3 +76,11 @@ def test_shapes_for_many_hidden_rows(M, rows, dense, want):
 def test_stream_initialisation(batch, window, longest, want):
     """a short prompt for a wide window may follow a stream that filled it, and one workgroup would undo it token by token"""
     assert choose.vocab_init_serial(batch, window, longest) == want
+
+
+def test_selection_in_chunks():
+    assert choose.topk_chunks(8, 10, topk_cap=65000) and choose.topk_chunks(8, 10, topk_cap=1, window=30000, distinct=True)     # lists that fill their room
+    assert choose.topk_chunks(16, 10, topk_cap=1, window=235312) and not choose.topk_chunks(16, 10, topk_cap=1, window=33303)    # windows of raw tokens
+    assert not choose.topk_chunks(8, 10, topk_cap=4000, window=13000) and not choose.topk_chunks(88, 10, topk_cap=65000)
+    assert not choose.topk_chunks(8, 40, topk_cap=32000) and choose.topk_chunks(8, 40, topk_cap=128000)
+    assert choose.topk_chunks(95, 40, dense=True) and not choose.topk_chunks(96, 1, dense=True)

@@ -55,15 +55,23 @@ def test_dense_rows(kind, rows, V, k):
 @pytest.mark.parametrize("kind", ["normal", "up", "equal", "coarse"])
 @pytest.mark.parametrize("n", [0, 1, 37, 8191, 8192, 8193, 16384, 16385, 16388, 32768, 32770, 39999])
 @pytest.mark.parametrize("batch,M,k", [(2, 3, 10), (1, 2, 64), (16, 32, 5)])
-def test_lists(kind, n, batch, M, k):
-    V, window = 60000, 40000
-    st = B.State(V, 8, batch, window, 1, M, k)
+@pytest.mark.parametrize("room", ["window", "candidates"])
+def test_lists(kind, n, batch, M, k, room):
+    """one workgroup per row, and -- room for a candidate set of the list's length -- chunks"""
+    V, window, T = 60000, 40000, 1
+    if room == "candidates":
+        V, window, T = 90000, 1000, 39999 if k <= 16 else 70000
+    st = B.State(V, 8, batch, window, T, M, k)
     assert st.capacity > 16384
     rng = np.random.default_rng(n + 1)
     live = [n if b % 2 == 0 else n // 3 for b in range(batch)]
     lists = [np.sort(rng.permutation(V)[:x]).astype(np.int32) for x in live]
     flat, off = csr(lists)
-    B.nanospec_vocab_init(st.h, dev_ids(flat) if len(flat) else None, off, None, np.zeros(batch + 1, np.int32))
+    none = np.zeros(batch + 1, np.int32)
+    if room == "window":
+        B.nanospec_vocab_init(st.h, dev_ids(flat), off, None, none)
+    else:
+        B.nanospec_vocab_init(st.h, None, none, dev_ids(flat), off)
     logits = torch.full((batch, M, st.capacity), 1e30, device="cuda")       # what lies behind a list must not matter
     ids = torch.full((batch, M, k), -7, dtype=torch.int32, device="cuda")
     vals, logp = torch.full((batch, M, k), 9.0, device="cuda"), torch.full((batch, M, k), 9.0, device="cuda")
@@ -155,8 +163,8 @@ def test_lists_with_nans(how, n, batch, M, k):
 
 
 @pytest.mark.parametrize("how", HOW)
-@pytest.mark.parametrize("rows,V,k", [(3, 40003, 10), (96, 32771, 40), (515, 24589, 64)])
-def test_rows_with_minus_infinity(how, rows, V, k):
+@pytest.mark.parametrize("rows,V,k,T", [(3, 40003, 10, 1), (3, 40003, 10, 20000), (96, 32771, 40, 1), (515, 24589, 64, 1)])
+def test_rows_with_minus_infinity(how, rows, V, k, T):
     """in a long row a logit of -inf (a masked token) is an empty slot, as a dense row and as a list of the same length"""
     x = _without(_rows("normal", rows, V), how, -torch.inf)
     nbytes = B.nanospec_dense_topk_workspace(V, rows, k)
@@ -165,7 +173,7 @@ def test_rows_with_minus_infinity(how, rows, V, k):
     vals = torch.full((rows, k), 9.0, device="cuda")
     B.nanospec_dense_topk(x, V, rows, k, ids, vals, ws, nbytes)
     _check_missing(x, ids, vals, k)
-    st = B.State(V, 8, 1, V, 1, rows, k)
+    st = B.State(V, 8, 1, V, T, rows, k)
     names = torch.arange(V, dtype=torch.int32, device="cuda")
     B.nanospec_vocab_init(st.h, names, np.array([0, V], np.int32), None, np.zeros(2, np.int32))
     logits = torch.full((rows, st.capacity), 1e30, device="cuda")
