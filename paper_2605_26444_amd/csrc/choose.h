@@ -203,15 +203,13 @@ inline int32_t tile64_fast(int32_t M, int32_t d) { return d % 512 != 0 ? 0 : (M 
 constexpr int32_t kInitFewSeqs = 16;           // more fill the chip with larger id ranges
 
 // One launch of one workgroup per sequence (vocab_init_kernel) or the id ranges counted all over the chip (two launches, three for long prompts).
-// The former's time grows with the prompt -- the additions to the counters, a frequent token's all to one address in L2, about 2 us per 1024 tokens -- and with the stream it
-// replaces, whose ring of up to `window` tokens it undoes one scattered store each; the host knows the window only.  The latter's is as good as constant, and grows with
-// the sequences.  V = 128256, |T| = 2000, over a stream that filled the window, one launch / ranges, us: one sequence, window 1024, 64 tokens 5.8 / 6.9, 256
-// 7.1 / 7.0, 600 9.8 / 7.6; window 4096, 64 tokens 7.1 / 6.9; 16384 10.2 / 6.9; 235312 75 / 7.4; 16 sequences, window 1024, 512 tokens 9.6 / 10.1; 64 sequences, window 1024, 1024
-// tokens 13.9 / 18.4; 4096, 1500 tokens 19.1 / 18.2; 8192, 600 15.9 / 17.2, 1500 21.7 / 18.8; 16384, 600 19.1 / 17.6; 235312, 64 125 / 15; 200 sequences, window 8192, 2000 tokens 31 / 39.
-inline bool vocab_init_serial(int32_t batch, int32_t window, int32_t longest) {
-  const int32_t most = batch <= kInitFewSeqs ? 272 + 20 * batch : batch <= 128 ? 1024 + 8 * batch : 2048;
-  return longest + window / 16 <= most;
-}
+// The former's time grows with the prompt -- the additions to the counters, a frequent token's all to one address in L2, about 0.7 us per 100 tokens -- and with the
+// stream it replaces, whose ring of up to `window` tokens it undoes one scattered store each, 0.26 us per 1024; the host knows the window only.  The latter's is as good as
+// constant, and grows with the sequences.  V = 128256, |T| = 2000, initialisations back to back over a stream that filled the window, one launch / ranges, us: one
+// sequence, window 1024, 64 tokens 5.8 / 6.9, 600 9.8 / 7.6; window 8192, 64 tokens 7.9 / 7.3; 16384 10.2 / 6.9; 65536 25 / 7.2; 235312 75 / 7.4; 64 sequences, window 1024, 1024 tokens 13.9 /
+// 18.4; 8192, 600 15.9 / 17.2, 1500 21.7 / 18.8; 65536, 64 37 / 15; 235312 125 / 15.  In front of a draft step the second launch costs about 3 us more than that (requests of
+// one sequence and 192 to 331 tokens 1.8 to 3.4 us, of three and 214 to 463 2.5 to 3.2), so the lines for a small window are 640 and 1536 tokens.
+inline bool vocab_init_serial(int32_t batch, int32_t window, int32_t longest) { return longest + window / 24 <= (batch <= kInitFewSeqs ? 640 : 1536); }
 
 // ---- selection from rows that one workgroup's registers do not hold (topk.hip) --------------------------------------------------
 

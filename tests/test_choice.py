@@ -70,8 +70,8 @@ def test_shapes_for_many_hidden_rows(M, rows, dense, want):
 
 
 @pytest.mark.parametrize("batch,window,longest,want", [
-    (1, 256, 256, True), (1, 1024, 64, True), (1, 1024, 256, False), (1, 1024, 600, False), (1, 8192, 64, False), (1, 235312, 500, False), (1, 16384, 0, False), (16, 1024, 512, True), (16, 16384, 64, False),
-    (64, 1024, 1024, True), (64, 8192, 600, True), (64, 8192, 1500, False), (64, 16384, 600, False), (64, 235312, 64, False), (17, 2048, 1500, False), (200, 8192, 1500, True),
+    (1, 256, 256, True), (1, 640, 600, True), (1, 1024, 600, False), (1, 4096, 331, True), (1, 8192, 64, True), (1, 8192, 500, False), (1, 16384, 0, False), (1, 235312, 64, False),
+    (16, 512, 512, True), (16, 16384, 64, False), (64, 1024, 1024, True), (64, 8192, 600, True), (64, 8192, 1500, False), (64, 65536, 64, False), (64, 235312, 64, False),
 ])
 def test_stream_initialisation(batch, window, longest, want):
     """a short prompt for a wide window may follow a stream that filled it, and one workgroup would undo it token by token"""

@@ -37,8 +37,8 @@ def _check(st, orc, what):
     (50001, 32769, [40000, 32769, 16384], 128),
     (128256, 40000, [39999, 70000], 2000),
     # around the longest prompts of one workgroup per sequence, and prompts of its range behind longer ones
-    (30000, 256, [256], 40), (30000, 1024, [228], 40), (30000, 1024, [229], 40), (30000, 1024, [600], 40),
-    (30001, 2048, [1032 - (b & 1) for b in range(17)], 40), (30001, 2048, [1033 - (b & 1) for b in range(17)], 40), (30001, 4096, [2200 + b for b in range(17)], 40),
+    (30000, 256, [256], 40), (30000, 1024, [598], 40), (30000, 1024, [599], 40), (30000, 1024, [1500], 40),
+    (30001, 2048, [1451 - (b & 1) for b in range(17)], 40), (30001, 2048, [1452 - (b & 1) for b in range(17)], 40), (30001, 4096, [2200 + b for b in range(17)], 40),
 ])
 def test_init_over_any_earlier_state(policy, V, window, lengths, nT):
     nb = len(lengths)
