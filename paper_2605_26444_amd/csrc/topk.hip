@@ -753,17 +753,17 @@ __global__ __launch_bounds__(64 * NW) void topk_list_kernel(const float* __restr
 // among all of them as (candidate, group of four) work items over the workgroup.  (17 rows of 128256, k = 40,
 // selection and merge: 24.9 -> 19.7 us against rounds of one wavefront; k = 10 11.9 -> 9.6; 8 rows of 32000, k = 40 22.9 -> 9.1; 256
 // threads instead of 1024: k = 40 39 us.)
-template <bool LSE>
+template <bool LIST, bool LSE>   // LIST: not dense rows, whose positions are the ids and whose length is known to need the chunks
 __global__ __launch_bounds__(1024) void topk_merge_kernel(const float* __restrict__ cand_val, const int32_t* __restrict__ cand_pos,
                                                           const float2* __restrict__ cand_ms, int nchunks,
                                                           const int32_t* __restrict__ ids, int64_t ids_stride, int M, int k,
                                                           int32_t* __restrict__ out_ids, float* __restrict__ out_vals,
-                                                          const int32_t* __restrict__ n_dev, int n_fixed) {
+                                                          const int32_t* __restrict__ n_dev) {
   __shared__ __attribute__((aligned(16))) float s_v[1024 + 4];
   __shared__ int s_r[1024];
   const int tid = threadIdx.x, lane = tid & 63;
   const int m = blockIdx.y, b = blockIdx.z;
-  if ((n_dev ? n_dev[b] : n_fixed) <= kTopkChunk) return;   // the first chunk's workgroup has written the result
+  if (LIST && n_dev[b] <= kTopkChunk) return;               // the first chunk's workgroup has written the result
   const int64_t row = (int64_t)b * M + m;
   const int total = nchunks * k;
   float val = -INFINITY;
@@ -775,7 +775,7 @@ __global__ __launch_bounds__(1024) void topk_merge_kernel(const float* __restric
     s_r[tid] = 0;
   }
   if (tid < 4) s_v[total + tid] = __builtin_nanf("");       // pads the last group of four; compares false with everything
-  const int gid = ids && val != -INFINITY ? ids[b * ids_stride + pos] : pos;   // requested before the ranking, used behind it
+  const int gid = LIST && val != -INFINITY ? ids[b * ids_stride + pos] : pos;   // requested before the ranking, used behind it
   float lse = 0.f;
   if (LSE) {                                              // chunk (max, sum) pairs -> one log sum exp; at most 16 chunks
     const float2 ms = lane < nchunks ? cand_ms[row * nchunks + lane] : make_float2(0.f, 0.f);
@@ -860,7 +860,8 @@ static hipError_t launch_topk_t(const float* logits, int64_t ld, const int32_t* 
                                                                             out_vals, cv, cp, ms);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  topk_merge_kernel<LSE><<<rows, 1024, 0, s>>>(cv, cp, ms, nch, ids, ids_stride, M, k, out_ids, out_vals, n_dev, n_fixed);
+  if (n_dev) topk_merge_kernel<true, LSE><<<rows, 1024, 0, s>>>(cv, cp, ms, nch, ids, ids_stride, M, k, out_ids, out_vals, n_dev);
+  else if constexpr (!LSE) topk_merge_kernel<false, false><<<rows, 1024, 0, s>>>(cv, cp, ms, nch, ids, ids_stride, M, k, out_ids, out_vals, n_dev);
   return hipGetLastError();
 }
 
