@@ -38,9 +38,9 @@ HBM_PEAK_GBPS = 8000.0      # MI355X published HBM3E peak
 # Bytes per sparse-head launch that leave L2 towards HBM, from the rocprofv3 --pmc runs summarised under
 # profiles/ (FETCH_SIZE x 2.0 +
 # WRITE_SIZE x 1.0, factors from copy / stream kernels of known size), as bytes per active row so that it
-# follows the realised |active|.  c3: the split-K kernel without its reduce kernel; c5: measured at 32k rows.
-PMC_TRAFFIC_PER_ROW = {"c2": 25313690 / 3004, "c3": 25943859 / 2998, "c4": 767895347 / 144911,
-                       "c5@32000": 533476454 / 32007}
+# follows the realised |active|.  c5: measured at 32k rows.
+PMC_TRAFFIC_PER_ROW = {"c2": 25348608 / 3008, "c3": 25940480 / 2987, "c4": 779214656 / 144911,
+                       "c5@32000": 533876000 / 32007}
 
 
 def main():

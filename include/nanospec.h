@@ -268,7 +268,8 @@ NANOSPEC_API nanospec_status nanospec_dense_head(const void* d_W_bf16, const voi
 
 /* Top-k over dense logits (the selection step of the full-vocabulary comparison point):
  * rows [M_total][V], ids are the column indices; same ordering rule as nanospec_topk_remap.
- *   d_workspace : device scratch of at least nanospec_dense_topk_workspace(V, M_total, k) bytes.
+ *   d_workspace : device scratch of at least nanospec_dense_topk_workspace(V, M_total, k) bytes.  Asked for whatever
+ *                 M_total is, also where the rows are selected without it.
  * Errors: EINVAL (null, sizes < 1, k > 64), ECAPACITY (workspace too small).  Asynchronous. */
 NANOSPEC_API int64_t nanospec_dense_topk_workspace(int32_t V, int32_t M_total, int32_t k);
 NANOSPEC_API nanospec_status nanospec_dense_topk(const float* d_logits, int32_t V, int32_t M_total, int32_t k,

@@ -129,7 +129,8 @@ inline WideShape wide_shape(int32_t M, int32_t d, int32_t batch, int32_t cap_row
 // Sequences hold many of the same rows, and a die's L2 sees a row again only if the sequences that hold it run there at the
 // same time: for few hidden rows each die takes one eighth of every list (64 sequences of 2300 rows, M = 8: 135 -> 130.5 us, 32: 79
 // -> 73.5, 16: 47 -> 43; 8, M = 16: 31.1 -> 29.4), but not where the hidden rows of all sequences, which every die then needs, are as
-// many bytes as the rows (64 sequences, M = 16: 140 -> 145; M = 60 on 8 sequences 25 -> 26).
+// many bytes as the rows (64 sequences, M = 16: 140 -> 145; M = 60 on 8 sequences 25 -> 26).  The kernels of head.hip, which fetch all
+// hidden rows of a sequence for every 16 list rows, lose by the same order.
 inline bool wide_by_die(int32_t M, int32_t batch, int32_t cap_rows, bool dense) {
   const int64_t rows = (int64_t)cap_rows * batch * (dense ? 2 : 1);
   return batch >= 8 && M <= 16 && (M <= 8 || rows < 131072);

@@ -65,7 +65,7 @@ struct nanospec_state {
   nanospec::VocabPtrs vp;
   char* base;               // the one device allocation everything lives in
   float* partial;           // split-K partial logits
-  char* topk_ws;            // two-pass top-k candidates
+  char* topk_ws;            // two-pass top-k candidates (lists longer than 16 384, where they are selected in chunks)
   int64_t partial_bytes, topk_ws_bytes;
   int32_t* h_err_pinned;    // pinned host word for reading the device flags
   int vocab_lds_bytes, unique_lds_bytes, unique_cap, fifo_lds_bytes;

@@ -322,7 +322,8 @@ __global__ __launch_bounds__(256 * NRG) void head_quad_kernel(const uint16_t* __
   // tile's weight loads issued before the epilogue 136 us; as a kernel of its own with two register sets of weights,
   // every load unconditional and the tile loop fully unrolled, one workgroup per compute unit: 135 us), and handing each of the chip's eight dies one eighth of
   // every sequence's list so that the sequences' copies of a row meet in one L2 (more fabric traffic, not less:
-  // every die then needs all sequences' hidden rows in its L2).
+  // every die then needs all sequences' hidden rows, which this kernel fetches again for every 16 list rows; the
+  // register-blocked kernel, which fetches them once for 64 or 32, gains from that order: wide_by_die in choose.h).
   if (!UNCOND && tile * (NRG * RPG) >= n) return;
   // where the logit this thread will store goes (see head_quad_private_kernel); asked for now, used at the end
   static_assert(NOUT <= 256, "one output per thread");

@@ -809,6 +809,8 @@ __global__ __launch_bounds__(1024) void topk_merge_kernel(const float* __restric
 
 static int chunks_for(int32_t cap) { return (cap + kTopkChunk - 1) / kTopkChunk; }
 
+// What the chunks of these rows need.  It is asked for at every size, also where one workgroup per row or per list runs and leaves it
+// unused, so that what a caller has to hold and what is refused does not change with the choice of the kernel.
 int64_t topk_workspace_bytes(int32_t cap, int32_t rows, int32_t k) {
   if (cap <= kTopkChunk) return 0;
   return (int64_t)rows * chunks_for(cap) * (k * 8 + 8);   // (value, position) per winner + (max, sum) per chunk

@@ -154,7 +154,7 @@ __global__ __launch_bounds__(64 * WR * WH) void head_wide_kernel(const uint16_t*
     const char* As = smem + stage * STAGE + (wr * FR * 16) * STR + frag_off;
     const char* Bs = smem + stage * STAGE + BM * STR + (wh * FH * 16) * STR + frag_off;
     constexpr int KK = BK / 32;
-    if constexpr (WR * WH != 8) {                     // memory-bound shape: the plain order, scheduled by the compiler (205 against 217 us)
+    if constexpr (WR * WH != 8) {                     // four wavefronts, memory-bound: the plain order, scheduled by the compiler (205 against 217 us)
 #pragma unroll
       for (int kk = 0; kk < KK; ++kk) {
         bf16x8 bq[FH];
@@ -190,9 +190,10 @@ __global__ __launch_bounds__(64 * WR * WH) void head_wide_kernel(const uint16_t*
       }
     }
     // The order above is the order wanted; left alone, the scheduler puts every fragment read right in front of its
-    // first use.  Groups: the LDS reads of the next fragment(s), then FH matrix instructions.  Only for the
-    // compute-bound shapes (eight wavefronts): 644 -> 614 us at 512 hidden rows on 256 x 128 logits; the memory-bound
-    // four-wavefront shape loses with it (205 -> 218 us at 64 hidden rows).
+    // first use.  Groups: the LDS reads of the next fragment(s), then FH matrix instructions.  For the shapes of eight
+    // wavefronts, of which the compute-bound ones gain: 644 -> 614 us at 512 hidden rows on 256 x 128 logits.  The 32 x 64 and
+    // 64 x 64 shapes are memory-bound and do not care (16 sequences of 64 x 2000 rows, d = 3584: 46.8 with, 46.7 without);
+    // the four-wavefront shapes lose with it (205 -> 218 us at 64 hidden rows).
     if constexpr (WR * WH == 8) {
       __builtin_amdgcn_sched_group_barrier(0x100, FH + 1, 0);
 #pragma unroll
@@ -310,11 +311,13 @@ __device__ __forceinline__ void lds_fetch16(uint32_t lds, const void* base, uint
 //     conflicts without padding;
 //   * a step is four phases, each a quarter of the block (row half x hidden half) of 16 matrix instructions per wavefront, and the
 //     second four wavefronts run one phase half behind the first: while one wavefront of a SIMD multiplies, the other one
-//     asks for its next fragments.  Fragments are asked for one barrier before they are needed;
+//     asks for its next fragments (the eight-wavefront ping-pong schedule published for this chip, HipKittens, arXiv 2511.08083;
+//     the split of the fetches, the permutation, the phases and the waits are this kernel's).  Fragments are asked for one barrier
+//     before they are needed;
 //   * a piece of LDS is refilled one phase after all its readers have consumed it (the barriers between say so), and is read
 //     after every wavefront has waited for its own fetches of it (the counted waits, then a barrier).
 // 1024 hidden rows on the 128k x 4096 matrix: 896 us = 1.20 PFLOP/s (head_wide_kernel's 256 x 256 shape: 1036); the loop takes
-// 1.16 times its matrix cycles, at the 1.7 GHz that this load leaves the clock.  512 hidden rows 532 -> 490 us, 130: 309 -> 275.  The
+// 1.16 times its matrix cycles, at the 1.7 GHz this load runs at.  512 hidden rows 532 -> 490 us, 130: 309 -> 275.  The
 // sums are taken in the same order: results are bit-equal.
 __global__ __launch_bounds__(512, 2) void head_gemm_kernel(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H,
                                                            const int32_t* __restrict__ ids, const int32_t* __restrict__ n_dev, int n_fixed,
