@@ -199,6 +199,72 @@ inline bool head_split(int32_t M, int32_t d, int32_t batch, int32_t cap_rows, bo
 // head_tile64_kernel's FAST: 0 = every load tested, 1 = whole slices, hidden rows clamped, 2 = and every wavefront's sixteen hidden rows exist
 inline int32_t tile64_fast(int32_t M, int32_t d) { return d % 512 != 0 ? 0 : (M == 64 ? 2 : 1); }
 
+// ---- the hidden rows in registers (hold.hip), up to 16 of them -----------------------------------------------------------
+
+// NW wavefronts of 1024 columns, 8 * parts workgroups per sequence, segments of at most `seg` rows between two sums over the wavefronts.
+struct HoldPlan {
+  int32_t NW, parts, seg;
+};
+
+// How many of the chip's 256 compute units have work on average until the last of `groups` equal workgroups ends, in 1/64.
+inline int32_t hold_fill(int64_t groups) { return (int32_t)(groups * 64 / ((groups + 255) / 256 * 256)); }
+
+// Workgroups: one per compute unit while the list's pieces fit that (one list of 8400 x 8192, M = 16: 256 workgroups 29.7 us, 384 33.5, 512 32.2; 30000 x 4096, M = 8:
+// 46.0 / 48.8 / 48.6), two of few wavefronts where sequences share them (16 of 5000 x 2048, M = 8: 256 44 us, 512 38).  Numbers of sequences that do not divide
+// them leave compute units idle: the most pieces that fit, if they fill three quarters, else the fewest beyond that fill 51 of 64 (48 of 2300 x 4096, M = 8: 384 workgroups 96 us, 768 84;
+// 24: 192 59, 384 56).  Dense heads are long enough for the chip to hand them out again as workgroups end (128k x 8192, M = 16: 256 workgroups 358 us, 1024 348;
+// 128k x 4096 187 / 186, 512 185).
+inline HoldPlan hold_plan(int32_t d, int32_t batch, bool dense) {
+  HoldPlan h = {(d + 1023) / 1024, 32, 256};
+  if (dense) h.parts = 16 * h.NW;
+  else if (batch > 1) {
+    const int32_t cu = h.NW <= 2 ? 512 : 256;
+    h.parts = cu / (8 * batch);
+    if (h.parts < 1 || 8 * batch * h.parts * 4 < cu * 3) {
+      h.parts = h.parts < 1 ? 1 : h.parts;
+      while (h.parts < 64 && (8 * batch * h.parts < cu || hold_fill(8ll * batch * h.parts) < 51)) ++h.parts;
+    }
+  }
+  return h;
+}
+
+inline int64_t hold_lds(const HoldPlan& h, int32_t M) { return (int64_t)h.NW * ((M + 3) / 4 * 4) * (h.seg + 4) * 4; }
+
+// Which products it takes.  Against the kernels of head.hip and wide.hip; two figures: around 0.3 and 0.9 of the capacity live.  It is launched over the live rows, so it
+// gains most on lists that are far from full, and loses on short ones, where the others ask for weights before the row count has arrived (1000 rows x 4096, M = 8: 5.1 against 4.1 us).
+//  One list (capacity):
+//   * d > 4096, M > 4: from 2560 on (x 8192, M = 16: 3072 0.98 / 0.85 of the time, 16384 0.80 / 0.98, 8400 of 33303 37.8 -> 29.7 us, 32800 of 128256 107 -> 100; M = 8: 3072 1.07 / 0.91,
+//     16384 0.92 / 1.04; x 5120, M = 8: 9000 1.0 / 0.91, 65536 0.80 / 0.88; below 2048 1.01 / 1.01, M = 8 1.09 / 1.06), but not from 49152 on with M > 8 and d < 5120 (x 4608 1.09 / 1.03);
+//     M <= 4 loses as much as it gains (x 8192: 16384 0.97 / 1.09, x 5120 1.0 / 1.04);
+//   * d = 4096, M > 4: beyond 4096 (M = 16: 5120 0.74 / 0.84, 16384 0.94 / 0.93; M = 8: 5120 0.86 / 0.90, 8192 0.81 / 1.0, 8400 of 33303 22.1 -> 16.4 us; 4096 1.02 / 1.13);
+//   * 2048 < d < 4096, M > 4: beyond 4096 up to 12288 (x 3072, M = 16: 5120 0.70 / 0.84, 9000 0.59 / 0.78, 20000 1.10 / 0.95; M = 8: 9000 0.69 / 0.90, 20000 1.01 / 0.92);
+//   * 2048 < d <= 4096, M <= 4: 4097 to 6144 and from 12288 on (x 4096: 5120 0.86 / 0.94, 8192 0.93 / 1.07, 16384 0.78 / 1.04);
+//   * d = 2048: from 16384 on, M > 8 32768 (M = 8: 16384 0.87 / 0.94, 9000 0.96 / 1.09; M = 16: 65536 0.98 / 0.90, 20000 1.08 / 0.96).
+//  Several sequences (capacities together; a die takes the same eighth of every list, see wide_by_die):
+//   * d > 4096: from 2560 on for four or more, two or three beyond 4096 (x 8192: 4 of 600 out of 1000, M = 8 0.86, 2 of them 1.03; 16 of 2300 out of 5120 0.73, 64 239 -> 217 us; x 5120: 16 of 2300 out of 5120
+//     69.6 -> 44.5); M <= 4 where the workgroups fill the chip (24: 1.03); M > 8 and d < 5120 up to 196608 (x 4608, M = 16: 64 of 2300 out of 5120 1.11, 16 0.90);
+//   * 2048 < d <= 4096: beyond 4096 (x 4096, M = 8: 8 of 600 out of 1000 0.80, 16 of 2300 out of 5120 0.80, 32 73 -> 59 us, 64 122 -> 107; M = 16: 32 80 -> 64, 64 133 -> 120; 4 of 1000 1.07; x 3072, M = 16: 16 of 600
+//     out of 1100 0.64; x 2560, M = 4: 2 of 2300 out of 5120 1.04);
+//   * d = 2048: M <= 8 from 16384 on (16 of 2300 out of 5120 0.81, 2 1.05), M > 8 from 65536 on (0.89, 8 of 5120 1.01).
+//  Dense heads: M > 8, d of 4096 or 8192, of which a compute unit takes eight wavefronts (128k x 4096, M = 16 207 -> 186 us, M = 9 188 -> 180; 32000 x 8192 104 -> 93; x 5120 1.05, x 2048, M = 9 1.06).
+inline bool hold_supported(int32_t V, int32_t M, int32_t d, int32_t batch, int32_t cap_rows, bool dense) {
+  if (M > 16 || d > 8192 || d < 2048 || !wide_reaches(V, M, d)) return false;
+  const int64_t rows = (int64_t)cap_rows * batch;
+  if (rows > 0x20000000ll) return false;
+  if (dense) return M > 8 && (d == 4096 || d == 8192) && rows >= 16384;
+  if (batch > 1) {
+    if (d > 4096 && rows <= (batch >= 4 ? 2560 : 4096)) return false;
+    if (d > 4096 && M <= 4) return hold_fill(8ll * batch * hold_plan(d, batch, false).parts) >= 51;
+    if (d > 4096) return M <= 8 || d >= 5120 || rows < 196608;
+    return d > 2048 ? rows > (batch < 4 && M <= 8 && d < 3072 ? 12288 : 4096) : rows >= (M <= 8 ? 16384 : 65536);
+  }
+  if (d > 4096) return M > 4 && rows > 2560 && (M <= 8 || d >= 5120 || rows < 49152);
+  if (d == 2048) return rows >= (M <= 8 ? 16384 : 32768);
+  if (rows <= 4096) return false;
+  if (M <= 4) return rows <= 6144 || rows >= 12288;
+  return d == 4096 || rows <= 12288;
+}
+
 // ---- stream initialisation (vocab.hip) -------------------------------------------------------------------------------------
 
 constexpr int32_t kInitFewSeqs = 16;           // more fill the chip with larger id ranges

@@ -28,12 +28,18 @@ void c_quad_plan(int M, int d, int batch, int cap, int dense, int* o) {
 int c_head_split(int M, int d, int batch, int cap, int dense, long long partial_bytes, long long ld) { return head_split(M, d, batch, cap, dense != 0, partial_bytes, ld); }
 int c_vocab_init_serial(int batch, int window, int longest) { return vocab_init_serial(batch, window, longest); }
 int c_topk_chunks(int list, long long rows, int k, int topk_cap, int window, int distinct) { return topk_chunks(list != 0, rows, k, topk_expected(topk_cap, window, distinct != 0)); }
+int c_hold_supported(int V, int M, int d, int batch, int cap, int dense) { return hold_supported(V, M, d, batch, cap, dense != 0); }
+void c_hold_plan(int d, int batch, int dense, int M, int* o) {
+  const HoldPlan h = hold_plan(d, batch, dense != 0);
+  o[0] = h.NW; o[1] = h.parts; o[2] = h.seg; o[3] = (int)hold_lds(h, M);
+}
 int c_tile64_fast(int M, int d) { return tile64_fast(M, d); }
 }
 """
 
 Quad = namedtuple("Quad", "MT KS NRG RT loop")
 Block = namedtuple("Block", "WR WH FR FH BK D")
+Hold = namedtuple("Hold", "NW parts seg lds")
 
 
 def _load():
@@ -54,6 +60,16 @@ GEMM = _lib.c_gemm_shape()
 
 def wide_supported(V, M, d, batch, cap, dense=False):
     return bool(_lib.c_wide_supported(V, M, d, batch, cap, int(dense)))
+
+
+def hold_supported(V, M, d, batch, cap, dense=False):
+    return bool(_lib.c_hold_supported(V, M, d, batch, cap, int(dense)))
+
+
+def hold_plan(d, batch, M, dense=False):
+    o = (C.c_int * 4)()
+    _lib.c_hold_plan(d, batch, int(dense), M, o)
+    return Hold(*o)
 
 
 def wide_reaches(V, M, d):
