@@ -136,9 +136,14 @@ inline bool wide_by_die(int32_t M, int32_t batch, int32_t cap_rows, bool dense) 
   return batch >= 8 && M <= 16 && (M <= 8 || rows < 131072);
 }
 
-// One list shared by the hidden rows of several sequences (see launch_head_shared).  It runs beside the per-sequence product, so what
-// counts is how little it takes from that one: 64-sequence request of four steps 714 us with 64 x 64 blocks, 754 with 128 x 64, 840
-// with 256 x 128 (too few workgroups), 734 with the slice-loop kernel (64 hidden rows at a time).
+// Whether the batch-union head works from its lists -- shared rows once against all hidden rows, the rest per sequence -- or as the per-sequence head, whose workgroups
+// take the same eighth of every list on one die and so find most shared rows in its L2.  The latter over the former, 512 to 8192 columns, 2 to 64 sequences: M >= 8 0.28 to 0.92 of
+// the time (64 of 2300 x 4096, M = 8: 107 / 122 us, 36 of them for the shared rows and 84 for the rest, M = 64: 187 / 409); M = 4 0.3 to 0.99, but for most rows (64 of 6000 out of 7000
+// x 8192 502 / 451, x 4096 251 / 238, x 2048 124 / 119, x 1024 84 / 78; 64 of 2300 out of 5120 x 8192 213 / 202, x 4096 103 / 103, x 1024 32 / 37; 32 of 6000 x 8192 264 / 255; 32 of 5120 x 8192 114 / 125).
+inline bool union_split(int32_t M, int32_t d, int32_t batch, int32_t cap_rows) { return M <= 4 && d >= 2048 && (int64_t)cap_rows * batch >= 196608; }
+
+// One list shared by the hidden rows of several sequences (see launch_head_shared): 64 sequences' hidden rows on 7400 rows 36 us with 64 x 64 blocks, 39 with 128 x 64,
+// 70 with 256 x 128 (too few workgroups).
 inline WideShape wide_shared_shape(int32_t rows_total) { return rows_total <= 16 ? kWide32x16 : rows_total <= 32 ? kWide32x32 : kWide64x64; }
 
 // ---- the kernels of head.hip, up to 64 hidden rows per sequence and launch ----------------------------------------------

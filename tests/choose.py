@@ -33,6 +33,7 @@ void c_hold_plan(int d, int batch, int dense, int M, int* o) {
   const HoldPlan h = hold_plan(d, batch, dense != 0);
   o[0] = h.NW; o[1] = h.parts; o[2] = h.seg; o[3] = (int)hold_lds(h, M);
 }
+int c_union_split(int M, int d, int batch, int cap) { return union_split(M, d, batch, cap); }
 int c_tile64_fast(int M, int d) { return tile64_fast(M, d); }
 }
 """
@@ -70,6 +71,10 @@ def hold_plan(d, batch, M, dense=False):
     o = (C.c_int * 4)()
     _lib.c_hold_plan(d, batch, int(dense), M, o)
     return Hold(*o)
+
+
+def union_split(M, d, batch, cap):
+    return bool(_lib.c_union_split(M, d, batch, cap))
 
 
 def wide_reaches(V, M, d):

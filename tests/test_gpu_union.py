@@ -11,6 +11,7 @@ import oracle
 from paper_2605_26444_amd import binding as B
 from paper_2605_26444_amd import synth
 
+import choose
 from harness import assert_logits_close, check_topk, csr, dev_bf16, dev_ids, host_W
 
 pytestmark = pytest.mark.gpu
@@ -197,8 +198,7 @@ def test_union_c4_shape():
 
 
 def test_union_step_recorded_in_hip_graph_replays_correctly():
-    """update + list build + union head (whose shared-row product forks onto the state's side stream and joins back) +
-    selection captured in one HIP graph: every replay, with eager work and synchronisations in between, gives the
+    """update + list build + union head + selection captured in one HIP graph: every replay, with eager work and synchronisations in between, gives the
     oracle's vocabulary, the eager union head's bits and the oracle's logits."""
     rng = np.random.default_rng(26)
     V, d, M, k, window, nb = 8000, 512, 8, 6, 128, 12
@@ -260,4 +260,30 @@ def test_union_step_recorded_in_hip_graph_replays_correctly():
         for b in range(nb):
             orc[b].update(extra[b])
     assert B.nanospec_last_device_error(st.h) == 0
+    st.close()
+
+
+@pytest.mark.parametrize("M,d,split", [(3, 2056, True), (4, 2048, True), (5, 2048, False), (4, 2040, False)])
+def test_union_head_on_either_side_of_the_choice_to_split(M, d, split):
+    """shared list and rest lists, or whole lists: both within d * 2^-24 * sum |w h| (an fp32 sum of d exact products) of fp64"""
+    V, nb, window = 20000, 64, 3100
+    rng = np.random.default_rng(M)
+    common = rng.permutation(V)[:1500]
+    ids = [np.unique(np.concatenate([common[rng.random(1500) < 0.6], rng.permutation(V)[:rng.integers(0, 2000)]])).astype(np.int32)[:window] for _ in range(nb)]
+    ids[1] = ids[1][:0]
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    W = torch.empty((V, d), dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+    H = torch.empty((nb, M, d), dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+    st = B.State(V, d, nb, window, 1, M, 1)
+    assert choose.union_split(M, d, nb, st.capacity) == split
+    B.nanospec_union_enable(st.h, 0, 0)
+    flat, off = csr(ids)
+    B.nanospec_vocab_init(st.h, dev_ids(flat), off, None, np.zeros(nb + 1, np.int32))
+    B.nanospec_union_build(st.h)
+    logits = torch.full((nb, M, st.capacity), 7.0, dtype=torch.float32, device="cuda")
+    B.nanospec_union_head(st.h, W, H, M, logits)
+    for b in range(nb):
+        w, h, n = W[torch.from_numpy(ids[b]).long().cuda()].double(), H[b].double(), len(ids[b])
+        assert torch.all((logits[b, :, :n].double() - h @ w.T).abs() <= d * 2.0 ** -24 * (h.abs() @ w.abs().T)), b
     st.close()
