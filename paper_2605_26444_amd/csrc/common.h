@@ -130,6 +130,7 @@ hipError_t launch_topk(const float* logits, int64_t ld, const int32_t* ids, int6
                        int32_t* out_ids, float* out_vals, bool logprob, char* ws, int64_t ws_bytes, hipStream_t s);
 
 // packed.hip
+hipError_t packed_configure_device();
 hipError_t launch_packed_reset(const nanospec_state* st, hipStream_t s);
 hipError_t launch_packed_gather(const nanospec_state* st, const void* W, hipStream_t s);
 

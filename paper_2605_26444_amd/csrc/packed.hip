@@ -99,129 +99,190 @@ __global__ __launch_bounds__(kSyncThreads) void packed_sync_kernel(VocabPtrs p, 
   }
 }
 
-// The same for capacities of up to Q x 4096 slots in two memory round trips and one scan (the walk above takes two round
-// trips, two ranks and their stores' latency per 1024 slots and again per 1024 ids: 8.4 us at 3750 slots).  Thread t holds slots and list
-// positions q * 4096 + 4t .. + 3: slot ids and listed ids are asked for together, then the bitmap words of the former
-// and the slots of the latter -- a listed id's slot is not freed by this call, so the two do not wait for each other.
-// Free slots and ids without a slot are ranked in one scan; the free list lives in LDS.  All stores come last: the
-// f-th free slot is taken by the f-th new id, so the thread that frees a slot clears its tables only if it stays free.
+// The same for capacities of up to Q x 4096 slots in one memory round trip.  What bounds it is instruction issue on its one compute unit and the address
+// rate of scattered look-ups, a cycle per lane: every slot's id in both bitmaps and every listed id's slot were 12 of them per thread.  Here the bitmaps come into LDS in whole
+// lines; a kept slot's position in the list is the rank of its id in the bitmap (words before it, from one scan, and bits below it), and the ids that enter are the
+// active bits that no slot holds.  Thread t holds slots q * 4096 + 4t .. + 3 and wpt consecutive bitmap words.  The f-th free slot is taken by the f-th entering id, both
+// ascending; the thread that holds a slot clears its tables only if it stays free.  No table by id is kept.  With the copy's launch behind it, against the look-ups: 3776 slots
+// 7.3 -> 4.9 us, 1280 6.0 -> 4.8, 8000 10.2 -> 6.2, 15936 (then a walk in 1024s) 18.3 -> 10.0; with scans over __shfl and one LDS read per total 7.35 us at 3776.
+// Sixteen wavefronts share four SIMDs, so an instruction that all execute costs 7 ns: scans are DPP chains, two counts of up to 16384 to a register.
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ int sync_dpp_add(int x) {
+  return x + __builtin_amdgcn_update_dpp(0, x, CTRL, ROW_MASK, 0xf, false);            // lanes without a source add 0
+}
+
+// inclusive prefix sum over the 64 lanes (row_shr 1, 2, 4, 8 inside rows of 16, row totals carried by row_bcast 15 and 31)
+__device__ __forceinline__ int sync_scan(int x) {
+  x = sync_dpp_add<0x111, 0xf>(x);
+  x = sync_dpp_add<0x112, 0xf>(x);
+  x = sync_dpp_add<0x114, 0xf>(x);
+  x = sync_dpp_add<0x118, 0xf>(x);
+  x = sync_dpp_add<0x142, 0xa>(x);
+  return sync_dpp_add<0x143, 0xc>(x);
+}
+
+// sum over each row of 16 lanes, in all of them (quad_perm neighbours, row_half_mirror, row_mirror)
+__device__ __forceinline__ int sync_row_sum(int x) {
+  x = sync_dpp_add<0xB1, 0xf>(x);
+  x = sync_dpp_add<0x4E, 0xf>(x);
+  x = sync_dpp_add<0x141, 0xf>(x);
+  return sync_dpp_add<0x140, 0xf>(x);
+}
+
 template <int Q>
 __global__ __launch_bounds__(kSyncThreads) void packed_sync_short_kernel(VocabPtrs p, PackedPtrs k) {
-  constexpr int NW = kSyncThreads / 64;
-  __shared__ int s_free[Q * 4096];
-  __shared__ int2 s_tot[Q][NW];
-  __shared__ int s_top;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int cap = k.cap;                                   // a multiple of 64, as are the lists' lengths
-  int sid[Q][4], id[Q][4], sl[Q][4];
-  uint32_t fr[Q], nw[Q];                                   // bit e: slot free (bit 4 + e: by this call) / id without a slot
+  constexpr int NW = kSyncThreads / 64, S = (Q + 1) / 2 + (Q > 1 ? 1 : 0);   // scans: (bits, free of q = 0), then two q each
+  static_assert(NW == 16, "a row of lanes holds one total per wavefront");
+  extern __shared__ __attribute__((aligned(16))) uint32_t smem[];   // active bits, bits that a slot holds, rank of each word's first bit; free slots
+  uint32_t *act = smem, *held = smem + p.nwords;
+  int *pre = reinterpret_cast<int*>(held + p.nwords), *s_free = pre + p.nwords;
+  __shared__ int s_tot[S][NW], s_new[NW], s_top[NW];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, cap = k.cap;   // a multiple of 64
+  const int wpt = ((p.nwords + kSyncThreads - 1) / kSyncThreads + 3) & ~3;   // nwords is a multiple of 4
+  const int w0 = tid * wpt, w1 = w0 + wpt < p.nwords ? w0 + wpt : p.nwords;
+  int sid[Q][4];
 #pragma unroll
   for (int q = 0; q < Q; ++q) {
     const int s = q * 4096 + tid * 4;
     const int4 a = *reinterpret_cast<const int4*>(k.slot_id + (s < cap ? s : 0));
-    const int4 b = *reinterpret_cast<const int4*>(p.ids + (s < cap ? s : 0));
     sid[q][0] = a.x; sid[q][1] = a.y; sid[q][2] = a.z; sid[q][3] = a.w;
-    id[q][0] = b.x; id[q][1] = b.y; id[q][2] = b.z; id[q][3] = b.w;
   }
-  const int n = p.n[0];
-  if (tid == 0) s_top = -1;
-#pragma unroll
-  for (int q = 0; q < Q; ++q) {
-    const int s = q * 4096 + tid * 4;
-    uint32_t word[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int w = sid[q][e] >= 0 ? sid[q][e] >> 5 : 0;
-      word[e] = p.wbit[w] | p.tbit[w];
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) sl[q][e] = k.slot_of[s + e < n ? id[q][e] : 0];   // entries past n may be anything
-    fr[q] = nw[q] = 0u;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const bool gone = sid[q][e] >= 0 && !((word[e] >> (sid[q][e] & 31)) & 1u);
-      if (s < cap && (sid[q][e] < 0 || gone)) fr[q] |= (gone ? 17u : 1u) << e;
-      if (s + e < n && sl[q][e] < 0) nw[q] |= 1u << e;
-    }
-  }
-  // ranks in (q, thread, e) order = ascending slots / ids
-  int2 incl[Q];
-#pragma unroll
-  for (int q = 0; q < Q; ++q) {
-    incl[q] = make_int2(__popc(fr[q] & 15u), __popc(nw[q]));
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int x = __shfl_up(incl[q].x, o), y = __shfl_up(incl[q].y, o);
-      incl[q].x += lane >= o ? x : 0;
-      incl[q].y += lane >= o ? y : 0;
-    }
-    if (lane == 63) s_tot[q][wave] = incl[q];
+  int pop = 0;
+  for (int w = w0; w < w1; w += 4) {
+    const uint4 a = *reinterpret_cast<const uint4*>(p.wbit + w), t = *reinterpret_cast<const uint4*>(p.tbit + w);
+    const uint4 v = make_uint4(a.x | t.x, a.y | t.y, a.z | t.z, a.w | t.w);
+    *reinterpret_cast<uint4*>(act + w) = v;
+    *reinterpret_cast<uint4*>(held + w) = make_uint4(0u, 0u, 0u, 0u);
+    pop += __popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w);
   }
   __syncthreads();
-  int fbase[Q], nbase[Q], ftot = 0, ncopy = 0;
+  uint32_t fr[Q], gone[Q], word[Q][4];                     // bit e: slot free / by this call; the bitmap word of its id
+  int top = -1;
 #pragma unroll
   for (int q = 0; q < Q; ++q) {
-    int fo = ftot, no = ncopy;
+    fr[q] = gone[q] = 0u;
+    int mine = -1;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) {
-      const int2 t = s_tot[q][w];
-      fo += w < wave ? t.x : 0;
-      no += w < wave ? t.y : 0;
-      ftot += t.x;
-      ncopy += t.y;
+    for (int e = 0; e < 4; ++e) {
+      // flags by arithmetic: with the two cases as branches the compiler lost the free bit of one of them (q = 1, e = 0)
+      const int s = q * 4096 + tid * 4 + e, id = sid[q][e];
+      word[q][e] = act[id >= 0 ? id >> 5 : 0];
+      const uint32_t in = s < cap ? 1u : 0u, has = id >= 0 ? in : 0u, stays = has & (word[q][e] >> (id & 31));
+      if (stays) atomicOr(&held[id >> 5], 1u << (id & 31));
+      mine = stays ? s : mine;
+      fr[q] |= (in & ~stays) << e;
+      gone[q] |= (has & ~stays) << e;
     }
-    fbase[q] = fo + incl[q].x - __popc(fr[q] & 15u);
-    nbase[q] = no + incl[q].y - __popc(nw[q]);
+    const unsigned long long any = __ballot(mine >= 0);    // slots ascend with the lane
+    if (any) top = __builtin_amdgcn_readlane(mine, 63 - __clzll((long long)any));
   }
+  int incl[S];
+  incl[0] = sync_scan(pop << 16 | __popc(fr[0]));
+#pragma unroll
+  for (int i = 1; i < S; ++i) incl[i] = sync_scan((2 * i < Q ? __popc(fr[2 * i < Q ? 2 * i : 0]) << 16 : 0) | __popc(fr[2 * i - 1]));
+  if (lane == 63) {
+#pragma unroll
+    for (int i = 0; i < S; ++i) s_tot[i][wave] = incl[i];
+    s_top[wave] = top;
+  }
+  __syncthreads();
+  int before[S], total[S];
+#pragma unroll
+  for (int i = 0; i < S; ++i) {
+    const int t = s_tot[i][lane & 15];
+    before[i] = sync_row_sum((lane & 15) < wave ? t : 0);
+    total[i] = sync_row_sum(t);
+  }
+  int fresh = 0, rank = (before[0] >> 16) + (incl[0] >> 16) - pop;
+  for (int w = w0; w < w1; w += 4) {
+    const uint4 v = *reinterpret_cast<const uint4*>(act + w), h = *reinterpret_cast<const uint4*>(held + w);
+    int4 r;
+    r.x = rank;
+    r.y = r.x + __popc(v.x);
+    r.z = r.y + __popc(v.y);
+    r.w = r.z + __popc(v.z);
+    rank = r.w + __popc(v.w);
+    *reinterpret_cast<int4*>(pre + w) = r;
+    fresh += __popc(v.x & ~h.x) + __popc(v.y & ~h.y) + __popc(v.z & ~h.z) + __popc(v.w & ~h.w);
+  }
+  const int ninc = sync_scan(fresh);
+  if (lane == 63) s_new[wave] = ninc;
+  int fbase[Q], ftot = 0;
 #pragma unroll
   for (int q = 0; q < Q; ++q) {
+    const int i = (q + 1) / 2, sh = q > 0 && q % 2 == 0 ? 16 : 0, mask = 0xffff;
+    fbase[q] = ftot + ((before[i] >> sh) & mask) + ((incl[i] >> sh) & mask) - __popc(fr[q]);
+    ftot += (total[i] >> sh) & mask;
     int f = fbase[q];
 #pragma unroll
     for (int e = 0; e < 4; ++e)
       if ((fr[q] >> e) & 1u) s_free[f++] = q * 4096 + tid * 4 + e;
   }
   __syncthreads();
-  int top = -1;
+  const int tn = s_new[lane & 15], ncopy = sync_row_sum(tn);
+  int r = sync_row_sum((lane & 15) < wave ? tn : 0) + ninc - fresh;
 #pragma unroll
   for (int q = 0; q < Q; ++q) {
-    int r = nbase[q];
+    const int s = q * 4096 + tid * 4;
+    int out[4], f = fbase[q];
+    uint32_t taken = 0u;                                   // bit e: free slot that an entering id takes, which writes its tables
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      if ((nw[q] >> e) & 1u) sl[q][e] = s_free[r++];       // n <= cap and every active id holds one slot: there is one
-      if (q * 4096 + tid * 4 + e < n) top = max(top, sl[q][e]);
+      const int id = sid[q][e];
+      const uint32_t isfree = (fr[q] >> e) & 1u;
+      const int at = pre[id >= 0 ? id >> 5 : 0] + __popc(word[q][e] & ((1u << (id & 31)) - 1u));
+      out[e] = isfree ? -1 : at;
+      taken |= (f < ncopy ? isfree : 0u) << e;
+      f += isfree;
+    }
+    if (s < cap) {
+      if (taken == 0u) {
+        *reinterpret_cast<int4*>(k.out_pos + s) = make_int4(out[0], out[1], out[2], out[3]);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (!((taken >> e) & 1u)) k.out_pos[s + e] = out[e];
+      }
+      const uint32_t clear = gone[q] & ~taken;
+      if (clear) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if ((clear >> e) & 1u) k.slot_id[s + e] = -1;
+      }
     }
   }
-  for (int o = 32; o > 0; o >>= 1) top = max(top, __shfl_xor(top, o));
-  if (lane == 0) atomicMax(&s_top, top);
-  __syncthreads();
+  if (fresh)
+    for (int w = w0; w < w1; ++w) {
+      const uint32_t bits = act[w];
+      for (uint32_t nb = bits & ~held[w]; nb; nb &= nb - 1u, ++r) {
+        const int e = __ffs(nb) - 1, id = w * 32 + e, sl = s_free[r];   // n <= cap and every active id holds one slot: there is one
+        k.slot_id[sl] = id;
+        k.out_pos[sl] = pre[w] + __popc(bits & ((1u << e) - 1u));
+        k.copy_list[2 * r] = id;
+        k.copy_list[2 * r + 1] = sl;
+      }
+    }
   if (tid == 0) {
-    k.scal[0] = s_top + 1;                                 // hi
+    int hi = ncopy > 0 ? s_free[ncopy - 1] : -1;           // free slots are taken in ascending order
+#pragma unroll
+    for (int w = 0; w < NW; ++w) hi = max(hi, s_top[w]);
+    k.scal[0] = hi + 1;
     k.scal[1] = ncopy;
   }
-#pragma unroll
-  for (int q = 0; q < Q; ++q) {
-    int f = fbase[q], r = nbase[q];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int s = q * 4096 + tid * 4 + e;                // slot and list position
-      if ((fr[q] >> (4 + e)) & 1u) {
-        k.slot_of[sid[q][e]] = -1;
-        if (f >= ncopy) {
-          k.slot_id[s] = -1;
-          k.out_pos[s] = -1;
-        }
-      }
-      f += (fr[q] >> e) & 1u;
-      if (s < n) k.out_pos[sl[q][e]] = s;
-      if ((nw[q] >> e) & 1u) {
-        k.slot_of[id[q][e]] = sl[q][e];
-        k.slot_id[sl[q][e]] = id[q][e];
-        k.copy_list[2 * r] = id[q][e];
-        k.copy_list[2 * r + 1] = sl[q][e];
-        ++r;
-      }
-    }
+}
+
+// dynamic LDS of packed_sync_short_kernel; packed_sync_kernel where it is more than a compute unit has
+constexpr int kSyncLds = 156 * 1024;
+static int64_t sync_lds(const nanospec_state* st) { return 12ll * st->vp.nwords + 4ll * st->pk.cap; }
+
+hipError_t packed_configure_device() {
+  const void* fns[] = {reinterpret_cast<const void*>(packed_sync_short_kernel<1>), reinterpret_cast<const void*>(packed_sync_short_kernel<2>),
+                       reinterpret_cast<const void*>(packed_sync_short_kernel<4>)};
+  for (const void* f : fns) {
+    hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kSyncLds);
+    if (e != hipSuccess) return e;
   }
+  return hipSuccess;
 }
 
 // Copy the listed rows W[id] -> buf[slot]: the weight-gather kernel.  Two small workgroups per compute unit (a decoding step copies a
@@ -269,9 +330,11 @@ hipError_t launch_packed_reset(const nanospec_state* st, hipStream_t s) {
 
 hipError_t launch_packed_gather(const nanospec_state* st, const void* W, hipStream_t s) {
   const int cap = st->pk.cap;
-  if (cap <= 4096) packed_sync_short_kernel<1><<<1, kSyncThreads, 0, s>>>(st->vp, st->pk);
-  else if (cap <= 8192) packed_sync_short_kernel<2><<<1, kSyncThreads, 0, s>>>(st->vp, st->pk);
-  else packed_sync_kernel<<<1, kSyncThreads, 0, s>>>(st->vp, st->pk);
+  const int64_t lds = sync_lds(st);
+  if (cap > 16384 || lds > kSyncLds) packed_sync_kernel<<<1, kSyncThreads, 0, s>>>(st->vp, st->pk);
+  else if (cap <= 4096) packed_sync_short_kernel<1><<<1, kSyncThreads, lds, s>>>(st->vp, st->pk);
+  else if (cap <= 8192) packed_sync_short_kernel<2><<<1, kSyncThreads, lds, s>>>(st->vp, st->pk);
+  else packed_sync_short_kernel<4><<<1, kSyncThreads, lds, s>>>(st->vp, st->pk);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   packed_copy_kernel<<<512, 256, 0, s>>>(static_cast<const uint4*>(W), st->pk, st->d / 8);
