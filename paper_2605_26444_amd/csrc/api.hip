@@ -74,6 +74,7 @@ hipError_t ensure_device_configured() {
   if (e == hipSuccess) e = union_configure_device();
   if (e == hipSuccess) e = wide_configure_device();
   if (e == hipSuccess) e = hold_configure_device();
+  if (e == hipSuccess) e = kslice_configure_device();
   if (e == hipSuccess) e = packed_configure_device();
   if (e == hipSuccess) g_cfg_done[dev] = true;
   return e;

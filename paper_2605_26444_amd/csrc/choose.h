@@ -270,6 +270,69 @@ inline bool hold_supported(int32_t V, int32_t M, int32_t d, int32_t batch, int32
   return d == 4096 || rows <= 12288;
 }
 
+// ---- K sliced over the wavefronts (kslice.hip), 17 to 64 hidden rows -------------------------------------------------------
+
+// 8 * LB hidden rows per workgroup (hid_blocks of them), 8 * parts pieces per list, blocks of at most `rows` list rows.  over_*: 2^32 / x rounded up, 0 for 1: n / x is the high
+// word of n times it while n * x is below 2^32 (n <= 262144 rows or workgroups, at most 512 pieces, 32 hidden blocks, batch 16).
+struct SlicePlan {
+  int32_t LB, parts, hid_blocks, rows;
+  uint32_t over_hid, over_batch, over_pieces;
+};
+inline uint32_t slice_reciprocal(uint32_t x) { return x > 1 ? (uint32_t)(((1ull << 32) + x - 1) / x) : 0u; }
+
+// What a workgroup fetches for n rows, list rows (blocks of a multiple of 8, at most 64) and hidden rows together.  Blocks of fewer than 24 list rows cost as if they were larger, and hidden blocks that
+// share a piece fetch its rows each for itself, beyond the first 16 rows at half the gain (M = 64, 3000 x 3584, 24 rows + 32 hidden rows 9.35 us, 40 + 24 10.0, 48 + 16 10.4, 16 + 64 11.2; 1000 x 4096: 16 + 16
+// 6.3, 16 + 24 6.5, 8 + 32 6.6, 8 + 64 9.2; M = 40, 3000 x 4096: 24 + 24 9.7, 24 + 32 9.3 to 9.8, 16 + 40 10.6; 4 lists of 1500: 48 + 40 13.2, 48 + 24 15.0; M = 64, 8400 x 8192: 40 + 64 42.7, 2 x (40 + 32) 50.8).
+// Two workgroups per compute unit take 0.88 of two in turn, as the second one's fetches fill the first one's gaps.
+inline int64_t kslice_cost(int64_t n, int64_t LB, int64_t hb, int64_t parts, int64_t batch) {
+  const int64_t rows = (n + 8 * parts - 1) / (8 * parts), segs = rows > 64 ? (rows + 63) / 64 : 1, block = ((rows + segs - 1) / segs + 7) / 8 * 8;
+  const int64_t each = segs * (10 * (block + 8 * LB) + (block > 16 ? 6 * (hb - 1) * (block - 16) : 0) + (block < 24 ? 10 * (24 - block) : 0));
+  const int64_t turns = (8 * parts * hb * batch + 255) / 256;
+  return each * turns * (turns > 1 ? 88 : 100);
+}
+
+// The cheapest of 256 and 512 workgroups and all widths; the host knows the capacity only, lists are taken for 0.45 and 0.8 full.
+inline SlicePlan kslice_plan(int32_t M, int32_t batch, int32_t cap_rows, bool dense) {
+  const int32_t sizes[6] = {8, 6, 5, 4, 3, 2};
+  SlicePlan best = {8, 1, 1, 64, 0, 0, 0};
+  int64_t least = INT64_MAX;
+  for (int i = 0; i < 6; ++i)
+    for (int twice = 1; twice <= 2; ++twice) {
+      const int64_t LB = sizes[i], hb = (M + 8 * LB - 1) / (8 * LB);
+      const int64_t parts = 256 * twice / (8 * hb * batch) > 1 ? 256 * twice / (8 * hb * batch) : 1;
+      const int64_t cost = dense ? kslice_cost(cap_rows, LB, hb, parts, batch)
+                                 : 3 * kslice_cost((int64_t)cap_rows * 9 / 20, LB, hb, parts, batch) + 2 * kslice_cost((int64_t)cap_rows * 4 / 5, LB, hb, parts, batch);
+      if (cost < least) {
+        least = cost;
+        best.LB = (int32_t)LB;
+        best.parts = (int32_t)parts;
+        best.hid_blocks = (int32_t)hb;
+      }
+    }
+  const int32_t piece = (cap_rows + 8 * best.parts - 1) / (8 * best.parts);
+  best.rows = piece > 48 ? 64 : (piece + 7) / 8 * 8;
+  best.over_hid = slice_reciprocal(best.hid_blocks);
+  best.over_batch = slice_reciprocal(batch);
+  best.over_pieces = slice_reciprocal(8 * best.parts);
+  return best;
+}
+
+// Which products it takes, operands 16-byte aligned (its fetches go straight into LDS); time over that of split-K or the register-blocked product:
+//  * one list: d >= 1024 up to the capacity at which those fill the chip with larger blocks.  x 5120: M = 20 640 0.83, 4352 0.57 to 0.75, 8200 0.79 to 1.0, 33000 0.84 to 0.89; M = 64 1300 0.74 to
+//    0.79, 16500 0.76, 33000 0.90 to 1.03.  x 3584: M = 20 0.61 to 0.92, 33000 0.92; M = 64 0.68 to 0.97, 33000 0.88 to 1.06, 128256 1.16.  x 2048: M = 32 0.60 to 0.89 (8200, nine tenths live 1.01), 33000
+//    0.79 to 0.96; M = 64 0.65 to 0.97, 33000 0.93 to 1.12.  x 1024: M = 32 0.68 to 0.89, 33000 0.82 to 1.0, 128256 1.2; M = 64 0.75 to 0.97.  x 512: up to 2600 M = 32 0.81 to 0.87, M = 64 0.84 to 0.96, 8200 1.04;
+//  * several: while 205 of 256 workgroups can be had for equal shares and the work is little (4096: 4 of 600 out of 1000 0.63 to 0.69, of 2300 out of 5120 0.68 to 0.87; 8 of 3500, M = 20 0.83, M = 64 1.06; 12 of
+//    600 1.0 to 1.1; 16 of 600 0.71 to 0.82, of 1800 out of 2000, M = 32 0.88, M = 48 1.04; 24 1.1 to 1.7; x 1024: 3 of 2300 0.89 to 1.0, 16 of 600, M = 32 0.77);
+//  * no dense heads (128k x 4096 1.01 to 1.15, 32000 x 4096 1.0 to 1.1, x 8192 0.92 to 0.99, 128k x 8192 1.02 to 1.2, x 1024 1.2 to 1.3).
+inline bool kslice_supported(int32_t V, int32_t M, int32_t d, int32_t batch, int32_t cap_rows, bool dense, bool aligned) {
+  if (M <= 16 || M > 64 || d < 512 || dense || !aligned || !wide_reaches(V, M, d)) return false;
+  const int64_t rows = (int64_t)cap_rows * batch;
+  if (d < 1024) return rows <= 3072;
+  if (batch > 1) return batch <= 16 && 256 / (8 * batch) * (8 * batch) >= 205 && rows * M <= (d < 2048 ? 700000 : batch <= 8 ? 1400000 : 1000000);
+  if (M <= 32) return rows <= (d >= 4096 ? 65536 : d >= 2048 ? 40960 : 20480);
+  return rows <= (M <= 48 && d >= 3072 ? 40960 : d >= 2048 ? 24576 : 20480);
+}
+
 // ---- stream initialisation (vocab.hip) -------------------------------------------------------------------------------------
 
 constexpr int32_t kInitFewSeqs = 16;           // more fill the chip with larger id ranges

@@ -118,6 +118,11 @@ hipError_t hold_configure_device();
 hipError_t launch_head_hold(const void* W, const void* H, const int32_t* ids, const int32_t* n_dev, int32_t n_fixed, int32_t V, int32_t batch, int32_t M,
                             int32_t d, int64_t ld, int64_t ids_stride, float* logits, const int32_t* opos, hipStream_t s);
 
+// kslice.hip: 17 to 64 hidden rows, K sliced over the wavefronts
+hipError_t kslice_configure_device();
+hipError_t launch_head_kslice(const void* W, const void* H, const int32_t* ids, const int32_t* n_dev, int32_t n_fixed, int32_t cap_rows, int32_t V, int32_t batch, int32_t M,
+                              int32_t d, int64_t ld, int64_t ids_stride, float* logits, const int32_t* opos, hipStream_t s);
+
 // union.hip
 hipError_t union_configure_device();
 hipError_t launch_union_reset(const nanospec_state* st, hipStream_t s);

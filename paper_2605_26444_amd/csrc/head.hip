@@ -800,9 +800,12 @@ hipError_t launch_head(const void* W, const void* H, const int32_t* ids, const i
                        float* logits, float* partial, int64_t partial_bytes, const int32_t* opos, hipStream_t s) {
   const uint16_t* Wp = static_cast<const uint16_t*>(W);
   const uint16_t* Hp = static_cast<const uint16_t*>(H);
-  // the hidden rows in registers, the register-blocked product: each wherever it is the fastest one
+  // the hidden rows in registers, K sliced over the wavefronts, the register-blocked product: each wherever it is the fastest one
   if (hold_supported(V, M, d, batch, cap_rows, n_dev == nullptr))
     return launch_head_hold(W, H, ids, n_dev, n_fixed, V, batch, M, d, ld_logits, ids_stride, logits, opos, s);
+  const bool aligned = ((reinterpret_cast<uintptr_t>(W) | reinterpret_cast<uintptr_t>(H)) & 15) == 0;   // of the fetches into LDS
+  if (kslice_supported(V, M, d, batch, cap_rows, n_dev == nullptr, aligned))
+    return launch_head_kslice(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld_logits, ids_stride, logits, opos, s);
   if (wide_supported(V, M, d, batch, cap_rows, n_dev == nullptr))
     return launch_head_wide(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld_logits, ids_stride, logits, opos, s);
   if (M <= 64)

@@ -33,6 +33,11 @@ void c_hold_plan(int d, int batch, int dense, int M, int* o) {
   const HoldPlan h = hold_plan(d, batch, dense != 0);
   o[0] = h.NW; o[1] = h.parts; o[2] = h.seg; o[3] = (int)hold_lds(h, M);
 }
+int c_kslice_supported(int V, int M, int d, int batch, int cap, int dense, int aligned) { return kslice_supported(V, M, d, batch, cap, dense != 0, aligned != 0); }
+void c_kslice_plan(int M, int batch, int cap, int dense, int* o) {
+  const SlicePlan p = kslice_plan(M, batch, cap, dense != 0);
+  o[0] = p.LB; o[1] = p.parts; o[2] = p.hid_blocks; o[3] = p.rows;
+}
 int c_union_split(int M, int d, int batch, int cap) { return union_split(M, d, batch, cap); }
 int c_tile64_fast(int M, int d) { return tile64_fast(M, d); }
 }
@@ -40,6 +45,7 @@ int c_tile64_fast(int M, int d) { return tile64_fast(M, d); }
 
 Quad = namedtuple("Quad", "MT KS NRG RT loop")
 Block = namedtuple("Block", "WR WH FR FH BK D")
+Slice = namedtuple("Slice", "LB parts hid_blocks rows")
 Hold = namedtuple("Hold", "NW parts seg lds")
 
 
@@ -71,6 +77,16 @@ def hold_plan(d, batch, M, dense=False):
     o = (C.c_int * 4)()
     _lib.c_hold_plan(d, batch, int(dense), M, o)
     return Hold(*o)
+
+
+def kslice_supported(V, M, d, batch, cap, dense=False, aligned=True):
+    return bool(_lib.c_kslice_supported(V, M, d, batch, cap, int(dense), int(aligned)))
+
+
+def kslice_plan(M, batch, cap, dense=False):
+    o = (C.c_int * 4)()
+    _lib.c_kslice_plan(M, batch, cap, int(dense), o)
+    return Slice(*o)
 
 
 def union_split(M, d, batch, cap):
