@@ -71,7 +71,6 @@ hipError_t ensure_device_configured() {
   e = head_configure_device();
   if (e == hipSuccess) e = vocab_configure_device();
   if (e == hipSuccess) e = calib_configure_device();
-  if (e == hipSuccess) e = union_configure_device();
   if (e == hipSuccess) e = wide_configure_device();
   if (e == hipSuccess) e = hold_configure_device();
   if (e == hipSuccess) e = kslice_configure_device();
@@ -264,7 +263,7 @@ int64_t nanospec_union_bytes(const nanospec_state* st, int32_t shared_cap) {
   if (shared_cap == 0) shared_cap = (int32_t)cap;
   if (shared_cap < 64 || shared_cap % 64 != 0 || shared_cap > cap) return -1;
   const int64_t groups = (B * st->m_cap + 63) / 64;
-  return 2 * round_up(nw * 4, 256) + round_up((int64_t)shared_cap * 4, 256) + round_up(groups * 4, 256) +
+  return 2 * round_up(nw * 4, 256) /* twice the bitmap: the size is part of the interface */ + round_up((int64_t)shared_cap * 4, 256) + round_up(groups * 4, 256) +
          round_up(B * shared_cap * 4, 256) + 2 * round_up(B * cap * 4, 256) + round_up(B * 4, 256);
 }
 
@@ -288,7 +287,6 @@ nanospec_status nanospec_union_enable(nanospec_state* st, int32_t min_share, int
   u.shared_cap = shared_cap;
   u.min_share = min_share;
   u.shared_bits = reinterpret_cast<uint32_t*>(take(nw * 4));
-  u.shared_cnt = reinterpret_cast<int32_t*>(take(nw * 4));
   u.shared_ids = reinterpret_cast<int32_t*>(take((int64_t)shared_cap * 4));
   u.shared_n = reinterpret_cast<int32_t*>(take((int64_t)st->un_groups * 4));
   u.shared_pos = reinterpret_cast<int32_t*>(take(B * shared_cap * 4));

@@ -46,7 +46,6 @@ struct PackedPtrs {
 // Batch-union head (several sequences): rows shared by many sequences, and what is left per sequence.
 struct UnionPtrs {
   uint32_t* shared_bits;  // [nwords] bit = id held by at least min_share sequences
-  int32_t* shared_cnt;    // [nwords] set bits per word
   int32_t* shared_ids;    // [shared_cap] the lowest shared_cap such ids, ascending
   int32_t* shared_n;      // [groups] their number, repeated once per group of 64 hidden rows
   int32_t* shared_pos;    // [batch][shared_cap] column of shared row r in the sequence's logits, -1 if the sequence lacks it
@@ -124,7 +123,6 @@ hipError_t launch_head_kslice(const void* W, const void* H, const int32_t* ids, 
                               int32_t d, int64_t ld, int64_t ids_stride, float* logits, const int32_t* opos, hipStream_t s);
 
 // union.hip
-hipError_t union_configure_device();
 hipError_t launch_union_reset(const nanospec_state* st, hipStream_t s);
 hipError_t launch_union_build(const nanospec_state* st, hipStream_t s);
 
