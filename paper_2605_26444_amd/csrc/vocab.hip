@@ -52,6 +52,14 @@ __device__ __forceinline__ int wave_incl_scan(int x, int /*lane*/) {
   return x;
 }
 
+// sum over each row of 16 lanes, in all of them (quad_perm neighbours, row_half_mirror, row_mirror)
+__device__ __forceinline__ int row_sum(int x) {
+  x = dpp_add_int<0xB1, 0xf>(x);
+  x = dpp_add_int<0x4E, 0xf>(x);
+  x = dpp_add_int<0x141, 0xf>(x);
+  return dpp_add_int<0x140, 0xf>(x);
+}
+
 // Ascending compaction of a bitmap held in LDS: popcount per thread, workgroup exclusive scan,
 // emission in id order.  word4(i) yields bitmap words i..i+3 (i a multiple of 4); out[0..total) receives
 // the ids (at most cap are stored).  Every thread of the workgroup must call it, after a barrier that
@@ -83,13 +91,10 @@ __device__ __forceinline__ int compact_bitmap(Word4Fn word4, int nwords, int32_t
   const int incl = wave_incl_scan(mine, lane);
   if (lane == 63) sc[wave] = incl;
   __syncthreads();
-  int off = incl - mine, total = 0;
-#pragma unroll
-  for (int w = 0; w < kVocabThreads / 64; w += 4) {
-    const int4 t = *reinterpret_cast<const int4*>(sc + w);
-    off += (w < wave ? t.x : 0) + (w + 1 < wave ? t.y : 0) + (w + 2 < wave ? t.z : 0) + (w + 3 < wave ? t.w : 0);
-    total += t.x + t.y + t.z + t.w;
-  }
+  // One total to each lane of a row of 16, summed there: against every lane adding up all sixteen, appending 80 candidates to one sequence (V = 128256,
+  // ~2700 live ids) 6.06 -> 5.69 us, 20 new ids to each of 64 sequences 5.95 -> 5.6; below 512 live ids of a small vocabulary no change.
+  const int totals = sc[lane & 15];
+  const int off = incl - mine + row_sum((lane & 15) < wave ? totals : 0), total = row_sum(totals);
   // Emission costs one trip round a short loop per set bit and wavefront-wide per word (the lane with the
   // most bits sets the pace), on a workgroup whose sixteen wavefronts share four SIMDs: it is bound by
   // instruction issue, so the loop is kept to the bare minimum -- two words at a time as one 64-bit
