@@ -318,16 +318,7 @@ __device__ __forceinline__ int inc_patch(int32_t* ids, int cap, int n_old, int (
     // them with readlane instead of waiting for LDS once per change
     const int chg = sC[lane & (2 * kIncMax - 1)], chgo = sO[lane & (2 * kIncMax - 1)];
     const int passes = n_old / kIncPass + 1;
-    for (int pass = 0; pass < passes; ++pass) {
-      int4 qn = make_int4(INT_MAX, INT_MAX, INT_MAX, INT_MAX);
-      int qnn = INT_MAX;
-      if (pass + 1 < passes) {                 // the next pass is read before this one is written
-        const int j1 = (pass + 1) * kIncPass + 4 * tid;
-        if (j1 < cap) qn = *reinterpret_cast<const int4*>(ids + j1);
-        if (j1 + 4 < cap) qnn = ids[j1 + 4];
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-      }
+    auto move = [&](int pass, const int (&xs)[5]) {
       const int j0 = pass * kIncPass + 4 * tid;
       const bool head = j0 == 0;
       if ((xs[0] != INT_MAX && xs[4] > lowest) || head) {   // entries below every change stay where they are; past the end there are none
@@ -376,7 +367,42 @@ __device__ __forceinline__ int inc_patch(int32_t* ids, int cap, int n_old, int (
         for (int i = 0; i < 4; ++i)
           if (xs[i] != INT_MAX && !dead[i] && mv[i] != 0) ids[j0 + i + mv[i]] = xs[i];
       }
-      inc_mask(pass + 1, tid, n_old, qn, qnn, xs);
+    };
+    // A later pass is read before an earlier one is written: entries move by at most kIncMax places.  Four passes are asked for together, one round trip to L2 and one
+    // barrier for them: an update of 3 ids on 31000 4.87 -> 4.45 us, 90000 14.2 -> 11.7; 12 ids on 29700 10.0 -> 8.8.  Passes past the end are skipped (read and moved all the same: 7000 ids 3.46 -> 3.99).
+    constexpr int G = 4;
+    int xg[G][5];
+    auto ahead = [&](int pass) {
+      int4 q[G];
+      int nx[G];
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        const int j = (pass + g) * kIncPass + 4 * tid;
+        q[g] = make_int4(INT_MAX, INT_MAX, INT_MAX, INT_MAX);
+        nx[g] = INT_MAX;
+        if (pass + g < passes) {
+          if (j < cap) q[g] = *reinterpret_cast<const int4*>(ids + j);
+          if (j + 4 < cap) nx[g] = ids[j + 4];
+        }
+      }
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
+#pragma unroll
+      for (int g = 0; g < G; ++g)
+        if (pass + g < passes) inc_mask(pass + g, tid, n_old, q[g], nx[g], xg[g]);
+    };
+    if (passes > 1) ahead(1);
+    move(0, xs);
+    for (int pass = 1; pass < passes; pass += G) {
+      int xc[G][5];
+#pragma unroll
+      for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int i = 0; i < 5; ++i) xc[g][i] = xg[g][i];
+      if (pass + G < passes) ahead(pass + G);
+#pragma unroll
+      for (int g = 0; g < G; ++g)
+        if (pass + g < passes) move(pass + g, xc[g]);
     }
   }
   return nA - nR;

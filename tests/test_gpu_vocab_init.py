@@ -117,3 +117,39 @@ def test_init_recorded_in_a_graph():
                 g.replay()
                 _check(st, [o], (policy, length, replay))
             st.close()
+
+
+@pytest.mark.parametrize("policy", [B.POLICY_WINDOW, B.POLICY_FIFO])
+@pytest.mark.parametrize("n", [4094, 4096, 8191, 16384, 20478, 20480, 20490, 36863, 40000, 53248])
+def test_patched_lists_of_several_passes(policy, n):
+    """Appends that patch a list of n ids in place, 4096 entries to a pass and four passes read ahead of the one that is written: every step lets as many ids go as enter, at
+    the list's ends, around the edges of passes and at random, alternately above and below each other so that runs of entries move both ways."""
+    V, rng = 128256, np.random.default_rng(n)
+    st = B.State(V, 64, 1, n, 16, 1, 1)
+    B.nanospec_set_stream_policy(st.h, policy)
+    orc = (oracle.Vocab if policy == B.POLICY_WINDOW else oracle.FifoVocab)(V, n)
+    ids = np.sort(rng.choice(V, n, replace=False)).astype(np.int32)
+    out = np.setdiff1d(np.arange(V, dtype=np.int32), ids)
+    edges = [j for e in range(0, n + 1, 4096) for j in (e - 1, e, e + 1, e + 15) if 0 <= j < n]
+    leave = list(dict.fromkeys([0, n - 1] + edges))
+    leave = np.array(leave[:48] + [j for j in rng.permutation(n)[:80] if j not in set(leave)])
+    ctx = np.concatenate([ids[leave], ids[np.setdiff1d(np.arange(n), leave)]])
+    T = np.array([ids[0], out[-1]], np.int32)                  # one of them is in the window when it leaves
+    f, o = csr([ctx])
+    tf, to = csr([T])
+    B.nanospec_vocab_init(st.h, dev_ids(f), o, dev_ids(tf), to)
+    orc.init(ctx, T)
+    for step, a in enumerate((16, 1, 7, 16, 2, 16, 15)):
+        new = out[rng.integers(0, len(out), a)]
+        if step == 1:
+            new = out[:1]
+        if step == 3:
+            new = np.concatenate([out[-8:], out[1:9]])
+        if step == 5:                                          # ids right beside the edges of passes
+            new = out[np.clip(np.searchsorted(out, ids[np.array(edges)[rng.integers(0, len(edges), a)]]), 0, len(out) - 1)]
+        f, o = csr([new])
+        B.nanospec_vocab_update(st.h, dev_ids(f), o)
+        orc.update(new)
+        _check(st, [orc], (policy, n, step))
+    assert B.nanospec_last_device_error(st.h) == 0
+    st.close()
