@@ -13,6 +13,42 @@ constexpr int kTopkThreads = 1024;    // single-pass top-k workgroup
 constexpr int kMaxK = 64;
 constexpr int kCandMax = 256;          // top-k fast path: most candidates ranked directly
 
+// Sums over lanes of integers by DPP (row of 16 lanes; a lane without a source adds 0): an instruction per step where a shuffle through LDS is several.
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ int dpp_add_int(int x) {
+  return x + __builtin_amdgcn_update_dpp(0, x, CTRL, ROW_MASK, 0xf, false);
+}
+
+// inclusive prefix sum over the 64 lanes: Hillis-Steele inside each row of 16 (row_shr 1, 2, 4, 8), then the row totals
+// carried across (row_bcast:15 into rows 1 and 3, row_bcast:31 into rows 2 and 3)
+__device__ __forceinline__ int wave_incl_scan(int x) {
+  x = dpp_add_int<0x111, 0xf>(x);
+  x = dpp_add_int<0x112, 0xf>(x);
+  x = dpp_add_int<0x114, 0xf>(x);
+  x = dpp_add_int<0x118, 0xf>(x);
+  x = dpp_add_int<0x142, 0xa>(x);
+  return dpp_add_int<0x143, 0xc>(x);
+}
+
+// sum over each row of 16 lanes, in all of them (quad_perm neighbours, row_half_mirror, row_mirror)
+__device__ __forceinline__ int row_sum(int x) {
+  x = dpp_add_int<0xB1, 0xf>(x);
+  x = dpp_add_int<0x4E, 0xf>(x);
+  x = dpp_add_int<0x141, 0xf>(x);
+  return dpp_add_int<0x140, 0xf>(x);
+}
+
+// The clobber of M0 is what it says: the compiler keeps nothing there across statements (it writes M0 in front of each use of its
+// own), and warns at every inlined copy only because it reserves the register.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+__device__ __forceinline__ void lds_fetch16(uint32_t lds, const void* base, uint32_t off) {
+  // 16 bytes per lane from base + off straight into LDS at lds + 16 * lane; no destination register.  A load into LDS may read M0
+  // one wait state after a scalar write of it, and nothing puts that state between two instructions of one statement: the s_nop.
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory", "m0");
+}
+#pragma clang diagnostic pop
+
 // Per-sequence offsets travel by value in the kernel argument block (no H2D copy, graph-safe).
 struct Offsets {
   int32_t v[NANOSPEC_MAX_BATCH + 1];

@@ -23,16 +23,7 @@ constexpr int kSliceWaves = 4;
 // slots of a wavefront's ring, one step (8 rows of 128 bytes to the KB) of L KB to a slot
 constexpr int slice_ring(int L) { return L <= 4 ? 4 : L <= 6 ? 3 : 2; }
 
-// The clobber of M0 is what it says: the compiler keeps nothing there across statements (it writes M0 in front of each use of its
-// own), and warns at every inlined copy only because it reserves the register.
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-__device__ __forceinline__ void slice_fetch16(uint32_t lds, const void* base, uint32_t off) {
-  // 16 bytes per lane from base + off straight into LDS at lds + 16 * lane.  A load into LDS may read M0 one wait state after a scalar
-  // write of it, and nothing puts that state between two instructions of one statement: the s_nop.
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory", "m0");
-}
-#pragma clang diagnostic pop
+// the wait behind lds_fetch16 (global_load_lds, common.h)
 template <int N>
 __device__ __forceinline__ void slice_wait() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
@@ -79,15 +70,15 @@ __device__ __forceinline__ void slice_block(char* smem, const uint16_t* __restri
     if (k0 + 64 <= d) {
       const char *wb = reinterpret_cast<const char*>(W) + (int64_t)k0 * 2, *hb = reinterpret_cast<const char*>(H) + (int64_t)k0 * 2;
 #pragma unroll
-      for (int q = 0; q < LB; ++q) slice_fetch16(l + (LA + q) * 1024, hb, boff[q]);
+      for (int q = 0; q < LB; ++q) lds_fetch16(l + (LA + q) * 1024, hb, boff[q]);
 #pragma unroll
-      for (int q = 0; q < LA; ++q) slice_fetch16(l + q * 1024, wb, aoff[q]);
+      for (int q = 0; q < LA; ++q) lds_fetch16(l + q * 1024, wb, aoff[q]);
     } else {
       const uint32_t co = k0 + pc * 8 < d ? k0 * 2 : (uint32_t)-pc * 16;   // offsets hold pc * 16
 #pragma unroll
-      for (int q = 0; q < LB; ++q) slice_fetch16(l + (LA + q) * 1024, H, boff[q] + co);
+      for (int q = 0; q < LB; ++q) lds_fetch16(l + (LA + q) * 1024, H, boff[q] + co);
 #pragma unroll
-      for (int q = 0; q < LA; ++q) slice_fetch16(l + q * 1024, W, aoff[q] + co);
+      for (int q = 0; q < LA; ++q) lds_fetch16(l + q * 1024, W, aoff[q] + co);
     }
   };
 #pragma unroll

@@ -106,29 +106,6 @@ __global__ __launch_bounds__(kSyncThreads) void packed_sync_kernel(VocabPtrs p, 
 // ascending; the thread that holds a slot clears its tables only if it stays free.  No table by id is kept.  With the copy's launch behind it, against the look-ups: 3776 slots
 // 7.3 -> 4.9 us, 1280 6.0 -> 4.8, 8000 10.2 -> 6.2, 15936 (then a walk in 1024s) 18.3 -> 10.0; with scans over __shfl and one LDS read per total 7.35 us at 3776.
 // Sixteen wavefronts share four SIMDs, so an instruction that all execute costs 7 ns: scans are DPP chains, two counts of up to 16384 to a register.
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ int sync_dpp_add(int x) {
-  return x + __builtin_amdgcn_update_dpp(0, x, CTRL, ROW_MASK, 0xf, false);            // lanes without a source add 0
-}
-
-// inclusive prefix sum over the 64 lanes (row_shr 1, 2, 4, 8 inside rows of 16, row totals carried by row_bcast 15 and 31)
-__device__ __forceinline__ int sync_scan(int x) {
-  x = sync_dpp_add<0x111, 0xf>(x);
-  x = sync_dpp_add<0x112, 0xf>(x);
-  x = sync_dpp_add<0x114, 0xf>(x);
-  x = sync_dpp_add<0x118, 0xf>(x);
-  x = sync_dpp_add<0x142, 0xa>(x);
-  return sync_dpp_add<0x143, 0xc>(x);
-}
-
-// sum over each row of 16 lanes, in all of them (quad_perm neighbours, row_half_mirror, row_mirror)
-__device__ __forceinline__ int sync_row_sum(int x) {
-  x = sync_dpp_add<0xB1, 0xf>(x);
-  x = sync_dpp_add<0x4E, 0xf>(x);
-  x = sync_dpp_add<0x141, 0xf>(x);
-  return sync_dpp_add<0x140, 0xf>(x);
-}
-
 template <int Q>
 __global__ __launch_bounds__(kSyncThreads) void packed_sync_short_kernel(VocabPtrs p, PackedPtrs k) {
   constexpr int NW = kSyncThreads / 64, S = (Q + 1) / 2 + (Q > 1 ? 1 : 0);   // scans: (bits, free of q = 0), then two q each
@@ -177,9 +154,9 @@ __global__ __launch_bounds__(kSyncThreads) void packed_sync_short_kernel(VocabPt
     if (any) top = __builtin_amdgcn_readlane(mine, 63 - __clzll((long long)any));
   }
   int incl[S];
-  incl[0] = sync_scan(pop << 16 | __popc(fr[0]));
+  incl[0] = wave_incl_scan(pop << 16 | __popc(fr[0]));
 #pragma unroll
-  for (int i = 1; i < S; ++i) incl[i] = sync_scan((2 * i < Q ? __popc(fr[2 * i < Q ? 2 * i : 0]) << 16 : 0) | __popc(fr[2 * i - 1]));
+  for (int i = 1; i < S; ++i) incl[i] = wave_incl_scan((2 * i < Q ? __popc(fr[2 * i < Q ? 2 * i : 0]) << 16 : 0) | __popc(fr[2 * i - 1]));
   if (lane == 63) {
 #pragma unroll
     for (int i = 0; i < S; ++i) s_tot[i][wave] = incl[i];
@@ -190,8 +167,8 @@ __global__ __launch_bounds__(kSyncThreads) void packed_sync_short_kernel(VocabPt
 #pragma unroll
   for (int i = 0; i < S; ++i) {
     const int t = s_tot[i][lane & 15];
-    before[i] = sync_row_sum((lane & 15) < wave ? t : 0);
-    total[i] = sync_row_sum(t);
+    before[i] = row_sum((lane & 15) < wave ? t : 0);
+    total[i] = row_sum(t);
   }
   int fresh = 0, rank = (before[0] >> 16) + (incl[0] >> 16) - pop;
   for (int w = w0; w < w1; w += 4) {
@@ -205,7 +182,7 @@ __global__ __launch_bounds__(kSyncThreads) void packed_sync_short_kernel(VocabPt
     *reinterpret_cast<int4*>(pre + w) = r;
     fresh += __popc(v.x & ~h.x) + __popc(v.y & ~h.y) + __popc(v.z & ~h.z) + __popc(v.w & ~h.w);
   }
-  const int ninc = sync_scan(fresh);
+  const int ninc = wave_incl_scan(fresh);
   if (lane == 63) s_new[wave] = ninc;
   int fbase[Q], ftot = 0;
 #pragma unroll
@@ -219,8 +196,8 @@ __global__ __launch_bounds__(kSyncThreads) void packed_sync_short_kernel(VocabPt
       if ((fr[q] >> e) & 1u) s_free[f++] = q * 4096 + tid * 4 + e;
   }
   __syncthreads();
-  const int tn = s_new[lane & 15], ncopy = sync_row_sum(tn);
-  int r = sync_row_sum((lane & 15) < wave ? tn : 0) + ninc - fresh;
+  const int tn = s_new[lane & 15], ncopy = row_sum(tn);
+  int r = row_sum((lane & 15) < wave ? tn : 0) + ninc - fresh;
 #pragma unroll
   for (int q = 0; q < Q; ++q) {
     const int s = q * 4096 + tid * 4;

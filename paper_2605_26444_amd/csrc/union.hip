@@ -36,29 +36,6 @@ __global__ __launch_bounds__(1024) void union_count_kernel(VocabPtrs p, UnionPtr
   if (lane == 0) u.shared_bits[w] = pop;
 }
 
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ int union_dpp_add(int x) {
-  return x + __builtin_amdgcn_update_dpp(0, x, CTRL, ROW_MASK, 0xf, false);            // lanes without a source add 0
-}
-
-// inclusive prefix sum over the 64 lanes (row_shr 1, 2, 4, 8 inside rows of 16, row totals carried by row_bcast 15 and 31)
-__device__ __forceinline__ int union_scan(int x) {
-  x = union_dpp_add<0x111, 0xf>(x);
-  x = union_dpp_add<0x112, 0xf>(x);
-  x = union_dpp_add<0x114, 0xf>(x);
-  x = union_dpp_add<0x118, 0xf>(x);
-  x = union_dpp_add<0x142, 0xa>(x);
-  return union_dpp_add<0x143, 0xc>(x);
-}
-
-// what lies before this wavefront of sixteen totals in LDS, and their sum (rows of 16 lanes: quad_perm neighbours, row_half_mirror, row_mirror)
-__device__ __forceinline__ int union_row_sum(int x) {
-  x = union_dpp_add<0xB1, 0xf>(x);
-  x = union_dpp_add<0x4E, 0xf>(x);
-  x = union_dpp_add<0x141, 0xf>(x);
-  return union_dpp_add<0x140, 0xf>(x);
-}
-
 // One workgroup per sequence, N consecutive bitmap words per thread: everything follows from the bitmaps, fetched together in one round trip.  A shared id's rank is the
 // count of shared bits before it (workgroup 0 writes the list), its column in this sequence the count of active bits before it; an active bit that is not
 // shared -- or whose rank finds no room on the list -- goes to the sequence's own list, at the count of such bits before it.  Three DPP scans, two barriers.  Against the walk over the
@@ -95,16 +72,16 @@ __global__ __launch_bounds__(kListThreads) void union_lists_kernel(VocabPtrs p, 
     ns += __popc(sh[i]);
     na += __popc(ac[i]);
   }
-  const int si = union_scan(ns), ai = union_scan(na);
+  const int si = wave_incl_scan(ns), ai = wave_incl_scan(na);
   if (lane == 63) {
     s_shared[wave] = si;
     s_active[wave] = ai;
   }
   __syncthreads();
   const int ts = s_shared[lane & 15], ta = s_active[lane & 15];
-  int r = union_row_sum((lane & 15) < wave ? ts : 0) + si - ns;          // rank of this thread's first shared bit
-  int pos = union_row_sum((lane & 15) < wave ? ta : 0) + ai - na;        // column of its first active bit
-  const int all = union_row_sum(ts), listed = all < u.shared_cap ? all : u.shared_cap;
+  int r = row_sum((lane & 15) < wave ? ts : 0) + si - ns;          // rank of this thread's first shared bit
+  int pos = row_sum((lane & 15) < wave ? ta : 0) + ai - na;        // column of its first active bit
+  const int all = row_sum(ts), listed = all < u.shared_cap ? all : u.shared_cap;
   if (r + ns > u.shared_cap) {                                           // bits without room on the list are not shared
     int room = u.shared_cap - r;
 #pragma unroll
@@ -117,11 +94,11 @@ __global__ __launch_bounds__(kListThreads) void union_lists_kernel(VocabPtrs p, 
   int nr = 0;
 #pragma unroll
   for (int i = 0; i < N; ++i) nr += __popc(ac[i] & ~sh[i]);
-  const int ri = union_scan(nr);
+  const int ri = wave_incl_scan(nr);
   if (lane == 63) s_rest[wave] = ri;
   __syncthreads();
-  const int tr = s_rest[lane & 15], nrest = union_row_sum(tr);
-  int q = union_row_sum((lane & 15) < wave ? tr : 0) + ri - nr;
+  const int tr = s_rest[lane & 15], nrest = row_sum(tr);
+  int q = row_sum((lane & 15) < wave ? tr : 0) + ri - nr;
   int32_t* mypos = u.shared_pos + (size_t)b * u.shared_cap;
   int32_t* rid = u.rest_ids + (size_t)b * p.cap;
   int32_t* rpos = u.rest_pos + (size_t)b * p.cap;

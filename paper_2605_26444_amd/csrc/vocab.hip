@@ -35,31 +35,6 @@ __global__ __launch_bounds__(256) void vocab_clear_kernel(VocabPtrs p, int batch
   }
 }
 
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ int dpp_add_int(int x) {
-  return x + __builtin_amdgcn_update_dpp(0, x, CTRL, ROW_MASK, 0xf, false);   // lanes without a source add 0
-}
-
-// inclusive prefix sum over the 64 lanes: Hillis-Steele inside each row of 16 (row_shr 1/2/4/8), then the
-// row totals carried across (row_bcast:15 into rows 1 and 3, row_bcast:31 into rows 2 and 3)
-__device__ __forceinline__ int wave_incl_scan(int x, int /*lane*/) {
-  x = dpp_add_int<0x111, 0xf>(x);
-  x = dpp_add_int<0x112, 0xf>(x);
-  x = dpp_add_int<0x114, 0xf>(x);
-  x = dpp_add_int<0x118, 0xf>(x);
-  x = dpp_add_int<0x142, 0xa>(x);
-  x = dpp_add_int<0x143, 0xc>(x);
-  return x;
-}
-
-// sum over each row of 16 lanes, in all of them (quad_perm neighbours, row_half_mirror, row_mirror)
-__device__ __forceinline__ int row_sum(int x) {
-  x = dpp_add_int<0xB1, 0xf>(x);
-  x = dpp_add_int<0x4E, 0xf>(x);
-  x = dpp_add_int<0x141, 0xf>(x);
-  return dpp_add_int<0x140, 0xf>(x);
-}
-
 // Ascending compaction of a bitmap held in LDS: popcount per thread, workgroup exclusive scan,
 // emission in id order.  word4(i) yields bitmap words i..i+3 (i a multiple of 4); out[0..total) receives
 // the ids (at most cap are stored).  Every thread of the workgroup must call it, after a barrier that
@@ -88,7 +63,7 @@ __device__ __forceinline__ int compact_bitmap(Word4Fn word4, int nwords, int32_t
     const uint4 x = word4(i);
     mine += __popc(x.x) + __popc(x.y) + __popc(x.z) + __popc(x.w);
   }
-  const int incl = wave_incl_scan(mine, lane);
+  const int incl = wave_incl_scan(mine);
   if (lane == 63) sc[wave] = incl;
   __syncthreads();
   // One total to each lane of a row of 16, summed there: against every lane adding up all sixteen, appending 80 candidates to one sequence (V = 128256,
@@ -690,7 +665,7 @@ __global__ __launch_bounds__(kEmitThreads) void vocab_emit_kernel(VocabPtrs p) {
     below += __popc(x.x | y.x) + __popc(x.y | y.y) + __popc(x.z | y.z) + __popc(x.w | y.w);
   }
   const int mine = __popcll(bits);
-  const int incl = wave_incl_scan(mine, lane), binc = wave_incl_scan(below, lane);
+  const int incl = wave_incl_scan(mine), binc = wave_incl_scan(below);
   if (lane == 63) {
     sc[wave] = incl;
     sc[kEmitThreads / 64 + wave] = binc;

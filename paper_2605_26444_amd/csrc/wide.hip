@@ -281,16 +281,7 @@ static hipError_t run_wide(const uint16_t* W, const uint16_t* H, const int32_t* 
 
 constexpr int kGemmStage = 4 * 128 * 128;        // bytes of one stage: A0, A1, B0, B1 (128 rows x 128 bytes each)
 
-// The clobber of M0 is what it says: the compiler keeps nothing there across statements (it writes M0 in front of each use of its
-// own), and warns at every inlined copy only because it reserves the register.
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-__device__ __forceinline__ void lds_fetch16(uint32_t lds, const void* base, uint32_t off) {
-  // 16 bytes per lane from base + off straight into LDS at lds + 16 * lane; no destination register.  A load into LDS may read M0
-  // one wait state after a scalar write of it, and nothing puts that state between two instructions of one statement: the s_nop.
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory", "m0");
-}
-#pragma clang diagnostic pop
+// operands by lds_fetch16 (global_load_lds, common.h) and counted waits
 #define NS_WAIT_VM(n) asm volatile("s_waitcnt vmcnt(" #n ")" ::: "memory")
 #define NS_BARRIER()                        \
   do {                                      \
