@@ -96,3 +96,45 @@ def test_infinities_at_a_row_s_start_stay_infinities():
     st, ids, logits = _lists(V, 1, M, d, 5000, [5000], W, H)
     assert torch.all(torch.isposinf(logits[0, :, :5000]))
     st.close()
+
+
+def off_alignment(t):
+    """the same values 8 bytes past a 16-byte boundary"""
+    buf = torch.zeros(t.numel() + 4, dtype=t.dtype, device="cuda")
+    buf[4:].copy_(t.reshape(-1))
+    out = buf[4:].view(t.shape)
+    assert out.data_ptr() % 16 == 8
+    return out
+
+
+@pytest.mark.parametrize("batch,M,d,window,sizes", [(1, 16, 8192, 9000, [1500]), (1, 8, 3592, 9000, [8195]), (8, 6, 4096, 2300, [2300, 9])])
+def test_operands_off_alignment(batch, M, d, window, sizes):
+    V = 20000
+    W, H = off_alignment(_normal(9, V, d)), off_alignment(_normal(10, batch, M, d))
+    st, ids, logits = _lists(V, batch, M, d, window, sizes, W, H)
+    for b in range(batch):
+        n = len(ids[b])
+        _check(logits[b, :, :n], W[torch.from_numpy(ids[b]).long().cuda()], H[b], b)
+        assert torch.all(logits[b, :, n:] == 7.0), b
+    st.close()
+
+
+def check_nan_rows(st, ids, logits, W, H, nan_id, nan_row):
+    """a NaN in a listed row or a hidden row stays in that column or row: all other logits are as without it"""
+    n = len(ids)
+    got, bad = logits[0, :, :n], torch.from_numpy(ids == nan_id).cuda()
+    assert bad.sum() == 1 and torch.all(torch.isnan(got[:, bad])) and torch.all(torch.isnan(got[nan_row]))
+    rows = [m for m in range(got.shape[0]) if m != nan_row]
+    _check(got[rows][:, ~bad], W[torch.from_numpy(ids).long().cuda()][~bad], H[0, rows], "beside NaN")
+    st.close()
+
+
+@pytest.mark.parametrize("M,d", [(8, 3592), (13, 4096)])
+def test_nan_stays_in_its_row(M, d):
+    V, n = 20000, 4999
+    W, H = _normal(11, V, d), _normal(12, 1, M, d)
+    nan_id = int(np.sort(np.random.default_rng(1000 + M).permutation(V)[:n])[n - 2])   # beside the copies of the last row
+    W[nan_id, d - 1] = float("nan")
+    H[0, M - 1, 0] = float("nan")                                                        # the row that stands in for those past M
+    st, ids, logits = _lists(V, 1, M, d, 6000, [n], W, H)
+    check_nan_rows(st, ids[0], logits, W, H, nan_id, M - 1)

@@ -10,7 +10,7 @@ import choose
 from paper_2605_26444_amd import binding as B
 
 from harness import csr, dev_ids
-from test_gpu_head_hold import _check, _normal
+from test_gpu_head_hold import _check, _normal, check_nan_rows
 
 pytestmark = pytest.mark.gpu
 
@@ -90,3 +90,14 @@ def test_infinities_at_a_row_s_start_stay_infinities():
     st, ids, logits = _run(V, 1, M, d, 2000, [n], W, H)
     assert torch.all(torch.isposinf(logits[0, :, :n]))
     st.close()
+
+
+def test_nan_stays_in_its_row():
+    """also where the last fragment's second half is whatever lies behind it in LDS"""
+    V, d, M, n = 9000, 1032, 20, 1499
+    W, H = _normal(11, V, d), _normal(12, 1, M, d)
+    nan_id = int(np.sort(np.random.default_rng(1000 + M).permutation(V)[:n])[n - 2])
+    W[nan_id, d - 1] = float("nan")
+    H[0, M - 1, 0] = float("nan")
+    st, ids, logits = _run(V, 1, M, d, 2000, [n], W, H)
+    check_nan_rows(st, ids[0], logits, W, H, nan_id, M - 1)
