@@ -235,38 +235,57 @@ inline HoldPlan hold_plan(int32_t d, int32_t batch, bool dense) {
 
 inline int64_t hold_lds(const HoldPlan& h, int32_t M) { return (int64_t)h.NW * ((M + 3) / 4 * 4) * (h.seg + 4) * 4; }
 
-// Which products it takes.  Against the kernels of head.hip and wide.hip; two figures: around 0.3 and 0.9 of the capacity live.  It is launched over the live rows, so it
-// gains most on lists that are far from full, and loses on short ones, where the others ask for weights before the row count has arrived (1000 rows x 4096, M = 8: 5.1 against 4.1 us).
+// Which products it takes: those where the kernels of head.hip and wide.hip are nowhere clearly faster, whatever part of the capacity is live.  Figures: its time over theirs with 0.04 / 0.15 / 0.35 /
+// 0.6 / 0.9 of the capacity live (of a batch 0.05 / 0.3 / 0.6 / 0.9).  It is launched over the live rows and so gains by lists far from full; it loses on few rows, where
+// the others ask for weights before the row count has arrived, by hidden rows fetched for pieces of a few rows, and where d fills its last wavefront's 1024 columns badly.
 //  One list (capacity):
-//   * d > 4096, M > 4: from 2560 on (x 8192, M = 16: 3072 0.98 / 0.85 of the time, 16384 0.80 / 0.98, 8400 of 33303 37.8 -> 29.7 us, 32800 of 128256 107 -> 100; M = 8: 3072 1.07 / 0.91,
-//     16384 0.92 / 1.04; x 5120, M = 8: 9000 1.0 / 0.91, 65536 0.80 / 0.88; below 2048 1.01 / 1.01, M = 8 1.09 / 1.06), but not from 49152 on with M > 8 and d < 5120 (x 4608 1.09 / 1.03);
-//     M <= 4 loses as much as it gains (x 8192: 16384 0.97 / 1.09, x 5120 1.0 / 1.04);
-//   * d = 4096, M > 4: beyond 4096 (M = 16: 5120 0.74 / 0.84, 16384 0.94 / 0.93; M = 8: 5120 0.86 / 0.90, 8192 0.81 / 1.0, 8400 of 33303 22.1 -> 16.4 us; 4096 1.02 / 1.13);
-//   * 2048 < d < 4096, M > 4: beyond 4096 up to 12288 (x 3072, M = 16: 5120 0.70 / 0.84, 9000 0.59 / 0.78, 20000 1.10 / 0.95; M = 8: 9000 0.69 / 0.90, 20000 1.01 / 0.92);
-//   * 2048 < d <= 4096, M <= 4: 4097 to 6144 and from 12288 on (x 4096: 5120 0.86 / 0.94, 8192 0.93 / 1.07, 16384 0.78 / 1.04);
-//   * d = 2048: from 16384 on, M > 8 32768 (M = 8: 16384 0.87 / 0.94, 9000 0.96 / 1.09; M = 16: 65536 0.98 / 0.90, 20000 1.08 / 0.96).
-//  Several sequences (capacities together; a die takes the same eighth of every list, see wide_by_die):
-//   * d > 4096: from 2560 on for four or more, two or three beyond 4096 (x 8192: 4 of 600 out of 1000, M = 8 0.86, 2 of them 1.03; 16 of 2300 out of 5120 0.73, 64 239 -> 217 us; x 5120: 16 of 2300 out of 5120
-//     69.6 -> 44.5); M <= 4 where the workgroups fill the chip (24: 1.03); M > 8 and d < 5120 up to 196608 (x 4608, M = 16: 64 of 2300 out of 5120 1.11, 16 0.90);
-//   * 2048 < d <= 4096: beyond 4096 (x 4096, M = 8: 8 of 600 out of 1000 0.80, 16 of 2300 out of 5120 0.80, 32 73 -> 59 us, 64 122 -> 107; M = 16: 32 80 -> 64, 64 133 -> 120; 4 of 1000 1.07; x 3072, M = 16: 16 of 600
-//     out of 1100 0.64; x 2560, M = 4: 2 of 2300 out of 5120 1.04);
-//   * d = 2048: M <= 8 from 16384 on (16 of 2300 out of 5120 0.81, 2 1.05), M > 8 from 65536 on (0.89, 8 of 5120 1.01).
+//   * d > 4096, M > 8: from 8192 on (x 8192, M = 16: 8448 0.81 / 0.81 / 0.93 / 0.80 / 0.93, 5632 1.10 / 1.11 / 1.07 / 0.88 / 0.81, 3072 1.28 / 1.09 / 1.07 / 1.06 / 0.83; x 5248: 8448
+//     0.91 / 0.94 / 1.00 / 0.89 / 1.01, 7168 1.14 / 1.12 / 1.01 / 0.86 / 0.85; x 4224: 3072 1.21 / 1.15 / 1.12 / 1.10 / 1.12), but not from 32768 on with d < 5120 (x 4352, M = 15 35712 0.73 / 1.21 / 1.04 / 1.01 / 0.95);
+//     M 5 to 8: beyond 5120, d > 7168 from 8192 (M = 8: x 6144 5632 0.97 / 0.99 / 0.98 / 1.01 / 0.89, 4160 0.99 of the time on average, x 5248 4160 1.04; x 8192 8448 1.11 / 1.09 / 0.91 / 0.90 / 0.93,
+//     5632 1.14 / 1.15 / 1.08 / 0.94 / 0.90, 3072 1.29 / 1.12 / 1.12 / 1.04 / 0.90); M <= 4 loses as much as it gains (x 8192: 16384 0.97 / 1.09 at 0.3 / 0.9);
+//   * 2048 < d <= 4096, M 5 to 8: beyond 4096, d > 3072 beyond 5120 (x 4096, M = 8: 5632 0.66 / 0.76 / 0.91 / 0.93 / 0.90, 4608 0.66 / 0.73 / 0.88 / 1.09 / 0.89 and 1.14 at 0.75; x 3072: 4608
+//     0.63 / 0.69 / 0.81 / 0.98 / 0.91), M > 8: beyond 4096, not from 9216 on where the register-blocked product is as fast, d < 3840 (M <= 12 d < 3072; x 2560, M = 16: 9216 0.79 / 0.84 / 1.05 /
+//     1.15 / 0.88, M = 12 0.67 / 0.73 / 0.93 / 1.06 / 0.83 and 1.12 at 0.75; x 4000, M = 16 0.57 / 0.66 / 0.84 / 0.96 / 0.77), nor d < 4096 beyond 12288 (x 3072: 20000 1.10 / 0.95 at 0.3 / 0.9);
+//   * 2048 < d <= 4096, M <= 4: 4097 to 6144 and from 12288 on (x 4096: 5120 0.86 / 0.94, 8192 0.93 / 1.07, 16384 0.78 / 1.04 at 0.3 / 0.9);
+//   * d = 2048: from 16384 on, M > 8 32768, M > 12 65536 (M = 8: 16384 0.87 / 0.94, 9000 0.96 / 1.09; M = 16: 65536 0.98 / 0.90 at 0.3 / 0.9, 33024 1.14 at 0.15).
+//  Several sequences (a die takes the same eighth of every list, see wide_by_die), by the launch rather than the capacity:
+//   * up to 32: where one round of workgroups holds them -- 11, 18, 20 and 22 sequences need a second one for an even load: 1.0 to 1.1 on average, up to 2.1 with 0.05 live -- and a piece is
+//     16 rows of the capacity or more, d > 4096 32, M <= 4 or M <= 8 with d <= 3072 64, beyond 16 sequences 128 (a piece fetches the hidden rows whatever it holds: 16 of 640 x 2560, M = 16, 40 rows,
+//     1.15, 24 of 640 x 8192 1.35 / 0.89 / 0.89, 5 of 640 x 8192 M = 4 1.17);  8 of 640 x 4096, M = 16 0.69, 16 of 2304 0.76, M = 8 0.82, 32 73 -> 58 us; 16 of 2304 x 5120, M = 12 0.68;
+//   * more: M <= 8 where the rounds are nine tenths full and pieces 128 rows (64 of 2300 out of 5120 x 4096 122 -> 107 us, x 8192 239 -> 217; 33 x 4224, 0.83 full, 1.0 to 3.1; 64 of 640 x 8192
+//     2.0 / 1.03 / 0.9 / 0.82; M = 16, 64 of 5120 x 4096 1.27 / 0.95 / 0.9 / 0.84, 48 1.58);
+//   * a round less than nine tenths full only with four wavefronts or more and, but for d = 4096 and 8192, less than 98304 rows (24 of 8192 x 2176, M = 8 1.20 / 1.21 / 1.30, x 5120 1.11, x 4096 0.93);
+//   * d > 4096: beyond 5120 rows together (2 of 2304 x 4224, M = 16 1.09, 5 of 640 x 8192 1.15), M <= 4 for eight or more, a last wavefront nearly full and four fifths of the round (x 4608: 11 to 22 1.07 to
+//     1.10, 2 x 8192 1.0 to 1.2), M > 8 and d < 5120 up to 196608 (x 4608, M = 16: 64 of 2300 out of 5120 1.11);
+//   * 2048 < d <= 4096: beyond 4096 (4 of 1000 x 4096 1.07), two or three with M <= 8 and d < 3072 beyond 12288 (2 of 2300 out of 5120 x 2560, M = 4 1.04);
+//   * d = 2048: five or more, from 16384 rows on, M > 8 65536 (3 of 8192, M = 4 1.10; 16 of 5120, M = 8 0.79, M = 16 0.86).
 //  Dense heads: M > 8, d of 4096 or 8192, of which a compute unit takes eight wavefronts (128k x 4096, M = 16 207 -> 186 us, M = 9 188 -> 180; 32000 x 8192 104 -> 93; x 5120 1.05, x 2048, M = 9 1.06).
+inline bool hold_batch_supported(int32_t M, int32_t d, int32_t batch, int32_t cap_rows) {
+  const HoldPlan h = hold_plan(d, batch, false);
+  const int64_t rows = (int64_t)cap_rows * batch;
+  const int32_t groups = 8 * batch * h.parts, round = h.NW <= 2 ? 512 : 256;
+  const bool even = (int64_t)groups * 10 >= ((int64_t)groups + round - 1) / round * round * 9;
+  if (batch > 32 ? M > 8 || !even : groups > round) return false;
+  const int32_t piece = batch > 16 ? 128 : M <= 4 ? 64 : d > 4096 ? 32 : d > 3072 || M > 8 ? 16 : 64;
+  if (cap_rows < 8 * h.parts * piece) return false;
+  if (d == 2048) return batch >= 5 && even && rows >= (M <= 8 ? 16384 : 65536);
+  if (!even && (h.NW <= 3 || (rows >= 98304 && d != 4096 && d != 8192))) return false;
+  if (d <= 4096) return rows > (batch < 4 && M <= 8 && d < 3072 ? 12288 : 4096);
+  if (M <= 4) return rows > 5120 && batch >= 8 && d >= 960 * h.NW && hold_fill(groups) >= 51;
+  return rows > 5120 && (M <= 8 || d >= 5120 || rows < 196608);
+}
+
 inline bool hold_supported(int32_t V, int32_t M, int32_t d, int32_t batch, int32_t cap_rows, bool dense) {
   if (M > 16 || d > 8192 || d < 2048 || !wide_reaches(V, M, d)) return false;
   const int64_t rows = (int64_t)cap_rows * batch;
   if (rows > 0x20000000ll) return false;
   if (dense) return M > 8 && (d == 4096 || d == 8192) && rows >= 16384;
-  if (batch > 1) {
-    if (d > 4096 && rows <= (batch >= 4 ? 2560 : 4096)) return false;
-    if (d > 4096 && M <= 4) return hold_fill(8ll * batch * hold_plan(d, batch, false).parts) >= 51;
-    if (d > 4096) return M <= 8 || d >= 5120 || rows < 196608;
-    return d > 2048 ? rows > (batch < 4 && M <= 8 && d < 3072 ? 12288 : 4096) : rows >= (M <= 8 ? 16384 : 65536);
-  }
-  if (d > 4096) return M > 4 && rows > 2560 && (M <= 8 || d >= 5120 || rows < 49152);
-  if (d == 2048) return rows >= (M <= 8 ? 16384 : 32768);
-  if (rows <= 4096) return false;
+  if (batch > 1) return hold_batch_supported(M, d, batch, cap_rows);
+  if (d > 4096) return M > 8 ? rows >= 8192 && (d >= 5120 || rows < 32768) : M > 4 && (d > 7168 ? rows >= 8192 : rows > 5120);
+  if (d == 2048) return rows >= (M <= 8 ? 16384 : M <= 12 ? 32768 : 65536);
+  if (rows <= (M > 4 && M <= 8 && d > 3072 ? 5120 : 4096)) return false;
   if (M <= 4) return rows <= 6144 || rows >= 12288;
+  if (M > 8 && rows >= 9216 && d < (M > 12 ? 3840 : 3072)) return false;
   return d == 4096 || rows <= 12288;
 }
 

@@ -43,8 +43,8 @@ def check(M, d, batch, cap, n, rows=V, dense=False, pad=4):
     assert covered == n
 
 
-@pytest.mark.parametrize("M,d,batch,cap", [(16, 8192, 1, 33344), (5, 8192, 1, 128256), (8, 4096, 64, 5120), (8, 4096, 24, 5120), (1, 2048, 48, 5120), (16, 2568, 3, 5120), (9, 4104, 2, 9216),
-                                           (13, 7160, 5, 640), (8, 2048, 1, 16384), (16, 4096, 256, 320), (1, 3584, 1, 12288), (4, 8192, 64, 9216)])
+@pytest.mark.parametrize("M,d,batch,cap", [(16, 8192, 1, 33344), (5, 8192, 1, 128256), (8, 4096, 64, 5120), (8, 4096, 24, 5120), (1, 2048, 64, 5120), (16, 2568, 3, 5120), (9, 4104, 2, 9216),
+                                           (13, 7160, 5, 1600), (8, 2048, 1, 16384), (8, 4096, 256, 1024), (1, 3584, 1, 12288), (4, 8192, 64, 9216)])
 def test_pieces_and_addresses(M, d, batch, cap):
     assert choose.hold_supported(V, M, d, batch, cap)
     for n in (0, 1, 7, 8 * choose.hold_plan(d, batch, M).parts + 1, cap // 3, cap):
@@ -63,11 +63,13 @@ def test_a_row_stride_without_room_for_the_segment_is_rejected():
 
 
 @pytest.mark.parametrize("M,d,batch,cap,want", [
-    (16, 8192, 1, 2560, False), (16, 8192, 1, 3072, True), (4, 8192, 1, 33344, False), (8, 5120, 1, 65536, True), (16, 4608, 1, 65536, False), (8, 4096, 1, 4096, False),
-    (8, 4096, 1, 5120, True), (16, 3072, 1, 9216, True), (16, 3072, 1, 20032, False), (4, 4096, 1, 5120, True), (4, 4096, 1, 8192, False), (4, 4096, 1, 16384, True),
-    (8, 2048, 1, 9216, False), (8, 2048, 1, 16384, True), (16, 2048, 1, 20032, False), (16, 2048, 1, 65536, True), (8, 1536, 1, 128256, False), (17, 4096, 8, 5120, False),
-    (8, 8192, 2, 1024, False), (8, 8192, 4, 1024, True), (4, 8192, 24, 5120, False), (4, 8192, 32, 5120, True), (8, 4096, 4, 1024, False), (8, 4096, 8, 1024, True), (4, 2560, 2, 5120, False),
-    (16, 4608, 64, 5120, False), (16, 4608, 16, 5120, True), (8, 2048, 2, 5120, False), (8, 2048, 16, 1024, True), (16, 2048, 8, 5120, False), (16, 2048, 16, 5120, True), (8, 16384, 64, 5120, False),
+    (16, 8192, 1, 2560, False), (16, 8192, 1, 3072, False), (16, 8192, 1, 8192, True), (8, 8192, 1, 8128, False), (8, 8192, 1, 8192, True), (16, 5120, 1, 8128, False), (8, 7168, 1, 5120, False), (8, 7168, 1, 5184, True), (4, 8192, 1, 33344, False), (8, 5120, 1, 65536, True), (16, 4608, 1, 65536, False), (8, 4096, 1, 4096, False),
+    (8, 4096, 1, 5120, False), (8, 4096, 1, 5184, True), (8, 3072, 1, 4160, True), (16, 3072, 1, 9216, False), (16, 3072, 1, 9152, True), (12, 2560, 1, 9216, False), (12, 3072, 1, 9216, True), (16, 3840, 1, 9216, True), (16, 3072, 1, 20032, False), (4, 4096, 1, 5120, True), (4, 4096, 1, 8192, False), (4, 4096, 1, 16384, True),
+    (8, 2048, 1, 9216, False), (8, 2048, 1, 16384, True), (16, 2048, 1, 20032, False), (12, 2048, 1, 32768, True), (16, 2048, 1, 32768, False), (16, 2048, 1, 65536, True), (8, 1536, 1, 128256, False), (17, 4096, 8, 5120, False),
+    (8, 8192, 2, 1024, False), (8, 8192, 4, 1024, False), (8, 8192, 4, 2048, True), (4, 8192, 24, 5120, False), (4, 8192, 32, 5120, True), (8, 4096, 4, 1024, False), (8, 4096, 8, 1024, True), (4, 2560, 2, 5120, False),
+    (16, 4608, 64, 5120, False), (16, 4608, 16, 5120, True), (8, 2048, 2, 5120, False), (8, 2048, 16, 1024, False), (8, 2048, 16, 2048, True), (8, 2048, 3, 8192, False), (16, 2048, 8, 5120, False), (16, 2048, 16, 5120, True), (8, 16384, 64, 5120, False),
+    (8, 4096, 11, 5120, False), (8, 4096, 20, 5120, False), (8, 4096, 22, 5120, False), (8, 4096, 32, 1024, True), (8, 4096, 32, 960, False), (8, 4096, 33, 5120, False), (8, 4096, 64, 1024, True), (8, 4096, 64, 640, False), (12, 4096, 64, 5120, False),
+    (8, 2560, 12, 5120, False), (8, 4224, 12, 5120, True), (8, 4224, 24, 5120, False), (8, 4096, 24, 5120, True), (1, 4608, 8, 5120, False), (1, 5120, 8, 5120, True), (1, 5120, 4, 5120, False), (8, 2560, 8, 2048, True), (8, 2560, 8, 1984, False), (16, 2560, 8, 640, True),
 ])
 def test_choice(M, d, batch, cap, want):
     assert choose.hold_supported(V, M, d, batch, cap) == want
