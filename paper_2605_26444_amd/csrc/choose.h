@@ -336,20 +336,30 @@ inline SlicePlan kslice_plan(int32_t M, int32_t batch, int32_t cap_rows, bool de
   return best;
 }
 
-// Which products it takes, operands 16-byte aligned (its fetches go straight into LDS); time over that of split-K or the register-blocked product:
-//  * one list: d >= 1024 up to the capacity at which those fill the chip with larger blocks.  x 5120: M = 20 640 0.83, 4352 0.57 to 0.75, 8200 0.79 to 1.0, 33000 0.84 to 0.89; M = 64 1300 0.74 to
-//    0.79, 16500 0.76, 33000 0.90 to 1.03.  x 3584: M = 20 0.61 to 0.92, 33000 0.92; M = 64 0.68 to 0.97, 33000 0.88 to 1.06, 128256 1.16.  x 2048: M = 32 0.60 to 0.89 (8200, nine tenths live 1.01), 33000
-//    0.79 to 0.96; M = 64 0.65 to 0.97, 33000 0.93 to 1.12.  x 1024: M = 32 0.68 to 0.89, 33000 0.82 to 1.0, 128256 1.2; M = 64 0.75 to 0.97.  x 512: up to 2600 M = 32 0.81 to 0.87, M = 64 0.84 to 0.96, 8200 1.04;
-//  * several: while 205 of 256 workgroups can be had for equal shares and the work is little (4096: 4 of 600 out of 1000 0.63 to 0.69, of 2300 out of 5120 0.68 to 0.87; 8 of 3500, M = 20 0.83, M = 64 1.06; 12 of
-//    600 1.0 to 1.1; 16 of 600 0.71 to 0.82, of 1800 out of 2000, M = 32 0.88, M = 48 1.04; 24 1.1 to 1.7; x 1024: 3 of 2300 0.89 to 1.0, 16 of 600, M = 32 0.77);
+// Which products it takes, operands 16-byte aligned (its fetches go straight into LDS); its time over that of split-K or the register-blocked product with 0.04 / 0.2 / 0.45 / 0.75 / 0.95 of the capacity live:
+//  * one list: d >= 1024 up to the capacity at which those fill the chip with larger blocks.  M <= 32: x 2304, M = 17 24576 0.62 / 0.86 / 0.81 / 0.93 / 1.0, 32768 1.0 / 1.21 / 1.07 / 1.02 / 0.95; x 5120,
+//    M = 24 24576 0.57 / 0.93 / 0.81 / 0.88 / 0.95, 32768 0.98 / 1.29 / 1.03 / 0.99 / 0.93; x 2048 20480 0.69 / 0.85 / 0.82 / 1.07 / 1.07, 24576 0.69 / 0.92 / 0.94 / 1.05 / 1.13.  M > 32: x 4096, M = 64 20480
+//    0.49 / 0.70 / 0.91 / 1.07 / 0.91, 40960 1.0 on average; x 2048, M = 64 16384 0.85 / 0.91 / 1.05 / 0.93 / 1.03, 20480 0.65 / 0.75 / 0.96 / 1.10 / 1.03; x 1024, M = 48 16384 0.80 / 0.83 / 1.04 / 0.93 / 1.0, 20480
+//    0.62 / 0.70 / 0.97 / 1.12 / 1.06, M = 64 5120 0.88, 10240 0.86 / 0.81 / 1.01 / 1.13 / 0.93.  x 512: up to 2600 M = 32 0.81 to 0.87, M = 64 0.84 to 0.96, 8200 1.04;
+//  * but few long rows, which split-K spreads over more of the chip (x 8192, M = 17 640 1.17 / 1.14 / 1.09 / 1.04 / 1.0, 1920 1.16 / 1.09 / 0.95 / 0.85 / 0.82, 2560 1.0 / 0.93 / 0.83 / 0.79 / 0.77; M = 64 640 1.08 / 1.04
+//    / 0.98 / 0.91 / 0.88, 1280 0.99 / 1.0 / 0.84 / 0.79 / 0.87; x 7168, M = 17 640 1.07 / 1.07 / 1.04 / 0.99 / 0.95, 1280 1.08 / 1.08 / 0.88 / 0.80 / 0.80; x 6144 0.91 to 0.99);
+//  * several: while 205 of 256 workgroups can be had for equal shares and the work is little (4 of 600 out of 1000 x 4096 0.63 to 0.69, of 2300 out of 5120 0.68 to 0.87; 8 of 3500, M = 20 0.83, M = 64 1.06; 12 of
+//    600 1.0 to 1.1; 16 of 1280 M = 48 0.73 to 0.89; 24 of 600 1.1 to 1.7), 28672 rows together (2 of 20480 x 4096, M = 17 1.26 with 0.2 live), d <= 2048 16384 (2 of 10240 x 2048, M = 64 1.11 with 0.75); not where pieces
+//    are few rows beside many hidden rows -- more than eight sequences with M > 32 below 1024 rows each (16 of 320 x 5120, M = 48 1.29 / 1.19 / 1.01 / 0.79 / 0.75; 14 of 640 x 3584, M = 64 1.09 / 1.14 / 1.17 / 0.85 /
+//    0.70), any number with d > 6144 (8 of 320 x 8192, M = 48 1.27 / 1.26 / 1.14 / 0.87 / 0.83; 6 of 960 1.28 / 1.10 / 0.88 / 0.81 / 0.79);
 //  * no dense heads (128k x 4096 1.01 to 1.15, 32000 x 4096 1.0 to 1.1, x 8192 0.92 to 0.99, 128k x 8192 1.02 to 1.2, x 1024 1.2 to 1.3).
 inline bool kslice_supported(int32_t V, int32_t M, int32_t d, int32_t batch, int32_t cap_rows, bool dense, bool aligned) {
   if (M <= 16 || M > 64 || d < 512 || dense || !aligned || !wide_reaches(V, M, d)) return false;
   const int64_t rows = (int64_t)cap_rows * batch;
   if (d < 1024) return rows <= 3072;
-  if (batch > 1) return batch <= 16 && 256 / (8 * batch) * (8 * batch) >= 205 && rows * M <= (d < 2048 ? 700000 : batch <= 8 ? 1400000 : 1000000);
-  if (M <= 32) return rows <= (d >= 4096 ? 65536 : d >= 2048 ? 40960 : 20480);
-  return rows <= (M <= 48 && d >= 3072 ? 40960 : d >= 2048 ? 24576 : 20480);
+  if (batch > 1) {
+    if (batch > 16 || 256 / (8 * batch) * (8 * batch) < 205) return false;
+    if (cap_rows < 1024 && (d > 6144 || (batch > 8 && M > 32))) return false;
+    return rows <= (d <= 2048 ? 16384 : 28672) && rows * M <= (d < 2048 ? 700000 : batch <= 8 ? 1400000 : 1000000);
+  }
+  if (rows < (M <= 32 ? (d > 7168 ? 2048 : d > 6144 ? 1024 : 0) : d > 7168 ? 1024 : 0)) return false;
+  if (M <= 32) return rows <= (d > 2048 ? 24576 : 20480);
+  return rows <= (d >= 3072 ? 20480 : d < 2048 && M > 48 ? 8192 : 16384);
 }
 
 // ---- stream initialisation (vocab.hip) -------------------------------------------------------------------------------------

@@ -43,7 +43,7 @@ def test_blocks(M, batch, d, window, sizes):
 
 
 @pytest.mark.parametrize("batch,M,d,window,sizes", [
-    (1, 20, 512, 3000, [2999]), (1, 64, 520, 2900, [1500]), (1, 64, 8192, 24000, [23999]), (1, 17, 4096, 60000, [41000]), (16, 20, 4096, 3000, [3000, 17, 0]), (8, 60, 2048, 2800, [2800, 1, 1800]), (13, 33, 3000, 2000, [2000, 64]),
+    (1, 20, 512, 3000, [2999]), (1, 64, 520, 2900, [1500]), (1, 64, 8192, 20400, [20399]), (1, 17, 4096, 24500, [24100]), (16, 20, 4096, 1700, [1700, 17, 0]), (8, 60, 2048, 2000, [2000, 1, 1800]), (13, 33, 3000, 2000, [2000, 64]),
 ])
 def test_sizes_of_its_range(batch, M, d, window, sizes):
     V = 70000 if window > 16000 else 20000
