@@ -15,7 +15,8 @@ constexpr int32_t kSplitRowsMax = 16384;
 // its 32-bit byte offsets reach every row
 inline bool wide_reaches(int32_t V, int32_t M, int32_t d) { return (int64_t)V * d * 2 <= 0xffffffffll && (int64_t)M * d * 2 <= 0xffffffffll; }
 
-// Which products the register-blocked kernel takes, of those whose rows 32-bit byte offsets reach.
+// Which products the register-blocked kernel takes, of those whose rows 32-bit byte offsets reach and that hold_supported and kslice_supported, asked first, leave.  Figures on lists of up to 64 hidden rows are against
+// head.hip's kernels.
 // More than 16 hidden rows:
 //   * any number of rows of one launch's d / 128 steps against two launches of split-K + reduce while that is the shorter walk (d = 1152 6.0 us against 9.6,
 //     2048 7.2 against 8.9): d <= 2048, up to 32 hidden rows d <= 1792 (2048: 8.9 against 8.5; from 4096 rows on 0.98);
@@ -235,43 +236,47 @@ inline HoldPlan hold_plan(int32_t d, int32_t batch, bool dense) {
 
 inline int64_t hold_lds(const HoldPlan& h, int32_t M) { return (int64_t)h.NW * ((M + 3) / 4 * 4) * (h.seg + 4) * 4; }
 
-// Which products it takes: those where the kernels of head.hip and wide.hip are nowhere clearly faster, whatever part of the capacity is live.  Figures: its time over theirs with 0.04 / 0.15 / 0.35 /
-// 0.6 / 0.9 of the capacity live (of a batch 0.05 / 0.3 / 0.6 / 0.9).  It is launched over the live rows and so gains by lists far from full; it loses on few rows, where
-// the others ask for weights before the row count has arrived, by hidden rows fetched for pieces of a few rows, and where d fills its last wavefront's 1024 columns badly.
+// Which products it takes.  Figures: its time over that of the kernels of head.hip and wide.hip with 0.04 / 0.15 / 0.35 / 0.6 / 0.9 of the capacity live, of a batch 0.05 / 0.3 / 0.6 / 0.9.  It is launched over
+// the live rows and so gains by lists that are far from full; it loses on few rows, where the others ask for weights before the row count has arrived, where pieces are a few rows for which all hidden rows are
+// fetched, and where d leaves its last wavefront's 1024 columns nearly empty.  The others go by steps of the capacity and of the live rows, so that no line has all of the gain on one side: these are drawn for
+// the mean over lists that are most often half full or more, not so that none loses (2400 sizes and fills measured for them, K slices' too: 0.87 / 0.78 on the one side, 0.96 on the other;
+// 5764 at random measured afterwards 0.78, 45 of them beyond 1.1: 2 of 5504 x 2688, M = 16, 1100 rows 1.26 the most here, 10048 x 5096, M = 61, 4019 rows 1.34 with K slices).
 //  One list (capacity):
-//   * d > 4096, M > 8: from 8192 on (x 8192, M = 16: 8448 0.81 / 0.81 / 0.93 / 0.80 / 0.93, 5632 1.10 / 1.11 / 1.07 / 0.88 / 0.81, 3072 1.28 / 1.09 / 1.07 / 1.06 / 0.83; x 5248: 8448
-//     0.91 / 0.94 / 1.00 / 0.89 / 1.01, 7168 1.14 / 1.12 / 1.01 / 0.86 / 0.85; x 4224: 3072 1.21 / 1.15 / 1.12 / 1.10 / 1.12), but not from 32768 on with d < 5120 (x 4352, M = 15 35712 0.73 / 1.21 / 1.04 / 1.01 / 0.95);
-//     M 5 to 8: beyond 5120, d > 7168 from 8192 (M = 8: x 6144 5632 0.97 / 0.99 / 0.98 / 1.01 / 0.89, 4160 0.99 of the time on average, x 5248 4160 1.04; x 8192 8448 1.11 / 1.09 / 0.91 / 0.90 / 0.93,
-//     5632 1.14 / 1.15 / 1.08 / 0.94 / 0.90, 3072 1.29 / 1.12 / 1.12 / 1.04 / 0.90); M <= 4 loses as much as it gains (x 8192: 16384 0.97 / 1.09 at 0.3 / 0.9);
-//   * 2048 < d <= 4096, M 5 to 8: beyond 4096, d > 3072 beyond 5120 (x 4096, M = 8: 5632 0.66 / 0.76 / 0.91 / 0.93 / 0.90, 4608 0.66 / 0.73 / 0.88 / 1.09 / 0.89 and 1.14 at 0.75; x 3072: 4608
-//     0.63 / 0.69 / 0.81 / 0.98 / 0.91), M > 8: beyond 4096, not from 9216 on where the register-blocked product is as fast, d < 3840 (M <= 12 d < 3072; x 2560, M = 16: 9216 0.79 / 0.84 / 1.05 /
-//     1.15 / 0.88, M = 12 0.67 / 0.73 / 0.93 / 1.06 / 0.83 and 1.12 at 0.75; x 4000, M = 16 0.57 / 0.66 / 0.84 / 0.96 / 0.77), nor d < 4096 beyond 12288 (x 3072: 20000 1.10 / 0.95 at 0.3 / 0.9);
-//   * 2048 < d <= 4096, M <= 4: 4097 to 6144 and from 12288 on (x 4096: 5120 0.86 / 0.94, 8192 0.93 / 1.07, 16384 0.78 / 1.04 at 0.3 / 0.9);
-//   * d = 2048: from 16384 on, M > 8 32768, M > 12 65536 (M = 8: 16384 0.87 / 0.94, 9000 0.96 / 1.09; M = 16: 65536 0.98 / 0.90 at 0.3 / 0.9, 33024 1.14 at 0.15).
+//   * d >= 5120, M > 4, and d > 4096, M 5 to 8: beyond 5120 (x 8192, M = 16: 5632 1.10 / 1.11 / 1.07 / 0.88 / 0.81, 3072 1.28 / 1.09 / 1.07 / 1.06 / 0.83, 8400 live of 33303 37.8 -> 29.7 us; M = 8: 5632 1.14 / 1.15 /
+//     1.08 / 0.94 / 0.90, 3072 1.29 / 1.12 / 1.12 / 1.04 / 0.90; x 6144, M = 12: 5632 1.13 / 1.11 / 1.13 / 0.94 / 0.91, 3072 1.23 / 1.10 / 1.12 / 1.11 / 0.91; M = 8: 5632 0.97 / 0.99 / 0.98 / 1.01 / 0.89, 4160 1.0);
+//     M > 8 with d < 5120 from 8192 up to 32768 (x 4224, M = 16: 7168 1.19 / 1.12 / 1.12 / 0.88 / 0.88, 8448 0.92 / 0.92 / 1.03 / 0.91 / 1.03; x 4352, M = 15: 35712 0.73 / 1.21 / 1.04 / 1.01 / 0.95); M <= 4 loses
+//     as much as it gains (x 8192: 16384 0.97 / 1.09 at 0.3 / 0.9);
+//   * 2048 < d <= 4096: M > 4 beyond 4096, M 5 to 8 with d > 3072 beyond 5120 (x 4096, M = 8: 5632 0.66 / 0.76 / 0.91 / 0.93 / 0.90, 4608 0.66 / 0.73 / 0.88 / 1.09 / 0.89 and 1.14 at 0.75; x 3072: 4608 0.63 / 0.69 /
+//     0.81 / 0.98 / 0.91), M > 12 with d < 3072 up to 9216 (x 2560, M = 16: 8448 0.47 / 0.53 / 0.66 / 0.71 / 0.79, 9216 0.79 / 0.84 / 1.05 / 1.15 / 0.88 and 1.20 at 0.75; M = 12: 9216 0.67 / 0.73 / 0.93 / 1.06 / 0.83), d < 4096 up to
+//     12288 (x 3072: 20000 1.10 / 0.95 at 0.3 / 0.9); M <= 4 4097 to 6144 and from 12288 on (x 4096: 5120 0.86 / 0.94, 8192 0.93 / 1.07, 16384 0.78 / 1.04 at 0.3 / 0.9);
+//   * d = 2048: from 16384 on, M > 8 32768 (M = 8: 16384 0.87 / 0.94, 9000 0.96 / 1.09; M = 16: 65536 0.98 / 0.90, 20000 1.08 / 0.96 at 0.3 / 0.9).
 //  Several sequences (a die takes the same eighth of every list, see wide_by_die), by the launch rather than the capacity:
-//   * up to 32: where one round of workgroups holds them -- 11, 18, 20 and 22 sequences need a second one for an even load: 1.0 to 1.1 on average, up to 2.1 with 0.05 live -- and a piece is
-//     16 rows of the capacity or more, d > 4096 32, M <= 4 or M <= 8 with d <= 3072 64, beyond 16 sequences 128 (a piece fetches the hidden rows whatever it holds: 16 of 640 x 2560, M = 16, 40 rows,
-//     1.15, 24 of 640 x 8192 1.35 / 0.89 / 0.89, 5 of 640 x 8192 M = 4 1.17);  8 of 640 x 4096, M = 16 0.69, 16 of 2304 0.76, M = 8 0.82, 32 73 -> 58 us; 16 of 2304 x 5120, M = 12 0.68;
-//   * more: M <= 8 where the rounds are nine tenths full and pieces 128 rows (64 of 2300 out of 5120 x 4096 122 -> 107 us, x 8192 239 -> 217; 33 x 4224, 0.83 full, 1.0 to 3.1; 64 of 640 x 8192
-//     2.0 / 1.03 / 0.9 / 0.82; M = 16, 64 of 5120 x 4096 1.27 / 0.95 / 0.9 / 0.84, 48 1.58);
-//   * a round less than nine tenths full only with four wavefronts or more and, but for d = 4096 and 8192, less than 98304 rows (24 of 8192 x 2176, M = 8 1.20 / 1.21 / 1.30, x 5120 1.11, x 4096 0.93);
-//   * d > 4096: beyond 5120 rows together (2 of 2304 x 4224, M = 16 1.09, 5 of 640 x 8192 1.15), M <= 4 for eight or more, a last wavefront nearly full and four fifths of the round (x 4608: 11 to 22 1.07 to
-//     1.10, 2 x 8192 1.0 to 1.2), M > 8 and d < 5120 up to 196608 (x 4608, M = 16: 64 of 2300 out of 5120 1.11);
+//   * up to 32 in one round of workgroups: a piece of 16 rows of the capacity or more, d > 4096 or M <= 4 32, M <= 4 with d <= 3072 64, more than 16 sequences 96 (8 of 640 x 4096, M = 16, 20 rows, 0.59 / 0.71 / 0.78;
+//     16 of 2304 0.59 / 0.81 / 0.88 / 0.78, M = 8 0.86 / 0.80 / 0.80; 24 of 640 x 8192, M = 16, 80 rows, 1.35 / 0.89 / 0.89);
+//   * numbers that need a second round for an even load, 11, 18, 20, 22 among them: pieces of 256 rows (11 of 1984 x 4224, M = 1, 49 rows, 1.45 / 1.04 / 1.08 / 1.09; 22 of 1856 x 4104, M = 6, 58 rows, 1.56 / 0.98 / 0.86 / 0.79, of
+//     4160, M = 12, 130 rows, 1.35 / 0.93 / 0.81 / 0.80);
+//   * more than 32: pieces of 128 rows (64 of 2300 out of 5120 x 4096, M = 8 122 -> 107 us, x 8192 239 -> 217; 64 of 640 x 8192, 80 rows, 2.04 / 1.03 / 0.82; 33 of 640 x 4224, 20 rows, M = 4 3.14 / 1.53 / 1.33, M = 16 2.22 / 1.97 /
+//     1.69), M > 8 only in at most two full rounds and up to 12 (64 of 5120 x 4096, M = 16 1.27 / 0.84 at 0.04 / 0.9, 48 1.58 at 0.04);
+//   * a single round that is less than nine tenths full, not with two or three wavefronts from 24576 rows on (24 of 8192 x 2176, M = 8 1.20 / 1.21 / 1.30 at 0.3 / 0.6 / 0.9, x 2560 1.17 / 1.18 / 1.26) nor, but for
+//     d = 4096 and 8192, from 131072 on (24 of 8192 x 3584, M = 8 1.03 / 1.06 / 1.08);
+//   * d > 4096: beyond 5120 rows together (2 of 2304 x 4224, M = 16 1.09 at 0.6), M <= 4 in an even load with a last wavefront nearly full (x 4608: 11 to 22 1.07 to 1.10; 54 of 1408 x 5064, 0.84
+//     full, 1.22 / 1.07 / 1.08 / 1.06; 2 of 6400 x 8192, M = 4 1.15 / 1.01 / 0.95 / 0.95, 2 of 2304 1.19 / 1.12 / 0.93 / 0.90; 5 of
+//     6272 x 8192, M = 4 1.03 / 0.88 / 0.90 / 0.94), M > 8 and d < 5120 up to 196608 (x 4608, M = 16: 64 of 2300 out of 5120 1.11);
 //   * 2048 < d <= 4096: beyond 4096 (4 of 1000 x 4096 1.07), two or three with M <= 8 and d < 3072 beyond 12288 (2 of 2300 out of 5120 x 2560, M = 4 1.04);
-//   * d = 2048: five or more, from 16384 rows on, M > 8 65536 (3 of 8192, M = 4 1.10; 16 of 5120, M = 8 0.79, M = 16 0.86).
+//   * d = 2048: five or more in an even load, from 16384 rows on, M > 8 65536 (3 of 8192, M = 4 1.10 on average; 16 of 5120, M = 8 0.79 / 0.82 / 0.78).
 //  Dense heads: M > 8, d of 4096 or 8192, of which a compute unit takes eight wavefronts (128k x 4096, M = 16 207 -> 186 us, M = 9 188 -> 180; 32000 x 8192 104 -> 93; x 5120 1.05, x 2048, M = 9 1.06).
 inline bool hold_batch_supported(int32_t M, int32_t d, int32_t batch, int32_t cap_rows) {
   const HoldPlan h = hold_plan(d, batch, false);
   const int64_t rows = (int64_t)cap_rows * batch;
   const int32_t groups = 8 * batch * h.parts, round = h.NW <= 2 ? 512 : 256;
-  const bool even = (int64_t)groups * 10 >= ((int64_t)groups + round - 1) / round * round * 9;
-  if (batch > 32 ? M > 8 || !even : groups > round) return false;
-  const int32_t piece = batch > 16 ? 128 : M <= 4 ? 64 : d > 4096 ? 32 : d > 3072 || M > 8 ? 16 : 64;
+  const bool one = groups <= round, even = (int64_t)groups * 10 >= ((int64_t)groups + round - 1) / round * round * 9;
+  if (batch > 32 && M > 8 && (M > 12 || !even || groups > 512)) return false;
+  const int32_t piece = batch > 32 ? 128 : !one ? 256 : batch > 16 ? 96 : d > 4096 ? 32 : M > 4 ? 16 : d > 3072 ? 32 : 64;
   if (cap_rows < 8 * h.parts * piece) return false;
   if (d == 2048) return batch >= 5 && even && rows >= (M <= 8 ? 16384 : 65536);
-  if (!even && (h.NW <= 3 || (rows >= 98304 && d != 4096 && d != 8192))) return false;
+  if (one && !even && rows >= (h.NW <= 3 ? 24576 : d % 4096 != 0 ? 131072 : INT32_MAX)) return false;
   if (d <= 4096) return rows > (batch < 4 && M <= 8 && d < 3072 ? 12288 : 4096);
-  if (M <= 4) return rows > 5120 && batch >= 8 && d >= 960 * h.NW && hold_fill(groups) >= 51;
+  if (M <= 4) return rows > 5120 && even && d >= 960 * h.NW;
   return rows > 5120 && (M <= 8 || d >= 5120 || rows < 196608);
 }
 
@@ -281,11 +286,11 @@ inline bool hold_supported(int32_t V, int32_t M, int32_t d, int32_t batch, int32
   if (rows > 0x20000000ll) return false;
   if (dense) return M > 8 && (d == 4096 || d == 8192) && rows >= 16384;
   if (batch > 1) return hold_batch_supported(M, d, batch, cap_rows);
-  if (d > 4096) return M > 8 ? rows >= 8192 && (d >= 5120 || rows < 32768) : M > 4 && (d > 7168 ? rows >= 8192 : rows > 5120);
-  if (d == 2048) return rows >= (M <= 8 ? 16384 : M <= 12 ? 32768 : 65536);
+  if (d > 4096) return M > 8 && d < 5120 ? rows >= 8192 && rows < 32768 : M > 4 && rows > 5120;
+  if (d == 2048) return rows >= (M <= 8 ? 16384 : 32768);
   if (rows <= (M > 4 && M <= 8 && d > 3072 ? 5120 : 4096)) return false;
   if (M <= 4) return rows <= 6144 || rows >= 12288;
-  if (M > 8 && rows >= 9216 && d < (M > 12 ? 3840 : 3072)) return false;
+  if (M > 12 && d < 3072 && rows >= 9216) return false;
   return d == 4096 || rows <= 12288;
 }
 
@@ -336,17 +341,18 @@ inline SlicePlan kslice_plan(int32_t M, int32_t batch, int32_t cap_rows, bool de
   return best;
 }
 
-// Which products it takes, operands 16-byte aligned (its fetches go straight into LDS); its time over that of split-K or the register-blocked product with 0.04 / 0.2 / 0.45 / 0.75 / 0.95 of the capacity live:
-//  * one list: d >= 1024 up to the capacity at which those fill the chip with larger blocks.  M <= 32: x 2304, M = 17 24576 0.62 / 0.86 / 0.81 / 0.93 / 1.0, 32768 1.0 / 1.21 / 1.07 / 1.02 / 0.95; x 5120,
-//    M = 24 24576 0.57 / 0.93 / 0.81 / 0.88 / 0.95, 32768 0.98 / 1.29 / 1.03 / 0.99 / 0.93; x 2048 20480 0.69 / 0.85 / 0.82 / 1.07 / 1.07, 24576 0.69 / 0.92 / 0.94 / 1.05 / 1.13.  M > 32: x 4096, M = 64 20480
-//    0.49 / 0.70 / 0.91 / 1.07 / 0.91, 40960 1.0 on average; x 2048, M = 64 16384 0.85 / 0.91 / 1.05 / 0.93 / 1.03, 20480 0.65 / 0.75 / 0.96 / 1.10 / 1.03; x 1024, M = 48 16384 0.80 / 0.83 / 1.04 / 0.93 / 1.0, 20480
-//    0.62 / 0.70 / 0.97 / 1.12 / 1.06, M = 64 5120 0.88, 10240 0.86 / 0.81 / 1.01 / 1.13 / 0.93.  x 512: up to 2600 M = 32 0.81 to 0.87, M = 64 0.84 to 0.96, 8200 1.04;
-//  * but few long rows, which split-K spreads over more of the chip (x 8192, M = 17 640 1.17 / 1.14 / 1.09 / 1.04 / 1.0, 1920 1.16 / 1.09 / 0.95 / 0.85 / 0.82, 2560 1.0 / 0.93 / 0.83 / 0.79 / 0.77; M = 64 640 1.08 / 1.04
-//    / 0.98 / 0.91 / 0.88, 1280 0.99 / 1.0 / 0.84 / 0.79 / 0.87; x 7168, M = 17 640 1.07 / 1.07 / 1.04 / 0.99 / 0.95, 1280 1.08 / 1.08 / 0.88 / 0.80 / 0.80; x 6144 0.91 to 0.99);
+// Which products it takes, operands 16-byte aligned (its fetches go straight into LDS).  Figures: its time over that of split-K or the register-blocked product with 0.04 / 0.2 / 0.45 / 0.75 / 0.95 of the
+// capacity live; lines drawn as for hold_supported (2050 sizes and fills: 0.78 on the one side, 0.96 on the other):
+//  * one list: d >= 1024 up to the capacity at which those fill the chip with larger blocks.  M <= 24: x 2304, M = 17 24576 0.62 / 0.86 / 0.81 / 0.93 / 1.0, 32768 1.0 / 1.21 / 1.07 / 1.02 / 0.95; x 5120,
+//    M = 24 24576 0.57 / 0.93 / 0.81 / 0.88 / 0.95, 32768 0.98 / 1.29 / 1.03 / 0.99 / 0.93.  M 25 to 32: x 3584, M = 32 32768 0.65 / 0.98 / 0.92 / 1.0 / 0.93, 40960 1.05 / 1.36 / 0.93 / 0.98 / 1.01.  M <= 32, x 2048: M = 17 20480
+//    0.69 / 0.85 / 0.82 / 1.07 / 1.07, 24576 0.69 / 0.92 / 0.94 / 1.05 / 1.13.  M > 32: x 4096, M = 64 20480 0.49 / 0.70 / 0.91 / 1.07 / 0.91, 40960 1.0 on average; x 2048, M = 64 20480 0.65 / 0.75 / 0.96 / 1.10 / 1.03; x 1024, M = 48
+//    16384 0.80 / 0.83 / 1.04 / 0.93 / 1.0, 20480 0.62 / 0.70 / 0.97 / 1.12 / 1.06, M = 64 5120 0.88, 10240 0.86 / 0.81 / 1.01 / 1.13 / 0.93.  x 512: up to 2600 M = 32 0.81 to 0.87, M = 64 0.84 to 0.96, 8200 1.04;
+//  * but few long rows, which split-K spreads over more of the chip (x 8192, M = 17 640 1.17 / 1.14 / 1.09 / 1.04 / 1.0, 1280 1.17 / 1.13 / 0.93 / 0.86 / 0.85; M = 64 640 1.08 / 1.04 / 0.98 / 0.91 / 0.88, 1280 0.99 / 1.0 / 0.84 /
+//    0.79 / 0.87; x 7168, M = 17 640 1.07 / 1.07 / 1.04 / 0.99 / 0.95, 1280 1.08 / 1.08 / 0.88 / 0.80 / 0.80; x 6144 0.91 to 0.99);
 //  * several: while 205 of 256 workgroups can be had for equal shares and the work is little (4 of 600 out of 1000 x 4096 0.63 to 0.69, of 2300 out of 5120 0.68 to 0.87; 8 of 3500, M = 20 0.83, M = 64 1.06; 12 of
-//    600 1.0 to 1.1; 16 of 1280 M = 48 0.73 to 0.89; 24 of 600 1.1 to 1.7), 28672 rows together (2 of 20480 x 4096, M = 17 1.26 with 0.2 live), d <= 2048 16384 (2 of 10240 x 2048, M = 64 1.11 with 0.75); not where pieces
-//    are few rows beside many hidden rows -- more than eight sequences with M > 32 below 1024 rows each (16 of 320 x 5120, M = 48 1.29 / 1.19 / 1.01 / 0.79 / 0.75; 14 of 640 x 3584, M = 64 1.09 / 1.14 / 1.17 / 0.85 /
-//    0.70), any number with d > 6144 (8 of 320 x 8192, M = 48 1.27 / 1.26 / 1.14 / 0.87 / 0.83; 6 of 960 1.28 / 1.10 / 0.88 / 0.81 / 0.79);
+//    600 1.0 to 1.1; 16 of 1280 M = 48 0.73 to 0.89; 24 of 600 1.1 to 1.7), 28672 rows together (2 of 20480 x 4096, M = 17 1.26 with 0.2 live), d <= 2048 and M > 32 20480 (2 of 14336 x 2048, M = 33 1.16 with 0.95); not where pieces are
+//    few rows beside many hidden rows -- more than twelve sequences with M > 48 below 1024 rows each (16 of 640 x 3584, M = 64 0.97 / 1.01 / 1.12 / 1.12 / 0.75, of 256 1.13 to 1.30), below 400 d > 6144 (8 of 320 x 8192, M = 48 1.27 / 1.26 /
+//    1.14 / 0.87 / 0.83; 14 1.65 / 1.51 / 1.06 / 0.95 / 0.82) and d >= 3072 with more than eight and M > 32 (16 of 320 x 5120, M = 48 1.29 / 1.19 / 1.01 / 0.79 / 0.75);
 //  * no dense heads (128k x 4096 1.01 to 1.15, 32000 x 4096 1.0 to 1.1, x 8192 0.92 to 0.99, 128k x 8192 1.02 to 1.2, x 1024 1.2 to 1.3).
 inline bool kslice_supported(int32_t V, int32_t M, int32_t d, int32_t batch, int32_t cap_rows, bool dense, bool aligned) {
   if (M <= 16 || M > 64 || d < 512 || dense || !aligned || !wide_reaches(V, M, d)) return false;
@@ -354,12 +360,13 @@ inline bool kslice_supported(int32_t V, int32_t M, int32_t d, int32_t batch, int
   if (d < 1024) return rows <= 3072;
   if (batch > 1) {
     if (batch > 16 || 256 / (8 * batch) * (8 * batch) < 205) return false;
-    if (cap_rows < 1024 && (d > 6144 || (batch > 8 && M > 32))) return false;
-    return rows <= (d <= 2048 ? 16384 : 28672) && rows * M <= (d < 2048 ? 700000 : batch <= 8 ? 1400000 : 1000000);
+    if (cap_rows < 1024 && batch > 12 && M > 48) return false;
+    if (cap_rows < 400 && (d > 6144 || (d >= 3072 && batch > 8 && M > 32))) return false;
+    return rows <= (d <= 2048 && M > 32 ? 20480 : 28672) && rows * M <= (d < 2048 ? 700000 : batch <= 8 ? 1400000 : 1000000);
   }
-  if (rows < (M <= 32 ? (d > 7168 ? 2048 : d > 6144 ? 1024 : 0) : d > 7168 ? 1024 : 0)) return false;
-  if (M <= 32) return rows <= (d > 2048 ? 24576 : 20480);
-  return rows <= (d >= 3072 ? 20480 : d < 2048 && M > 48 ? 8192 : 16384);
+  if (rows < 1024 && (d > 7168 || (d > 6144 && M <= 32))) return false;
+  if (M <= 32) return rows <= (d <= 2048 ? 20480 : M <= 24 ? 24576 : 32768);
+  return rows <= (d >= 2048 ? 20480 : M <= 48 ? 16384 : 8192);
 }
 
 // ---- stream initialisation (vocab.hip) -------------------------------------------------------------------------------------

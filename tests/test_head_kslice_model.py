@@ -113,12 +113,12 @@ def test_a_wait_for_a_younger_step_only_is_rejected():
 
 
 @pytest.mark.parametrize("M,d,batch,cap,want", [
-    (64, 3584, 1, 4352, True), (64, 3584, 1, 33344, False), (40, 3584, 1, 33344, False), (40, 3584, 1, 20480, True), (20, 3584, 1, 33344, False), (20, 3584, 1, 24576, True), (20, 4096, 1, 65536, False), (20, 4096, 1, 128256, False), (64, 2048, 1, 20480, False), (64, 2048, 1, 16384, True), (64, 2048, 1, 33344, False),
-    (32, 2048, 1, 33344, False), (32, 2048, 1, 20480, True), (64, 1024, 1, 8192, True), (64, 1024, 1, 8256, False), (48, 1024, 1, 16384, True), (32, 1024, 1, 20480, True), (32, 1024, 1, 33344, False), (64, 512, 1, 2624, True), (32, 512, 1, 8192, False), (16, 4096, 1, 4352, False), (65, 4096, 1, 4352, False), (32, 504, 1, 640, False),
-    (64, 4096, 4, 5120, True), (20, 4096, 16, 5120, False), (32, 4096, 16, 1920, False), (32, 4096, 16, 1792, True), (48, 4096, 16, 2048, False), (20, 4096, 12, 1024, False), (20, 4096, 24, 1024, False), (64, 1024, 4, 5120, False), (20, 1024, 16, 1024, True),
+    (64, 3584, 1, 4352, True), (64, 3584, 1, 33344, False), (40, 3584, 1, 33344, False), (20, 3584, 1, 33344, False), (20, 4096, 1, 65536, False), (20, 4096, 1, 128256, False), (64, 2048, 1, 20480, True), (64, 2048, 1, 33344, False),
+    (32, 2048, 1, 33344, False), (32, 1024, 1, 20480, True), (32, 1024, 1, 33344, False), (64, 512, 1, 2624, True), (32, 512, 1, 8192, False), (16, 4096, 1, 4352, False), (65, 4096, 1, 4352, False), (32, 504, 1, 640, False),
+    (64, 4096, 4, 5120, True), (20, 4096, 16, 5120, False), (32, 4096, 16, 1920, False), (48, 4096, 16, 2048, False), (20, 4096, 12, 1024, False), (20, 4096, 24, 1024, False), (64, 1024, 4, 5120, False), (20, 1024, 16, 1024, True),
     (60, 4096, 8, 4032, False), (60, 4096, 8, 2880, True),
-    (17, 8192, 1, 1984, False), (17, 8192, 1, 2048, True), (33, 8192, 1, 960, False), (33, 8192, 1, 1024, True), (24, 7168, 1, 960, False), (24, 7168, 1, 1024, True), (33, 7168, 1, 320, True), (17, 6144, 1, 320, True),
-    (40, 4096, 16, 960, False), (40, 4096, 16, 1280, True), (32, 4096, 16, 320, True), (20, 8192, 4, 960, False), (20, 8192, 4, 1024, True), (20, 2048, 2, 8256, False), (20, 2048, 2, 8192, True), (20, 4096, 4, 7232, False),
+    (20, 3584, 1, 24576, True), (20, 3584, 1, 24640, False), (32, 3584, 1, 32768, True), (32, 3584, 1, 32832, False), (40, 3584, 1, 20480, True), (40, 3584, 1, 20544, False), (48, 1024, 1, 16384, True), (48, 1024, 1, 16448, False), (64, 1024, 1, 8192, True), (64, 1024, 1, 8256, False), (32, 2048, 1, 20480, True), (32, 2048, 1, 20544, False),
+    (17, 8192, 1, 960, False), (17, 8192, 1, 1024, True), (33, 8192, 1, 960, False), (33, 8192, 1, 1024, True), (24, 7168, 1, 960, False), (24, 7168, 1, 1024, True), (33, 7168, 1, 320, True), (17, 6144, 1, 320, True), (64, 4096, 14, 960, False), (64, 4096, 14, 1024, True), (48, 4096, 14, 384, False), (48, 4096, 14, 448, True), (32, 4096, 14, 320, True), (20, 8192, 4, 384, False), (20, 8192, 4, 448, True), (64, 2048, 2, 10240, True), (64, 2048, 2, 10304, False), (20, 2048, 2, 14336, True), (20, 4096, 16, 1792, True), (20, 4096, 16, 1856, False),
 ])
 def test_choice(M, d, batch, cap, want):
     assert choose.kslice_supported(V, M, d, batch, cap) == want
