@@ -71,6 +71,7 @@ hipError_t ensure_device_configured() {
   e = head_configure_device();
   if (e == hipSuccess) e = vocab_configure_device();
   if (e == hipSuccess) e = calib_configure_device();
+  if (e == hipSuccess) e = union_configure_device();
   if (e == hipSuccess) e = wide_configure_device();
   if (e == hipSuccess) e = hold_configure_device();
   if (e == hipSuccess) e = kslice_configure_device();

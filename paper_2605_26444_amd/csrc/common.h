@@ -159,6 +159,7 @@ hipError_t launch_head_kslice(const void* W, const void* H, const int32_t* ids, 
                               int32_t d, int64_t ld, int64_t ids_stride, float* logits, const int32_t* opos, hipStream_t s);
 
 // union.hip
+hipError_t union_configure_device();
 hipError_t launch_union_reset(const nanospec_state* st, hipStream_t s);
 hipError_t launch_union_build(const nanospec_state* st, hipStream_t s);
 

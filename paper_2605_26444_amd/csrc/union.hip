@@ -36,28 +36,46 @@ __global__ __launch_bounds__(1024) void union_count_kernel(VocabPtrs p, UnionPtr
   if (lane == 0) u.shared_bits[w] = pop;
 }
 
+// Lists longer than this are walked, shorter ones written from the bits (see union_lists_kernel).
+constexpr int kWalkFrom = 1024;
+constexpr int kListsLds = 150 * 1024;
+
 // One workgroup per sequence, N consecutive bitmap words per thread: everything follows from the bitmaps, fetched together in one round trip.  A shared id's rank is the
-// count of shared bits before it (workgroup 0 writes the list), its column in this sequence the count of active bits before it; an active bit that is not
-// shared -- or whose rank finds no room on the list -- goes to the sequence's own list, at the count of such bits before it.  Three DPP scans, two barriers.  Against the walk over the
-// id list that it replaces -- two look-ups per id, a rank among 1024 threads per 1024 ids, all columns cleared first --, with the counts: 64 sequences of 2300, V = 128256
-// 13.9 -> 10.1 us, 16 of 600, V = 32000 7.7 -> 6.6, 130 of 2000, V = 152064 19.1 -> 16.3, 48 of 6000 20.0 -> 20.6.
+// count of shared bits before it (each workgroup writes the list of its share of the words), its column in this sequence the count of active bits before it; an active bit that is not
+// shared -- or whose rank finds no room on the list -- goes to the sequence's own list, at the count of such bits before it.  Three DPP scans, two barriers.
+// Long lists are walked instead: their ids, coalesced, each with one look-up in an LDS table of its bitmap word -- a thread's bits are as many as the list is long in its part of the ids, all
+// one after the other, where ids cluster a few threads write the whole list, and nothing is coalesced.  Against the walk with two look-ups and a rank per id that came before the bits / the bits alone, with the
+// counts: 64 lists of 2000, V = 128256 14.1 / - / 10.1 us, of 8000 21.7 / 25.2 / 14.3, of 20000 45.9 / 53.3 / 25.2; 130 of 8000, V = 152064 28.0 / 43.7 / 23.1; 24 of 5000, V = 50000 16.1 / 15.1 / 11.7.
+// Walked over bits: up to 1.06 below 500 ids, at most 1.00 from 800 on.
 template <int N>
-__global__ __launch_bounds__(kListThreads) void union_lists_kernel(VocabPtrs p, UnionPtrs u, int groups) {
+__global__ __launch_bounds__(kListThreads) void union_lists_kernel(VocabPtrs p, UnionPtrs u, int batch, int groups, int tables) {
   constexpr int NW = kListThreads / 64;
   static_assert(NW == 16, "a row of lanes holds one total per wavefront");
+  extern __shared__ __attribute__((aligned(16))) uint4 tab[];   // per word: shared bits, active shared bits, rank of the first shared bit, active shared bits before
   __shared__ int s_shared[NW], s_active[NW], s_rest[NW];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, b = blockIdx.x, w0 = tid * N;
   const uint32_t* gw = p.wbit + (size_t)b * p.nwords;
   const uint32_t* gt = p.tbit + (size_t)b * p.nwords;
+  int32_t* mypos = u.shared_pos + (size_t)b * u.shared_cap;
+  const int n = p.n[b];
   uint32_t sh[N], ac[N];
   if constexpr (N == 1) {
     sh[0] = w0 < p.nwords ? u.shared_bits[w0] : 0u;
     ac[0] = w0 < p.nwords ? gw[w0] | gt[w0] : 0u;
+  } else if constexpr (N == 2) {
+    uint2 x = make_uint2(0, 0), y = x, z = x;
+    if (w0 < p.nwords) {                                                 // nwords is a multiple of 4
+      x = *reinterpret_cast<const uint2*>(u.shared_bits + w0);
+      y = *reinterpret_cast<const uint2*>(gw + w0);
+      z = *reinterpret_cast<const uint2*>(gt + w0);
+    }
+    sh[0] = x.x; sh[1] = x.y;
+    ac[0] = y.x | z.x; ac[1] = y.y | z.y;
   } else {
 #pragma unroll
     for (int c = 0; c < N; c += 4) {
       uint4 x = make_uint4(0, 0, 0, 0), y = x, z = x;
-      if (w0 + c < p.nwords) {                                           // nwords is a multiple of 4
+      if (w0 + c < p.nwords) {
         x = *reinterpret_cast<const uint4*>(u.shared_bits + w0 + c);
         y = *reinterpret_cast<const uint4*>(gw + w0 + c);
         z = *reinterpret_cast<const uint4*>(gt + w0 + c);
@@ -66,6 +84,7 @@ __global__ __launch_bounds__(kListThreads) void union_lists_kernel(VocabPtrs p, 
       ac[c] = y.x | z.x; ac[c + 1] = y.y | z.y; ac[c + 2] = y.z | z.z; ac[c + 3] = y.w | z.w;
     }
   }
+  for (int i = tid; i < u.shared_cap; i += kListThreads) mypos[i] = -1;   // shared ids the sequence lacks, and room that none takes; the barriers below are between these and the columns
   int ns = 0, na = 0;
 #pragma unroll
   for (int i = 0; i < N; ++i) {
@@ -79,8 +98,8 @@ __global__ __launch_bounds__(kListThreads) void union_lists_kernel(VocabPtrs p, 
   }
   __syncthreads();
   const int ts = s_shared[lane & 15], ta = s_active[lane & 15];
-  int r = row_sum((lane & 15) < wave ? ts : 0) + si - ns;          // rank of this thread's first shared bit
-  int pos = row_sum((lane & 15) < wave ? ta : 0) + ai - na;        // column of its first active bit
+  int r = row_sum((lane & 15) < wave ? ts : 0) + si - ns;                // rank of this thread's first shared bit
+  int pos = row_sum((lane & 15) < wave ? ta : 0) + ai - na;              // column of its first active bit
   const int all = row_sum(ts), listed = all < u.shared_cap ? all : u.shared_cap;
   if (r + ns > u.shared_cap) {                                           // bits without room on the list are not shared
     int room = u.shared_cap - r;
@@ -99,27 +118,54 @@ __global__ __launch_bounds__(kListThreads) void union_lists_kernel(VocabPtrs p, 
   __syncthreads();
   const int tr = s_rest[lane & 15], nrest = row_sum(tr);
   int q = row_sum((lane & 15) < wave ? tr : 0) + ri - nr;
-  int32_t* mypos = u.shared_pos + (size_t)b * u.shared_cap;
   int32_t* rid = u.rest_ids + (size_t)b * p.cap;
   int32_t* rpos = u.rest_pos + (size_t)b * p.cap;
+  if ((tid * batch) >> 10 == b) {                                        // this workgroup's share of the list of shared ids
+    int at = r;
 #pragma unroll
-  for (int i = 0; i < N; ++i) {
-    for (uint32_t x = sh[i] | ac[i]; x; x &= x - 1u) {
-      const uint32_t bit = x & (0u - x);
-      const int id = (w0 + i) * 32 + __ffs(x) - 1;
-      if (sh[i] & bit) {
-        mypos[r] = ac[i] & bit ? pos : -1;
-        if (b == 0) u.shared_ids[r] = id;
-        ++r;
+    for (int i = 0; i < N; ++i)
+      for (uint32_t x = sh[i]; x; x &= x - 1u) u.shared_ids[at++] = (w0 + i) * 32 + __ffs(x) - 1;
+  }
+  if (tables && n > kWalkFrom) {
+    int rank = r, before = pos - q;                                      // active shared bits before this thread's words
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      if (w0 + i < p.nwords) tab[w0 + i] = make_uint4(sh[i], ac[i] & sh[i], (uint32_t)rank, (uint32_t)before);
+      rank += __popc(sh[i]);
+      before += __popc(ac[i] & sh[i]);
+    }
+    __syncthreads();
+    const int32_t* ids = p.ids + (size_t)b * p.cap;
+    for (int j = tid; j < n; j += kListThreads) {
+      const int id = ids[j];
+      const uint4 t = tab[id >> 5];
+      const uint32_t below = (1u << (id & 31)) - 1u;
+      if ((t.x >> (id & 31)) & 1u) {
+        mypos[t.z + __popc(t.x & below)] = j;
       } else {
-        rid[q] = id;
-        rpos[q] = pos;
-        ++q;
+        const int at = j - (int)t.w - __popc(t.y & below);
+        rid[at] = id;
+        rpos[at] = j;
       }
-      pos += ac[i] & bit ? 1 : 0;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      for (uint32_t x = ac[i]; x; x &= x - 1u) {
+        const uint32_t bit = x & (0u - x);
+        const int id = (w0 + i) * 32 + __ffs(x) - 1;
+        if (sh[i] & bit) {
+          mypos[r + __popc(sh[i] & (bit - 1u))] = pos;
+        } else {
+          rid[q] = id;
+          rpos[q] = pos;
+          ++q;
+        }
+        ++pos;
+      }
+      r += __popc(sh[i]);
     }
   }
-  for (int i = listed + tid; i < u.shared_cap; i += kListThreads) mypos[i] = -1;
   if (b == 0)
     for (int g = tid; g < groups; g += kListThreads) u.shared_n[g] = listed;
   if (tid == 0) u.rest_n[b] = nrest;
@@ -137,6 +183,16 @@ __global__ __launch_bounds__(256) void union_reset_kernel(UnionPtrs u, int batch
   for (int64_t x = i; x < groups; x += stride) u.shared_n[x] = 0;
 }
 
+hipError_t union_configure_device() {
+  const void* fns[] = {reinterpret_cast<const void*>(union_lists_kernel<1>), reinterpret_cast<const void*>(union_lists_kernel<2>), reinterpret_cast<const void*>(union_lists_kernel<4>),
+                       reinterpret_cast<const void*>(union_lists_kernel<8>), reinterpret_cast<const void*>(union_lists_kernel<16>)};
+  for (const void* f : fns) {
+    hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kListsLds);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 hipError_t launch_union_reset(const nanospec_state* st, hipStream_t s) {
   union_reset_kernel<<<256, 256, 0, s>>>(st->un, st->batch, st->vp.cap, st->un_groups);
   return hipGetLastError();
@@ -147,10 +203,14 @@ hipError_t launch_union_build(const nanospec_state* st, hipStream_t s) {
   union_count_kernel<<<(nw + 15) / 16, 1024, 0, s>>>(st->vp, st->un, st->batch);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (nw <= kListThreads) union_lists_kernel<1><<<st->batch, kListThreads, 0, s>>>(st->vp, st->un, st->un_groups);
-  else if (nw <= 4 * kListThreads) union_lists_kernel<4><<<st->batch, kListThreads, 0, s>>>(st->vp, st->un, st->un_groups);
-  else if (nw <= 8 * kListThreads) union_lists_kernel<8><<<st->batch, kListThreads, 0, s>>>(st->vp, st->un, st->un_groups);
-  else if (nw <= 16 * kListThreads) union_lists_kernel<16><<<st->batch, kListThreads, 0, s>>>(st->vp, st->un, st->un_groups);
+  const int64_t tables = 16ll * nw;                                       // of lists that are walked; 300 000 ids and more are always written from the bits
+  const int walk = st->vp.cap > kWalkFrom && tables <= kListsLds;
+  const unsigned lds = walk ? (unsigned)tables : 0u;
+  if (nw <= kListThreads) union_lists_kernel<1><<<st->batch, kListThreads, lds, s>>>(st->vp, st->un, st->batch, st->un_groups, walk);
+  else if (nw <= 2 * kListThreads) union_lists_kernel<2><<<st->batch, kListThreads, lds, s>>>(st->vp, st->un, st->batch, st->un_groups, walk);
+  else if (nw <= 4 * kListThreads) union_lists_kernel<4><<<st->batch, kListThreads, lds, s>>>(st->vp, st->un, st->batch, st->un_groups, walk);
+  else if (nw <= 8 * kListThreads) union_lists_kernel<8><<<st->batch, kListThreads, lds, s>>>(st->vp, st->un, st->batch, st->un_groups, walk);
+  else if (nw <= 16 * kListThreads) union_lists_kernel<16><<<st->batch, kListThreads, lds, s>>>(st->vp, st->un, st->batch, st->un_groups, walk);
   else return hipErrorInvalidValue;                                       // more ids than a state takes: its bitmaps fill LDS three times over
   return hipGetLastError();
 }

@@ -287,3 +287,30 @@ def test_union_head_on_either_side_of_the_choice_to_split(M, d, split):
         w, h, n = W[torch.from_numpy(ids[b]).long().cuda()].double(), H[b].double(), len(ids[b])
         assert torch.all((logits[b, :, :n].double() - h @ w.T).abs() <= d * 2.0 ** -24 * (h.abs() @ w.abs().T)), b
     st.close()
+
+
+@pytest.mark.parametrize("V,window,share,shared_cap", [(20000, 6000, 3, 0), (32800, 6000, 1, 64), (128256, 9000, 2, 0), (128256, 9000, 3, 1024), (262400, 4000, 2, 0), (320032, 4000, 2, 256)])
+def test_lists_of_any_length(V, window, share, shared_cap):
+    """long lists are walked, short ones written from the bits, one beside the other in a batch; a shared list without room for all; vocabularies of every words-per-thread, up
+    to one whose tables do not fit LDS.  Ids and columns are the oracle's exactly."""
+    rng = np.random.default_rng(V)
+    common = np.concatenate([[0, 31, 32, V - 1], rng.permutation(V)[:window // 2]])
+    sizes = [window, 1025, 1024, 0, 1, 3500, 700]
+    ids = []
+    for n in sizes:
+        pool = np.unique(np.concatenate([common[rng.random(len(common)) < 0.7], rng.permutation(V)[:window]]))
+        ids.append(np.sort(rng.permutation(pool)[:n]).astype(np.int32))
+    assert [len(x) for x in ids] == sizes
+    st = B.State(V, 64, len(sizes), window, 1, 1, 1)
+    B.nanospec_union_enable(st.h, share, shared_cap)
+    for trial in range(2):                                   # the second build finds the first one's lists in place
+        flat, off = csr(ids)
+        B.nanospec_vocab_init(st.h, dev_ids(flat), off, None, np.zeros(len(sizes) + 1, np.int32))
+        B.nanospec_union_build(st.h)
+        sid, spos, rest, got_share, cap = st.read_union()
+        e_sid, e_pos, e_rest = oracle.shared_rows(ids, share, cap)
+        assert got_share == share and np.array_equal(sid, e_sid) and np.array_equal(spos, e_pos)
+        for b in range(len(sizes)):
+            assert np.array_equal(rest[b][0], e_rest[b][0]) and np.array_equal(rest[b][1], e_rest[b][1]), b
+        ids = ids[1:] + ids[:1]
+    st.close()
