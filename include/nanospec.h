@@ -206,27 +206,30 @@ NANOSPEC_API nanospec_status nanospec_packed_view(const nanospec_state* st, cons
                                                   const int32_t** d_out_pos, const int32_t** d_counts);
 
 /* Several sequences in one state (multi-sequence serving; Sec. 4.6 states only that the method's per-sequence cost
- * adds up over the batch): sequences drawing from one token distribution hold many of the same ids, and
- * nanospec_sparse_head fetches such a row once per sequence.  The batch-union head splits the active sets: an id
- * held by at least `min_share` of the sequences is a shared row -- listed once, fetched once, multiplied with the
- * hidden rows of all sequences --, every other id stays on a per-sequence list and is handled as before.  Every
- * (sequence, active id) pair is covered by exactly one part and its logit lands in the column the id has in that
- * sequence's ascending active list: the logits have the layout of nanospec_sparse_head (a sequence that lacks a
- * shared row has no column for it) and nanospec_topk_remap / nanospec_topk_logprob_remap apply unchanged.
+ * adds up over the batch): sequences drawing from one token distribution hold many of the same ids.  The lists split
+ * the active sets: an id held by at least `min_share` of the sequences is a shared row, listed once; every other id
+ * stays on a per-sequence list, and every (sequence, active id) pair is covered by exactly one part.  The head gives the
+ * logits of nanospec_sparse_head, in its layout, so that nanospec_topk_remap / nanospec_topk_logprob_remap apply
+ * unchanged.  How it computes them is chosen for speed, with batch * capacity the number of pairs there is room for:
+ *   - M <= 4, d >= 2048, batch * capacity >= 196608: from the split -- shared rows fetched once and multiplied with the
+ *     hidden rows of all sequences, the others per sequence;
+ *   - else M <= 16, batch * capacity >= 40960: as nanospec_union_build found the overlap, from the split where the
+ *     sequences hold nearly the same ids, else every list whole;
+ *   - else as nanospec_sparse_head, whose launch order has sequences find the rows they share in cache; min_share and
+ *     shared_cap then shape the lists only.
  *   nanospec_union_bytes  : device bytes nanospec_union_enable allocates for the given shared_cap (-1: bad argument).
  *   nanospec_union_enable : allocate and clear the lists.  min_share: 0 = max(2, batch/8).  shared_cap: room on the
  *                           shared list, a multiple of 64 in [64, capacity], 0 = capacity; when more ids qualify the
  *                           lowest shared_cap are shared and the others stay per sequence.  Synchronous; once per
  *                           state.  Errors: EINVAL (bad arguments, already enabled), ENOMEM, EHIP.
- *   nanospec_union_build  : rebuild the lists from the current vocabulary state (two launches); call after every
- *                           vocabulary call and before nanospec_union_head; it needs no hidden states, so it may run
- *                           beside the draft backbone.  Asynchronous.  Errors: EINVAL (not enabled), EHIP.
+ *   nanospec_union_build  : rebuild the lists from the current vocabulary state (two launches); it needs no hidden
+ *                           states, so it may run beside the draft backbone.  Asynchronous.  Errors: EINVAL (not enabled), EHIP.
  *   nanospec_union_head   : d_logits fp32 [batch][M][capacity] as nanospec_sparse_head (entries j >= n_b
- *                           unspecified), from d_W_bf16 [V][d] and d_H_bf16 [batch][M][d].  Works from the lists of the
- *                           last nanospec_union_build where that is the faster way (very many rows, few hidden rows
- *                           each), else as nanospec_sparse_head, whose launch order has the sequences find the rows
- *                           they share in cache.  Two calls on one state must not overlap.  Asynchronous.
- *                           Errors: EINVAL, ECAPACITY (M > m_cap), EHIP.
+ *                           unspecified), from d_W_bf16 [V][d] and d_H_bf16 [batch][M][d].  Call after a vocabulary call
+ *                           and the nanospec_union_build that follows it: where it works from the lists they are those of
+ *                           the last build, where it does not it reads the active sets themselves, so that a
+ *                           vocabulary call between build and head leaves the two out of step.  Two calls on one state
+ *                           must not overlap.  Asynchronous.  Errors: EINVAL, ECAPACITY (M > m_cap), EHIP.
  *   nanospec_union_view   : borrowed device views for inspection: shared ids [shared_cap] and their number
  *                           (first entry of d_shared_n), shared_pos [batch][shared_cap] (column or -1), rest ids
  *                           and columns [batch][capacity], rest_n [batch]; any pointer may be NULL. */

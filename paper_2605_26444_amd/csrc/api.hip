@@ -265,7 +265,8 @@ int64_t nanospec_union_bytes(const nanospec_state* st, int32_t shared_cap) {
   if (shared_cap < 64 || shared_cap % 64 != 0 || shared_cap > cap) return -1;
   const int64_t groups = (B * st->m_cap + 63) / 64;
   return 2 * round_up(nw * 4, 256) /* twice the bitmap: the size is part of the interface */ + round_up((int64_t)shared_cap * 4, 256) + round_up(groups * 4, 256) +
-         round_up(B * shared_cap * 4, 256) + 2 * round_up(B * cap * 4, 256) + round_up(B * 4, 256);
+         round_up(B * shared_cap * 4, 256) + 2 * round_up(B * cap * 4, 256) + round_up(B * 4, 256) +
+         (union_feeds(st->batch, st->vp.cap) ? round_up((nw + 15) / 16 * 8, 256) + 2 * round_up(B * cap * 4, 256) + round_up(B * 4, 256) + round_up(groups * 4, 256) : 0);
 }
 
 nanospec_status nanospec_union_enable(nanospec_state* st, int32_t min_share, int32_t shared_cap) {
@@ -294,6 +295,13 @@ nanospec_status nanospec_union_enable(nanospec_state* st, int32_t min_share, int
   u.rest_ids = reinterpret_cast<int32_t*>(take(B * cap * 4));
   u.rest_pos = reinterpret_cast<int32_t*>(take(B * cap * 4));
   u.rest_n = reinterpret_cast<int32_t*>(take(B * 4));
+  if (union_feeds(st->batch, st->vp.cap)) {
+    u.parts = reinterpret_cast<int2*>(take((nw + 15) / 16 * 8));
+    u.head_ids = reinterpret_cast<int32_t*>(take(B * cap * 4));
+    u.head_pos = reinterpret_cast<int32_t*>(take(B * cap * 4));
+    u.head_n = reinterpret_cast<int32_t*>(take(B * 4));
+    u.head_shared_n = reinterpret_cast<int32_t*>(take((int64_t)st->un_groups * 4));
+  }
   st->un_base = base;
   if (p - base > bytes || launch_union_reset(st, nullptr) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
     (void)hipGetLastError();
@@ -316,15 +324,16 @@ nanospec_status nanospec_union_head(nanospec_state* st, const void* d_W_bf16, co
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   const UnionPtrs& u = st->un;
   const int32_t cap = st->vp.cap;
-  if (!union_split(M, st->d, st->batch, cap))               // the dies' L2s see most shared rows once without the lists
+  const bool always = union_split(M, st->d, st->batch, cap);
+  if (!always && (M > 16 || !u.parts))                      // the dies' L2s see most shared rows once without the lists
     return nanospec_sparse_head(st, d_W_bf16, d_H_bf16, M, d_logits, hip_stream);
-  // shared rows: fetched once, multiplied with every sequence's hidden rows, scattered to each sequence's columns
-  hipError_t e = launch_head_shared(d_W_bf16, d_H_bf16, u.shared_ids, u.shared_n, u.shared_cap, st->V, st->batch * M, M, st->d, cap,
+  // shared rows, if the lists say that there are any: fetched once, multiplied with every sequence's hidden rows, scattered to each sequence's columns
+  hipError_t e = launch_head_shared(d_W_bf16, d_H_bf16, u.shared_ids, always ? u.shared_n : u.head_shared_n, u.shared_cap, st->V, st->batch * M, M, st->d, cap,
                                     d_logits, u.shared_pos, u.shared_cap, s);
-  // the rest per sequence, exactly as nanospec_sparse_head but on the shorter lists
+  // the rest per sequence, exactly as nanospec_sparse_head but on the lists' columns
   if (e == hipSuccess)
-    e = launch_head(d_W_bf16, d_H_bf16, u.rest_ids, u.rest_n, 0, cap, st->V, st->batch, M, st->d, cap, cap, d_logits, st->partial, st->partial_bytes,
-                    u.rest_pos, s);
+    e = launch_head(d_W_bf16, d_H_bf16, always ? u.rest_ids : u.head_ids, always ? u.rest_n : u.head_n, 0, cap, st->V, st->batch, M, st->d, cap, cap, d_logits,
+                    st->partial, st->partial_bytes, always ? u.rest_pos : u.head_pos, s);
   return e == hipSuccess ? NANOSPEC_OK : NANOSPEC_EHIP;
 }
 

@@ -137,11 +137,25 @@ inline bool wide_by_die(int32_t M, int32_t batch, int32_t cap_rows, bool dense) 
   return batch >= 8 && M <= 16 && (M <= 8 || rows < 131072);
 }
 
-// Whether the batch-union head works from its lists -- shared rows once against all hidden rows, the rest per sequence -- or as the per-sequence head, whose workgroups
-// take the same eighth of every list on one die and so find most shared rows in its L2.  The latter over the former, 512 to 8192 columns, 2 to 64 sequences: M >= 8 0.28 to 0.92 of
-// the time (64 of 2300 x 4096, M = 8: 107 / 122 us, 36 of them for the shared rows and 84 for the rest, M = 64: 187 / 409); M = 4 0.3 to 0.99, but for most rows (64 of 6000 out of 7000
-// x 8192 502 / 451, x 4096 251 / 238, x 2048 124 / 119, x 1024 84 / 78; 64 of 2300 out of 5120 x 8192 213 / 202, x 4096 103 / 103, x 1024 32 / 37; 32 of 6000 x 8192 264 / 255; 32 of 5120 x 8192 114 / 125).
+// Whether the batch-union head always works from the split -- shared rows once against all hidden rows, the rest per sequence: few hidden rows on most rows.  The per-sequence head's time over the
+// split's, sequences that draw from one Zipf distribution, M <= 4: 64 of 6000 out of 7000 x 8192 502 / 451, x 4096 251 / 238, x 2048 124 / 119, x 1024 84 / 78; 64 of 2300 out of 5120 x 8192 213 /
+// 202, x 4096 103 / 103, x 1024 32 / 37; 32 of 6000 x 8192 264 / 255; 32 of 5120 x 8192 114 / 125.
 inline bool union_split(int32_t M, int32_t d, int32_t batch, int32_t cap_rows) { return M <= 4 && d >= 2048 && (int64_t)cap_rows * batch >= 196608; }
+
+// Elsewhere up to 16 hidden rows it is the lists that say: the per-sequence head's workgroups take the same eighth of every list on one die and so find most shared rows in its L2, which is the faster
+// way (512 to 8192 columns, 2 to 64 sequences from one Zipf distribution 0.3 to 0.95 of the split's time; 64 of 2300 x 4096, M = 8: 107 / 122 us, 36 of them for the shared rows and 84 for the rest) but
+// where the sequences hold nearly the same rows -- samples of one prompt, one candidate set for all -- and there are many pairs of a sequence and a row.  Split over whole lists with 0.7 / 0.8 / 0.9 / 0.95
+// / all rows in common: 130000 to 400000 pairs M <= 4 0.82 / 0.71 / 0.62 / 0.57 / 0.45, M = 8 0.90 / 0.80 / 0.76 / 0.72 / 0.57, M = 16 1.02 / 0.93 / 0.89 / 0.86 / 0.78; 65000 to 130000 0.96 / 0.88 / 0.80 / 0.74 / 0.57, 1.03 /
+// 0.96 / 0.90 / 0.85 / 0.65, 1.10 / 1.04 / 1.03 / 1.00 / 0.84; 40000 to 65000 1.09 / 1.00 / 0.93 / 0.90 / 0.76, 1.20 / 1.11 / 1.06 / 1.04 / 0.87, 1.19 / 1.06 / 1.03 / 1.05 / 0.77; fewer 1.2 to 1.7.  So the part of the pairs that
+// may be left per sequence grows with their number.  More than 16 hidden rows: 1.3 to 1.5, all rows in common 1.07 to 1.2.
+constexpr int32_t kUnionPairs = 40960;
+inline bool union_feeds(int32_t batch, int32_t cap_rows) { return (int64_t)cap_rows * batch >= kUnionPairs; }
+#if defined(__HIPCC__)
+__host__ __device__
+#endif
+inline bool union_split_pairs(int32_t pairs, int32_t rest) {
+  return pairs >= kUnionPairs && (int64_t)rest * 524288 <= (int64_t)pairs * (pairs < 196608 ? pairs : 196608);
+}
 
 // One list shared by the hidden rows of several sequences (see launch_head_shared): 64 sequences' hidden rows on 7400 rows 36 us with 64 x 64 blocks, 39 with 128 x 64,
 // 70 with 256 x 128 (too few workgroups).

@@ -15,25 +15,44 @@ namespace nanospec {
 constexpr int kListThreads = 1024;
 
 // One wavefront per bitmap word: lane q looks at sequence q's word (window bitmap | T bitmap); 32 ballots count,
-// for every bit, the sequences that hold the id.  (Four words to a wavefront, sixteen bytes a lane: 1.9 us slower, a chain of 128 ballots.)
+// for every bit, the sequences that hold the id.  (Four words to a wavefront, sixteen bytes a lane: 1.9 us slower, a chain of 128 ballots.)  FEED: u.parts gets, per workgroup, the
+// pairs of a sequence and an active id, and those of ids that qualify as shared.
+template <bool FEED>
 __global__ __launch_bounds__(1024) void union_count_kernel(VocabPtrs p, UnionPtrs u, int batch) {
-  const int lane = threadIdx.x & 63;
-  const int w = blockIdx.x * 16 + (threadIdx.x >> 6);
-  if (w >= p.nwords) return;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int w = blockIdx.x * 16 + wave;
+  if (!FEED && w >= p.nwords) return;
+  constexpr int NB = (NANOSPEC_MAX_BATCH + 63) / 64;
+  uint32_t word[NB];
   int cnt[32];
 #pragma unroll
   for (int i = 0; i < 32; ++i) cnt[i] = 0;
-  for (int b0 = 0; b0 < batch; b0 += 64) {
-    const int b = b0 + lane;
-    uint32_t word = 0u;
-    if (b < batch) word = p.wbit[(size_t)b * p.nwords + w] | p.tbit[(size_t)b * p.nwords + w];
 #pragma unroll
-    for (int i = 0; i < 32; ++i) cnt[i] += __popcll(__ballot((word >> i) & 1u));
+  for (int k = 0; k < NB; ++k) {
+    word[k] = 0u;
+    if (k * 64 >= batch) continue;
+    const int b = k * 64 + lane;
+    if (b < batch && (!FEED || w < p.nwords)) word[k] = p.wbit[(size_t)b * p.nwords + w] | p.tbit[(size_t)b * p.nwords + w];
+#pragma unroll
+    for (int i = 0; i < 32; ++i) cnt[i] += __popcll(__ballot((word[k] >> i) & 1u));
   }
   uint32_t pop = 0u;
 #pragma unroll
   for (int i = 0; i < 32; ++i) pop |= (cnt[i] >= u.min_share ? 1u : 0u) << i;
-  if (lane == 0) u.shared_bits[w] = pop;
+  if (lane == 0 && (!FEED || w < p.nwords)) u.shared_bits[w] = pop;
+  if constexpr (FEED) {
+    __shared__ int s_sum[16];
+    int both = 0;                                                        // at most 8192 pairs to a word: two sums in one register
+#pragma unroll
+    for (int k = 0; k < NB; ++k) both += __popc(word[k]) << 16 | __popc(word[k] & pop);
+    both = wave_incl_scan(both);
+    if (lane == 63) s_sum[wave] = both;
+    __syncthreads();
+    if (wave == 0) {
+      const int x = s_sum[lane & 15], a = row_sum(x >> 16), c = row_sum(x & 0xffff);
+      if (lane == 0) u.parts[blockIdx.x] = make_int2(a, c);
+    }
+  }
 }
 
 // Lists longer than this are walked, shorter ones written from the bits (see union_lists_kernel).
@@ -47,12 +66,14 @@ constexpr int kListsLds = 150 * 1024;
 // one after the other, where ids cluster a few threads write the whole list, and nothing is coalesced.  Against the walk with two look-ups and a rank per id that came before the bits / the bits alone, with the
 // counts: 64 lists of 2000, V = 128256 14.1 / - / 10.1 us, of 8000 21.7 / 25.2 / 14.3, of 20000 45.9 / 53.3 / 25.2; 130 of 8000, V = 152064 28.0 / 43.7 / 23.1; 24 of 5000, V = 50000 16.1 / 15.1 / 11.7.
 // Walked over bits: up to 1.06 below 500 ids, at most 1.00 from 800 on.
+// What the head works from (u.head_*, kept where union_feeds says so): the split, or nothing shared and every list whole, by how many pairs the shared ids cover in
+// all sequences together; every workgroup comes to the same answer from the counts.
 template <int N>
 __global__ __launch_bounds__(kListThreads) void union_lists_kernel(VocabPtrs p, UnionPtrs u, int batch, int groups, int tables) {
   constexpr int NW = kListThreads / 64;
   static_assert(NW == 16, "a row of lanes holds one total per wavefront");
   extern __shared__ __attribute__((aligned(16))) uint4 tab[];   // per word: shared bits, active shared bits, rank of the first shared bit, active shared bits before
-  __shared__ int s_shared[NW], s_active[NW], s_rest[NW];
+  __shared__ int s_shared[NW], s_active[NW], s_rest[NW], s_pairs[NW], s_cover[NW];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, b = blockIdx.x, w0 = tid * N;
   const uint32_t* gw = p.wbit + (size_t)b * p.nwords;
   const uint32_t* gt = p.tbit + (size_t)b * p.nwords;
@@ -84,6 +105,8 @@ __global__ __launch_bounds__(kListThreads) void union_lists_kernel(VocabPtrs p, 
       ac[c] = y.x | z.x; ac[c + 1] = y.y | z.y; ac[c + 2] = y.z | z.z; ac[c + 3] = y.w | z.w;
     }
   }
+  int2 part = make_int2(0, 0);
+  if (u.parts && tid < (p.nwords + 15) / 16) part = u.parts[tid];        // at most 1024 of them: a state has fewer than 16384 words
   for (int i = tid; i < u.shared_cap; i += kListThreads) mypos[i] = -1;   // shared ids the sequence lacks, and room that none takes; the barriers below are between these and the columns
   int ns = 0, na = 0;
 #pragma unroll
@@ -96,11 +119,23 @@ __global__ __launch_bounds__(kListThreads) void union_lists_kernel(VocabPtrs p, 
     s_shared[wave] = si;
     s_active[wave] = ai;
   }
+  if (u.parts) {
+    const int pi = wave_incl_scan(part.x), ci = wave_incl_scan(part.y);
+    if (lane == 63) {
+      s_pairs[wave] = pi;
+      s_cover[wave] = ci;
+    }
+  }
   __syncthreads();
   const int ts = s_shared[lane & 15], ta = s_active[lane & 15];
   int r = row_sum((lane & 15) < wave ? ts : 0) + si - ns;                // rank of this thread's first shared bit
   int pos = row_sum((lane & 15) < wave ? ta : 0) + ai - na;              // column of its first active bit
   const int all = row_sum(ts), listed = all < u.shared_cap ? all : u.shared_cap;
+  bool split = false;
+  if (u.parts) {
+    const int pairs = row_sum(s_pairs[lane & 15]);
+    split = union_split_pairs(pairs, pairs - row_sum(s_cover[lane & 15]));
+  }
   if (r + ns > u.shared_cap) {                                           // bits without room on the list are not shared
     int room = u.shared_cap - r;
 #pragma unroll
@@ -120,6 +155,8 @@ __global__ __launch_bounds__(kListThreads) void union_lists_kernel(VocabPtrs p, 
   int q = row_sum((lane & 15) < wave ? tr : 0) + ri - nr;
   int32_t* rid = u.rest_ids + (size_t)b * p.cap;
   int32_t* rpos = u.rest_pos + (size_t)b * p.cap;
+  int32_t* hid = u.parts ? u.head_ids + (size_t)b * p.cap : nullptr;
+  int32_t* hpos = u.parts ? u.head_pos + (size_t)b * p.cap : nullptr;
   if ((tid * batch) >> 10 == b) {                                        // this workgroup's share of the list of shared ids
     int at = r;
 #pragma unroll
@@ -146,6 +183,14 @@ __global__ __launch_bounds__(kListThreads) void union_lists_kernel(VocabPtrs p, 
         const int at = j - (int)t.w - __popc(t.y & below);
         rid[at] = id;
         rpos[at] = j;
+        if (hid && split) {
+          hid[at] = id;
+          hpos[at] = j;
+        }
+      }
+      if (hid && !split) {
+        hid[j] = id;
+        hpos[j] = j;
       }
     }
   } else {
@@ -159,7 +204,15 @@ __global__ __launch_bounds__(kListThreads) void union_lists_kernel(VocabPtrs p, 
         } else {
           rid[q] = id;
           rpos[q] = pos;
+          if (hid && split) {
+            hid[q] = id;
+            hpos[q] = pos;
+          }
           ++q;
+        }
+        if (hid && !split) {
+          hid[pos] = id;
+          hpos[pos] = pos;
         }
         ++pos;
       }
@@ -167,8 +220,14 @@ __global__ __launch_bounds__(kListThreads) void union_lists_kernel(VocabPtrs p, 
     }
   }
   if (b == 0)
-    for (int g = tid; g < groups; g += kListThreads) u.shared_n[g] = listed;
-  if (tid == 0) u.rest_n[b] = nrest;
+    for (int g = tid; g < groups; g += kListThreads) {
+      u.shared_n[g] = listed;
+      if (hid) u.head_shared_n[g] = split ? listed : 0;
+    }
+  if (tid == 0) {
+    u.rest_n[b] = nrest;
+    if (hid) u.head_n[b] = split ? nrest : n;
+  }
 }
 
 __global__ __launch_bounds__(256) void union_reset_kernel(UnionPtrs u, int batch, int cap, int groups) {
@@ -181,6 +240,13 @@ __global__ __launch_bounds__(256) void union_reset_kernel(UnionPtrs u, int batch
   for (int64_t x = i; x < u.shared_cap; x += stride) u.shared_ids[x] = 0;
   for (int64_t x = i; x < batch; x += stride) u.rest_n[x] = 0;
   for (int64_t x = i; x < groups; x += stride) u.shared_n[x] = 0;
+  if (!u.parts) return;
+  for (int64_t x = i; x < (int64_t)batch * cap; x += stride) {
+    u.head_ids[x] = 0;
+    u.head_pos[x] = -1;
+  }
+  for (int64_t x = i; x < batch; x += stride) u.head_n[x] = 0;
+  for (int64_t x = i; x < groups; x += stride) u.head_shared_n[x] = 0;
 }
 
 hipError_t union_configure_device() {
@@ -200,7 +266,8 @@ hipError_t launch_union_reset(const nanospec_state* st, hipStream_t s) {
 
 hipError_t launch_union_build(const nanospec_state* st, hipStream_t s) {
   const int nw = st->vp.nwords;
-  union_count_kernel<<<(nw + 15) / 16, 1024, 0, s>>>(st->vp, st->un, st->batch);
+  if (st->un.parts) union_count_kernel<true><<<(nw + 15) / 16, 1024, 0, s>>>(st->vp, st->un, st->batch);
+  else union_count_kernel<false><<<(nw + 15) / 16, 1024, 0, s>>>(st->vp, st->un, st->batch);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int64_t tables = 16ll * nw;                                       // of lists that are walked; 300 000 ids and more are always written from the bits

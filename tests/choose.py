@@ -38,6 +38,8 @@ void c_kslice_plan(int M, int batch, int cap, int dense, int* o) {
   const SlicePlan p = kslice_plan(M, batch, cap, dense != 0);
   o[0] = p.LB; o[1] = p.parts; o[2] = p.hid_blocks; o[3] = p.rows;
 }
+int c_union_feeds(int batch, int cap) { return union_feeds(batch, cap); }
+int c_union_split_pairs(int pairs, int rest) { return union_split_pairs(pairs, rest); }
 int c_union_split(int M, int d, int batch, int cap) { return union_split(M, d, batch, cap); }
 int c_tile64_fast(int M, int d) { return tile64_fast(M, d); }
 }
@@ -91,6 +93,14 @@ def kslice_plan(M, batch, cap, dense=False):
 
 def union_split(M, d, batch, cap):
     return bool(_lib.c_union_split(M, d, batch, cap))
+
+
+def union_feeds(batch, cap):
+    return bool(_lib.c_union_feeds(batch, cap))
+
+
+def union_split_pairs(pairs, rest):
+    return bool(_lib.c_union_split_pairs(pairs, rest))
 
 
 def wide_reaches(V, M, d):

@@ -84,3 +84,10 @@ def test_selection_in_chunks():
     assert not choose.topk_chunks(8, 10, topk_cap=4000, window=13000) and not choose.topk_chunks(88, 10, topk_cap=65000)
     assert not choose.topk_chunks(8, 40, topk_cap=32000) and choose.topk_chunks(8, 40, topk_cap=128000)
     assert choose.topk_chunks(95, 40, dense=True) and not choose.topk_chunks(96, 1, dense=True)
+
+
+def test_batch_union_head():
+    assert not choose.union_feeds(16, 2496) and choose.union_feeds(16, 2560)
+    assert not choose.union_split_pairs(40959, 0) and choose.union_split_pairs(40960, 3200) and not choose.union_split_pairs(40960, 3201)        # 40 000 pairs: a thirteenth
+    assert choose.union_split_pairs(131072, 32768) and not choose.union_split_pairs(131072, 32769)                                            # 131 072: a quarter
+    assert choose.union_split_pairs(196608, 73728) and not choose.union_split_pairs(1 << 26, (1 << 26) * 3 // 8 + 1) and choose.union_split_pairs(1 << 26, (1 << 26) * 3 // 8)

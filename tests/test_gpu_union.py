@@ -314,3 +314,40 @@ def test_lists_of_any_length(V, window, share, shared_cap):
             assert np.array_equal(rest[b][0], e_rest[b][0]) and np.array_equal(rest[b][1], e_rest[b][1]), b
         ids = ids[1:] + ids[:1]
     st.close()
+
+
+@pytest.mark.parametrize("M,d,V,nb,n,common,shared_cap,split", [
+    (8, 1032, 20000, 30, 1800, 1790, 0, True), (16, 520, 20000, 70, 3300, 2800, 0, True), (1, 512, 20000, 30, 1800, 1790, 640, True),      # one row list serves (nearly) all; a shared list without room
+    (8, 1032, 20000, 30, 1800, 1500, 0, False), (16, 2048, 40000, 16, 3000, 0, 0, False), (17, 512, 20000, 30, 1800, 1790, 0, None),      # lists whole; more hidden rows never ask the lists
+])
+def test_head_from_whichever_lists_the_overlap_asks_for(M, d, V, nb, n, common, shared_cap, split):
+    """sequences with `common` ids in common, sequences of other lengths and an empty one beside them, the lists built again for the opposite overlap and back; every column of an active id is
+    written, within d * 2^-24 * sum |w h| of fp64"""
+    rng = np.random.default_rng(M + n)
+
+    def draw(common):
+        com = rng.permutation(V)[:common]
+        rest = np.setdiff1d(np.arange(V), com)
+        ids = [np.sort(np.concatenate([com, rng.permutation(rest)[:n - common]])).astype(np.int32) for _ in range(nb)]
+        ids[1], ids[2] = ids[1][:0], ids[2][:100]
+        return ids
+
+    W, H = (torch.randn(s, generator=torch.Generator().manual_seed(i)).to(torch.bfloat16).cuda() for i, s in enumerate(((V, d), (nb, M, d))))
+    st = B.State(V, d, nb, n, 1, M, 1)
+    B.nanospec_union_enable(st.h, 0, shared_cap)
+    assert choose.union_feeds(nb, st.capacity) and not choose.union_split(M, d, nb, st.capacity)
+    for trial, held in enumerate((common, n - common, common)):
+        ids = draw(held)
+        flat, off = csr(ids)
+        B.nanospec_vocab_init(st.h, dev_ids(flat), off, None, np.zeros(nb + 1, np.int32))
+        B.nanospec_union_build(st.h)
+        if split is not None and trial != 1:
+            count = np.bincount(flat, minlength=V)
+            assert choose.union_split_pairs(len(flat), int(count[count < max(2, nb // 8)].sum())) == split
+        logits = torch.full((nb, M, st.capacity), float("nan"), dtype=torch.float32, device="cuda")
+        B.nanospec_union_head(st.h, W, H, M, logits)
+        for b in range(nb):
+            w, h, k = W[torch.from_numpy(ids[b]).long().cuda()].double(), H[b].double(), len(ids[b])
+            assert torch.all((logits[b, :, :k].double() - h @ w.T).abs() <= d * 2.0 ** -24 * (h.abs() @ w.abs().T)), (trial, b)
+            assert torch.all(torch.isnan(logits[b, :, k:])), (trial, b)
+    st.close()
