@@ -14,67 +14,107 @@ namespace nanospec {
 
 constexpr int kListThreads = 1024;
 
-// One wavefront per bitmap word: lane q looks at sequence q's word (window bitmap | T bitmap); 32 ballots count,
-// for every bit, the sequences that hold the id.  (Four words to a wavefront, sixteen bytes a lane: 1.9 us slower, a chain of 128 ballots.)  FEED: u.parts gets, per workgroup, the
-// pairs of a sequence and an active id, and those of ids that qualify as shared.
-template <bool FEED>
-__global__ __launch_bounds__(1024) void union_count_kernel(VocabPtrs p, UnionPtrs u, int batch) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int w = blockIdx.x * 16 + wave;
-  if (!FEED && w >= p.nwords) return;
-  constexpr int NB = (NANOSPEC_MAX_BATCH + 63) / 64;
-  uint32_t word[NB];
-  int cnt[32];
+// acc += x, bit planes of 32 counts side by side (plane k holds bit k of each)
+template <int N, int NX>
+__device__ __forceinline__ void planes_add(uint32_t (&acc)[N], const uint32_t (&x)[NX]) {
+  uint32_t carry = 0u;
 #pragma unroll
-  for (int i = 0; i < 32; ++i) cnt[i] = 0;
-#pragma unroll
-  for (int k = 0; k < NB; ++k) {
-    word[k] = 0u;
-    if (k * 64 >= batch) continue;
-    const int b = k * 64 + lane;
-    if (b < batch && (!FEED || w < p.nwords)) word[k] = p.wbit[(size_t)b * p.nwords + w] | p.tbit[(size_t)b * p.nwords + w];
-#pragma unroll
-    for (int i = 0; i < 32; ++i) cnt[i] += __popcll(__ballot((word[k] >> i) & 1u));
-  }
-  uint32_t pop = 0u;
-#pragma unroll
-  for (int i = 0; i < 32; ++i) pop |= (cnt[i] >= u.min_share ? 1u : 0u) << i;
-  if (lane == 0 && (!FEED || w < p.nwords)) u.shared_bits[w] = pop;
-  if constexpr (FEED) {
-    __shared__ int s_sum[16];
-    int both = 0;                                                        // at most 8192 pairs to a word: two sums in one register
-#pragma unroll
-    for (int k = 0; k < NB; ++k) both += __popc(word[k]) << 16 | __popc(word[k] & pop);
-    both = wave_incl_scan(both);
-    if (lane == 63) s_sum[wave] = both;
-    __syncthreads();
-    if (wave == 0) {
-      const int x = s_sum[lane & 15], a = row_sum(x >> 16), c = row_sum(x & 0xffff);
-      if (lane == 0) u.parts[blockIdx.x] = make_int2(a, c);
-    }
+  for (int k = 0; k < N; ++k) {
+    const uint32_t y = k < NX ? x[k] : 0u, half = acc[k] ^ y, out = (acc[k] & y) | (half & carry);
+    acc[k] = half ^ carry;
+    carry = out;
   }
 }
 
-// Lists longer than this are walked, shorter ones written from the bits (see union_lists_kernel).
-constexpr int kWalkFrom = 1024;
+// Sixteen bitmap words (window bitmap | T bitmap) per workgroup, a row of 16 lanes each of them for one sequence: 64 bytes in one piece.  A thread adds its word of
+// sequences g, g + 16, ... into bit planes (32 counts at once, P planes), sixteen such sums meet in LDS, and the ids whose count reaches min_share are a borrow chain over the planes.
+// What bounds it is the round trip of its loads.  A wavefront per word with a sequence to each lane and 32 ballots, as before, took a cache line per lane and load, and its 160 scalar
+// instructions a wavefront share one scalar unit.  With the lists behind it: 64 sequences of 2300, V = 128256 9.0 -> 7.65 us, 16 of 600, V = 32000 6.9 -> 6.0, 130 of 8000, V = 152064
+// 21.3 -> 16.0, 256 of 2000, V = 128256 14.2 -> 11.0.  The two halves of a cache line on one die: the same.
+// u.parts, where kept: per workgroup the pairs of a sequence and an active id, and those of ids that qualify as shared.
+constexpr int kCountThreads = 256;
+template <int P>
+__global__ __launch_bounds__(kCountThreads) void union_count_kernel(VocabPtrs p, UnionPtrs u, int batch) {
+  constexpr int G = kCountThreads / 16, N = P + 4;                       // at most 2^(P - 1) words a thread, 16 threads a word
+  static_assert(G == 16, "four groups to a lane of the first wavefront, four lanes to a word");
+  __shared__ uint32_t s_plane[P][kCountThreads];
+  const int tid = threadIdx.x, lane = tid & 63, g = tid >> 4, w = blockIdx.x * 16 + (tid & 15);
+  const bool in = w < p.nwords;
+  uint32_t pl[P];
+#pragma unroll
+  for (int k = 0; k < P; ++k) pl[k] = 0u;
+  for (int s0 = 0; s0 < batch; s0 += 4 * G) {
+    uint32_t v[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int s = s0 + j * G + g;
+      const size_t at = (size_t)(s < batch ? s : 0) * p.nwords + (in ? w : 0);
+      v[j] = p.wbit[at] | p.tbit[at];
+      v[j] = in && s < batch ? v[j] : 0u;
+    }
+    const uint32_t h1 = v[0] ^ v[1], one = h1 ^ v[2], c1 = (v[0] & v[1]) | (h1 & v[2]), c2 = one & v[3];
+    planes_add(pl, {one ^ v[3], c1 ^ c2, c1 & c2});
+  }
+#pragma unroll
+  for (int k = 0; k < P; ++k) s_plane[k][tid] = pl[k];
+  __syncthreads();
+  if (tid >= 64) return;
+  uint32_t sum[N];
+#pragma unroll
+  for (int k = 0; k < N; ++k) sum[k] = 0u;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    uint32_t x[P];
+#pragma unroll
+    for (int k = 0; k < P; ++k) x[k] = s_plane[k][j * 64 + lane];
+    planes_add(sum, x);
+  }
+#pragma unroll
+  for (int o = 16; o < 64; o <<= 1) {
+    uint32_t x[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) x[k] = __shfl_xor(sum[k], o);
+    planes_add(sum, x);
+  }
+  uint32_t less = 0u;                                                    // bit = that count - min_share borrows
+#pragma unroll
+  for (int k = 0; k < N; ++k) less = (u.min_share >> k) & 1 ? less | ~sum[k] : less & ~sum[k];
+  const uint32_t pop = u.min_share >> N ? 0u : ~less;
+  if (lane < 16 && in) u.shared_bits[w] = pop;
+  if (u.parts) {
+    int pairs = 0, cover = 0;
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+      pairs += __popc(sum[k]) << k;
+      cover += __popc(sum[k] & pop) << k;
+    }
+    pairs = row_sum(pairs);
+    cover = row_sum(cover);
+    if (lane == 0) u.parts[blockIdx.x] = make_int2(pairs, cover);
+  }
+}
+
 constexpr int kListsLds = 150 * 1024;
 
-// One workgroup per sequence, N consecutive bitmap words per thread: everything follows from the bitmaps, fetched together in one round trip.  A shared id's rank is the
+// Per sequence, N consecutive bitmap words per thread: everything follows from the bitmaps, fetched together in one round trip.  A shared id's rank is the
 // count of shared bits before it (each workgroup writes the list of its share of the words), its column in this sequence the count of active bits before it; an active bit that is not
-// shared -- or whose rank finds no room on the list -- goes to the sequence's own list, at the count of such bits before it.  Three DPP scans, two barriers.
-// Long lists are walked instead: their ids, coalesced, each with one look-up in an LDS table of its bitmap word -- a thread's bits are as many as the list is long in its part of the ids, all
-// one after the other, where ids cluster a few threads write the whole list, and nothing is coalesced.  Against the walk with two look-ups and a rank per id that came before the bits / the bits alone, with the
-// counts: 64 lists of 2000, V = 128256 14.1 / - / 10.1 us, of 8000 21.7 / 25.2 / 14.3, of 20000 45.9 / 53.3 / 25.2; 130 of 8000, V = 152064 28.0 / 43.7 / 23.1; 24 of 5000, V = 50000 16.1 / 15.1 / 11.7.
-// Walked over bits: up to 1.06 below 500 ids, at most 1.00 from 800 on.
+// shared -- or whose rank finds no room on the list -- goes to the sequence's own list, at the count of such bits before it.  Three DPP scans.
+// The list is then walked: its ids, coalesced, each with one look-up in an LDS table of its bitmap word -- written from the bits themselves, a thread's are as many as the list is long in its part of the ids,
+// all one after the other, where ids cluster a few threads write the whole list, and nothing is coalesced.  Figures with the counts; the bits / walked, one workgroup a sequence:
+// 64 lists of 2300, V = 128256 10.2 / 9.9 us, of 20000 44.6 / 20.8, 130 of 8000, V = 152064 32.3 / 21.7, 24 of 5000, V = 50000 15.4 / 10.0; with the workgroups below 64 of 300 7.1 / 6.5, 16 of 300, V = 32000 5.9 / 5.6.
+// A workgroup's sixteen wavefronts share four SIMDs, so up to four workgroups (gridDim.y, as many as fill the chip) write a sequence's lists, each for `per` threads' words and from its own scans of them all:
+// 64 lists of 2300 9.9 -> 9.0 us, of 20000 20.8 -> 15.3, 8 of 3000 8.8 -> 7.7, 40 of 4000, V = 262400 17.8 -> 15.5 (eight: 0.1 us less for 8 and 24 sequences; two: 0.3 more for 64).
 // What the head works from (u.head_*, kept where union_feeds says so): the split, or nothing shared and every list whole, by how many pairs the shared ids cover in
 // all sequences together; every workgroup comes to the same answer from the counts.
 template <int N>
-__global__ __launch_bounds__(kListThreads) void union_lists_kernel(VocabPtrs p, UnionPtrs u, int batch, int groups, int tables) {
+__global__ __launch_bounds__(kListThreads) void union_lists_kernel(VocabPtrs p, UnionPtrs u, int batch, int groups, int per) {
   constexpr int NW = kListThreads / 64;
   static_assert(NW == 16, "a row of lanes holds one total per wavefront");
-  extern __shared__ __attribute__((aligned(16))) uint4 tab[];   // per word: shared bits, active shared bits, rank of the first shared bit, active shared bits before
-  __shared__ int s_shared[NW], s_active[NW], s_rest[NW], s_pairs[NW], s_cover[NW];
+  extern __shared__ __attribute__((aligned(16))) uint4 tab[];   // per word of this workgroup: shared bits, active shared bits, rank of the first shared bit, active shared bits before
+  __shared__ int s_shared[NW], s_active[NW], s_rest[NW], s_pairs[NW], s_cover[NW], s_rank[2], s_pos[2];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, b = blockIdx.x, w0 = tid * N;
+  const int first = blockIdx.y * per, final = blockIdx.y == gridDim.y - 1;
+  const bool mine = tid >= first && tid < first + per;
   const uint32_t* gw = p.wbit + (size_t)b * p.nwords;
   const uint32_t* gt = p.tbit + (size_t)b * p.nwords;
   int32_t* mypos = u.shared_pos + (size_t)b * u.shared_cap;
@@ -105,9 +145,8 @@ __global__ __launch_bounds__(kListThreads) void union_lists_kernel(VocabPtrs p, 
       ac[c] = y.x | z.x; ac[c + 1] = y.y | z.y; ac[c + 2] = y.z | z.z; ac[c + 3] = y.w | z.w;
     }
   }
-  int2 part = make_int2(0, 0);
-  if (u.parts && tid < (p.nwords + 15) / 16) part = u.parts[tid];        // at most 1024 of them: a state has fewer than 16384 words
-  for (int i = tid; i < u.shared_cap; i += kListThreads) mypos[i] = -1;   // shared ids the sequence lacks, and room that none takes; the barriers below are between these and the columns
+  int2 sums = make_int2(0, 0);
+  if (u.parts && tid < (p.nwords + 15) / 16) sums = u.parts[tid];        // at most 1024 of them: a state has fewer than 16384 words
   int ns = 0, na = 0;
 #pragma unroll
   for (int i = 0; i < N; ++i) {
@@ -120,7 +159,7 @@ __global__ __launch_bounds__(kListThreads) void union_lists_kernel(VocabPtrs p, 
     s_active[wave] = ai;
   }
   if (u.parts) {
-    const int pi = wave_incl_scan(part.x), ci = wave_incl_scan(part.y);
+    const int pi = wave_incl_scan(sums.x), ci = wave_incl_scan(sums.y);
     if (lane == 63) {
       s_pairs[wave] = pi;
       s_cover[wave] = ci;
@@ -131,6 +170,14 @@ __global__ __launch_bounds__(kListThreads) void union_lists_kernel(VocabPtrs p, 
   int r = row_sum((lane & 15) < wave ? ts : 0) + si - ns;                // rank of this thread's first shared bit
   int pos = row_sum((lane & 15) < wave ? ta : 0) + ai - na;              // column of its first active bit
   const int all = row_sum(ts), listed = all < u.shared_cap ? all : u.shared_cap;
+  if (tid == first) {
+    s_rank[0] = r < listed ? r : listed;
+    s_pos[0] = pos;
+  }
+  if (tid == (final ? first : first + per - 1)) {
+    s_rank[1] = final ? u.shared_cap : r + ns < listed ? r + ns : listed;
+    s_pos[1] = final ? n : pos + na;
+  }
   bool split = false;
   if (u.parts) {
     const int pairs = row_sum(s_pairs[lane & 15]);
@@ -157,74 +204,50 @@ __global__ __launch_bounds__(kListThreads) void union_lists_kernel(VocabPtrs p, 
   int32_t* rpos = u.rest_pos + (size_t)b * p.cap;
   int32_t* hid = u.parts ? u.head_ids + (size_t)b * p.cap : nullptr;
   int32_t* hpos = u.parts ? u.head_pos + (size_t)b * p.cap : nullptr;
-  if ((tid * batch) >> 10 == b) {                                        // this workgroup's share of the list of shared ids
+  for (int i = s_rank[0] + tid; i < s_rank[1]; i += kListThreads) mypos[i] = -1;   // shared ids the sequence lacks, and room that none takes; the barrier below is between these and the columns
+  if (mine && (tid * batch) >> 10 == b) {                                // this workgroup's share of the list of shared ids
     int at = r;
 #pragma unroll
     for (int i = 0; i < N; ++i)
       for (uint32_t x = sh[i]; x; x &= x - 1u) u.shared_ids[at++] = (w0 + i) * 32 + __ffs(x) - 1;
   }
-  if (tables && n > kWalkFrom) {
+  if (mine) {
     int rank = r, before = pos - q;                                      // active shared bits before this thread's words
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-      if (w0 + i < p.nwords) tab[w0 + i] = make_uint4(sh[i], ac[i] & sh[i], (uint32_t)rank, (uint32_t)before);
+      tab[(tid - first) * N + i] = make_uint4(sh[i], ac[i] & sh[i], (uint32_t)rank, (uint32_t)before);
       rank += __popc(sh[i]);
       before += __popc(ac[i] & sh[i]);
     }
-    __syncthreads();
-    const int32_t* ids = p.ids + (size_t)b * p.cap;
-    for (int j = tid; j < n; j += kListThreads) {
-      const int id = ids[j];
-      const uint4 t = tab[id >> 5];
-      const uint32_t below = (1u << (id & 31)) - 1u;
-      if ((t.x >> (id & 31)) & 1u) {
-        mypos[t.z + __popc(t.x & below)] = j;
-      } else {
-        const int at = j - (int)t.w - __popc(t.y & below);
-        rid[at] = id;
-        rpos[at] = j;
-        if (hid && split) {
-          hid[at] = id;
-          hpos[at] = j;
-        }
-      }
-      if (hid && !split) {
-        hid[j] = id;
-        hpos[j] = j;
+  }
+  __syncthreads();
+  const int32_t* ids = p.ids + (size_t)b * p.cap;
+  for (int j = s_pos[0] + tid; j < s_pos[1]; j += kListThreads) {
+    const int id = ids[j];
+    const uint4 t = tab[(id >> 5) - first * N];
+    const uint32_t below = (1u << (id & 31)) - 1u;
+    if ((t.x >> (id & 31)) & 1u) {
+      mypos[t.z + __popc(t.x & below)] = j;
+    } else {
+      const int at = j - (int)t.w - __popc(t.y & below);
+      rid[at] = id;
+      rpos[at] = j;
+      if (hid && split) {
+        hid[at] = id;
+        hpos[at] = j;
       }
     }
-  } else {
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-      for (uint32_t x = ac[i]; x; x &= x - 1u) {
-        const uint32_t bit = x & (0u - x);
-        const int id = (w0 + i) * 32 + __ffs(x) - 1;
-        if (sh[i] & bit) {
-          mypos[r + __popc(sh[i] & (bit - 1u))] = pos;
-        } else {
-          rid[q] = id;
-          rpos[q] = pos;
-          if (hid && split) {
-            hid[q] = id;
-            hpos[q] = pos;
-          }
-          ++q;
-        }
-        if (hid && !split) {
-          hid[pos] = id;
-          hpos[pos] = pos;
-        }
-        ++pos;
-      }
-      r += __popc(sh[i]);
+    if (hid && !split) {
+      hid[j] = id;
+      hpos[j] = j;
     }
   }
-  if (b == 0)
+  if (b == 0 && final)
     for (int g = tid; g < groups; g += kListThreads) {
       u.shared_n[g] = listed;
       if (hid) u.head_shared_n[g] = split ? listed : 0;
     }
-  if (tid == 0) {
+  if (final && tid == 0) {
     u.rest_n[b] = nrest;
     if (hid) u.head_n[b] = split ? nrest : n;
   }
@@ -266,19 +289,21 @@ hipError_t launch_union_reset(const nanospec_state* st, hipStream_t s) {
 
 hipError_t launch_union_build(const nanospec_state* st, hipStream_t s) {
   const int nw = st->vp.nwords;
-  if (st->un.parts) union_count_kernel<true><<<(nw + 15) / 16, 1024, 0, s>>>(st->vp, st->un, st->batch);
-  else union_count_kernel<false><<<(nw + 15) / 16, 1024, 0, s>>>(st->vp, st->un, st->batch);
+  static_assert(NANOSPEC_MAX_BATCH <= 256, "sixteen words a thread");
+  if (st->batch <= 64) union_count_kernel<3><<<(nw + 15) / 16, kCountThreads, 0, s>>>(st->vp, st->un, st->batch);
+  else union_count_kernel<5><<<(nw + 15) / 16, kCountThreads, 0, s>>>(st->vp, st->un, st->batch);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const int64_t tables = 16ll * nw;                                       // of lists that are walked; 300 000 ids and more are always written from the bits
-  const int walk = st->vp.cap > kWalkFrom && tables <= kListsLds;
-  const unsigned lds = walk ? (unsigned)tables : 0u;
-  if (nw <= kListThreads) union_lists_kernel<1><<<st->batch, kListThreads, lds, s>>>(st->vp, st->un, st->batch, st->un_groups, walk);
-  else if (nw <= 2 * kListThreads) union_lists_kernel<2><<<st->batch, kListThreads, lds, s>>>(st->vp, st->un, st->batch, st->un_groups, walk);
-  else if (nw <= 4 * kListThreads) union_lists_kernel<4><<<st->batch, kListThreads, lds, s>>>(st->vp, st->un, st->batch, st->un_groups, walk);
-  else if (nw <= 8 * kListThreads) union_lists_kernel<8><<<st->batch, kListThreads, lds, s>>>(st->vp, st->un, st->batch, st->un_groups, walk);
-  else if (nw <= 16 * kListThreads) union_lists_kernel<16><<<st->batch, kListThreads, lds, s>>>(st->vp, st->un, st->batch, st->un_groups, walk);
-  else return hipErrorInvalidValue;                                       // more ids than a state takes: its bitmaps fill LDS three times over
+  const int N = nw <= kListThreads ? 1 : nw <= 2 * kListThreads ? 2 : nw <= 4 * kListThreads ? 4 : nw <= 8 * kListThreads ? 8 : 16;
+  const int parts = st->batch <= 64 ? 4 : st->batch <= 128 || 16ll * nw > kListsLds ? 2 : 1;              // as many workgroups as compute units, and tables that fit LDS
+  const int per = ((nw + N - 1) / N + parts - 1) / parts, lds = per * N * 16;
+  const dim3 grid(st->batch, parts);
+  if (nw > 16 * kListThreads || lds > kListsLds) return hipErrorInvalidValue;   // more ids than a state takes: its bitmaps fill LDS three times over
+  if (N == 1) union_lists_kernel<1><<<grid, kListThreads, lds, s>>>(st->vp, st->un, st->batch, st->un_groups, per);
+  else if (N == 2) union_lists_kernel<2><<<grid, kListThreads, lds, s>>>(st->vp, st->un, st->batch, st->un_groups, per);
+  else if (N == 4) union_lists_kernel<4><<<grid, kListThreads, lds, s>>>(st->vp, st->un, st->batch, st->un_groups, per);
+  else if (N == 8) union_lists_kernel<8><<<grid, kListThreads, lds, s>>>(st->vp, st->un, st->batch, st->un_groups, per);
+  else union_lists_kernel<16><<<grid, kListThreads, lds, s>>>(st->vp, st->un, st->batch, st->un_groups, per);
   return hipGetLastError();
 }
 

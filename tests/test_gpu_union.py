@@ -291,8 +291,8 @@ def test_union_head_on_either_side_of_the_choice_to_split(M, d, split):
 
 @pytest.mark.parametrize("V,window,share,shared_cap", [(20000, 6000, 3, 0), (32800, 6000, 1, 64), (128256, 9000, 2, 0), (128256, 9000, 3, 1024), (262400, 4000, 2, 0), (320032, 4000, 2, 256)])
 def test_lists_of_any_length(V, window, share, shared_cap):
-    """long lists are walked, short ones written from the bits, one beside the other in a batch; a shared list without room for all; vocabularies of every words-per-thread, up
-    to one whose tables do not fit LDS.  Ids and columns are the oracle's exactly."""
+    """long lists, short ones and an empty one beside each other in a batch; a shared list without room for all; vocabularies of every words-per-thread.  Ids and columns are the
+    oracle's exactly."""
     rng = np.random.default_rng(V)
     common = np.concatenate([[0, 31, 32, V - 1], rng.permutation(V)[:window // 2]])
     sizes = [window, 1025, 1024, 0, 1, 3500, 700]
@@ -313,6 +313,31 @@ def test_lists_of_any_length(V, window, share, shared_cap):
         for b in range(len(sizes)):
             assert np.array_equal(rest[b][0], e_rest[b][0]) and np.array_equal(rest[b][1], e_rest[b][1]), b
         ids = ids[1:] + ids[:1]
+    st.close()
+
+
+@pytest.mark.parametrize("nb,V,window,share", [(1, 97, 60, 1), (3, 40000, 1500, 2), (16, 33000, 1500, 4), (17, 5000, 300, 17), (64, 20000, 1300, 9), (64, 3000, 1100, 65), (65, 20000, 700, 64), (129, 9000, 1200, 33), (256, 6000, 1100, 256), (256, 40000, 200, 500), (130, 320032, 60, 3)])
+def test_counts_and_parts_of_any_batch(nb, V, window, share):
+    """ids held by none to all of the sequences, thresholds up to and beyond their number; batches at which a thread's words, the bit planes or the workgroups per sequence change, the last for its tables' size.  Ids
+    and columns are the oracle's exactly."""
+    rng = np.random.default_rng(nb)
+    held = rng.random(V) ** 3                                # some ids in nearly every sequence, most in few
+    held[[0, V - 1]] = 1.0
+    ids = []
+    for b in range(nb):
+        got = np.flatnonzero(rng.random(V) < held * window / held.sum() * 1.5)
+        got = np.union1d(got if len(got) <= window - 2 else np.sort(rng.permutation(got)[:window - 2]), [0, V - 1]).astype(np.int32)
+        ids.append(got[:0] if b == 1 else got)
+    st = B.State(V, 64, nb, window, 1, 1, 1)
+    B.nanospec_union_enable(st.h, share, 0)
+    flat, off = csr(ids)
+    B.nanospec_vocab_init(st.h, dev_ids(flat), off, None, np.zeros(nb + 1, np.int32))
+    B.nanospec_union_build(st.h)
+    sid, spos, rest, got_share, cap = st.read_union()
+    e_sid, e_pos, e_rest = oracle.shared_rows(ids, share, cap)
+    assert got_share == share and np.array_equal(sid, e_sid) and np.array_equal(spos, e_pos)
+    for b in range(nb):
+        assert np.array_equal(rest[b][0], e_rest[b][0]) and np.array_equal(rest[b][1], e_rest[b][1]), b
     st.close()
 
 
