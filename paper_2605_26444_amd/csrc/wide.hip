@@ -25,7 +25,7 @@ constexpr int kWidePad = 32;     // bytes between LDS rows: rows r and r+4 share
 //   seq_rows > 0: one list for the hidden rows of several sequences, seq_rows each, with columns of their own ([..][ids_stride]).
 // d % BK == 0 (checked by the launcher).  Rows past n read row 0, hidden rows past M read row M-1; neither is stored.
 // Workgroup order: the chip hands consecutive workgroups to its eight dies in turn and each die has its own L2, so
-// the hidden-row blocks of one row block run back to back on one die (blockIdx -> (row block, hidden block) below)
+// the hidden-row blocks of one row block run back to back on one die (blk -> (row block, hidden block) below)
 // and find the row block's weights in that L2.
 // Several sequences (batch > 1): list, row count, hidden rows, logits and columns of sequence b lie at b times their
 // strides, and the sequences take turns (sequence fastest), so that one die works for few sequences and keeps their
@@ -33,11 +33,10 @@ constexpr int kWidePad = 32;     // bytes between LDS rows: rows r and r+4 share
 // TAIL: any d % 8 == 0 -- the last step's pieces past column d are fetched from column 0 and parked as zeros, and the
 // number of steps may be odd.  Without it d % (D * BK) == 0.
 template <int WR, int WH, int FR, int FH, int BK, int D, bool TAIL>
-__global__ __launch_bounds__(64 * WR * WH) void head_wide_kernel(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H,
-                                                        const int32_t* __restrict__ ids, const int32_t* __restrict__ n_dev, int n_fixed,
-                                                        int V, int batch, int M, int d, int64_t ld, int64_t ids_stride,
-                                                        float* __restrict__ logits, int row_blocks, int hid_blocks,
-                                                        const int32_t* __restrict__ opos, int opos_len, int seq_rows, int by_die) {
+__device__ __forceinline__ void wide_block(const uint32_t blk, const uint16_t* __restrict__ W, const uint16_t* __restrict__ H, const int32_t* __restrict__ ids,
+                                           const int32_t* __restrict__ n_dev, int n_fixed, int V, int batch, int M, int d, int64_t ld, int64_t ids_stride,
+                                           float* __restrict__ logits, int row_blocks, int hid_blocks, const int32_t* __restrict__ opos, int opos_len,
+                                           int seq_rows, int by_die) {
   constexpr int NT = 64 * WR * WH;
   constexpr int BM = WR * FR * 16, BN = WH * FH * 16;
   constexpr int CPR = BK / 8;                      // 16-byte pieces per row and step
@@ -49,17 +48,17 @@ __global__ __launch_bounds__(64 * WR * WH) void head_wide_kernel(const uint16_t*
   static_assert(D >= 2 && D % 2 == 0, "step s reads LDS stage s & 1: the unrolled group of D steps must keep that parity");
   extern __shared__ __attribute__((aligned(16))) char smem[];
 
-  // blockIdx -> die x = blockIdx % 8, slot r = blockIdx / 8; hidden block = r % hid_blocks, row block = (r / hid_blocks) * 8 + x
-  // several sequences: sequence = blockIdx % batch, hidden block and row block follow; by_die: die x takes the x-th eighth of every
+  // blk -> die x = blk % 8, slot r = blk / 8; hidden block = r % hid_blocks, row block = (r / hid_blocks) * 8 + x
+  // several sequences: sequence = blk % batch, hidden block and row block follow; by_die: die x takes the x-th eighth of every
   // sequence's row blocks (the cuts move by up to a block from sequence to sequence, so that the eighths even out)
   int b = 0, hb, rb, n;
   if (batch == 1) {
-    const int xq = blockIdx.x & 7, xr = blockIdx.x >> 3;
+    const int xq = blk & 7, xr = blk >> 3;
     hb = xr % hid_blocks;
     rb = (xr / hid_blocks) * 8 + xq;
     n = n_dev ? n_dev[0] : n_fixed;
   } else {
-    const int x = blockIdx.x & 7, xr = by_die ? blockIdx.x >> 3 : blockIdx.x;
+    const int x = blk & 7, xr = by_die ? blk >> 3 : blk;
     hb = by_die ? xr % hid_blocks : xr / batch % hid_blocks;
     b = (by_die ? xr / hid_blocks : xr) % batch;
     rb = xr / batch / hid_blocks;
@@ -257,6 +256,47 @@ __global__ __launch_bounds__(64 * WR * WH) void head_wide_kernel(const uint16_t*
       }
     }
   }
+}
+
+template <int WR, int WH, int FR, int FH, int BK, int D, bool TAIL>
+__global__ __launch_bounds__(64 * WR * WH) void head_wide_kernel(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H,
+                                                        const int32_t* __restrict__ ids, const int32_t* __restrict__ n_dev, int n_fixed,
+                                                        int V, int batch, int M, int d, int64_t ld, int64_t ids_stride,
+                                                        float* __restrict__ logits, int row_blocks, int hid_blocks,
+                                                        const int32_t* __restrict__ opos, int opos_len, int seq_rows, int by_die) {
+  wide_block<WR, WH, FR, FH, BK, D, TAIL>(blockIdx.x, W, H, ids, n_dev, n_fixed, V, batch, M, d, ld, ids_stride, logits, row_blocks, hid_blocks, opos, opos_len, seq_rows, by_die);
+}
+
+// The list that several sequences share.  Often it is empty -- the device says whether it is used at all --, so its launch is no more workgroups than the chip holds, each of
+// which takes every gridDim.x-th block (a multiple of 8 blocks apart: on one die) up to the list's end.  The last barrier of a block's K walk stands between its LDS and the next block's.
+// An empty list of 5120 places in front of 64 sequences of 2300 x 4096, M = 8: 2.25 us with 512 workgroups, 2.8 with one for each block that there is room for.
+template <int WR, int WH, int FR, int FH, int BK, int D, bool TAIL>
+__global__ __launch_bounds__(64 * WR * WH) void head_wide_shared_kernel(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H, const int32_t* __restrict__ ids,
+                                                                        const int32_t* __restrict__ n_dev, int V, int M, int d, int64_t ld, int64_t opos_stride,
+                                                                        float* __restrict__ logits, int row_blocks, int hid_blocks,
+                                                                        const int32_t* __restrict__ opos, int opos_len, int seq_rows) {
+  const int n = n_dev[0], used = (n + WR * FR * 16 - 1) / (WR * FR * 16);
+  const uint32_t blocks = (uint32_t)((used < row_blocks ? used : row_blocks) + 7) / 8 * 8 * hid_blocks;
+  for (uint32_t blk = blockIdx.x; blk < blocks; blk += gridDim.x)
+    wide_block<WR, WH, FR, FH, BK, D, TAIL>(blk, W, H, ids, nullptr, n, V, 1, M, d, ld, opos_stride, logits, row_blocks, hid_blocks, opos, opos_len, seq_rows, 0);
+}
+
+template <int WR, int WH, int FR, int FH, int BK, int D>
+static hipError_t run_wide_shared(const uint16_t* W, const uint16_t* H, const int32_t* ids, const int32_t* n_dev, int32_t cap_rows, int32_t V, int32_t M, int32_t d, int64_t ld,
+                                  int64_t opos_stride, float* logits, const int32_t* opos, int32_t seq_rows, hipStream_t s) {
+  constexpr int BM = WR * FR * 16, BN = WH * FH * 16;
+  constexpr int LDS = 2 * (BM + BN) * (BK * 2 + kWidePad), kResident = 256 * (160 * 1024 / LDS < 4 ? 160 * 1024 / LDS : 4);
+  const int row_blocks = (cap_rows + BM - 1) / BM, hid_blocks = (M + BN - 1) / BN;
+  const int64_t blocks = (int64_t)((row_blocks + 7) / 8) * hid_blocks * 8;
+  if (blocks > 0x7fffffff - kResident || !wide_reaches(V, M, d)) return hipErrorInvalidValue;
+  const unsigned grid = blocks < kResident ? (unsigned)blocks : kResident;
+  if (d % (D * BK) == 0)
+    head_wide_shared_kernel<WR, WH, FR, FH, BK, D, false><<<dim3(grid), 64 * WR * WH, LDS, s>>>(W, H, ids, n_dev, V, M, d, ld, opos_stride, logits, row_blocks, hid_blocks, opos,
+                                                                                              cap_rows / 4 * 4, seq_rows);
+  else
+    head_wide_shared_kernel<WR, WH, FR, FH, BK, D, true><<<dim3(grid), 64 * WR * WH, LDS, s>>>(W, H, ids, n_dev, V, M, d, ld, opos_stride, logits, row_blocks, hid_blocks, opos,
+                                                                                             cap_rows / 4 * 4, seq_rows);
+  return hipGetLastError();
 }
 
 template <int WR, int WH, int FR, int FH, int BK, int D>
@@ -487,6 +527,16 @@ static hipError_t run_gemm(const uint16_t* W, const uint16_t* H, const int32_t* 
 }
 
 template <WideShape SHAPE>
+static hipError_t configure_shared() {
+  constexpr WideBlock b = kWideBlocks[SHAPE];
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(head_wide_shared_kernel<b.WR, b.WH, b.FR, b.FH, b.BK, b.D, false>),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+  if (e != hipSuccess) return e;
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(head_wide_shared_kernel<b.WR, b.WH, b.FR, b.FH, b.BK, b.D, true>),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+}
+
+template <WideShape SHAPE>
 static hipError_t configure_wide() {
   constexpr WideBlock b = kWideBlocks[SHAPE];
   const void* fns[] = {reinterpret_cast<const void*>(head_wide_kernel<b.WR, b.WH, b.FR, b.FH, b.BK, b.D, false>),
@@ -508,6 +558,9 @@ hipError_t wide_configure_device() {
   if (e == hipSuccess) e = configure_wide<kWide128x64>();
   if (e == hipSuccess) e = configure_wide<kWide256x128>();
   if (e == hipSuccess) e = configure_wide<kWide256x256>();
+  if (e == hipSuccess) e = configure_shared<kWide32x16>();
+  if (e == hipSuccess) e = configure_shared<kWide32x32>();
+  if (e == hipSuccess) e = configure_shared<kWide64x64>();
   if (e == hipSuccess)
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(head_gemm_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   return e;
@@ -548,11 +601,22 @@ hipError_t launch_head_wide(const void* W, const void* H, const int32_t* ids, co
                         (int)wide_by_die(M, batch, cap_rows, dense), s);
 }
 
+template <WideShape SHAPE, typename... A>
+static hipError_t run_shared_shape(A... a) {
+  constexpr WideBlock b = kWideBlocks[SHAPE];
+  return run_wide_shared<b.WR, b.WH, b.FR, b.FH, b.BK, b.D>(a...);
+}
+
 hipError_t launch_head_wide_shared(const void* W, const void* H, const int32_t* ids, const int32_t* n_dev, int32_t cap_rows, int32_t V,
                                    int32_t rows_total, int32_t seq_rows, int32_t d, int64_t ld, float* logits, const int32_t* opos,
                                    int64_t opos_stride, hipStream_t s) {
-  return run_wide_shape(wide_shared_shape(rows_total), static_cast<const uint16_t*>(W), static_cast<const uint16_t*>(H), ids, n_dev, 0, cap_rows, V, 1,
-                        rows_total, d, ld, opos_stride, logits, opos, seq_rows, 0, s);
+  const uint16_t* Wp = static_cast<const uint16_t*>(W);
+  const uint16_t* Hp = static_cast<const uint16_t*>(H);
+  switch (wide_shared_shape(rows_total)) {
+    case kWide32x16: return run_shared_shape<kWide32x16>(Wp, Hp, ids, n_dev, cap_rows, V, rows_total, d, ld, opos_stride, logits, opos, seq_rows, s);
+    case kWide32x32: return run_shared_shape<kWide32x32>(Wp, Hp, ids, n_dev, cap_rows, V, rows_total, d, ld, opos_stride, logits, opos, seq_rows, s);
+    default: return run_shared_shape<kWide64x64>(Wp, Hp, ids, n_dev, cap_rows, V, rows_total, d, ld, opos_stride, logits, opos, seq_rows, s);
+  }
 }
 
 }  // namespace nanospec
