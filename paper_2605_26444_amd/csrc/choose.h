@@ -330,7 +330,7 @@ inline int64_t kslice_cost(int64_t n, int64_t LB, int64_t hb, int64_t parts, int
 }
 
 // The cheapest of 256 and 512 workgroups and all widths; the host knows the capacity only, lists are taken for 0.45 and 0.8 full.
-inline SlicePlan kslice_plan(int32_t M, int32_t batch, int32_t cap_rows, bool dense) {
+inline SlicePlan kslice_plan(int32_t M, int32_t batch, int32_t cap_rows) {
   const int32_t sizes[6] = {8, 6, 5, 4, 3, 2};
   SlicePlan best = {8, 1, 1, 64, 0, 0, 0};
   int64_t least = INT64_MAX;
@@ -338,8 +338,7 @@ inline SlicePlan kslice_plan(int32_t M, int32_t batch, int32_t cap_rows, bool de
     for (int twice = 1; twice <= 2; ++twice) {
       const int64_t LB = sizes[i], hb = (M + 8 * LB - 1) / (8 * LB);
       const int64_t parts = 256 * twice / (8 * hb * batch) > 1 ? 256 * twice / (8 * hb * batch) : 1;
-      const int64_t cost = dense ? kslice_cost(cap_rows, LB, hb, parts, batch)
-                                 : 3 * kslice_cost((int64_t)cap_rows * 9 / 20, LB, hb, parts, batch) + 2 * kslice_cost((int64_t)cap_rows * 4 / 5, LB, hb, parts, batch);
+      const int64_t cost = 3 * kslice_cost((int64_t)cap_rows * 9 / 20, LB, hb, parts, batch) + 2 * kslice_cost((int64_t)cap_rows * 4 / 5, LB, hb, parts, batch);
       if (cost < least) {
         least = cost;
         best.LB = (int32_t)LB;

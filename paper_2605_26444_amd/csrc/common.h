@@ -70,10 +70,10 @@ struct VocabPtrs {
 // Packed-buffer variant (one sequence): slot tables and the row copies.
 struct PackedPtrs {
   uint16_t* buf;        // [cap][d] bf16: one row per slot
-  int32_t* slot_of;     // [V]   slot that holds the id's row, or -1
+  int32_t* slot_of;     // [V]   slot that holds the id's row, or -1: of packed_sync_kernel, which takes what does not fit packed_sync_short_kernel
   int32_t* slot_id;     // [cap] id whose row the slot holds, or -1
   int32_t* out_pos;     // [cap] position of that id in the ascending active list, or -1
-  int32_t* free_list;   // [cap] scratch of one gather: free slots ascending
+  int32_t* free_list;   // [cap] scratch of one gather: free slots ascending, of the same kernel
   int32_t* copy_list;   // [cap][2] scratch of one gather: (id, slot) of the rows to copy
   int32_t* scal;        // [0] slots that may hold a row (highest slot in use + 1), [1] rows on the copy list
   int32_t cap;
@@ -161,7 +161,7 @@ hipError_t launch_head_hold(const void* W, const void* H, const int32_t* ids, co
 
 // kslice.hip: 17 to 64 hidden rows, K sliced over the wavefronts
 hipError_t kslice_configure_device();
-hipError_t launch_head_kslice(const void* W, const void* H, const int32_t* ids, const int32_t* n_dev, int32_t n_fixed, int32_t cap_rows, int32_t V, int32_t batch, int32_t M,
+hipError_t launch_head_kslice(const void* W, const void* H, const int32_t* ids, const int32_t* n_dev, int32_t cap_rows, int32_t V, int32_t batch, int32_t M,
                               int32_t d, int64_t ld, int64_t ids_stride, float* logits, const int32_t* opos, hipStream_t s);
 
 // union.hip

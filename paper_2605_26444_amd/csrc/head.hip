@@ -805,7 +805,7 @@ hipError_t launch_head(const void* W, const void* H, const int32_t* ids, const i
     return launch_head_hold(W, H, ids, n_dev, n_fixed, V, batch, M, d, ld_logits, ids_stride, logits, opos, s);
   const bool aligned = ((reinterpret_cast<uintptr_t>(W) | reinterpret_cast<uintptr_t>(H)) & 15) == 0;   // of the fetches into LDS
   if (kslice_supported(V, M, d, batch, cap_rows, n_dev == nullptr, aligned))
-    return launch_head_kslice(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld_logits, ids_stride, logits, opos, s);
+    return launch_head_kslice(W, H, ids, n_dev, cap_rows, V, batch, M, d, ld_logits, ids_stride, logits, opos, s);
   if (wide_supported(V, M, d, batch, cap_rows, n_dev == nullptr))
     return launch_head_wide(W, H, ids, n_dev, n_fixed, cap_rows, V, batch, M, d, ld_logits, ids_stride, logits, opos, s);
   if (M <= 64)

@@ -158,12 +158,12 @@ __device__ __forceinline__ uint32_t slice_over(uint32_t n, uint32_t over) { retu
 // division in the way of the first fetch takes longer than the rest of this.
 template <int LB>
 __global__ __launch_bounds__(64 * kSliceWaves, 2) void head_kslice_kernel(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H,
-                                                                          const int32_t* __restrict__ ids, const int32_t* __restrict__ n_dev, int n_fixed, int V,
+                                                                          const int32_t* __restrict__ ids, const int32_t* __restrict__ n_dev, int V,
                                                                           int batch, int M, int d, int64_t ld, int64_t ids_stride, float* __restrict__ logits,
                                                                           SlicePlan plan, const int32_t* __restrict__ opos) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const uint32_t x = blockIdx.x & 7, xr = blockIdx.x >> 3, y = slice_over(xr, plan.over_hid), hb = xr - y * plan.hid_blocks, part = slice_over(y, plan.over_batch), b = y - part * batch;
-  const int n = n_dev ? n_dev[b] : n_fixed;
+  const int n = n_dev[b];
   const int np = 8 * plan.parts, p = x * plan.parts + part, each = slice_over(n, plan.over_pieces), more = n - each * np;   // the first `more` pieces have a row more
   const int r0 = p * each + (p < more ? p : more), r1 = r0 + each + (p < more ? 1 : 0);
   if (r0 >= r1) return;
@@ -206,23 +206,23 @@ constexpr int slice_lds(int LB, int rows) {
 static_assert(slice_lds(8, 64) <= 160 * 1024 && slice_lds(2, 64) <= 160 * 1024, "LDS of a compute unit");
 
 template <int LB>
-static hipError_t run_kslice(const void* W, const void* H, const int32_t* ids, const int32_t* n_dev, int32_t n_fixed, int32_t V, int32_t batch, int32_t M, int32_t d, int64_t ld,
+static hipError_t run_kslice(const void* W, const void* H, const int32_t* ids, const int32_t* n_dev, int32_t V, int32_t batch, int32_t M, int32_t d, int64_t ld,
                              int64_t ids_stride, float* logits, const int32_t* opos, const SlicePlan& p, hipStream_t s) {
   head_kslice_kernel<LB><<<dim3(8u * p.parts * p.hid_blocks * batch), 64 * kSliceWaves, slice_lds(LB, p.rows), s>>>(
-      static_cast<const uint16_t*>(W), static_cast<const uint16_t*>(H), ids, n_dev, n_fixed, V, batch, M, d, ld, ids_stride, logits, p, opos);
+      static_cast<const uint16_t*>(W), static_cast<const uint16_t*>(H), ids, n_dev, V, batch, M, d, ld, ids_stride, logits, p, opos);
   return hipGetLastError();
 }
 
-hipError_t launch_head_kslice(const void* W, const void* H, const int32_t* ids, const int32_t* n_dev, int32_t n_fixed, int32_t cap_rows, int32_t V, int32_t batch, int32_t M,
+hipError_t launch_head_kslice(const void* W, const void* H, const int32_t* ids, const int32_t* n_dev, int32_t cap_rows, int32_t V, int32_t batch, int32_t M,
                               int32_t d, int64_t ld, int64_t ids_stride, float* logits, const int32_t* opos, hipStream_t s) {
-  const SlicePlan p = kslice_plan(M, batch, cap_rows, n_dev == nullptr);
+  const SlicePlan p = kslice_plan(M, batch, cap_rows);
   switch (p.LB) {
-    case 2: return run_kslice<2>(W, H, ids, n_dev, n_fixed, V, batch, M, d, ld, ids_stride, logits, opos, p, s);
-    case 3: return run_kslice<3>(W, H, ids, n_dev, n_fixed, V, batch, M, d, ld, ids_stride, logits, opos, p, s);
-    case 4: return run_kslice<4>(W, H, ids, n_dev, n_fixed, V, batch, M, d, ld, ids_stride, logits, opos, p, s);
-    case 5: return run_kslice<5>(W, H, ids, n_dev, n_fixed, V, batch, M, d, ld, ids_stride, logits, opos, p, s);
-    case 6: return run_kslice<6>(W, H, ids, n_dev, n_fixed, V, batch, M, d, ld, ids_stride, logits, opos, p, s);
-    default: return run_kslice<8>(W, H, ids, n_dev, n_fixed, V, batch, M, d, ld, ids_stride, logits, opos, p, s);
+    case 2: return run_kslice<2>(W, H, ids, n_dev, V, batch, M, d, ld, ids_stride, logits, opos, p, s);
+    case 3: return run_kslice<3>(W, H, ids, n_dev, V, batch, M, d, ld, ids_stride, logits, opos, p, s);
+    case 4: return run_kslice<4>(W, H, ids, n_dev, V, batch, M, d, ld, ids_stride, logits, opos, p, s);
+    case 5: return run_kslice<5>(W, H, ids, n_dev, V, batch, M, d, ld, ids_stride, logits, opos, p, s);
+    case 6: return run_kslice<6>(W, H, ids, n_dev, V, batch, M, d, ld, ids_stride, logits, opos, p, s);
+    default: return run_kslice<8>(W, H, ids, n_dev, V, batch, M, d, ld, ids_stride, logits, opos, p, s);
   }
 }
 

@@ -34,8 +34,8 @@ void c_hold_plan(int d, int batch, int dense, int M, int* o) {
   o[0] = h.NW; o[1] = h.parts; o[2] = h.seg; o[3] = (int)hold_lds(h, M);
 }
 int c_kslice_supported(int V, int M, int d, int batch, int cap, int dense, int aligned) { return kslice_supported(V, M, d, batch, cap, dense != 0, aligned != 0); }
-void c_kslice_plan(int M, int batch, int cap, int dense, int* o) {
-  const SlicePlan p = kslice_plan(M, batch, cap, dense != 0);
+void c_kslice_plan(int M, int batch, int cap, int* o) {
+  const SlicePlan p = kslice_plan(M, batch, cap);
   o[0] = p.LB; o[1] = p.parts; o[2] = p.hid_blocks; o[3] = p.rows;
 }
 int c_union_feeds(int batch, int cap) { return union_feeds(batch, cap); }
@@ -85,9 +85,9 @@ def kslice_supported(V, M, d, batch, cap, dense=False, aligned=True):
     return bool(_lib.c_kslice_supported(V, M, d, batch, cap, int(dense), int(aligned)))
 
 
-def kslice_plan(M, batch, cap, dense=False):
+def kslice_plan(M, batch, cap):
     o = (C.c_int * 4)()
-    _lib.c_kslice_plan(M, batch, cap, int(dense), o)
+    _lib.c_kslice_plan(M, batch, cap, o)
     return Slice(*o)
 
 

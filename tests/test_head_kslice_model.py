@@ -55,8 +55,8 @@ def check_block(rows, most, LB, M, d, m0, waits=lambda R, L: (R - 1) * L):
     assert m0 < M
 
 
-def check(M, d, batch, cap, n, dense=False):
-    plan = choose.kslice_plan(M, batch, cap, dense)
+def check(M, d, batch, cap, n):
+    plan = choose.kslice_plan(M, batch, cap)
     assert plan.LB in (2, 3, 4, 5, 6, 8) and plan.hid_blocks == -(-M // (8 * plan.LB)) and plan.parts >= 1
     assert plan.rows % 8 == 0 and 8 <= plan.rows <= 64 and plan.rows != 56
     grid = 8 * plan.parts * plan.hid_blocks * batch
