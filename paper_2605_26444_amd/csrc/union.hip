@@ -104,14 +104,14 @@ constexpr int kListsLds = 150 * 1024;
 // 64 lists of 2300, V = 128256 10.2 / 9.9 us, of 20000 44.6 / 20.8, 130 of 8000, V = 152064 32.3 / 21.7, 24 of 5000, V = 50000 15.4 / 10.0; with the workgroups below 64 of 300 7.1 / 6.5, 16 of 300, V = 32000 5.9 / 5.6.
 // A workgroup's sixteen wavefronts share four SIMDs, so up to four workgroups (gridDim.y, as many as fill the chip) write a sequence's lists, each for `per` threads' words and from its own scans of them all:
 // 64 lists of 2300 9.9 -> 9.0 us, of 20000 20.8 -> 15.3, 8 of 3000 8.8 -> 7.7, 40 of 4000, V = 262400 17.8 -> 15.5 (eight: 0.1 us less for 8 and 24 sequences; two: 0.3 more for 64).
-// What the head works from (u.head_*, kept where union_feeds says so): the split, or nothing shared and every list whole, by how many pairs the shared ids cover in
-// all sequences together; every workgroup comes to the same answer from the counts.
+// What the head works from (u.head_*, kept where union_feeds says so): the split, or nothing shared and every list whole, by how many pairs the listed ids cover in
+// all sequences together (to the count's sixteen words); every workgroup comes to the same answer.
 template <int N>
 __global__ __launch_bounds__(kListThreads) void union_lists_kernel(VocabPtrs p, UnionPtrs u, int batch, int groups, int per) {
   constexpr int NW = kListThreads / 64;
   static_assert(NW == 16, "a row of lanes holds one total per wavefront");
   extern __shared__ __attribute__((aligned(16))) uint4 tab[];   // per word of this workgroup: shared bits, active shared bits, rank of the first shared bit, active shared bits before
-  __shared__ int s_shared[NW], s_active[NW], s_rest[NW], s_pairs[NW], s_cover[NW], s_rank[2], s_pos[2];
+  __shared__ int s_shared[NW], s_active[NW], s_rest[NW], s_pairs[NW], s_cover[NW], s_rank[2], s_pos[2], s_cut;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, b = blockIdx.x, w0 = tid * N;
   const int first = blockIdx.y * per, final = blockIdx.y == gridDim.y - 1;
   const bool mine = tid >= first && tid < first + per;
@@ -159,11 +159,8 @@ __global__ __launch_bounds__(kListThreads) void union_lists_kernel(VocabPtrs p, 
     s_active[wave] = ai;
   }
   if (u.parts) {
-    const int pi = wave_incl_scan(sums.x), ci = wave_incl_scan(sums.y);
-    if (lane == 63) {
-      s_pairs[wave] = pi;
-      s_cover[wave] = ci;
-    }
+    const int pi = wave_incl_scan(sums.x);
+    if (lane == 63) s_pairs[wave] = pi;
   }
   __syncthreads();
   const int ts = s_shared[lane & 15], ta = s_active[lane & 15];
@@ -178,11 +175,8 @@ __global__ __launch_bounds__(kListThreads) void union_lists_kernel(VocabPtrs p, 
     s_rank[1] = final ? u.shared_cap : r + ns < listed ? r + ns : listed;
     s_pos[1] = final ? n : pos + na;
   }
-  bool split = false;
-  if (u.parts) {
-    const int pairs = row_sum(s_pairs[lane & 15]);
-    split = union_split_pairs(pairs, pairs - row_sum(s_cover[lane & 15]));
-  }
+  // the first of the count's workgroups whose ids do not all find room on the list
+  if (all <= u.shared_cap ? tid == 0 : r <= u.shared_cap && r + ns > u.shared_cap) s_cut = all <= u.shared_cap ? kListThreads : w0 / 16;
   if (r + ns > u.shared_cap) {                                           // bits without room on the list are not shared
     int room = u.shared_cap - r;
 #pragma unroll
@@ -198,6 +192,10 @@ __global__ __launch_bounds__(kListThreads) void union_lists_kernel(VocabPtrs p, 
   const int ri = wave_incl_scan(nr);
   if (lane == 63) s_rest[wave] = ri;
   __syncthreads();
+  if (u.parts) {
+    const int ci = wave_incl_scan(tid < s_cut ? sums.y : 0);
+    if (lane == 63) s_cover[wave] = ci;
+  }
   const int tr = s_rest[lane & 15], nrest = row_sum(tr);
   int q = row_sum((lane & 15) < wave ? tr : 0) + ri - nr;
   int32_t* rid = u.rest_ids + (size_t)b * p.cap;
@@ -221,6 +219,11 @@ __global__ __launch_bounds__(kListThreads) void union_lists_kernel(VocabPtrs p, 
     }
   }
   __syncthreads();
+  bool split = false;
+  if (u.parts) {
+    const int pairs = row_sum(s_pairs[lane & 15]);
+    split = union_split_pairs(pairs, pairs - row_sum(s_cover[lane & 15]));
+  }
   const int32_t* ids = p.ids + (size_t)b * p.cap;
   for (int j = s_pos[0] + tid; j < s_pos[1]; j += kListThreads) {
     const int id = ids[j];

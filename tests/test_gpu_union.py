@@ -342,8 +342,8 @@ def test_counts_and_parts_of_any_batch(nb, V, window, share):
 
 
 @pytest.mark.parametrize("M,d,V,nb,n,common,shared_cap,split", [
-    (8, 1032, 20000, 30, 1800, 1790, 0, True), (16, 520, 20000, 70, 3300, 2800, 0, True), (1, 512, 20000, 30, 1800, 1790, 640, True),      # one row list serves (nearly) all; a shared list without room
-    (8, 1032, 20000, 30, 1800, 1500, 0, False), (16, 2048, 40000, 16, 3000, 0, 0, False), (17, 512, 20000, 30, 1800, 1790, 0, None),      # lists whole; more hidden rows never ask the lists
+    (8, 1032, 20000, 30, 1800, 1790, 0, True), (16, 520, 20000, 70, 3300, 2800, 0, True), (1, 512, 20000, 30, 1800, 1790, 1728, True),      # one row list serves (nearly) all; a shared list without room
+    (1, 512, 20000, 30, 1800, 1790, 640, False), (8, 1032, 20000, 30, 1800, 1500, 0, False), (16, 2048, 40000, 16, 3000, 0, 0, False), (17, 512, 20000, 30, 1800, 1790, 0, None),      # lists whole; more hidden rows never ask the lists
 ])
 def test_head_from_whichever_lists_the_overlap_asks_for(M, d, V, nb, n, common, shared_cap, split):
     """sequences with `common` ids in common, sequences of other lengths and an empty one beside them, the lists built again for the opposite overlap and back; every column of an active id is
@@ -368,11 +368,16 @@ def test_head_from_whichever_lists_the_overlap_asks_for(M, d, V, nb, n, common, 
         B.nanospec_union_build(st.h)
         if split is not None and trial != 1:
             count = np.bincount(flat, minlength=V)
-            assert choose.union_split_pairs(len(flat), int(count[count < max(2, nb // 8)].sum())) == split
+            listed = np.flatnonzero(count >= max(2, nb // 8))[:shared_cap or None]
+            assert choose.union_split_pairs(len(flat), len(flat) - int(count[listed].sum())) == split
         logits = torch.full((nb, M, st.capacity), float("nan"), dtype=torch.float32, device="cuda")
         B.nanospec_union_head(st.h, W, H, M, logits)
         for b in range(nb):
             w, h, k = W[torch.from_numpy(ids[b]).long().cuda()].double(), H[b].double(), len(ids[b])
             assert torch.all((logits[b, :, :k].double() - h @ w.T).abs() <= d * 2.0 ** -24 * (h.abs() @ w.abs().T)), (trial, b)
             assert torch.all(torch.isnan(logits[b, :, k:])), (trial, b)
+        if split is False and trial != 1:                    # lists whole: the per-sequence head's own sums
+            alone = torch.full_like(logits, float("nan"))
+            B.nanospec_sparse_head(st.h, W, H, M, alone)
+            assert torch.equal(torch.nan_to_num(logits, nan=7.0), torch.nan_to_num(alone, nan=7.0)), trial
     st.close()
