@@ -89,7 +89,7 @@ struct UnionPtrs {
   int32_t* rest_pos;      // [batch][cap] their columns
   int32_t* rest_n;        // [batch]
   // What the head works from where the overlap decides (union_feeds in choose.h), else null: the lists above, or nothing shared and every list whole.
-  int2* parts;            // [workgroups of the count] pairs of a sequence and an active id / those of ids that qualify as shared
+  int2* parts;            // [workgroups of the count] pairs of a sequence and an active id / those of ids that qualify as shared (the lists count those with room)
   int32_t* head_ids;      // [batch][cap]
   int32_t* head_pos;      // [batch][cap]
   int32_t* head_n;        // [batch]

@@ -4,8 +4,8 @@
 // written once and read by two to four wavefronts, 32 KB of LDS reads for 16 KB of operands with 32 x 32 blocks, and a step is a chain of a park, a barrier and the reads
 // behind it -- 620 cycles for 16 KB a compute unit could take out of L2 in 256.  Here a wavefront multiplies the whole block over its own steps of 64 columns
 // (w, w + 4, ...): every byte goes straight from memory into the wavefront's own ring of LDS slots and is read once, nobody waits for anybody until the
-// sums of the four wavefronts are added in fixed order at the end.  What then bounds a launch that fits the chip is the bytes a compute unit fetches, rows and hidden
-// rows alike (86 GB/s each), so the pieces are equal: the live rows are dealt out over as many workgroups as the chip holds, in blocks of any multiple of
+// sums of the four wavefronts are added in fixed order at the end.  A launch that fits the chip then takes about 5 us (launch, row count, ids and first rows one after the other, the sums) and the bytes a compute unit
+// fetches, rows and hidden rows alike (93 GB/s each), so the pieces are equal: the live rows are dealt out over as many workgroups as the chip holds, in blocks of any multiple of
 // 8 rows, and the block of hidden rows is what makes (rows + hidden rows) of a workgroup smallest (kslice_plan in choose.h).
 // Measured (before): 3000 x 3584, M = 64 9.5 us (11.2), 1000 x 4096, M = 64 6.4 (9.5), 3000 x 4096, M = 40 9.8 (12.1), 8400 x 8192, M = 64 41.5 (62.5), 2000 out of 7000 x 4096, M = 24 7.4 (11.4),
 // 8 sequences of 600 x 4096, M = 48 13.7 (19), 4 of 1500 out of 3000, M = 40 13.2 (16.2).

@@ -5,6 +5,8 @@
 //     of them), fetched once and multiplied with the hidden rows of all sequences; a sequence that does not hold
 //     it simply has no column for it;
 //   * everything else stays on a per-sequence list and goes through the per-sequence head as before.
+// The per-sequence head's launch order finds most shared rows in cache, so that the split is the faster way only where the lists overlap enough (union_split_pairs
+// in choose.h); elsewhere the head is given every list whole.
 // Every (sequence, active id) pair is covered by exactly one of the two parts and its logit lands in the column
 // the id has in that sequence's ascending active list, so the logits have the layout of nanospec_sparse_head and
 // the selection applies unchanged.

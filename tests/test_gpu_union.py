@@ -124,7 +124,7 @@ def test_union_under_the_queue_reading_of_the_vocabulary():
 
 
 def test_union_more_sequences_than_a_wavefront_has_lanes():
-    """130 sequences: the per-id count walks the batch in chunks of 64 lanes; 130 x 2 hidden rows = 4 groups and a tail of 4"""
+    """130 sequences: the per-id count takes the batch in chunks of 64; 130 x 2 hidden rows = 4 groups and a tail of 4"""
     rng = np.random.default_rng(28)
     V, d, M, k, window = 2000, 256, 2, 3, 48
     W = synth.normal_bf16(9160, 0, (V, d), 0.02)
