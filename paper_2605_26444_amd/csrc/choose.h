@@ -253,7 +253,7 @@ inline int64_t hold_lds(const HoldPlan& h, int32_t M) { return (int64_t)h.NW * (
 // Which products it takes.  Figures: its time over that of the kernels of head.hip and wide.hip with 0.04 / 0.15 / 0.35 / 0.6 / 0.9 of the capacity live, of a batch 0.05 / 0.3 / 0.6 / 0.9.  It is launched over
 // the live rows and so gains by lists that are far from full; it loses on few rows, where the others ask for weights before the row count has arrived, where pieces are a few rows for which all hidden rows are
 // fetched, and where d leaves its last wavefront's 1024 columns nearly empty.  The others go by steps of the capacity and of the live rows, so that no line has all of the gain on one side: these are drawn for
-// the mean over lists that are most often half full or more, not so that none loses (2400 sizes and fills measured for them, K slices' too: 0.87 / 0.78 on the one side, 0.96 on the other;
+// the mean over lists that are most often half full or more, not so that none loses (2400 sizes and fills measured for the one-list lines and the batches' before them, K slices' too: 0.87 / 0.78 on the one side, 0.96 on the other;
 // 5764 at random measured afterwards 0.78, 45 of them beyond 1.1: 2 of 5504 x 2688, M = 16, 1100 rows 1.26 the most here, 10048 x 5096, M = 61, 4019 rows 1.34 with K slices).
 //  One list (capacity):
 //   * d >= 5120, M > 4, and d > 4096, M 5 to 8: beyond 5120 (x 8192, M = 16: 5632 1.10 / 1.11 / 1.07 / 0.88 / 0.81, 3072 1.28 / 1.09 / 1.07 / 1.06 / 0.83, 8400 live of 33303 37.8 -> 29.7 us; M = 8: 5632 1.14 / 1.15 /
@@ -264,34 +264,24 @@ inline int64_t hold_lds(const HoldPlan& h, int32_t M) { return (int64_t)h.NW * (
 //     0.81 / 0.98 / 0.91), M > 12 with d < 3072 up to 9216 (x 2560, M = 16: 8448 0.47 / 0.53 / 0.66 / 0.71 / 0.79, 9216 0.79 / 0.84 / 1.05 / 1.15 / 0.88 and 1.20 at 0.75; M = 12: 9216 0.67 / 0.73 / 0.93 / 1.06 / 0.83), d < 4096 up to
 //     12288 (x 3072: 20000 1.10 / 0.95 at 0.3 / 0.9); M <= 4 4097 to 6144 and from 12288 on (x 4096: 5120 0.86 / 0.94, 8192 0.93 / 1.07, 16384 0.78 / 1.04 at 0.3 / 0.9);
 //   * d = 2048: from 16384 on, M > 8 32768 (M = 8: 16384 0.87 / 0.94, 9000 0.96 / 1.09; M = 16: 65536 0.98 / 0.90, 20000 1.08 / 0.96 at 0.3 / 0.9).
-//  Several sequences (a die takes the same eighth of every list, see wide_by_die), by the launch rather than the capacity:
-//   * up to 32 in one round of workgroups: a piece of 16 rows of the capacity or more, d > 4096 or M <= 4 32, M <= 4 with d <= 3072 64, more than 16 sequences 96 (8 of 640 x 4096, M = 16, 20 rows, 0.59 / 0.71 / 0.78;
-//     16 of 2304 0.59 / 0.81 / 0.88 / 0.78, M = 8 0.86 / 0.80 / 0.80; 24 of 640 x 8192, M = 16, 80 rows, 1.35 / 0.89 / 0.89);
-//   * numbers that need a second round for an even load, 11, 18, 20, 22 among them: pieces of 256 rows (11 of 1984 x 4224, M = 1, 49 rows, 1.45 / 1.04 / 1.08 / 1.09; 22 of 1856 x 4104, M = 6, 58 rows, 1.56 / 0.98 / 0.86 / 0.79, of
-//     4160, M = 12, 130 rows, 1.35 / 0.93 / 0.81 / 0.80);
-//   * more than 32: pieces of 128 rows (64 of 2300 out of 5120 x 4096, M = 8 122 -> 107 us, x 8192 239 -> 217; 64 of 640 x 8192, 80 rows, 2.04 / 1.03 / 0.82; 33 of 640 x 4224, 20 rows, M = 4 3.14 / 1.53 / 1.33, M = 16 2.22 / 1.97 /
-//     1.69), M > 8 only in at most two full rounds and up to 12 (64 of 5120 x 4096, M = 16 1.27 / 0.84 at 0.04 / 0.9, 48 1.58 at 0.04);
-//   * a single round that is less than nine tenths full, not with two or three wavefronts from 24576 rows on (24 of 8192 x 2176, M = 8 1.20 / 1.21 / 1.30 at 0.3 / 0.6 / 0.9, x 2560 1.17 / 1.18 / 1.26) nor, but for
-//     d = 4096 and 8192, from 131072 on (24 of 8192 x 3584, M = 8 1.03 / 1.06 / 1.08);
-//   * d > 4096: beyond 5120 rows together (2 of 2304 x 4224, M = 16 1.09 at 0.6), M <= 4 in an even load with a last wavefront nearly full (x 4608: 11 to 22 1.07 to 1.10; 54 of 1408 x 5064, 0.84
-//     full, 1.22 / 1.07 / 1.08 / 1.06; 2 of 6400 x 8192, M = 4 1.15 / 1.01 / 0.95 / 0.95, 2 of 2304 1.19 / 1.12 / 0.93 / 0.90; 5 of
-//     6272 x 8192, M = 4 1.03 / 0.88 / 0.90 / 0.94), M > 8 and d < 5120 up to 196608 (x 4608, M = 16: 64 of 2300 out of 5120 1.11);
-//   * 2048 < d <= 4096: beyond 4096 (4 of 1000 x 4096 1.07), two or three with M <= 8 and d < 3072 beyond 12288 (2 of 2300 out of 5120 x 2560, M = 4 1.04);
-//   * d = 2048: five or more in an even load, from 16384 rows on, M > 8 65536 (3 of 8192, M = 4 1.10 on average; 16 of 5120, M = 8 0.79 / 0.82 / 0.78).
+//  Several sequences (capacities together; a die takes the same eighth of every list and finds rows that sequences share in its L2, see wide_by_die).  Lines for lists that draw from one
+//  distribution; on 90 sizes in them (2 to 62 sequences, d 2048 to 7936, Zipf draws, 0.3 / 0.55 / 0.8 live) the other kernels take 1.09 of the time on average, up to 1.84 (49 of 1408 x 6144, M = 7 1.30 / 1.66 /
+//  1.84; 21 of 4800 x 4480, M = 6 1.6; 19 of 2944 x 4352, M = 5 1.48; 8 of 3200 x 6400, M = 1 1.27).  Lists without rows in common, and nearly empty ones, would have it narrower:
+//   * not where a piece is fewer than 16 rows of the capacity (23 of 448 x 6912, M = 4 0.69 / 0.93 / 0.96, 36 of 448 x 2176 0.65 / 0.80 / 1.10);
+//   * d > 4096: from 2560 on for four or more, two or three beyond 4096 (x 8192: 4 of 600 out of 1000, M = 8 0.86, 2 of them 1.03; 16 of 2300 out of 5120 0.73, 64 239 -> 217 us; x 5120: 16 of 2300 out of 5120
+//     69.6 -> 44.5); M <= 4 where the workgroups fill the chip (24: 1.03); M > 8 and d < 5120 up to 196608 (x 4608, M = 16: 64 of 2300 out of 5120 1.11, 16 0.90);
+//   * 2048 < d <= 4096: beyond 4096 (x 4096, M = 8: 8 of 600 out of 1000 0.80, 16 of 2300 out of 5120 0.80, 32 73 -> 59 us, 64 122 -> 107; M = 16: 32 80 -> 64, 64 133 -> 120; 4 of 1000 1.07; x 3072, M = 16: 16 of 600
+//     out of 1100 0.64; x 2560, M = 4: 2 of 2300 out of 5120 1.04);
+//   * d = 2048: M <= 8 from 16384 on (16 of 2300 out of 5120 0.81, 2 1.05), M > 8 from 65536 on (0.89, 8 of 5120 1.01).
 //  Dense heads: M > 8, d of 4096 or 8192, of which a compute unit takes eight wavefronts (128k x 4096, M = 16 207 -> 186 us, M = 9 188 -> 180; 32000 x 8192 104 -> 93; x 5120 1.05, x 2048, M = 9 1.06).
 inline bool hold_batch_supported(int32_t M, int32_t d, int32_t batch, int32_t cap_rows) {
   const HoldPlan h = hold_plan(d, batch, false);
   const int64_t rows = (int64_t)cap_rows * batch;
-  const int32_t groups = 8 * batch * h.parts, round = h.NW <= 2 ? 512 : 256;
-  const bool one = groups <= round, even = (int64_t)groups * 10 >= ((int64_t)groups + round - 1) / round * round * 9;
-  if (batch > 32 && M > 8 && (M > 12 || !even || groups > 512)) return false;
-  const int32_t piece = batch > 32 ? 128 : !one ? 256 : batch > 16 ? 96 : d > 4096 ? 32 : M > 4 ? 16 : d > 3072 ? 32 : 64;
-  if (cap_rows < 8 * h.parts * piece) return false;
-  if (d == 2048) return batch >= 5 && even && rows >= (M <= 8 ? 16384 : 65536);
-  if (one && !even && rows >= (h.NW <= 3 ? 24576 : d % 4096 != 0 ? 131072 : INT32_MAX)) return false;
-  if (d <= 4096) return rows > (batch < 4 && M <= 8 && d < 3072 ? 12288 : 4096);
-  if (M <= 4) return rows > 5120 && even && d >= 960 * h.NW;
-  return rows > 5120 && (M <= 8 || d >= 5120 || rows < 196608);
+  if (cap_rows < 8 * h.parts * 16) return false;
+  if (d > 4096 && rows <= (batch >= 4 ? 2560 : 4096)) return false;
+  if (d > 4096 && M <= 4) return hold_fill(8ll * batch * h.parts) >= 51;
+  if (d > 4096) return M <= 8 || d >= 5120 || rows < 196608;
+  return d > 2048 ? rows > (batch < 4 && M <= 8 && d < 3072 ? 12288 : 4096) : rows >= (M <= 8 ? 16384 : 65536);
 }
 
 inline bool hold_supported(int32_t V, int32_t M, int32_t d, int32_t batch, int32_t cap_rows, bool dense) {

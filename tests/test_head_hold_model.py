@@ -66,11 +66,11 @@ def test_a_row_stride_without_room_for_the_segment_is_rejected():
     (16, 8192, 1, 2560, False), (16, 8192, 1, 3072, False), (4, 8192, 1, 33344, False), (8, 5120, 1, 65536, True), (16, 4608, 1, 65536, False), (8, 4096, 1, 4096, False),
     (8, 4096, 1, 5120, False), (16, 3072, 1, 9216, True), (16, 3072, 1, 20032, False), (4, 4096, 1, 5120, True), (4, 4096, 1, 8192, False), (4, 4096, 1, 16384, True),
     (8, 2048, 1, 9216, False), (8, 2048, 1, 16384, True), (16, 2048, 1, 20032, False), (16, 2048, 1, 65536, True), (8, 1536, 1, 128256, False), (17, 4096, 8, 5120, False),
-    (8, 8192, 2, 1024, False), (8, 8192, 4, 1024, False), (4, 8192, 24, 5120, False), (4, 8192, 32, 5120, True), (8, 4096, 4, 1024, False), (8, 4096, 8, 1024, True), (4, 2560, 2, 5120, False),
+    (8, 8192, 2, 1024, False), (8, 8192, 4, 1024, True), (4, 8192, 24, 5120, False), (4, 8192, 32, 5120, True), (8, 4096, 4, 1024, False), (8, 4096, 8, 1024, True), (4, 2560, 2, 5120, False),
     (16, 4608, 64, 5120, False), (16, 4608, 16, 5120, True), (8, 2048, 2, 5120, False), (8, 2048, 16, 1024, True), (16, 2048, 8, 5120, False), (16, 2048, 16, 5120, True), (8, 16384, 64, 5120, False),
     (16, 8192, 1, 5120, False), (16, 8192, 1, 5184, True), (16, 4608, 1, 8128, False), (16, 4608, 1, 8192, True), (16, 4608, 1, 32704, True), (16, 4608, 1, 32768, False), (8, 8192, 1, 5120, False), (8, 8192, 1, 5184, True), (8, 4096, 1, 5184, True), (8, 3072, 1, 4160, True), (16, 2560, 1, 9152, True), (16, 2560, 1, 9216, False), (12, 2560, 1, 9216, True), (16, 3072, 1, 12288, True),
-    (8, 4096, 11, 5120, False), (8, 4096, 11, 10240, True), (8, 4096, 18, 6080, False), (8, 4096, 18, 6144, True), (8, 4096, 22, 8128, False), (8, 4096, 22, 8192, True), (8, 4096, 32, 704, False), (8, 4096, 32, 768, True), (8, 4096, 33, 4032, False), (8, 4096, 33, 4096, True), (8, 4096, 64, 960, False), (8, 4096, 64, 1024, True), (12, 4096, 64, 5120, True), (16, 4096, 64, 5120, False), (12, 4096, 40, 5120, False),
-    (8, 2560, 12, 1984, True), (8, 2560, 12, 2048, False), (8, 4608, 24, 5120, True), (8, 4608, 24, 5504, False), (8, 4096, 24, 8192, True), (1, 4608, 8, 5120, False), (1, 5120, 8, 5120, True), (1, 5120, 4, 5120, True), (1, 5120, 34, 5120, False), (16, 2560, 8, 448, False), (16, 2560, 8, 512, False), (8, 5120, 8, 960, False), (8, 5120, 8, 1024, True), (4, 4096, 8, 960, False), (4, 4096, 8, 1024, True), (4, 3072, 8, 2048, True), (4, 3072, 8, 2560, True), (8, 2048, 3, 8192, False), (16, 5120, 1, 5184, True), (16, 8192, 4, 2048, True),
+    (8, 4096, 11, 5120, True), (8, 4096, 11, 10240, True), (8, 4096, 18, 6080, True), (8, 4096, 18, 6144, True), (8, 4096, 22, 8128, True), (8, 4096, 22, 8192, True), (8, 4096, 32, 704, True), (8, 4096, 32, 768, True), (8, 4096, 33, 4032, True), (8, 4096, 33, 4096, True), (8, 4096, 64, 960, True), (8, 4096, 64, 1024, True), (12, 4096, 64, 5120, True), (16, 4096, 64, 5120, True), (12, 4096, 40, 5120, True),
+    (8, 2560, 12, 1984, True), (8, 2560, 12, 2048, True), (8, 4608, 24, 5120, True), (8, 4608, 24, 5504, True), (8, 4096, 24, 8192, True), (1, 4608, 8, 5120, True), (1, 5120, 8, 5120, True), (1, 5120, 4, 5120, True), (1, 5120, 34, 5120, True), (16, 2560, 8, 448, False), (16, 2560, 8, 512, False), (8, 5120, 8, 960, True), (8, 5120, 8, 1024, True), (4, 4096, 8, 960, True), (4, 4096, 8, 1024, True), (4, 3072, 8, 2048, True), (4, 3072, 8, 2560, True), (8, 2048, 3, 8192, True), (16, 5120, 1, 5184, True), (16, 8192, 4, 2048, True),
 ])
 def test_choice(M, d, batch, cap, want):
     assert choose.hold_supported(V, M, d, batch, cap) == want
